@@ -64,7 +64,9 @@ typedef struct {
   int32_t n_q_heads;   /* H_q */
   int32_t n_kv_heads;  /* H_kv, divides H_q */
   int32_t head_dim;    /* d */
-  int32_t seq_len;     /* N, only read by cake_window_scores / cake_workspace_bytes */
+  int32_t seq_len;     /* N: read by the score, plan and decode calls and by cake_workspace_bytes.
+                          cake_evict_planned takes the row lengths from its plan; seq_len - window only says
+                          which lengths to expect there (longer rows are selected correctly, but slower) */
   int32_t window;      /* S_w */
   int32_t dtype;       /* cake_dtype of Q, K, V */
 } cake_shape;

@@ -140,8 +140,12 @@ int launch_plan(const cake_shape* shape, const double* pref, int pref_ld, int64_
                 void* pool_idx, void* pool_k, void* pool_v, void* pool_ind, void* plan, size_t plan_bytes,
                 int32_t* status, const PlanMirror& mirror, hipStream_t stream);
 // top-k and compaction of all layers with the counts and output places read from a plan
-int launch_topk_planned(const cake_shape* shape, const float* const* indicator, const PlanView& plan, int64_t max_cur /* bound of every current length */,
+// max_cur: the longest row to expect; `bounded` if no current length of the plan exceeds it
+int launch_topk_planned(const cake_shape* shape, const float* const* indicator, const PlanView& plan, int64_t max_cur, bool bounded,
                         hipStream_t stream);
+// cake_evict_planned; `bounded` if the plan was made with current lengths of at most seq_len - window
+int evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,
+                  const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded, void* stream);
 constexpr int kPlanMaskWords = 32;       // one bit per layer, n_layers <= 1024
 int launch_compact_planned(const cake_shape* shape, const void* const* k_in, const void* const* v_in,
                            const int64_t* kv_strides, const uint8_t* compacted, const float* const* ind_in,

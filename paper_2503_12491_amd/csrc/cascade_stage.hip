@@ -211,7 +211,7 @@ extern "C" int cake_cascade_stage(const cake_cascade* c, int32_t m, const void* 
                                             c->pref + m, c->hv + 2 * m, L, L, st)) return rc;
   if (int rc = launch_plan(&shape, c->pref, L, c->total_budget, c->cur, c->idx, c->k_store, c->v_store, c->ind[m & 1], c->plan[m & 1],
                            c->plan_bytes, c->status, PlanMirror{}, st)) return rc;
-  if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(c->tables), a.plan, a.prefix_len, st)) return rc;
+  if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(c->tables), a.plan, a.prefix_len, true, st)) return rc;
   const int64_t shares = std::min<int64_t>((a.prefix_len + kThreads) / kThreads, 2048 / ((int64_t)bh * (m + 1)));
   hipLaunchKernelGGL(renew_lists, dim3(bh, m + 1, (unsigned)std::max<int64_t>(shares, 1)), dim3(kThreads), 0, st, a);
   // as many workgroups as the most rows the layer can keep fill, up to four for each compute unit

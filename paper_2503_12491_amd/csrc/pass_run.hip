@@ -27,7 +27,8 @@ extern "C" int cake_pass_launch(const cake_pass* p, int32_t parts, uint32_t tick
     const PlanMirror mirror{ticket ? p->mirror : nullptr, p->hv, ticket};
     if (int rc = launch_plan(&p->shape, p->pref, p->shape.n_layers, p->total_budget, nullptr, p->pool_idx, p->pool_k,
                              p->pool_v, p->pool_ind, p->plan, p->plan_bytes, p->status, mirror, st)) return rc;
-    return cake_evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, stream);
+    // the plan above takes every row at its full length
+    return evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, true, stream);
   }
   return CAKE_OK;
 }

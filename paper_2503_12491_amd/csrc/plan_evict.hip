@@ -387,10 +387,9 @@ extern "C" int cake_plan_layout(const cake_shape* shape, size_t* offsets) {
   return CAKE_OK;
 }
 
-extern "C" int cake_evict_planned(const cake_shape* shape, const float* const* indicator,
-                                  const void* const* k_in, const void* const* v_in, const int64_t* kv_strides,
-                                  const uint8_t* compacted,
-                                  const void* plan, size_t plan_bytes, void* stream) {
+int cake::evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,
+                        const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded,
+                        void* stream) {
   if (int rc = check_shape_basic(shape)) return rc;
   CAKE_REQUIRE(indicator && k_in && v_in && kv_strides && plan, "a pointer argument is NULL");
   CAKE_REQUIRE((int64_t)shape->n_layers * shape->batch * shape->n_kv_heads <= 65535 * 64,
@@ -404,8 +403,17 @@ extern "C" int cake_evict_planned(const cake_shape* shape, const float* const* i
   CAKE_REQUIRE(plan_bytes >= lay.total, "plan has %zu bytes, %zu needed", plan_bytes, lay.total);
   const PlanView view = plan_view(plan, shape->n_layers, shape->batch);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  // no current length exceeds the prefix; without a length in the shape the kernel for any length serves
+  // without a length in the shape the kernel for any length serves
   const int64_t max_cur = shape->seq_len > shape->window ? shape->seq_len - shape->window : 0x7fffffff;
-  if (int rc = launch_topk_planned(shape, indicator, view, max_cur, st)) return rc;
+  if (int rc = launch_topk_planned(shape, indicator, view, max_cur, bounded, st)) return rc;
   return launch_compact_planned(shape, k_in, v_in, kv_strides, compacted, indicator, view, st);
+}
+
+// The lengths are the plan's, device data that this call cannot look at: the shape's length only says which rows
+// are worth a kernel of their own.
+extern "C" int cake_evict_planned(const cake_shape* shape, const float* const* indicator,
+                                  const void* const* k_in, const void* const* v_in, const int64_t* kv_strides,
+                                  const uint8_t* compacted,
+                                  const void* plan, size_t plan_bytes, void* stream) {
+  return evict_planned(shape, indicator, k_in, v_in, kv_strides, compacted, plan, plan_bytes, false, stream);
 }

@@ -42,6 +42,7 @@ struct TopkPlan {
   const int32_t* keep;        // [L*B]
   const int32_t* cap_cur;     // [L]
   const int32_t* cap_keep;    // [L]
+  int32_t served_slots;       // the kernel for any length leaves rows of up to so many slots to the register kernel launched before it
 };
 
 // Larger float <=> larger key.  -0 is folded onto +0 first so that they compare equal.  Key 0 stands for
@@ -348,6 +349,7 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(TopkArgs a, Ragge
   __shared__ __attribute__((aligned(16))) SelectLds lds;
   const RowTask t = row_task<kPlanned>(a, dims, plan);
   if (t.keep <= 0) return;
+  if (kPlanned && t.row.n_slots > kThreads * kSlots) return;       // a plan's row longer than the caller's shape says: the next launch's
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (t.keep >= t.row.cur) {                           // everything stays
     for (int i = tid; i < t.row.cur; i += kThreads) t.out[i] = i;
@@ -386,6 +388,7 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
   const RowTask t = row_task<kPlanned>(a, dims, plan);
   if (t.keep <= 0) return;
   const Row& row = t.row;
+  if (kPlanned && row.n_slots <= plan.served_slots) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, copy = lane & (kCopies - 1);
   if (t.keep >= row.cur) {
     for (int i = tid; i < row.cur; i += kLongThreads) t.out[i] = i;
@@ -482,16 +485,23 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
 }
 
 // The kernel for rows of up to `most` entries.  A short row in a large workgroup would leave its waves
-// idle at every barrier, and small workgroups let several rows share a compute unit.
+// idle at every barrier, and small workgroups let several rows share a compute unit.  Where `most` is only
+// what the caller's shape suggests (!bounded: the lengths are device data), rows that do not fit it are left out
+// by that kernel and served by the one for any length, launched behind it.
 template <bool kPlanned>
-int launch_topk(dim3 grid, int64_t most, const TopkArgs& a, const RaggedDims& dims, const TopkPlan& plan, hipStream_t stream) {
+int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs& a, const RaggedDims& dims, TopkPlan plan, hipStream_t stream) {
   const int64_t need = most + 3;                       // up to three absent entries in front
-#define CAKE_TOPK(T, S) hipLaunchKernelGGL((select_topk_kernel<kPlanned, T, S>), grid, dim3(T), 0, stream, a, dims, plan)
+  plan.served_slots = 0;
+#define CAKE_TOPK(T, S)                                                                                    \
+  do {                                                                                                     \
+    hipLaunchKernelGGL((select_topk_kernel<kPlanned, T, S>), grid, dim3(T), 0, stream, a, dims, plan);     \
+    plan.served_slots = T * S;                                                                             \
+  } while (0)
   if (need <= 256 * 4 * 4) CAKE_TOPK(256, 4);
   else if (need <= 512 * 8 * 4) CAKE_TOPK(512, 8);
   else if (need <= 1024 * 8 * 4) CAKE_TOPK(1024, 8);
   else if (need <= 1024 * 16 * 4) CAKE_TOPK(1024, 16);
-  else {
+  if (plan.served_slots == 0 || !bounded) {
     auto kern = select_topk_long_kernel<kPlanned>;
     CAKE_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)sizeof(LongLds)));
@@ -506,14 +516,14 @@ int launch_topk(dim3 grid, int64_t most, const TopkArgs& a, const RaggedDims& di
 }  // namespace cake
 
 int cake::launch_topk_planned(const cake_shape* shape, const float* const* indicator, const PlanView& plan, int64_t max_cur,
-                              hipStream_t stream) {
+                              bool bounded, hipStream_t stream) {
   TopkArgs a{};
   a.indicator = indicator;
   a.idx = reinterpret_cast<int32_t* const*>(plan.idx);
   a.batch = shape->batch;
   a.h_kv = shape->n_kv_heads;
-  const TopkPlan tp{plan.cur_len, plan.keep, plan.cap_cur, plan.cap_keep};
-  return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers), max_cur, a, RaggedDims{}, tp, stream);
+  const TopkPlan tp{plan.cur_len, plan.keep, plan.cap_cur, plan.cap_keep, 0};
+  return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers), max_cur, bounded, a, RaggedDims{}, tp, stream);
 }
 
 using namespace cake;
@@ -555,7 +565,7 @@ extern "C" int cake_select_topk(const cake_shape* shape, const float* const* ind
       rows = std::max(rows, ck);
     }
     if (rows > 0)
-      if (int rc = launch_topk<false>(dim3(B * shape->n_kv_heads, nl), most, a, dims, TopkPlan{}, st)) return rc;
+      if (int rc = launch_topk<false>(dim3(B * shape->n_kv_heads, nl), most, true, a, dims, TopkPlan{}, st)) return rc;
     l0 += nl;
   }
   return CAKE_OK;
