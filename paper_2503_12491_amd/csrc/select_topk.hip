@@ -376,9 +376,12 @@ constexpr int kListKeys = 14336;                       // 160 KiB of LDS cannot:
 static_assert(kListKeys <= kLongThreads * kListSlots * 4 && kListKeys % 4 == 0, "the list is re-read in slots of four");
 struct LongLds {
   SelectLds sel;
-  uint32_t key[kListKeys];
+  alignas(16) uint32_t key[kListKeys];                 // read in 16-byte pieces
   int32_t pos[kListKeys];
 };
+static_assert(offsetof(LongLds, key) % 16 == 0 && sizeof(LongLds) <= 160 * 1024, "aligned pieces, a compute unit's LDS");
+static_assert(offsetof(SelectLds, hist) % 16 == 0 && offsetof(SelectLds, few) % 16 == 0 && offsetof(SelectLds, few_pos) % 16 == 0,
+              "read in 16-byte pieces from a 16-byte aligned block");
 
 template <bool kPlanned>
 __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs a, RaggedDims dims, TopkPlan plan) {
