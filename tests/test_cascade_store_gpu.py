@@ -51,8 +51,8 @@ def test_rows_of_the_store_are_those_of_the_copying_cascade(name):
         host.admit(q, k, v)
         if l == L // 2:
             early, early_want = dev.result(), host.result()
-            kept = [t.clone() for t in early.k_out + early.v_out]
+            kept = [t.clone() for t in early.k_out + early.v_out + early.ind_out]
             _same(early, early_want, S_w)
     _same(dev.result(), host.result(), S_w)
-    for a, b in zip(early.k_out + early.v_out, kept):
+    for a, b in zip(early.k_out + early.v_out + early.ind_out, kept, strict=True):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
