@@ -40,6 +40,10 @@ void cake_pass_mirror_layout(int32_t n_layers, int32_t batch, uint64_t* offsets 
 // Enqueues the parts asked for.  With CAKE_PASS_EVICT and ticket != 0 the plan is also written to
 // the mirror, `ticket` last.
 int cake_pass_launch(const cake_pass* pass, int32_t parts, uint32_t ticket, void* stream);
+// The places of the layers' outputs in the pass's pools for row capacities the host knows (the rule of
+// cake_plan_eviction): four device tables [4][n_layers] of idx, K, V and indicator outputs.  The counts travel as
+// kernel arguments: nothing of the caller's is read after the call, and a captured call keeps its own.
+int cake_pass_place(const cake_pass* pass, const int32_t* caps /* host [n_layers] */, void** tables, void* stream);
 // Returns when the mirror holds the plan of `ticket` (the launches behind it may still be running).
 int cake_pass_wait_plan(const void* mirror, uint32_t ticket, void* stream);
 // Returns when everything enqueued on the stream has run.

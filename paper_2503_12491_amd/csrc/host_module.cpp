@@ -41,6 +41,13 @@ PyObject* pass_launch(PyObject*, PyObject* const* args, Py_ssize_t n) {
   return PyLong_FromLong(cake_pass_launch(at<const cake_pass>(a[0]), (int32_t)a[1], (uint32_t)a[2], at<void>(a[3])));
 }
 
+// pass_place(pass, caps, tables, stream) -> return code
+PyObject* pass_place(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  uint64_t a[4];
+  if (!parse(args, n, 4, a)) return nullptr;
+  return PyLong_FromLong(cake_pass_place(at<const cake_pass>(a[0]), at<const int32_t>(a[1]), at<void*>(a[2]), at<void>(a[3])));
+}
+
 // wait_plan(mirror, ticket, stream) -> return code
 PyObject* wait_plan(PyObject*, PyObject* const* args, Py_ssize_t n) {
   uint64_t a[3];
@@ -163,7 +170,7 @@ PyObject* cascade_gather(PyObject*, PyObject* const* args, Py_ssize_t n) {
 }
 
 #define METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(name)), METH_FASTCALL, nullptr}
-PyMethodDef kMethods[] = {METHOD(pass_launch), METHOD(wait_plan), METHOD(stream_wait), METHOD(layer_views), METHOD(decode_run),
+PyMethodDef kMethods[] = {METHOD(pass_launch), METHOD(pass_place), METHOD(wait_plan), METHOD(stream_wait), METHOD(layer_views), METHOD(decode_run),
                           METHOD(cascade_stage), METHOD(cascade_gather),
                           {nullptr, nullptr, 0, nullptr}};
 PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_host", nullptr, -1, kMethods, nullptr, nullptr, nullptr, nullptr};

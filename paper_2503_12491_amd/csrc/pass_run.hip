@@ -7,6 +7,30 @@
 #include "cake_internal.h"
 #include "cake_pass.h"
 
+namespace cake {
+namespace {
+
+constexpr int kPlaceLayers = 256;            // per launch: 2 KiB of arguments
+struct PlaceArgs {
+  char *idx, *k, *v, *ind;
+  void** tables;                             // [4][n_layers]
+  int64_t row_i, row_kv;                     // bytes of a row of all heads in the pools
+  int32_t n_layers, first, count, window;
+  int64_t rows_before[kPlaceLayers];
+};
+__global__ __launch_bounds__(kPlaceLayers) void place_outputs(PlaceArgs a) {
+  const int i = threadIdx.x, l = a.first + i;
+  if (i >= a.count) return;
+  const int64_t before = a.rows_before[i], before_kv = before + (int64_t)l * a.window;
+  a.tables[l] = a.idx + before * a.row_i;
+  a.tables[a.n_layers + l] = a.k + before_kv * a.row_kv;
+  a.tables[2 * a.n_layers + l] = a.v + before_kv * a.row_kv;
+  a.tables[3 * a.n_layers + l] = a.ind + before * a.row_i;
+}
+
+}  // namespace
+}  // namespace cake
+
 using namespace cake;
 
 extern "C" void cake_pass_mirror_layout(int32_t n_layers, int32_t batch, uint64_t* offsets) {
@@ -30,6 +54,28 @@ extern "C" int cake_pass_launch(const cake_pass* p, int32_t parts, uint32_t tick
     // the plan above takes every row at its full length
     return evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, true, stream);
   }
+  return CAKE_OK;
+}
+
+extern "C" int cake_pass_place(const cake_pass* p, const int32_t* caps, void** tables, void* stream) {
+  CAKE_REQUIRE(p && caps && tables, "a pointer argument is NULL");
+  if (int rc = check_shape_basic(&p->shape)) return rc;
+  const cake_shape& s = p->shape;
+  for (int l = 0; l < s.n_layers; ++l) CAKE_REQUIRE(caps[l] >= 0, "caps[%d] = %d is negative", l, caps[l]);
+  const int64_t bh = (int64_t)s.batch * s.n_kv_heads;
+  PlaceArgs a{static_cast<char*>(p->pool_idx), static_cast<char*>(p->pool_k), static_cast<char*>(p->pool_v),
+              static_cast<char*>(p->pool_ind), tables, bh * 4, bh * s.head_dim * (int64_t)elem_bytes(s.dtype), s.n_layers, 0, 0,
+              s.window, {}};
+  int64_t rows = 0;
+  for (; a.first < s.n_layers; a.first += a.count) {
+    a.count = s.n_layers - a.first < kPlaceLayers ? s.n_layers - a.first : kPlaceLayers;
+    for (int i = 0; i < a.count; ++i) {
+      a.rows_before[i] = rows;
+      rows += caps[a.first + i];
+    }
+    hipLaunchKernelGGL(place_outputs, dim3(1), dim3(kPlaceLayers), 0, static_cast<hipStream_t>(stream), a);
+  }
+  CAKE_HIP_TRY(hipGetLastError());
   return CAKE_OK;
 }
 
