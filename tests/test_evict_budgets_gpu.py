@@ -100,3 +100,22 @@ def test_places_of_more_layers_than_one_launch_holds():
     got = _outputs(ev, ev.evict(budgets))
     torch.cuda.synchronize()
     _check(got, _expected(ev, budgets))
+
+
+def test_budgets_beyond_the_pools_are_refused_before_anything_is_launched():
+    cake = load_cake()
+    say("budgets that fill the pools and one row more")
+    ev = _make(cake, total=L * (S_W + 50))
+    fits = np.repeat(_budgets(150, 100, 50)[:, :1], B, axis=1)       # 300 = B * 3 * 50 rows: all there are
+    want = _outputs(ev, ev.evict(fits))
+    _check(want, _expected(ev, fits))
+    before = [t.clone() for t in (ev.pool_k, ev.pool_v, ev.pool_idx, ev.pool_ind, ev.tbl_out)]
+    over = fits.copy()
+    over[2, 1] += 1
+    for call in (ev.evict, ev.evict_launch):
+        with pytest.raises(ValueError, match="pools"):
+            call(over)
+    torch.cuda.synchronize()
+    for t, b in zip((ev.pool_k, ev.pool_v, ev.pool_idx, ev.pool_ind, ev.tbl_out), before):
+        assert torch.equal(t, b)
+    _check(_outputs(ev, ev.evict(fits)), want)
