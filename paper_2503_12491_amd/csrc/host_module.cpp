@@ -11,7 +11,8 @@
 
 namespace {
 
-// Releases the interpreter while the host waits for the device.
+// Releases the interpreter while the host launches or waits: with the device's queue full a launch waits too, and
+// the program's other threads are to go on.
 template <typename F>
 int without_gil(F f) {
   int rc;
@@ -38,14 +39,14 @@ template <typename T> T* at(uint64_t x) { return reinterpret_cast<T*>(static_cas
 PyObject* pass_launch(PyObject*, PyObject* const* args, Py_ssize_t n) {
   uint64_t a[4];
   if (!parse(args, n, 4, a)) return nullptr;
-  return PyLong_FromLong(cake_pass_launch(at<const cake_pass>(a[0]), (int32_t)a[1], (uint32_t)a[2], at<void>(a[3])));
+  return PyLong_FromLong(without_gil([&] { return cake_pass_launch(at<const cake_pass>(a[0]), (int32_t)a[1], (uint32_t)a[2], at<void>(a[3])); }));
 }
 
 // pass_place(pass, caps, tables, stream) -> return code
 PyObject* pass_place(PyObject*, PyObject* const* args, Py_ssize_t n) {
   uint64_t a[4];
   if (!parse(args, n, 4, a)) return nullptr;
-  return PyLong_FromLong(cake_pass_place(at<const cake_pass>(a[0]), at<const int32_t>(a[1]), at<void*>(a[2]), at<void>(a[3])));
+  return PyLong_FromLong(without_gil([&] { return cake_pass_place(at<const cake_pass>(a[0]), at<const int32_t>(a[1]), at<void*>(a[2]), at<void>(a[3])); }));
 }
 
 // wait_plan(mirror, ticket, stream) -> return code
@@ -136,8 +137,8 @@ PyObject* decode_run(PyObject*, PyObject* const* args, Py_ssize_t n) {
   const int64_t lead = dim - 3;
   const int64_t qs[3] = {lead ? q.stride(0) : 0, q.stride(lead), q.stride(lead + 1)};
   const int64_t ns[3] = {lead ? k.stride(0) : 0, k.stride(lead), k.stride(lead + 1)};
-  return PyLong_FromLong(cake_decode_run(at<const cake_decode_plan>(a[0]), q.data_ptr(), qs, k.data_ptr(), v.data_ptr(), ns,
-                                         at<void>(a[1])));
+  const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr();
+  return PyLong_FromLong(without_gil([&] { return cake_decode_run(at<const cake_decode_plan>(a[0]), qp, qs, kp, vp, ns, at<void>(a[1])); }));
 }
 
 // cascade_stage(cascade, m, q_win, k, v, indicator, stream) -> return code.  q_win, k, v are 4-d with contiguous d,
@@ -158,15 +159,21 @@ PyObject* cascade_stage(PyObject*, PyObject* const* args, Py_ssize_t n) {
     PyErr_SetString(PyExc_AssertionError, "expect [B, H, rows, d] with contiguous d, k and v alike");
     return nullptr;
   }
-  return PyLong_FromLong(cake_cascade_stage(at<const cake_cascade>(a[0]), (int32_t)a[1], q.data_ptr(), k.data_ptr(), v.data_ptr(),
-                                            static_cast<float*>(ind.data_ptr()), q.strides().data(), k.strides().data(), at<void>(a[2])));
+  const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr();
+  float* out = static_cast<float*>(ind.data_ptr());
+  const int64_t qs[3] = {q.stride(0), q.stride(1), q.stride(2)}, ks[3] = {k.stride(0), k.stride(1), k.stride(2)};
+  return PyLong_FromLong(without_gil([&] {
+    return cake_cascade_stage(at<const cake_cascade>(a[0]), (int32_t)a[1], qp, kp, vp, out, qs, ks, at<void>(a[2]));
+  }));
 }
 
 // cascade_gather(cascade, n_layers, pool_k, pool_v, stream) -> return code
 PyObject* cascade_gather(PyObject*, PyObject* const* args, Py_ssize_t n) {
   uint64_t a[5];
   if (!parse(args, n, 5, a)) return nullptr;
-  return PyLong_FromLong(cake_cascade_gather(at<const cake_cascade>(a[0]), (int32_t)a[1], at<void>(a[2]), at<void>(a[3]), at<void>(a[4])));
+  return PyLong_FromLong(without_gil([&] {
+    return cake_cascade_gather(at<const cake_cascade>(a[0]), (int32_t)a[1], at<void>(a[2]), at<void>(a[3]), at<void>(a[4]));
+  }));
 }
 
 #define METHOD(name) {#name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)(void)>(name)), METH_FASTCALL, nullptr}
