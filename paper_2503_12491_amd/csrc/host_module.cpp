@@ -2,6 +2,7 @@
 // caller and the launches on every pass or token, where a Python statement per layer or argument
 // costs as much as a kernel.  Argument hand-over and tensor views only.
 #include <Python.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <algorithm>
@@ -63,6 +64,9 @@ PyObject* stream_wait(PyObject*, PyObject* const* args, Py_ssize_t n) {
   return PyLong_FromLong(without_gil([&] { return cake_stream_wait(at<void>(a[0])); }));
 }
 
+// Calls that ask a tensor for anything turn the tensor library's exceptions into Python's (HANDLE_TH_ERRORS): a
+// sparse tensor has no strides, one inside vmap no memory.
+
 // A contiguous view of `base` at an element offset.  What Tensor.as_strided returns for a tensor that
 // takes no part in autograd, made directly: 0.3 us instead of 2.
 PyObject* view_of(const at::Tensor& base, int64_t offset, c10::IntArrayRef sizes) {
@@ -77,6 +81,7 @@ PyObject* view_of(const at::Tensor& base, int64_t offset, c10::IntArrayRef sizes
 //   -> (idx, k, v, ind) lists of per-layer views: [B, H_kv, cap (+ S_w, d)], cap = max over b of keep,
 //      the layers one after the other (the places cake_plan_eviction gives them)
 PyObject* layer_views(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   if (n != 10) {
     PyErr_SetString(PyExc_TypeError, "10 arguments expected");
     return nullptr;
@@ -116,11 +121,13 @@ PyObject* layer_views(PyObject*, PyObject* const* args, Py_ssize_t n) {
   PyObject* out = ok ? PyTuple_Pack(4, lists[0], lists[1], lists[2], lists[3]) : nullptr;
   for (auto& l : lists) Py_XDECREF(l);
   return out;
+  END_HANDLE_TH_ERRORS
 }
 
 // decode_run(plan, q_new, k_new, v_new, stream) -> return code.  The tensors are [(layers,) B, heads, d] of the
 // plan's rank with contiguous d, k_new and v_new alike.
 PyObject* decode_run(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   if (n != 5 || !THPVariable_Check(args[1]) || !THPVariable_Check(args[2]) || !THPVariable_Check(args[3])) {
     PyErr_SetString(PyExc_TypeError, "decode_run(plan, q_new, k_new, v_new, stream)");
     return nullptr;
@@ -139,11 +146,13 @@ PyObject* decode_run(PyObject*, PyObject* const* args, Py_ssize_t n) {
   const int64_t ns[3] = {lead ? k.stride(0) : 0, k.stride(lead), k.stride(lead + 1)};
   const void *qp = q.data_ptr(), *kp = k.data_ptr(), *vp = v.data_ptr();
   return PyLong_FromLong(without_gil([&] { return cake_decode_run(at<const cake_decode_plan>(a[0]), qp, qs, kp, vp, ns, at<void>(a[1])); }));
+  END_HANDLE_TH_ERRORS
 }
 
 // cascade_stage(cascade, m, q_win, k, v, indicator, stream) -> return code.  q_win, k, v are 4-d with contiguous d,
 // v has k's strides.
 PyObject* cascade_stage(PyObject*, PyObject* const* args, Py_ssize_t n) {
+  HANDLE_TH_ERRORS
   bool ok = n == 7;
   for (int i = 2; ok && i < 6; ++i) ok = THPVariable_Check(args[i]);
   if (!ok) {
@@ -165,6 +174,7 @@ PyObject* cascade_stage(PyObject*, PyObject* const* args, Py_ssize_t n) {
   return PyLong_FromLong(without_gil([&] {
     return cake_cascade_stage(at<const cake_cascade>(a[0]), (int32_t)a[1], qp, kp, vp, out, qs, ks, at<void>(a[2]));
   }));
+  END_HANDLE_TH_ERRORS
 }
 
 // cascade_gather(cascade, n_layers, pool_k, pool_v, stream) -> return code

@@ -57,3 +57,46 @@ def test_other_threads_run_while_it_launches(host, which):
         sys.setswitchinterval(before)
     thread.join(10)
     assert done, f"{name} kept the interpreter"
+
+
+def _without_storage(kind, shape):
+    """Tensors of that shape whose memory or strides cannot be asked for."""
+    if kind == "sparse":
+        return torch.zeros(shape).to_sparse()
+    if kind == "fake":
+        from torch._subclasses.fake_tensor import FakeTensorMode
+        with FakeTensorMode():
+            return torch.zeros(shape)
+    return torch._C._functorch._add_batch_dim(torch.zeros((2,) + shape), 0, torch._C._functorch._vmap_increment_nesting(2, "error"))
+
+
+@pytest.mark.parametrize("kind", ["sparse", "fake", "vmap"])
+@pytest.mark.parametrize("entry", ["decode_run", "cascade_stage", "layer_views"])
+def test_tensors_without_memory_raise(entry, kind):
+    """An error of the tensor library becomes a Python exception, whichever call meets it (in a process of its own:
+    an exception that leaves the module ends the process)."""
+    import os
+    import subprocess
+    code = f"""
+import ctypes, numpy as np, torch, sys
+sys.path.insert(0, {os.path.dirname(os.path.abspath(__file__))!r})
+from test_host_module import _calls, _without_storage, _ffi
+host = _ffi.host()
+_, keep = _calls(host)
+x, y, z = [_without_storage({kind!r}, s) for s in ((1, 2, 64), (1, 2, 32, 64), (65536,))]
+rows = np.ones((1, 1), dtype=np.int32)
+try:
+    if {entry!r} == "decode_run": host.decode_run(ctypes.addressof(keep[2]), x, x, x, 0)
+    elif {entry!r} == "cascade_stage": host.cascade_stage(0, 0, y, y, y, y, 0)
+    else: host.layer_views(z, z, z, z, rows.ctypes.data, 1, 1, 2, 32, 64)
+except Exception as e:
+    print("raised", type(e).__name__, str(e)[:100].replace("\\n", " "))
+else:
+    print("returned")
+"""
+    r = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=120,
+                       cwd=os.path.dirname(os.path.dirname(os.path.abspath(__file__))))
+    print(r.stdout, r.stderr[-300:])
+    assert r.returncode == 0, (r.returncode, r.stderr[-400:])
+    if kind != "fake":                       # a fake tensor's address is 0, which the library refuses where it reads it
+        assert r.stdout.startswith("raised")
