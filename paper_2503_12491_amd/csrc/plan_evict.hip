@@ -16,9 +16,9 @@
 // would have awarded before touching any seat at or below lambda.  Only fp64 divisions and
 // comparisons decide, so host and device agree bit for bit whatever level the search stops at.
 //
-// Latency is all there is to this step: budgets, places and work list are one launch of one
-// workgroup, the level is found by a secant search on the piecewise-linear seat count (three to five
-// counts where a plain bisection took twenty-odd).
+// Latency is all there is to this step: budgets, places and work list of a few sequences are one launch
+// of one workgroup, the level is found by a secant search on the piecewise-linear seat count (three to five
+// counts where a plain bisection took twenty-odd).  More sequences are allocated by workgroups of their own.
 #include <algorithm>
 #include <cmath>
 
@@ -80,9 +80,11 @@ struct PlanArgs {
   char *pool_idx, *pool_k, *pool_v, *pool_ind;
   void **idx_tbl, **k_tbl, **v_tbl, **ind_tbl;
   PlanMirror mirror;
+  bool allocated;             // budgets, keep and cur are there already (allocate_kernel)
 };
 
 constexpr int kPlanMaxWaves = 16;
+constexpr int kPlanOneLaunch = 12;
 constexpr size_t kPlanLdsPerLayer = 2 * sizeof(double) + sizeof(int32_t);     // p, prio, bud of one layer of one sequence
 
 // A value per layer, entry l only ever touched by lane l mod 64 (so that nothing here synchronises): a
@@ -227,6 +229,15 @@ __device__ void allocate_sequence(const PlanArgs& a, int b, int lane, double* p_
   }
 }
 
+// The first step of a large batch alone, a workgroup of one wave per sequence.
+__global__ __launch_bounds__(64) void allocate_kernel(PlanArgs a) {
+  extern __shared__ __attribute__((aligned(8))) char plan_lds[];
+  const int n_layers = a.n_layers;
+  double* p = reinterpret_cast<double*>(plan_lds);
+  if (n_layers <= 64) allocate_sequence<true>(a, blockIdx.x, threadIdx.x, nullptr, nullptr, nullptr);
+  else allocate_sequence<false>(a, blockIdx.x, threadIdx.x, p, p + n_layers, reinterpret_cast<int32_t*>(p + 2 * n_layers));
+}
+
 // The whole plan in one workgroup: budgets and keep counts (a wave per sequence), row capacities of
 // every layer (the largest count over the batch), the places of the layers' outputs, one after the
 // other, in the four pools, the compaction's work list, and on request a copy of what the host wants
@@ -235,7 +246,7 @@ __global__ __launch_bounds__(64 * kPlanMaxWaves) void plan_kernel(PlanArgs a) {
   extern __shared__ __attribute__((aligned(8))) char plan_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
   const int n_layers = a.n_layers, batch = a.batch;
-  {
+  if (!a.allocated) {
     double* p = reinterpret_cast<double*>(plan_lds) + (size_t)wave * 2 * n_layers;
     int32_t* bud = reinterpret_cast<int32_t*>(plan_lds + (size_t)n_waves * n_layers * 2 * sizeof(double)) + (size_t)wave * n_layers;
     for (int b = wave; b < batch; b += n_waves) {
@@ -245,14 +256,28 @@ __global__ __launch_bounds__(64 * kPlanMaxWaves) void plan_kernel(PlanArgs a) {
   }
   __threadfence_block();
   __syncthreads();
-  for (int l = tid; l < n_layers; l += blockDim.x) {
-    int ck = 0, cc = 0;
-    for (int b = 0; b < batch; ++b) {
-      ck = max(ck, a.keep[(int64_t)l * batch + b]);
-      cc = max(cc, a.cur[(int64_t)l * batch + b]);
+  if (a.allocated) {                       // many sequences: a wave per layer
+    for (int l = wave; l < n_layers; l += n_waves) {
+      uint32_t ck = 0, cc = 0;             // counts are not negative
+      for (int b = lane; b < batch; b += 64) {
+        ck = max(ck, (uint32_t)a.keep[(int64_t)l * batch + b]);
+        cc = max(cc, (uint32_t)a.cur[(int64_t)l * batch + b]);
+      }
+      auto umax = [](uint32_t x, uint32_t y) { return max(x, y); };
+      ck = wave_scan(ck, umax);
+      cc = wave_scan(cc, umax);
+      if (lane == 63) { a.cap_keep[l] = (int32_t)ck; a.cap_cur[l] = (int32_t)cc; }
     }
-    a.cap_keep[l] = ck;
-    a.cap_cur[l] = cc;
+  } else {
+    for (int l = tid; l < n_layers; l += blockDim.x) {
+      int ck = 0, cc = 0;
+      for (int b = 0; b < batch; ++b) {
+        ck = max(ck, a.keep[(int64_t)l * batch + b]);
+        cc = max(cc, a.cur[(int64_t)l * batch + b]);
+      }
+      a.cap_keep[l] = ck;
+      a.cap_cur[l] = cc;
+    }
   }
   __threadfence_block();
   __syncthreads();
@@ -358,11 +383,21 @@ int cake::launch_plan(const cake_shape* shape, const double* pref, int pref_ld, 
   void** tables = reinterpret_cast<void**>(b + lay.off_tables);
   a.idx_tbl = tables; a.k_tbl = tables + L; a.v_tbl = tables + 2 * L; a.ind_tbl = tables + 3 * L;
   a.mirror = mirror;
-  // a wave per sequence, as many as 64 KiB of LDS hold (at least two, so that the two scans run side by side)
   const size_t per_wave = L > 64 ? kPlanLdsPerLayer * L : 0;
   const int by_lds = per_wave ? (int)((size_t)65536 / per_wave) : kPlanMaxWaves;
-  const int waves = std::max(std::min(std::max(shape->batch, 2), std::min(kPlanMaxWaves, by_lds)), 1);
-  hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64 * waves), per_wave * waves, stream, a);
+  // Up to twelve sequences share the plan's workgroup (a launch less: 1, 4 and 12 sequences of 32 layers 5.9, 8.5 and
+  // 16.3 us, with a launch of their own 7.7, 10.0 and 16.3), unless its LDS holds fewer; more of them would wait for
+  // each other there (16, 64 and 256 sequences 20.8, 76 and 252 us against 17.5, 26 and 63; 64 of 1024 layers 3350
+  // against 617).
+  if (shape->batch > std::min(kPlanOneLaunch, by_lds)) {
+    hipLaunchKernelGGL(allocate_kernel, dim3(shape->batch), dim3(64), per_wave, stream, a);
+    a.allocated = true;
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64 * kPlanMaxWaves), 0, stream, a);
+  } else {
+    // a wave per sequence (at least two, so that the two scans run side by side)
+    const int waves = std::max(shape->batch, std::min(2, by_lds));
+    hipLaunchKernelGGL(plan_kernel, dim3(1), dim3(64 * waves), per_wave * waves, stream, a);
+  }
   CAKE_HIP_TRY(hipGetLastError());
   return CAKE_OK;
 }

@@ -66,6 +66,43 @@ def test_device_budgets_equal_the_oracle_allocator(cake):
     say(f"device allocation: {cases} sequences identical to the oracle allocator")
 
 
+@pytest.mark.parametrize("L,B", [(3, 12), (3, 13), (64, 13), (65, 12), (65, 13), (300, 10), (300, 11), (1024, 3), (1024, 4), (2, 64), (2, 65), (5, 256)])
+def test_plans_of_batches_of_every_size(cake, L, B):
+    """Few sequences are allocated in the plan's workgroup, more by workgroups of their own, and the row capacities are
+    then found another way: budgets against the oracle; capacities, places and work list by their definitions."""
+    from paper_2503_12491_amd import binding as C
+    say(f"plan of {B} sequences x {L} layers")
+    rng = np.random.default_rng(L + B)
+    window, seq_len, h_kv, d = 8, 90, 2, 64
+    total = L * 30
+    pref = np.exp(1.5 * rng.standard_normal((B, L)))
+    bad = B // 2
+    pref[bad, L - 1] = -1.0
+    cur = rng.integers(0, seq_len - window + 1, size=(L, B))
+    shape = C.make_shape(B, L, h_kv, h_kv, d, seq_len, window, torch.float32)
+    plan = torch.zeros(C.cake_plan_bytes(shape), dtype=torch.uint8, device=DEV)
+    status = torch.full((B,), -1, dtype=torch.int32, device=DEV)
+    pools = [torch.zeros(64, dtype=torch.uint8, device=DEV) for _ in range(4)]
+    C.cake_plan_eviction(shape, torch.tensor(pref, device=DEV), total, torch.tensor(cur.reshape(-1), dtype=torch.int32, device=DEV),
+                         *pools, plan, status)
+    budgets, keep, cur_out, cap_keep = C.plan_fields(plan.cpu(), L, B)
+    assert status.tolist() == [int(b == bad) for b in range(B)]
+    pref[bad] = 1.0
+    for b in range(B):
+        assert list(budgets[:, b]) == co.cascade_allocate(pref[b], total, window, seq_len), b
+    assert np.array_equal(keep, np.clip(budgets - window, 0, cur)) and np.array_equal(cur_out, cur)
+    raw, lay = plan.cpu().numpy(), C.cake_plan_layout(shape)
+    part = lambda name, dt, n: raw[lay[name]: lay[name] + n * np.dtype(dt).itemsize].view(dt)
+    assert np.array_equal(cap_keep, keep.max(axis=1)) and np.array_equal(part("cap_cur", np.int32, L), cur.max(axis=1))
+    blocks = -(-(keep.reshape(-1) + window) * (d * 4 // 16) // 1024)
+    assert np.array_equal(part("copy_blocks", np.int32, L * B + 1), np.concatenate([[0], np.cumsum(blocks)]))
+    before = np.concatenate([[0], np.cumsum(cap_keep)[:-1]])
+    row = B * h_kv * d * 4
+    for name, pool, at in (("idx", 0, before * B * h_kv * 4), ("k_out", 1, (before + np.arange(L) * window) * row),
+                           ("v_out", 2, (before + np.arange(L) * window) * row), ("ind_out", 3, before * B * h_kv * 4)):
+        assert np.array_equal(part(name, np.int64, L), pools[pool].data_ptr() + at), name
+
+
 def test_keep_counts_respect_current_lengths_and_bad_preferences_are_flagged(cake):
     pref = np.array([[1.0, 2.0, 3.0], [0.5, float("nan"), 1.0]])
     cur = np.array([[10, 500], [3, 0], [400, 7]])                  # [L, B]
