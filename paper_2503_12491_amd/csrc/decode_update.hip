@@ -255,7 +255,8 @@ template <int D> struct RowDots<float, D> {
   }
 };
 
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }   // v_exp_f32
+// v_exp_f32, which returns 0 below 2^-126: for the terms of a sum that is at least 1
+__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 // Step kernel 1, one workgroup per 256 rows of a slice: the new row goes to its slot; logits of the G
 // heads for every listed row (kept for what follows) and the chunk's (reference, sum) pairs.
@@ -417,7 +418,7 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
       float s = 0.f;
 #pragma unroll
       for (int h = 0; h < kGroup; ++h)
-        if (h < group) s += fast_exp2(t[i][h] - lse[h]);
+        if (h < group) s += exp2f(t[i][h] - lse[h]);      // weights below 2^-126 too: they order rows whose indicators are still 0
       obs[half + j] = s * a.inv_g;
     }
   }

@@ -63,3 +63,30 @@ def test_steps_match_the_oracle_at_every_list_length(cake, cap, G, d, S_w, dtype
                 v_full = np.concatenate([v0[g], host64(vn[b])[g][None]], axis=0)
                 np.testing.assert_array_equal(host64(v1[g]), co.compact(v_full, sel, S_w))
                 assert_close(host64(i1[g]), upd[g][sel], f"indicator step {step} b={b} g={g}")
+
+
+@pytest.mark.parametrize("G", [1, 5])
+def test_weights_below_the_normal_range_still_order_the_rows(cake, G):
+    """Weights of 2^-126 .. 2^-146 are kept: rows whose indicators are still 0 differ by them alone.  A logit's fp32
+    rounding at 146 is 1.7e-5 of the weight, the weight's own rounding at most a step of 2^-149."""
+    say(f"decode step: weights below 2^-126, G = {G}")
+    cap, S_w, d = 40, 32, 64
+    log2w = np.random.default_rng(2).permutation(-126.0 - 0.5 * np.arange(cap))
+    rows = np.concatenate([log2w, [-130.0], [-200.0] * (S_w - 2), [0.0]])       # the oldest window row leaves; the newest takes all the weight
+    k = torch.zeros(1, 1, cap + S_w, d)
+    k[0, 0, :, 0] = torch.tensor(rows * np.log(2.0), dtype=torch.float32)
+    keep = np.array([[cap]])
+    res = cake.PassResult(keep + S_w, keep, None, None, [], [], [k.to(DEV)], [k.to(DEV)], [torch.zeros(1, 1, cap, device=DEV)])
+    slots = cake.DecodeSlots(res, G, S_w, cake.make_params(pool_kernel=1))
+    q = torch.zeros(1, G, d)
+    q[..., 0] = 8.0                                                             # scale 1/8: the logit is the key's first entry
+    new = torch.zeros(1, 1, d)
+    new[..., 0] = -200.0 * np.log(2.0)
+    slots.step(0, q.to(DEV), new.to(DEV), new.to(DEV))
+    torch.cuda.synchronize()
+    _, _, ind, evicted = slots.logical(0, 0)
+    want = np.exp2(rows[:cap + 1])
+    e = int(np.argmin(want))
+    assert int(evicted[0]) == e
+    want = np.delete(want, e)
+    assert np.all(np.abs(host64(ind[0]) - want) <= 2.0 ** -149 + 3e-5 * want)
