@@ -232,6 +232,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 template <typename T, int D> struct RowDots;
 template <int D> struct RowDots<__bf16, D> {
   typedef __bf16 frag __attribute__((ext_vector_type(8)));
+  typedef __bf16 loose __attribute__((ext_vector_type(8), aligned(2)));
   static constexpr int kSteps = D / 32;
   static constexpr int kBlocks = 4;                     // sixteen-row blocks loaded before the first is used: 64 registers
   static __device__ __forceinline__ f32x4 run(const frag (&k)[kSteps], const frag (&q)[kSteps]) {
@@ -243,6 +244,7 @@ template <int D> struct RowDots<__bf16, D> {
 };
 template <int D> struct RowDots<float, D> {
   typedef float frag __attribute__((ext_vector_type(4)));
+  typedef float loose __attribute__((ext_vector_type(4), aligned(4)));
   static constexpr int kSteps = D / 16;
   static constexpr int kBlocks = 2;
   static __device__ __forceinline__ f32x4 run(const frag (&k)[kSteps], const frag (&q)[kSteps]) {
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
   frag qf[Dots::kSteps];
 #pragma unroll
   for (int s = 0; s < Dots::kSteps; ++s) {
-    qf[s] = *reinterpret_cast<const frag*>(q + s * 4 * kElems + kg * kElems);
+    qf[s] = *reinterpret_cast<const typename Dots::loose*>(q + s * 4 * kElems + kg * kElems);     // q_new may start at any element
     if (li >= a.group)
 #pragma unroll
       for (int i = 0; i < kElems; ++i) qf[s][i] = (T)0.f;

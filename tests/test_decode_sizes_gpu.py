@@ -90,3 +90,26 @@ def test_weights_below_the_normal_range_still_order_the_rows(cake, G):
     assert int(evicted[0]) == e
     want = np.delete(want, e)
     assert np.all(np.abs(host64(ind[0]) - want) <= 2.0 ** -149 + 3e-5 * want)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_queries_may_start_at_any_element(cake, dtype):
+    """Only the strides of q_new are multiples of 16 bytes: its address is any element's."""
+    say(f"decode step: q_new off 16 bytes, {dtype}")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    gen = torch.Generator().manual_seed(4)
+    G, H_kv, d, S_w, B = 3, 2, 64, 32, 2
+    res = _result(cake, 300, B, H_kv, d, S_w, dt, gen)
+    q = torch.randn(B, G * H_kv, d, generator=gen).to(dt).to(DEV)
+    kn, vn = (torch.randn(B, H_kv, d, generator=gen).to(dt).to(DEV) for _ in range(2))
+    want = cake.DecodeSlots(res, G * H_kv, S_w)
+    want.step(0, q, kn, vn)
+    for off in (1, 3):
+        moved = torch.empty(q.numel() + off, dtype=dt, device=DEV)[off:].view(q.shape)
+        moved.copy_(q)
+        assert moved.data_ptr() % 16 != 0
+        got = cake.DecodeSlots(res, G * H_kv, S_w)
+        got.step(0, moved, kn, vn)
+        torch.cuda.synchronize()
+        for name in ("k", "v", "ind", "order", "state"):
+            assert torch.equal(getattr(got, name)[0], getattr(want, name)[0]), (off, name)
