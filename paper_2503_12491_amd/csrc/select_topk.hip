@@ -267,7 +267,8 @@ __device__ __forceinline__ void find_threshold(uint32_t (&key)[kSlots][4], int n
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const uint32_t v = key[u][j] - lo;
-          d[j] = v >> bits == 0 ? v >> shift : kBins;
+          // (an interval that holds the largest key may reach past 2^32, to where an absent key's difference wraps)
+          d[j] = v >> bits == 0 && key[u][j] != 0u ? v >> shift : kBins;
         }
         count_slot(d, false);
       }

@@ -68,3 +68,23 @@ def test_rows_of_nan_with_all_bits_set(cake, n):
         np.testing.assert_array_equal(idx[0, 0].cpu().numpy(), np.arange(k))
         want = co.select_topk(np.where(np.isnan(vals[1]), -1e30, vals[1]).astype(np.float64), k)
         np.testing.assert_array_equal(idx[0, 1].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n", [200, 1000, 5000, 40000, 70001])
+def test_rows_of_the_largest_key(cake, n):
+    # NaN of the bits 0x7fffffff has the largest key there is, and an interval of the search that holds it may reach
+    # past the keys' end: the absent entries behind a row are not in it.  More of them than are ranked, beside numbers.
+    say(f"top-k of rows of {n} with the largest key")
+    for m in (129, 190):
+        for k in (1, 100, m, m + 3):
+            vals = np.exp(np.random.default_rng(n + k).standard_normal((2, n))).astype(np.float32)
+            vals[:, n - m:] = np.uint32(0x7FFFFFFF).view(np.float32)
+            vals[1] = vals[1, ::-1]
+            ind = torch.from_numpy(vals.view(np.int32).copy()).to(DEV).view(torch.float32)[None]
+            idx = torch.full((1, 2, k), -1, dtype=torch.int32, device=DEV)
+            shape = cake.make_shape(1, 1, 2, 2, 64, n + 32, 32, torch.float32)
+            cake.cake_select_topk(shape, cake.ptr_table([ind]), [n], [k], cake.ptr_table([idx]))
+            torch.cuda.synchronize()
+            for h in range(2):
+                want = co.select_topk(np.where(np.isnan(vals[h]), 1e30, vals[h]).astype(np.float64), k)
+                np.testing.assert_array_equal(idx[0, h].cpu().numpy(), want, err_msg=f"m={m} k={k} row {h}")
