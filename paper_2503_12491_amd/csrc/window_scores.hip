@@ -214,11 +214,13 @@ __device__ __forceinline__ void pass1_logits(const char* tile, int sub,
 // The finished logits of a sub-tile (first key kb) folded into the rows' running
 // (reference, sum) pairs.  Key j is visible to window row r iff j <= n_p + r (and j < n);
 // kTail: some key of the sub-tile may be hidden or lie past the end.
-// A row starts from reference 0 and keeps it while its sum stays within 2^-60 .. 2^100, that is
-// nearly always: fp32 sums are as good at any magnitude, and terms below 2^-126 are nothing beside
-// 2^-60.  Outside (a logit outran the reference, all of them lie far below it, inf or NaN) the block is
-// redone with a reference of its own.
-constexpr uint32_t kSumLow = (127u - 60u) << 23, kSumHigh = (127u + 100u) << 23;      // the two bounds as float bits
+// A row starts from reference 0 and keeps it while its sum stays within 2^-24 .. 2^24, as it does in most
+// layers.  Outside (a logit outran the reference, all of them lie far below it, inf or NaN) the block is redone with
+// a reference of its own.  The bounds are narrow because an exponent is rounded at its distance from the
+// reference: with 2^-60 .. 2^100 rows whose largest logit exceeds some 35 (log2 units) got normalisers up to a quarter
+// further off than with references of their own from the first block on (2.85e-6 rms against 2.40e-6 at 72; 2.22e-6
+// with these bounds, which nowhere between logits of 2 and 92 are worse).
+constexpr uint32_t kSumLow = (127u - 24u) << 23, kSumHigh = (127u + 24u) << 23;      // the two bounds as float bits
 template <int MB, bool kTail>
 __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, float (&mref)[MB], float (&lsum)[MB],
                                            float cv, int n, int n_p, int c32, int hh) {
@@ -238,8 +240,11 @@ __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, floa
       float rmax = kMasked;
 #pragma unroll
       for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, hidden(v) ? kMasked : acc[nb][v] * cv);
-      sum = lsum[nb] == 0.f ? 0.f : lsum[nb] * fast_exp2(mref[nb] - rmax);      // (0 * 2^(mref - rmax) would be NaN from 2^128 on)
       if (rmax > kMasked) {               // (no key of the block is visible: nothing to refer to)
+        // the earlier terms, a half wave's share of a granule, are at most 2^10: some of them are as large as their
+        // sum by that, which the block's own largest logit need not be
+        if (lsum[nb] != 0.f) rmax = fmaxf(rmax, mref[nb] + (float)(__builtin_amdgcn_frexp_expf(lsum[nb]) - 10));
+        sum = lsum[nb] == 0.f ? 0.f : lsum[nb] * fast_exp2(mref[nb] - rmax);      // (0 * 2^(mref - rmax) would be NaN from 2^128 on)
         mref[nb] = rmax;
 #pragma unroll
         for (int v = 0; v < 16; ++v) sum += hidden(v) ? 0.f : fast_exp2(acc[nb][v] * cv - rmax);
@@ -408,8 +413,8 @@ __device__ __forceinline__ float combine_row(const float* p, int rows_per_slice,
   };
   merge(dpp_step<0xB1, 0xf, true>(m), dpp_step<0xB1, 0xf, true>(s), part & 1);      // quad_perm [1, 0, 3, 2]
   merge(dpp_step<0x4E, 0xf, true>(m), dpp_step<0x4E, 0xf, true>(s), part & 2);      // quad_perm [2, 3, 0, 1]
-  // log2 of the sum from its exponent and mantissa: the instruction's error is that of a value below 1
-  return (m + (float)__builtin_amdgcn_frexp_exp(s)) + __builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(s));
+  // log2 of the sum from its exponent and mantissa: the instruction's error is that of a value below 1; rounded once
+  return (float)((double)m + (double)__builtin_amdgcn_frexp_exp(s) + (double)__builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(s)));
 }
 
 __global__ __launch_bounds__(256) void scores_combine(ScoreArgs a, int rows_per_slice, int64_t total_rows) {

@@ -98,3 +98,29 @@ def test_misaligned_segments_are_rejected(cake):
     with pytest.raises(C.CakeError):
         C.cake_window_scores_finish(ep.shape, ep.params, 2, None, ep.workspace)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("spread,n", [(20.0, 4096 + 32), (16.0, 16384 + 32), (20.0, 1000)])
+def test_row_normalisers_of_peaked_rows(cake, spread, n):
+    """Rows whose largest logits lie some 40 to 100 (log2 units) above 0: the normalisers, which the segmented form leaves
+    at the start of the workspace, against float64.  One-hot queries make every logit a stored number times the scale.
+    Bound: the result's own rounding (half an ulp) and, of a sum relative to a reference that no term outruns by more
+    than 2^24, the rounding of the exponents (2^-20) and of the exponentials, partial sums and merges (some eight of 2^-23 / ln 2: few terms count)."""
+    say(f"normalisers of peaked rows, N={n}")
+    B, H, S_w, d = 2, 8, 32, 64
+    c = np.float32(0.125 * 1.4426950408889634)                   # the default scale of d = 64, in log2 units
+    rng = np.random.default_rng(n)
+    acc = np.zeros((B, H, n, d), dtype=np.float32)
+    acc[..., :S_w] = rng.standard_normal((B, H, n, S_w)) * spread / c
+    q = torch.eye(S_w, d, device=DEV).expand(B, H, S_w, d).contiguous()
+    k = torch.from_numpy(acc).to(DEV)
+    ev = cake.EvictionPass([q], [k], [k], S_w + n // 4)
+    ev.scores_segmented(cake.cake_scores_chunk_keys(ev.shape))
+    torch.cuda.synchronize()
+    got = ev.workspace[: B * H * S_w * 4].view(torch.float32).view(B, H, S_w).cpu().double().numpy()
+    t = acc[..., :S_w].transpose(0, 1, 3, 2).astype(np.float64) * float(c)
+    t = np.where(np.arange(n) <= n - S_w + np.arange(S_w)[:, None], t, -np.inf)       # key j is visible to row r up to n - S_w + r
+    top = t.max(axis=-1, keepdims=True)
+    want = top[..., 0] + np.log2(np.exp2(t - top).sum(axis=-1))
+    bound = 0.5 * np.spacing(np.abs(want).astype(np.float32)).astype(np.float64) + 2.0 ** -20 + 8 * 2.0 ** -23 * 1.4427
+    assert top.max() > 60.0 and np.all(np.abs(got - want) <= bound), np.max(np.abs(got - want) / bound)
