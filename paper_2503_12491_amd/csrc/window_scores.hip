@@ -247,7 +247,7 @@ __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, floa
         sum = lsum[nb] == 0.f ? 0.f : lsum[nb] * fast_exp2(mref[nb] - rmax);      // (0 * 2^(mref - rmax) would be NaN from 2^128 on)
         mref[nb] = rmax;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) sum += hidden(v) ? 0.f : fast_exp2(acc[nb][v] * cv - rmax);
+        for (int v = 0; v < 16; ++v) sum += hidden(v) ? 0.f : fast_exp2(fmaf(acc[nb][v], cv, -rmax));      // not from the rounded products
       } else {
         sum = lsum[nb];
       }
