@@ -32,7 +32,7 @@ struct QuantArgs {
   const void* const* v_hat;
   uint8_t* const* k_codes; float* const* k_scale; float* const* k_zero;
   uint8_t* const* v_codes; float* const* v_scale; float* const* v_zero;
-  int32_t batch, h_kv, bits, n_entries;
+  int32_t batch, h_kv, n_entries;
   int32_t cap[kMaxLaunchLayers];
   int32_t keep[kMaxLaunchEntries];                 // [layer of the launch][sequence]
   // workgroups before those of entry e: a workgroup serves kGroupsPerBlock consecutive token groups of
@@ -299,7 +299,7 @@ extern "C" int cake_quantize_kv(const cake_shape* shape, int32_t bits,
     a.k_hat = k_hat + l0; a.v_hat = v_hat + l0;
     a.k_codes = k_codes + l0; a.k_scale = k_scale + l0; a.k_zero = k_zero + l0;
     a.v_codes = v_codes + l0; a.v_scale = v_scale + l0; a.v_zero = v_zero + l0;
-    a.batch = B; a.h_kv = shape->n_kv_heads; a.bits = bits; a.n_entries = nl * B;
+    a.batch = B; a.h_kv = shape->n_kv_heads; a.n_entries = nl * B;
     int64_t n_blocks = 0;
     for (int ll = 0; ll < nl; ++ll) {
       int ck = 0;

@@ -92,8 +92,6 @@ struct ScoreArgs {
   const void* const* q_win;
   const void* const* k;
   float* const* indicator;
-  const void *q_one, *k_one;   // a single layer whose buffers the host knows: used where the tables are NULL
-  float* ind_one;
   int64_t qs[3], ks[3];      // element strides: batch, head, token
   int32_t batch, h_kv, group, n, n_p, chunk, wg_keys, granule, n_granules, n_granules_p, pool;   // wg_keys: keys per workgroup, granules each
   int32_t key_lo, key_hi;    // keys [key_lo, key_hi) are behind the k pointers (row 0 = key key_lo); the whole layer: 0, n
@@ -108,9 +106,6 @@ struct ScoreArgs {
   float* hv;                 // [slice][n_granules_p][G][2]
   float* raw;                // [slice][n_p]
 };
-
-__device__ __forceinline__ const void* layer_q(const ScoreArgs& a, int l) { return a.q_win ? a.q_win[l] : a.q_one; }
-__device__ __forceinline__ const void* layer_k(const ScoreArgs& a, int l) { return a.k ? a.k[l] : a.k_one; }
 
 // Transfer of keys [t0, t0+64) of one slice into an LDS tile.  The tile is moved as 1 KiB
 // groups, one wave-wide instruction each, group i by wave i mod G.  Lane j of a group fills LDS
@@ -304,10 +299,10 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass1(ScoreArgs a) 
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
-  const T* q = reinterpret_cast<const T*>(layer_q(a, l)) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
+  const T* q = reinterpret_cast<const T*>(a.q_win[l]) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
   const int64_t tok_bytes = a.ks[2] * (int64_t)sizeof(T);
   // address of key 0 of the slice (keys below key_lo are not behind the pointer and never touched)
-  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(layer_k(a, l)) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
+  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k[l]) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
                       (int64_t)a.key_lo * tok_bytes;
 
   const int key0 = a.key0 + blockIdx.x * a.wg_keys;
@@ -561,10 +556,10 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
-  const T* q = reinterpret_cast<const T*>(layer_q(a, l)) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
+  const T* q = reinterpret_cast<const T*>(a.q_win[l]) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
   const int64_t tok_bytes = a.ks[2] * (int64_t)sizeof(T);
   // address of key 0 of the slice (keys below key_lo are not behind the pointer and never touched)
-  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(layer_k(a, l)) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
+  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k[l]) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
                       (int64_t)a.key_lo * tok_bytes;
 
   const int key0 = a.key0 + blockIdx.x * a.wg_keys;
@@ -788,7 +783,7 @@ __global__ __launch_bounds__(256) void pool_indicator(ScoreArgs a, PrefArgs pa, 
   const int j0 = blockIdx.x * kPoolSpan;
   const int span = min(kPoolSpan, a.n_p - j0);
   const float* raw = a.raw + (int64_t)slice * a.n_p;
-  float* out = (a.indicator ? a.indicator[l] : a.ind_one) + ((int64_t)b * a.h_kv + g) * a.n_p;
+  float* out = a.indicator[l] + ((int64_t)b * a.h_kv + g) * a.n_p;
   // Rows of a multiple of four positions at 16-byte aligned addresses, windows of at most nine:
   // 16-byte loads and stores, four outputs per lane from three 16-byte LDS reads.
   const bool quads = a.n_p % 4 == 0 && half <= kPoolQuadHalf &&
@@ -865,8 +860,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
                   hipStream_t stream) {
   ScoreArgs a = a_in;
   const bool packing = a_in.pack > 1;
-  auto set_pack = [&](int pass, dim3& block, unsigned& gy, size_t& packed_bytes) {
-    (void)pass;
+  auto set_pack = [&](dim3& block, unsigned& gy, size_t& packed_bytes) {
     a.pack = packing ? slices_per_workgroup(a.group) : 1;
     block = dim3(64 * a.group * a.pack);
     gy = (unsigned)((n_slices + a.pack - 1) / a.pack);
@@ -888,7 +882,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     return (unsigned)((hi - lo + a.wg_keys - 1) / a.wg_keys);
   };
   auto run_pass1 = [&](int lo, int hi) -> hipError_t {
-    set_pack(1, block, gy, packed_bytes);
+    set_pack(block, gy, packed_bytes);
     const unsigned chunks = set_span(lo, hi);
     if constexpr (can_pack<T, MB>()) {
       if (a.pack > 1) {
@@ -903,7 +897,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     return hipSuccess;
   };
   auto run_pass2 = [&](int lo, int hi) -> hipError_t {
-    set_pack(2, block, gy, packed_bytes);
+    set_pack(block, gy, packed_bytes);
     const unsigned chunks = set_span(lo, hi);
     if constexpr (can_pack<T, MB>()) {
       if (a.pack > 1) {
@@ -939,7 +933,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     CAKE_HIP_TRY(run_pass1(0, a.n));
     mark(1, stream);
     // every workgroup of pass 2 reads its slice's pairs where it combines them itself: at most 16 MB in all
-    set_pack(2, block, gy, packed_bytes);
+    set_pack(block, gy, packed_bytes);
     const int64_t workgroups = (int64_t)gy * set_span(0, a.n_p);
     a.combine = can_combine<T, MB>() && workgroups * a.pack * rows * a.n_granules * 8 <= 16 << 20;
     if (!a.combine)
