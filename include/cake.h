@@ -298,8 +298,8 @@ int cake_compact_kv(const cake_shape* shape,
  *   compacted host [n_layers] or NULL (= all 0): 1 marks a layer whose k_in/v_in are themselves
  *             outputs of an earlier cake_evict_planned, contiguous [B, H_kv, cap_cur[l] + S_w, d]
  *             (cap_cur from this plan: the capacities are only known on the device); its strides
- *             are derived from the plan instead of kv_strides.  This is what lets the stages of
- *             the cascade (Alg. 1) follow one another without the host reading anything back.
+ *             are derived from the plan instead of kv_strides.  With it the stages of a
+ *             cascade (Alg. 1) can follow one another without the host reading anything back.
  *
  * cake_plan_layout gives the byte offsets of the plan's ten parts for `shape` (n_layers, batch):
  * budgets, keep, cur_len, cap_keep, cap_cur, copy_blocks, then the idx, k_out, v_out and ind_out

@@ -122,9 +122,9 @@ def test_cascade_with_handed_over_row_lse_equals_one_shot(cake):
 
 @pytest.mark.parametrize("name", ["tiny", "llama_reduced", "window64", "everything_fits_at_first", "batch3_group5"])
 def test_device_cascade_equals_host_cascade_and_one_shot(cake, name):
-    """DeviceCascade (stages chained on the device: plan over the layers seen so far, earlier layers
-    re-evicted from their compacted caches with strides taken from the plan) against the host-driven
-    CascadeSession stage by stage in the end result, and against the one-shot pass (Thm. 2)."""
+    """DeviceCascade (stages chained on the device: plan over the layers seen so far, rows kept in a store and lists
+    of their places renewed by every stage) against the host-driven CascadeSession in the end result, and against
+    the one-shot pass (Thm. 2)."""
     cfg = {"tiny": CONFIGS[1],
            "llama_reduced": CONFIGS[2].scaled(n_layers=6, seq_len=2048 + 32 + 9, total_budget=6 * 300),
            "window64": CONFIGS[4].scaled(n_layers=5, seq_len=4096 + 64 + 3, total_budget=5 * 500),

@@ -182,3 +182,60 @@ def test_planned_rows_of_any_length_whatever_the_shape_says(cake, n, seq_len):
                 assert torch.equal(i_out[b, h, :m], ind[l][b, h][want.long()])
                 assert torch.equal(k_out[b, h, : m + S_w], k[l][b, h][src]) and torch.equal(v_out[b, h, : m + S_w], v[l][b, h][src])
         before += c
+
+
+def test_layers_evicted_again_from_the_outputs_of_an_earlier_plan(cake):
+    """`compacted` layers: a second plan takes the first one's counts and output tables as device pointers
+    (cake_plan_layout), beside a layer that is evicted for the first time, with nothing read back in between."""
+    from paper_2503_12491_amd import binding as C
+    say("two plans in a row")
+    L, B, H, d, S_w, n = 3, 2, 2, 64, 32, 700
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    k, v = ([torch.randn(B, H, n + S_w, d, device=DEV, generator=gen) for _ in range(L)] for _ in range(2))
+    ind = [torch.exp(torch.randn(B, H, n, device=DEV, generator=gen)) for _ in range(L)]
+    strides = [k[0].stride(0), k[0].stride(1), k[0].stride(2)]
+    pref = torch.tensor([[3.0, 1.0, 2.0], [1.0, 2.5, 1.0]], dtype=torch.float64, device=DEV)
+    total = 900
+    tables = [C.ptr_table(t) for t in (ind, k, v)]
+    cur = torch.full((L * B,), n, dtype=torch.int32, device=DEV)
+    before = [np.arange(n) for _ in range(L * B * H)]                # prompt positions of the rows held, per (layer, sequence, head)
+    kept_before = np.full((L, B), n)
+    for layers in (2, 3):
+        shape = C.make_shape(B, layers, H, H, d, n + S_w, S_w, torch.float32)
+        rows = B * total
+        pools = [torch.zeros(B * H * rows, dtype=torch.int32, device=DEV)] + [
+            torch.full((B * H * (rows + layers * S_w) * d,), float("nan"), device=DEV) for _ in range(2)] + [
+            torch.full((B * H * rows,), float("nan"), device=DEV)]
+        plan = torch.zeros(C.cake_plan_bytes(shape), dtype=torch.uint8, device=DEV)
+        status = torch.zeros(B, dtype=torch.int32, device=DEV)
+        C.cake_plan_eviction(shape, pref[:, :layers].contiguous(), total, cur, *pools, plan, status)
+        C.cake_evict_planned(shape, *tables, strides, plan, compacted=[1] * 2 + [0] if layers == 3 else None)
+        # the next plan's lengths and inputs: this one's counts and outputs, then the new layer's
+        lay = C.cake_plan_layout(shape)
+        part = lambda name, words: plan[lay[name]: lay[name] + words].clone()
+        if layers == 2:
+            cur = torch.cat([part("keep", layers * B * 4).view(torch.int32), cur[layers * B:]])
+            tables = [torch.cat([part(name, layers * 8).view(torch.int64), t[layers:]]) for name, t in zip(("ind_out", "k_out", "v_out"), tables)]
+            first = pools                                             # alive until the second eviction has read them
+        torch.cuda.synchronize()
+        _, keep, cur_out, cap_keep = C.plan_fields(plan.cpu(), layers, B)
+        assert np.array_equal(cur_out, kept_before[:layers]) and np.all(keep < cur_out) and status.tolist() == [0] * B
+        at = 0
+        for l in range(layers):
+            c = int(cap_keep[l])
+            idx, i_out = (p[B * H * at: B * H * (at + c)].view(B, H, c) for p in (pools[0], pools[3]))
+            o = B * H * (at + l * S_w) * d
+            k_out, v_out = (p[o: o + B * H * (c + S_w) * d].view(B, H, c + S_w, d) for p in pools[1:3])
+            for b in range(B):
+                m = int(keep[l, b])
+                for h in range(H):
+                    e = (l * B + b) * H + h
+                    want = co.select_topk(ind[l][b, h].cpu().double().numpy()[before[e]], m)
+                    assert np.array_equal(idx[b, h, :m].cpu().numpy(), want), (layers, l, b, h)
+                    before[e] = before[e][want]
+                    src = torch.from_numpy(np.concatenate([before[e], np.arange(n, n + S_w)])).to(DEV)
+                    assert torch.equal(i_out[b, h, :m], ind[l][b, h][src[:m]])
+                    assert torch.equal(k_out[b, h, : m + S_w], k[l][b, h][src]) and torch.equal(v_out[b, h, : m + S_w], v[l][b, h][src])
+            at += c
+        kept_before[:layers] = keep
+    del first
