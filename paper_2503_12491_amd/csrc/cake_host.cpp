@@ -60,7 +60,8 @@ ScoreLayout score_layout(const cake_shape& s) {
   // bit-identical) whether it is scored alone (cascading) or batched with other layers.  The granule
   // is what a single layer is cut into: small enough that 8K keys of 8 heads fill the chip with one
   // workgroup per compute unit, large enough that the pairs of the long contexts stay a fraction of
-  // the keys' bytes.
+  // the keys' bytes.  (A layer of 8 heads alone has 256 to 512 workgroups from 8K to 16383 keys, 128 to 256 from
+  // there to 32767, as many as its chunks were before there were granules; of fewer heads accordingly fewer.)
   const int chunk = s.seq_len >= 32768 ? 2048 : s.seq_len >= 8192 ? 1024 : s.seq_len >= 2048 ? 512 : 256;
   const int granule = s.seq_len >= 65536 ? 2048 : s.seq_len >= 16384 ? 1024 : s.seq_len >= 2048 ? 256 : s.window > 32 ? 128 : 64;
   w.chunk = chunk;
