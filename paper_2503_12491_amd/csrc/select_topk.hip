@@ -14,10 +14,11 @@
 // descending, position ascending).
 //
 // What bounds it is latency, a chain of barriers and LDS round trips: 992 entries 19 -> 5.9 us, 1024
-// rows of 4061 89 -> 15 us, 256 rows of 32736 38 -> 21 us and of 131008 122 -> 90 us (where reading the
+// rows of 4061 89 -> 15 us, 256 rows of 32736 38 -> 21 us and of 131008 106 -> 71 us (where reading the
 // row twice at the 35 bytes/ns a compute unit gets is most of it), against four sweeps of the row with a
 // one-wave search of every histogram.
 #include <algorithm>
+#include <type_traits>
 
 #include "cake_internal.h"
 
@@ -401,13 +402,12 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
   // Digits of 11, 11 and 10 bits from the top, one sweep of the row each, until the entries of the
   // digit that holds the k-th largest fit the list (the first sweep nearly always does it) or the key
   // is known to the last bit.  Where those above it fit as well, the list takes the row's place.
+  // Too many entries of one digit are mostly one value (an indicator that is 0 nearly everywhere): the second
+  // sweep looks whether they are, and then knows the key.
   uint32_t prefix = 0, mask = 0, need = (uint32_t)t.keep;
-  bool fits = false, all_fit = false;
-  for (int pass = 0; pass < 3 && !fits; ++pass) {
-    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
-    const uint32_t digit_mask = pass == 2 ? 1023u : 2047u;
-    for (int i = tid; i < kBins * kCopies / 4; i += kLongThreads) reinterpret_cast<uint4*>(s.hist)[i] = uint4{0, 0, 0, 0};
-    __syncthreads();
+  bool fits = false, all_fit = false, one_value = false;
+  uint32_t ones = 0, zeros = 0;                          // bits set, and not set, in some entry of the digit at hand
+  auto count_digits = [&](auto first, int shift, uint32_t digit_mask) {
     for (int s0 = tid; s0 < row.n_slots; s0 += kLongThreads * kLongSlots) {
       uint32_t key[kLongSlots][4];
       row.load(kLongSlots, [&](int u) { return s0 + u * kLongThreads; }, key);
@@ -415,7 +415,11 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
       for (int u = 0; u < kLongSlots; ++u) {
         uint32_t d[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) d[j] = key[u][j] != 0u && (key[u][j] & mask) == prefix ? key[u][j] >> shift & digit_mask : kBins;
+        for (int j = 0; j < 4; ++j) {
+          const bool in = key[u][j] != 0u && (first || (key[u][j] & mask) == prefix);
+          d[j] = in ? key[u][j] >> shift & digit_mask : kBins;
+          if (!first && in) { ones |= key[u][j]; zeros |= ~key[u][j]; }
+        }
         if (d[0] == d[1] && d[1] == d[2] && d[2] == d[3]) {
           if (d[0] < kBins) atomicAdd(&s.hist[d[0] * kCopies + copy], 4u);
         } else {
@@ -425,19 +429,41 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
         }
       }
     }
+  };
+  for (int pass = 0; pass < 3 && !fits && !one_value; ++pass) {
+    const int shift = pass == 0 ? 21 : pass == 1 ? 10 : 0;
+    const uint32_t digit_mask = pass == 2 ? 1023u : 2047u;
+    for (int i = tid; i < kBins * kCopies / 4; i += kLongThreads) reinterpret_cast<uint4*>(s.hist)[i] = uint4{0, 0, 0, 0};
+    __syncthreads();
+    if (pass == 0) {
+      count_digits(std::true_type{}, shift, digit_mask);
+    } else {
+      ones = zeros = 0;
+      count_digits(std::false_type{}, shift, digit_mask);
+      auto bits_or = [](uint32_t a, uint32_t b) { return a | b; };
+      ones = wave_scan(ones, bits_or);
+      zeros = wave_scan(zeros, bits_or);
+      if (lane == 63) { s.few[2 * wave] = ones; s.few[2 * wave + 1] = zeros; }
+    }
     __syncthreads();
     find_interval<kLongThreads>(need, s);
+    if (pass == 1) {
+      ones = zeros = 0;
+#pragma unroll
+      for (int w = 0; w < kMaxWaves; ++w) { ones |= s.few[2 * w]; zeros |= s.few[2 * w + 1]; }
+      one_value = (ones & zeros) == 0u;
+    }
     prefix |= s.bin << shift;
     need -= s.above;
     mask |= digit_mask << shift;
     fits = s.count <= (uint32_t)kListKeys;
     all_fit = (uint32_t)t.keep - need + s.count <= (uint32_t)kListKeys;
+    if (one_value) prefix = ones;
   }
-  // Ordered sweep of the row; returns the number of entries picked.
-  auto sweep = [&](auto pick, auto store) {
-    uint32_t before = 0;
+  // Ordered sweep of the row from slot `from` on, `before` entries picked ahead of it; returns the number of entries picked.
+  auto sweep = [&](auto pick, auto store, int from = 0, uint32_t before = 0) {
     int parity = 0;
-    for (int t0 = 0; t0 < row.n_slots; t0 += kLongThreads * kLongSlots, parity ^= 1) {
+    for (int t0 = from; t0 < row.n_slots; t0 += kLongThreads * kLongSlots, parity ^= 1) {
       uint32_t key[kLongSlots][4];
       auto slot = [&](int u) { return t0 + wave * 64 * kLongSlots + u * 64 + lane; };
       row.load(kLongSlots, slot, key);
@@ -482,8 +508,56 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
       return;
     }
   } else {
-    sweep([&](uint32_t x, int) { return x == thr; }, [&](uint32_t rank, uint32_t, int pos) { if (rank + 1 == need) s.last = pos; });
-    last = s.last;
+    // The key is known: every entry above it and the first `need` equal to it, in one ordered sweep; behind the last of
+    // those that are equal only the ones above count.  Counts of a step travel as two halves of a word, at most 16 waves
+    // * 1024 entries each.  With two sweeps here and all three digits counted 8 rows of 131008 equal entries took 116 us, now
+    // 52, and rows of zeros with every 200th entry above them 124, now 77 (four sweeps: 80 and 89).
+    static_assert(kMaxWaves * 64 * kLongSlots * 4 < 1 << 16, "two counts of a step in one word");
+    uint32_t above = 0, equal = 0;                       // in the row before this step
+    int t0 = 0, parity = 0;
+    for (; equal < need && t0 < row.n_slots; t0 += kLongThreads * kLongSlots, parity ^= 1) {
+      uint32_t key[kLongSlots][4];
+      auto slot = [&](int u) { return t0 + wave * 64 * kLongSlots + u * 64 + lane; };
+      row.load(kLongSlots, slot, key);
+      uint32_t n = 0;
+#pragma unroll
+      for (int u = 0; u < kLongSlots; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) n += __popcll(__ballot(key[u][j] > thr)) + (__popcll(__ballot(key[u][j] == thr)) << 16);
+      if (lane == 0) s.wave_sel[parity][wave] = n;
+      __syncthreads();
+      uint32_t g = above, e = equal;                     // before the wave's entries
+#pragma unroll
+      for (int w = 0; w < kMaxWaves; ++w) {
+        const uint32_t c = s.wave_sel[parity][w];
+        above += c & 0xffffu;
+        equal += c >> 16;
+        if (w < wave) { g += c & 0xffffu; e += c >> 16; }
+      }
+#pragma unroll
+      for (int u = 0; u < kLongSlots; ++u) {
+        uint32_t rank_g = g, rank_e = e;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint64_t bg = __ballot(key[u][j] > thr), be = __ballot(key[u][j] == thr);
+          rank_g = __builtin_amdgcn_mbcnt_hi((uint32_t)(bg >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bg, rank_g));
+          rank_e = __builtin_amdgcn_mbcnt_hi((uint32_t)(be >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)be, rank_e));
+          g += __popcll(bg);
+          e += __popcll(be);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool is_above = key[u][j] > thr, is_equal = key[u][j] == thr;
+          if (is_above || (is_equal && rank_e < need)) t.out[rank_g + min(rank_e, need)] = 4 * slot(u) - row.pad + j;
+          rank_g += is_above ? 1u : 0u;
+          rank_e += is_equal ? 1u : 0u;
+        }
+      }
+    }
+    __syncthreads();                                     // the counts of the last step have been read
+    if (above + need < (uint32_t)t.keep)
+      sweep([&](uint32_t x, int) { return x > thr; }, [&](uint32_t rank, uint32_t, int pos) { t.out[rank] = pos; }, t0, above + need);
+    return;
   }
   sweep([&](uint32_t x, int pos) { return x > thr - (pos <= last ? 1u : 0u); }, [&](uint32_t rank, uint32_t, int pos) { t.out[rank] = pos; });
 }

@@ -29,6 +29,10 @@ def _values(kind, heads, n, rng):
         return rng.choice([-1.0, -0.0, 0.0, 1e-30, 3.0], size=(heads, n))
     if kind == "narrow":                                          # neighbouring floats: every interval but the last rounds is one key
         return 1.0 + rng.integers(0, 40, size=(heads, n)) * 2.0 ** -23
+    if kind == "pair":                                            # two neighbouring floats: more than the list of either
+        return 1.0 + rng.integers(0, 2, size=(heads, n)) * 2.0 ** -23
+    if kind == "zeros":                                           # 0 nearly everywhere, the entries above it anywhere
+        return np.where(rng.random((heads, n)) < 0.999, 0.0, rng.random((heads, n)))
     return rng.standard_normal((heads, n)) * 10.0 ** rng.integers(-30, 30, size=(heads, n))     # the whole range of a float
 
 
@@ -39,7 +43,7 @@ def test_selection_is_the_ordered_top_k(cake, n, ks):
     say(f"top-k of rows of {n}")
     rng = np.random.default_rng(n)
     heads = 4                                                     # odd n: the four rows start at all four alignments
-    for kind in ("pooled", "constant", "few", "narrow", "wide"):
+    for kind in ("pooled", "constant", "few", "narrow", "pair", "zeros", "wide"):
         vals = _values(kind, heads, n, rng).astype(np.float32)
         ind = torch.tensor(vals, device=DEV)[None]
         for k in ks:
