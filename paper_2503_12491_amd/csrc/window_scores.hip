@@ -869,21 +869,40 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   dim3 block;
   unsigned gy;
   size_t packed_bytes;
-  // Keys per workgroup: as many granules as leave the chip eight workgroups per compute unit, so that a
-  // workgroup's prologue (its queries, the first tile's way from memory) is paid as rarely as the size
-  // allows; a single layer's 8K keys take 256 workgroups of one granule instead of 64 of four (pass 1
-  // 20 -> 10 us, pass 2 24 -> 10.7 us).  Sums are kept per granule, whoever computes it.
-  auto set_span = [&](int lo, int hi) -> unsigned {
-    const int64_t want = 8 * 256;
-    int per = a.chunk / a.granule;
-    while (per > 1 && (int64_t)gy * ((hi - lo + per * a.granule - 1) / (per * a.granule)) < want) per >>= 1;
+  // Keys per workgroup: the chunk's granules, or a half or quarter of them where that shortens the rounds of workgroups
+  // over the chip.  A workgroup's prologue (its queries, the first tile's way from memory) counts as a tile of keys.  A
+  // compute unit holds as many workgroups as LDS and the registers of the pass allow; those of five and more heads of 64
+  // window rows count as all it holds, and in fp32, whose products keep a matrix core busy with one wave, those of three and
+  // more heads (of 32 rows of 64: six).  A single layer's 8K keys take 256 workgroups of one granule instead of 64 of four
+  // (pass 1 20 -> 10 us, pass 2 24 -> 10.7 us).  Cutting until there were 2048 workgroups, whatever the chip holds, was up
+  // to 36 % slower than whole chunks (16 layers of 6007 keys, 4 heads of 64 in fp32: 156 us against 115, by this rule 116; 8
+  // layers of 4093, 4 x 8 heads of 128 in bf16, 64 rows: 72 against 66, now 61); whole chunks alone are slower where they
+  // leave a round half empty (8 layers of 40000, 4 x 5 heads of 128, 64 rows: 405 us against 359).
+  // Sums are kept per granule, whoever computes it.
+  auto set_span = [&](int pass, int lo, int hi) -> unsigned {
+    constexpr bool kF32 = sizeof(T) == 4, kSmall = D == 64, kWide = MB == 2;
+    constexpr int kWaves1 = kF32 ? (kWide ? (kSmall ? 3 : 2) : (kSmall ? 4 : 3)) : (kWide ? (kSmall ? 4 : 3) : (kSmall ? 6 : 5));
+    constexpr int kWaves2 = kWide ? 2 : kF32 ? (kSmall ? 4 : 2) : (kSmall ? 5 : 4);      // waves per SIMD
+    constexpr int kLds = 2 * Tile<T, D>::kBytes + (int)sizeof(float) * 2 * 8 * kTileKeys;
+    const int by_waves = 4 * (pass == 1 ? kWaves1 : kWaves2) / a.group;
+    const bool alone = a.pack > 1 || a.group > (kF32 ? (kSmall && !kWide ? 5 : 2) : kWide ? 4 : 8);
+    const int64_t slots = 256 * (alone ? 1 : std::max(1, std::min(160 * 1024 / kLds, by_waves)));
+    int64_t least = INT64_MAX;
+    int best = 1;
+    for (int per = a.chunk / a.granule; per >= 1; per >>= 1) {
+      const int keys = per * a.granule, rest = (hi - lo) % keys;
+      const int64_t whole = (int64_t)gy * ((hi - lo) / keys), rounds = (whole + slots - 1) / slots;
+      // the shorter workgroups at the slices' ends: beside the last round, or a round of their own
+      const int64_t cost = rounds * (keys + kTileKeys) + (rest > 0 && whole + gy > rounds * slots ? rest + kTileKeys : 0);
+      if (cost < least) { least = cost; best = per; }
+    }
     a.key0 = lo;
-    a.wg_keys = per * a.granule;
+    a.wg_keys = best * a.granule;
     return (unsigned)((hi - lo + a.wg_keys - 1) / a.wg_keys);
   };
   auto run_pass1 = [&](int lo, int hi) -> hipError_t {
     set_pack(block, gy, packed_bytes);
-    const unsigned chunks = set_span(lo, hi);
+    const unsigned chunks = set_span(1, lo, hi);
     if constexpr (can_pack<T, MB>()) {
       if (a.pack > 1) {
         auto kern = scores_pass1<T, D, MB, true>;
@@ -898,7 +917,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   };
   auto run_pass2 = [&](int lo, int hi) -> hipError_t {
     set_pack(block, gy, packed_bytes);
-    const unsigned chunks = set_span(lo, hi);
+    const unsigned chunks = set_span(2, lo, hi);
     if constexpr (can_pack<T, MB>()) {
       if (a.pack > 1) {
         auto kern = scores_pass2<T, D, MB, kPivot, true>;
@@ -934,7 +953,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     mark(1, stream);
     // every workgroup of pass 2 reads its slice's pairs where it combines them itself: at most 16 MB in all
     set_pack(block, gy, packed_bytes);
-    const int64_t workgroups = (int64_t)gy * set_span(0, a.n_p);
+    const int64_t workgroups = (int64_t)gy * set_span(2, 0, a.n_p);
     a.combine = can_combine<T, MB>() && workgroups * a.pack * rows * a.n_granules * 8 <= 16 << 20;
     if (!a.combine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
