@@ -891,9 +891,11 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     int best = 1;
     for (int per = a.chunk / a.granule; per >= 1; per >>= 1) {
       const int keys = per * a.granule, rest = (hi - lo) % keys;
-      const int64_t whole = (int64_t)gy * ((hi - lo) / keys), rounds = (whole + slots - 1) / slots;
-      // the shorter workgroups at the slices' ends: beside the last round, or a round of their own
-      const int64_t cost = rounds * (keys + kTileKeys) + (rest > 0 && whole + gy > rounds * slots ? rest + kTileKeys : 0);
+      const int64_t whole = (int64_t)gy * ((hi - lo) / keys), all = whole + (rest > 0 ? gy : 0);
+      // The shorter workgroups at the slices' ends run beside the last round or as a round of their own; where one fills a
+      // compute unit they take a place in the order of dispatch like any other.
+      const int64_t rounds = ((alone ? all : whole) + slots - 1) / slots;
+      const int64_t cost = rounds * (keys + kTileKeys) + (all > rounds * slots ? rest + kTileKeys : 0);
       if (cost < least) { least = cost; best = per; }
     }
     a.key0 = lo;
