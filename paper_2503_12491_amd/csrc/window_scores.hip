@@ -38,6 +38,7 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) const void* global_cptr;
 typedef __attribute__((address_space(3))) void* lds_ptr;
 
@@ -74,17 +75,26 @@ template <> struct Frag<__bf16> {
     return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
   }
 };
+// Four 32x32x2 products in a row: a lane's share of eight reduction elements is one 16-byte piece, read at once.  (With a
+// 4-byte read per product the addresses of all pieces took 16 to 32 registers: 900 bytes a lane were spilled at two row blocks
+// of 128, and one row block ran two waves per SIMD instead of three.  8 layers of 6000 keys, 8 x 4 heads, 64 rows of 128:
+// pass 1 322 -> 217 us, pass 2 446 -> 223; 32 rows of 64: 69 -> 61 and 74 -> 68; one layer of 1024 keys, 8 x 4 heads, 32 rows of
+// 128: 17 -> 11 and 19 -> 13.)
 template <> struct Frag<float> {
-  using type = float;
-  static constexpr int kElems = 2;
-  static __device__ __forceinline__ type load_global(const float* row, int step, int hh) { return row[step * 2 + hh]; }
+  using type = f32x4;
+  typedef float loose __attribute__((ext_vector_type(4), aligned(4)));
+  static constexpr int kElems = 8;
+  static __device__ __forceinline__ type load_global(const float* row, int step, int hh) {
+    return *reinterpret_cast<const loose*>(row + step * 8 + hh * 4);
+  }
   template <typename TL>
   static __device__ __forceinline__ type load_lds(const char* tile, int r, int step, int hh) {
-    const int e = step * 2 + hh;
-    return *reinterpret_cast<const float*>(tile + TL::offset(r, e >> 2) + (e & 3) * 4);
+    return *reinterpret_cast<const f32x4*>(tile + TL::offset(r, 2 * step + hh));
   }
   static __device__ __forceinline__ f32x16 mfma(type a, type b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], c, 0, 0, 0);
+    return c;
   }
 };
 
@@ -881,8 +891,8 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   // Sums are kept per granule, whoever computes it.
   auto set_span = [&](int pass, int lo, int hi) -> unsigned {
     constexpr bool kF32 = sizeof(T) == 4, kSmall = D == 64, kWide = MB == 2;
-    constexpr int kWaves1 = kF32 ? (kWide ? (kSmall ? 3 : 2) : (kSmall ? 4 : 3)) : (kWide ? (kSmall ? 4 : 3) : (kSmall ? 6 : 5));
-    constexpr int kWaves2 = kWide ? 2 : kF32 ? (kSmall ? 4 : 2) : (kSmall ? 5 : 4);      // waves per SIMD
+    constexpr int kWaves1 = kF32 ? (kWide ? (kSmall ? 3 : 2) : (kSmall ? 5 : 4)) : (kWide ? (kSmall ? 4 : 3) : (kSmall ? 6 : 5));
+    constexpr int kWaves2 = kWide ? 2 : kF32 ? (kSmall ? 4 : 3) : (kSmall ? 5 : 4);      // waves per SIMD
     constexpr int kLds = 2 * Tile<T, D>::kBytes + (int)sizeof(float) * 2 * 8 * kTileKeys;
     const int by_waves = 4 * (pass == 1 ? kWaves1 : kWaves2) / a.group;
     const bool alone = a.pack > 1 || a.group > (kF32 ? (kSmall && !kWide ? 5 : 2) : kWide ? 4 : 8);
