@@ -106,7 +106,6 @@ struct ScoreArgs {
   int32_t batch, h_kv, group, n, n_p, chunk, wg_keys, granule, n_granules, n_granules_p, pool;   // wg_keys: keys per workgroup, granules each
   int32_t key_lo, key_hi;    // keys [key_lo, key_hi) are behind the k pointers (row 0 = key key_lo); the whole layer: 0, n
   int32_t key0;              // first key of the first workgroup of a launch
-  bool combine;              // pass 2 combines the pairs of pass 1 by itself
   int32_t n_slices, pack;    // slices in all; slices that share a workgroup (packed kernels), else 1
   float c;                   // scale * log2(e): logits are handled in the log2 domain
   float inv_sw, inv_swc, inv_g;
@@ -388,38 +387,130 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass1(ScoreArgs a) 
   }
 }
 
-// Combine the granules' pairs of a window row into lse2 = log2 sum_j 2^(t_j).  Four lanes share
+// Combine the granules' pairs of a window row into lse2 = log2 sum_j 2^(t_j).  Four chains share
 // a row: each folds every fourth granule into a running (reference, sum) pair in one sweep, the four
-// pairs are merged in a fixed order.  p: the row's first pair; all four lanes get the result.
-__device__ __forceinline__ float combine_row(const float* p, int rows_per_slice, int n_granules, int part) {
-  constexpr int kAhead = 8;               // pairs in flight per lane
-  float m = kMasked;
-  double s = 0.0;
-  for (int c0 = part; c0 < n_granules; c0 += 4 * kAhead) {
-    float2 pc[kAhead];
+// pairs are merged in a fixed order, so that the result does not depend on how the chains are dealt to lanes: kChains
+// of a lane's own (4, 2 or 1), the others' from `partner`, which returns another lane's value and whether that lane's
+// chains come first.  p: the row's first pair; chain0: the lane's first chain; all of a row's lanes get the result.
+// Bound by latency: a chain of loads, then of fp64 additions.  With four lanes a row and 16 rows a turn, pass 2 of one layer of
+// 8192 keys waited 5.6 us for its first tile (8 x 4 heads of 128; 16.5 us in all, now 12.6).
+constexpr int kCombineAhead = 8;          // pairs in flight per chain
+template <int kChains>
+struct RowPairs {
+  float2 x[kChains][kCombineAhead];
+  // the pairs of granules from `first` on; past the last one it is repeated, until drop_absent
+  __device__ __forceinline__ void load(const float* p, int rows_per_slice, int n_granules, int first, int chain0) {
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) {
-      pc[u] = make_float2(kMasked, 0.f);
-      if (c0 + 4 * u < n_granules) pc[u] = *reinterpret_cast<const float2*>(p + (int64_t)(c0 + 4 * u) * rows_per_slice * 2);
-    }
-    float top = m;
+    for (int u = 0; u < kCombineAhead; ++u)
 #pragma unroll
-    for (int u = 0; u < kAhead; ++u) top = fmaxf(top, pc[u].x);
-    s *= (double)fast_exp2(m - top);
-    m = top;
-#pragma unroll
-    for (int u = 0; u < kAhead; ++u) s += (double)pc[u].y * (double)fast_exp2(pc[u].x - m);
+      for (int c = 0; c < kChains; ++c) {
+        const int g = min(first + 4 * u + chain0 + c, n_granules - 1);
+        x[c][u] = *reinterpret_cast<const float2*>(p + (int64_t)g * rows_per_slice * 2);
+      }
   }
-  auto merge = [&](float om, double os, bool upper) {     // the lower lane's pair first: the same order in both partners
-    const float mm = fmaxf(m, om);
-    const double own = s * (double)fast_exp2(m - mm), other = os * (double)fast_exp2(om - mm);
-    s = upper ? other + own : own + other;
-    m = mm;
+  // Separate from the loads, so that no masks are held while they are under way.
+  __device__ __forceinline__ void drop_absent(int left /* granules from the lane's first chain's first pair on */) {
+    asm volatile("" : "+v"(left));
+#pragma unroll
+    for (int u = 0; u < kCombineAhead; ++u)
+#pragma unroll
+      for (int c = 0; c < kChains; ++c)
+        if (4 * u + c >= left) x[c][u] = make_float2(kMasked, 0.f);
+  }
+};
+template <int kChains, typename Partner>
+__device__ __forceinline__ float combine_row(RowPairs<kChains>& pairs, const float* p, int rows_per_slice, int n_granules, int chain0, Partner partner) {
+  float m[4];
+  double s[4];
+#pragma unroll
+  for (int c = 0; c < kChains; ++c) { m[c] = kMasked; s[c] = 0.0; }
+  for (int first = 0;;) {
+    pairs.drop_absent(n_granules - first - chain0);
+    // The references of a sweep are one and the same (0) in most layers: every factor below is 1 then.  The test is the
+    // wave's, its branch parts no lanes.
+    const float ref = pairs.x[0][0].x;
+    uint32_t other = 0;                   // bits in which some reference differs
+    auto compare = [&](float r) { other |= r == kMasked ? 0u : __float_as_uint(r) ^ __float_as_uint(ref); };
+#pragma unroll
+    for (int c = 0; c < kChains; ++c) {
+      compare(m[c]);
+#pragma unroll
+      for (int u = 0; u < kCombineAhead; ++u) {
+        compare(pairs.x[c][u].x);
+        asm volatile("" : "+v"(other));   // one after the other: the masks of all at once fill the scalar registers
+      }
+    }
+    if (__all(other == 0)) {
+#pragma unroll
+      for (int u = 0; u < kCombineAhead; ++u)
+#pragma unroll
+        for (int c = 0; c < kChains; ++c) s[c] += (double)pairs.x[c][u].y;
+#pragma unroll
+      for (int c = 0; c < kChains; ++c) m[c] = ref;
+    } else {
+#pragma unroll
+      for (int c = 0; c < kChains; ++c) {
+        float top = m[c];
+#pragma unroll
+        for (int u = 0; u < kCombineAhead; ++u) top = fmaxf(top, pairs.x[c][u].x);
+        s[c] *= (double)fast_exp2(m[c] - top);
+        m[c] = top;
+#pragma unroll
+        for (int u = 0; u < kCombineAhead; ++u) s[c] += (double)pairs.x[c][u].y * (double)fast_exp2(pairs.x[c][u].x - top);
+      }
+    }
+    first += 4 * kCombineAhead;
+    if (first >= n_granules) break;
+    pairs.load(p, rows_per_slice, n_granules, first, chain0);
+  }
+  auto merge = [](float& m0, double& s0, float m1, double s1) {
+    const float mm = fmaxf(m0, m1);
+    s0 = s0 * (double)fast_exp2(m0 - mm) + s1 * (double)fast_exp2(m1 - mm);
+    m0 = mm;
   };
-  merge(dpp_step<0xB1, 0xf, true>(m), dpp_step<0xB1, 0xf, true>(s), part & 1);      // quad_perm [1, 0, 3, 2]
-  merge(dpp_step<0x4E, 0xf, true>(m), dpp_step<0x4E, 0xf, true>(s), part & 2);      // quad_perm [2, 3, 0, 1]
+  if (kChains == 4) merge(m[2], s[2], m[3], s[3]);
+  if (kChains >= 2) merge(m[0], s[0], m[1], s[1]);
+  if (kChains == 4) merge(m[0], s[0], m[2], s[2]);
+  else partner(m[0], s[0], merge);
   // log2 of the sum from its exponent and mantissa: the instruction's error is that of a value below 1; rounded once
-  return (float)((double)m + (double)__builtin_amdgcn_frexp_exp(s) + (double)__builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(s)));
+  return (float)((double)m[0] + (double)__builtin_amdgcn_frexp_exp(s[0]) + (double)__builtin_amdgcn_logf((float)__builtin_amdgcn_frexp_mant(s[0])));
+}
+// The other chains of a row in neighbouring lanes, one chain each: lanes 4i .. 4i + 3.
+__device__ __forceinline__ auto quad_partner(int chain) {
+  return [chain](float& m, double& s, auto merge) {
+    auto with = [&](float om, double os, bool upper) {     // the lower lane's pair first: the same order in both partners
+      float a = upper ? om : m, b = upper ? m : om;
+      double x = upper ? os : s, y = upper ? s : os;
+      merge(a, x, b, y);
+      m = a;
+      s = x;
+    };
+    with(dpp_step<0xB1, 0xf, true>(m), dpp_step<0xB1, 0xf, true>(s), chain & 1);      // quad_perm [1, 0, 3, 2]
+    with(dpp_step<0x4E, 0xf, true>(m), dpp_step<0x4E, 0xf, true>(s), chain & 2);      // quad_perm [2, 3, 0, 1]
+  };
+}
+
+// Two chains each in lanes i and i + 32.
+__device__ __forceinline__ auto half_partner() {
+  return [](float& m, double& s, auto merge) {
+    uint32_t w[3];
+    __builtin_memcpy(w, &m, 4);
+    __builtin_memcpy(w + 1, &s, 8);
+    uint32_t lower[3], upper[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      const auto r = __builtin_amdgcn_permlane32_swap(w[i], w[i], false, false);
+      lower[i] = r[0];
+      upper[i] = r[1];
+    }
+    float om;
+    double os;
+    __builtin_memcpy(&m, lower, 4);
+    __builtin_memcpy(&s, lower + 1, 8);
+    __builtin_memcpy(&om, upper, 4);
+    __builtin_memcpy(&os, upper + 1, 8);
+    merge(m, s, om, os);
+  };
 }
 
 __global__ __launch_bounds__(256) void scores_combine(ScoreArgs a, int rows_per_slice, int64_t total_rows) {
@@ -427,7 +518,10 @@ __global__ __launch_bounds__(256) void scores_combine(ScoreArgs a, int rows_per_
   const int part = threadIdx.x & 3;
   const int64_t slice = i / rows_per_slice;
   const int row = (int)(i % rows_per_slice);
-  const float lse = combine_row(a.part + (slice * a.n_granules * rows_per_slice + row) * 2, rows_per_slice, a.n_granules, part);
+  const float* p = a.part + (slice * a.n_granules * rows_per_slice + row) * 2;
+  RowPairs<1> pairs;
+  pairs.load(p, rows_per_slice, a.n_granules, 0, part);
+  const float lse = combine_row(pairs, p, rows_per_slice, a.n_granules, part, quad_partner(part));
   if (part == 0) a.lse[i] = lse;
 }
 
@@ -537,12 +631,12 @@ __device__ __forceinline__ void pass2_tile_stats(const ColSums& s0, const ColSum
 }
 
 constexpr int kPackMaxWaves = 16;      // waves of a packed workgroup
-// Whether pass 2 has the code to combine the pairs of pass 1 by itself (not in the software-pipelined
-// form, whose registers are full: it measured 1-2 % slower with that code in its prologue).
-template <typename T, int MB>
-__host__ __device__ constexpr bool can_combine() { return !(sizeof(T) == 2 && MB == 2); }
+// Pass 2 comes with and without the code to combine the pairs of pass 1 by itself (kCombine).  The software-pipelined form has
+// it for a workgroup per compute unit only (its registers are full): 8192 keys of one layer, 8 x 4 heads, scores of 64 rows
+// 32.4 -> 29.7 us with it, 512 workgroups of 8 layers of 1000 keys 32.9 -> 33.9.
+template <typename T, int MB> constexpr bool kPipelinedForm = sizeof(T) == 2 && MB == 2;
 
-template <typename T, int D, int MB, bool kPivot, bool kPack>
+template <typename T, int D, int MB, bool kPivot, bool kPack, bool kCombine>
 __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) {
   using F = Frag<T>;
   using TL = Tile<T, D>;
@@ -577,6 +671,13 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
   const int n_tiles = (key_end - key0 + kTileKeys - 1) / kTileKeys;
   TileMover<T, D> mover;
   mover.init(kbase, tok_bytes, min(a.n, a.key_hi) - 1, w, n_waves, lane);
+  // Few workgroups: each wave combines its own rows' pairs beside the first tile's transfer, which spares the launch
+  // in between; their loads go out ahead of everything else.
+  constexpr int kChains = s_w / 16;        // 32 rows: two lanes each
+  const int chain0 = MB == 1 ? 2 * hh : 0;
+  const float* row_pairs = a.part + ((int64_t)slice * a.n_granules * (a.group * s_w) + w * s_w + (lane & (s_w - 1))) * 2;
+  RowPairs<kChains> pairs;
+  if (kCombine) pairs.load(row_pairs, a.group * s_w, a.n_granules, 0, chain0);
   mover.issue(tiles, key0);
 
   typename F::type qf[MB][kSteps];
@@ -592,16 +693,9 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
 #pragma unroll
       for (int v = 0; v < 16; ++v) init[mb][v] = lse[row_of(mb, v)] * neg_inv_c;
   };
-  if (can_combine<T, MB>() && a.combine) {
-    // few workgroups: each wave combines its own rows' pairs beside the first tile's transfer, which
-    // spares the launch in between (the wave's I_q row serves until its first tile is done)
-    float* mine = iq_row(0, w);
-#pragma unroll
-    for (int r0 = 0; r0 < s_w; r0 += 16) {
-      const float x = combine_row(a.part + ((int64_t)slice * a.n_granules * (a.group * s_w) + w * s_w + r0 + (lane >> 2)) * 2,
-                                  a.group * s_w, a.n_granules, lane & 3);
-      if ((lane & 3) == 0) mine[r0 + (lane >> 2)] = x;
-    }
+  if (kCombine) {
+    float* mine = iq_row(0, w);            // the wave's I_q row serves until its first tile is done
+    mine[lane & (s_w - 1)] = combine_row(pairs, row_pairs, a.group * s_w, a.n_granules, chain0, half_partner());
     load_init(mine);
   } else {
     load_init(a.lse + (int64_t)slice * (a.group * s_w) + w * s_w);
@@ -617,7 +711,7 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
   // (S_w = 64); with one row block the periods are too short and the plain order is faster, and
   // the fp32 kernels hold four times the query fragments and would spill.  Those run the two
   // phases of a sub-tile one after the other on a single set.
-  constexpr bool kPipelined = sizeof(T) == 2 && MB == 2;
+  constexpr bool kPipelined = kPipelinedForm<T, MB>;
   f32x16 acc_a[MB], acc_b[MB];
   ColSums cs0{}, cs1{};
 
@@ -870,15 +964,18 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
                   hipStream_t stream) {
   ScoreArgs a = a_in;
   const bool packing = a_in.pack > 1;
-  auto set_pack = [&](dim3& block, unsigned& gy, size_t& packed_bytes) {
-    a.pack = packing ? slices_per_workgroup(a.group) : 1;
-    block = dim3(64 * a.group * a.pack);
-    gy = (unsigned)((n_slices + a.pack - 1) / a.pack);
-    packed_bytes = (size_t)a.pack * 2 * Tile<T, D>::kBytes + sizeof(float) * 2 * kPackMaxWaves * kTileKeys;
-  };
   dim3 block;
   unsigned gy;
   size_t packed_bytes;
+  // A launch of few workgroups of one granule each packs none: its slices' chunks on compute units of their own are done
+  // sooner (one layer of 8192 keys, 8 x 5 heads of 128: pass 1 16.0 -> 12.4 us, pass 2 27 -> 17.6; of 16384 37 -> 27 and 50 -> 35).
+  auto set_pack = [&](int lo, int hi) {
+    const bool few = n_slices * ((hi - lo + a_in.granule - 1) / a_in.granule) <= 512;
+    a.pack = packing && !few ? slices_per_workgroup(a.group) : 1;
+    block = dim3(64 * a.group * a.pack);
+    gy = (unsigned)((n_slices + a.pack - 1) / a.pack);
+    packed_bytes = a.pack > 1 ? (size_t)a.pack * 2 * Tile<T, D>::kBytes + sizeof(float) * 2 * kPackMaxWaves * kTileKeys : 0;
+  };
   // Keys per workgroup: the chunk's granules, or a half or quarter of them where that shortens the rounds of workgroups
   // over the chip.  A workgroup's prologue (its queries, the first tile's way from memory) counts as a tile of keys.  A
   // compute unit holds as many workgroups as LDS and the registers of the pass allow; those of five and more heads of 64
@@ -912,35 +1009,27 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     a.wg_keys = best * a.granule;
     return (unsigned)((hi - lo + a.wg_keys - 1) / a.wg_keys);
   };
-  auto run_pass1 = [&](int lo, int hi) -> hipError_t {
-    set_pack(block, gy, packed_bytes);
-    const unsigned chunks = set_span(1, lo, hi);
-    if constexpr (can_pack<T, MB>()) {
-      if (a.pack > 1) {
-        auto kern = scores_pass1<T, D, MB, true>;
-        if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)packed_bytes); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(chunks, gy), block, packed_bytes, stream, a);
-        return hipSuccess;
-      }
-    }
-    hipLaunchKernelGGL((scores_pass1<T, D, MB, false>), dim3(chunks, gy), block, 0, stream, a);
+  auto run = [&](auto kern, unsigned chunks) -> hipError_t {
+    if (packed_bytes > 0)
+      if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                             (int)packed_bytes); e != hipSuccess) return e;
+    hipLaunchKernelGGL(kern, dim3(chunks, gy), block, packed_bytes, stream, a);
     return hipSuccess;
   };
-  auto run_pass2 = [&](int lo, int hi) -> hipError_t {
-    set_pack(block, gy, packed_bytes);
+  auto run_pass1 = [&](int lo, int hi) -> hipError_t {
+    set_pack(lo, hi);
+    const unsigned chunks = set_span(1, lo, hi);
+    if constexpr (can_pack<T, MB>())
+      if (a.pack > 1) return run(scores_pass1<T, D, MB, true>, chunks);
+    return run(scores_pass1<T, D, MB, false>, chunks);
+  };
+  auto run_pass2 = [&](int lo, int hi, bool combine) -> hipError_t {
+    set_pack(lo, hi);
     const unsigned chunks = set_span(2, lo, hi);
-    if constexpr (can_pack<T, MB>()) {
-      if (a.pack > 1) {
-        auto kern = scores_pass2<T, D, MB, kPivot, true>;
-        if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               (int)packed_bytes); e != hipSuccess) return e;
-        hipLaunchKernelGGL(kern, dim3(chunks, gy), block, packed_bytes, stream, a);
-        return hipSuccess;
-      }
-    }
-    hipLaunchKernelGGL((scores_pass2<T, D, MB, kPivot, false>), dim3(chunks, gy), block, 0, stream, a);
-    return hipSuccess;
+    if constexpr (can_pack<T, MB>())
+      if (a.pack > 1) return run(scores_pass2<T, D, MB, kPivot, true, false>, chunks);
+    if (combine) return run(scores_pass2<T, D, MB, kPivot, false, true>, chunks);
+    return run(scores_pass2<T, D, MB, kPivot, false, false>, chunks);
   };
   const int rows = a.group * MB * 32;
   const int64_t total_rows = n_slices * rows;
@@ -952,7 +1041,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     else if (parts == kPartsCombine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
     else if (parts == kPartsPass2Segment && hi2 > a.key_lo)
-      CAKE_HIP_TRY(run_pass2(a.key_lo, hi2));
+      CAKE_HIP_TRY(run_pass2(a.key_lo, hi2, false));
     else if (parts == kPartsPool)
       hipLaunchKernelGGL(pool_indicator<false>, dim3((a.n_p + kPoolSpan - 1) / kPoolSpan, (unsigned)n_slices), dim3(256), 0,
                          stream, a, PrefArgs{}, 0);
@@ -960,14 +1049,15 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     return CAKE_OK;
   }
   mark(0, stream);
+  bool combine = false;
   if (row_lse == nullptr) {
     CAKE_HIP_TRY(run_pass1(0, a.n));
     mark(1, stream);
     // every workgroup of pass 2 reads its slice's pairs where it combines them itself: at most 16 MB in all
-    set_pack(block, gy, packed_bytes);
+    set_pack(0, a.n_p);
     const int64_t workgroups = (int64_t)gy * set_span(2, 0, a.n_p);
-    a.combine = can_combine<T, MB>() && workgroups * a.pack * rows * a.n_granules * 8 <= 16 << 20;
-    if (!a.combine)
+    combine = a.pack == 1 && workgroups * rows * a.n_granules * 8 <= 16 << 20 && (!kPipelinedForm<T, MB> || workgroups <= 256);
+    if (!combine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
   } else {
     const int64_t per_layer = (int64_t)a.batch * a.h_kv * rows;
@@ -976,7 +1066,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     mark(1, stream);
   }
   mark(2, stream);
-  CAKE_HIP_TRY(run_pass2(0, a.n_p));
+  CAKE_HIP_TRY(run_pass2(0, a.n_p, combine));
   mark(3, stream);
   const unsigned spans = (a.n_p + kPoolSpan - 1) / kPoolSpan;
   const unsigned pref_rows = pref ? (pref->n_layers * pref->batch + spans - 1) / spans : 0;

@@ -1,0 +1,61 @@
+"""The score passes at the sizes where their forms change: element types and row blocks, and launches of a few
+workgroups (which combine pass 1's pairs inside pass 2 and pack no slices) against launches of many."""
+import pytest
+import torch
+
+from gpu_util import assert_close, load_cake, oracle_layer, say
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _inputs(layers, h_q, h_kv, d, n, window, dtype, seed, peak=1.0):
+    gen = torch.Generator(device=DEV).manual_seed(seed)
+    mk = lambda h, rows, t: [(torch.randn(1, h, rows, d, device=DEV, generator=gen) * t).to(dtype) for _ in range(layers)]
+    return mk(h_q, window, peak), mk(h_kv, n, 1.0), mk(h_kv, n, 1.0)
+
+
+@pytest.mark.parametrize("window", [32, 64])
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("n", [97, 640 + 31])      # one key past a tile; a ragged last tile behind whole granules
+def test_fp32_scores_against_the_oracle(d, window, n):
+    cake = load_cake()
+    say(f"scores fp32 d={d} S_w={window} N={n}")
+    q, k, v = _inputs(1, 6, 2, d, n, window, torch.float32, d + window + n, 2.0)
+    params = cake.make_params()
+    ev = cake.EvictionPass(q, k, v, 2 * window, params)
+    ev.scores()
+    want = oracle_layer(q[0][0], k[0][0], params)
+    # fp32 sums of d products and of n exponentials, whose arguments (up to some 30) are rounded to 2^-24 of themselves;
+    # gamma = 200 times a variance that is a difference of sums: 1e-4 leaves a factor of ten over what that adds up to
+    assert_close(ev.indicator[0, 0].cpu().numpy(), want["indicator"], "indicator", rtol=1e-4)
+    pref, hv = ev.preferences_to_host()
+    assert_close(hv[0, 0, 0], want["H"], "H", rtol=1e-5)
+    assert_close(hv[0, 0, 1], want["V"], "V", rtol=1e-4)
+
+
+@pytest.mark.parametrize("peak", [1.0, 12.0])      # references all 0; references of their own
+@pytest.mark.parametrize("dtype,window,group,d,n", [
+    (torch.bfloat16, 32, 4, 128, 160),             # 3 granules of 64
+    (torch.bfloat16, 32, 5, 64, 32 * 64),          # 8 granules of 256, packed where there are many
+    (torch.bfloat16, 32, 6, 128, 33 * 256 - 7),    # 33 granules: one more than a sweep of the pairs
+    (torch.bfloat16, 32, 1, 128, 8192),            # 32 granules: one sweep
+    (torch.bfloat16, 64, 4, 128, 31 * 256 + 1),    # 32 granules of the software-pipelined form, one key in the last
+    (torch.float32, 64, 3, 64, 1999),              # 16 granules of 128
+    (torch.float32, 32, 2, 128, 2100),
+])
+def test_a_layer_alone_scores_to_the_same_bits_as_among_many(dtype, window, group, d, n, peak):
+    cake = load_cake()
+    say(f"scores alone and among many {dtype} S_w={window} G={group} d={d} N={n} peak={peak}")
+    h_kv, layers = 2, 1 + 4096 // (2 * (-(-n // 256)) + 1)
+    layers = min(layers, 160)
+    q, k, v = _inputs(2, h_kv * group, h_kv, d, n, window, dtype, n, peak)
+    many = cake.EvictionPass([q[i % 2] for i in range(layers)], [k[i % 2] for i in range(layers)], [v[i % 2] for i in range(layers)],
+                             layers * window)
+    many.scores()
+    for l in range(2):
+        alone = cake.EvictionPass(q[l:l + 1], k[l:l + 1], v[l:l + 1], window)
+        alone.scores()
+        assert torch.equal(alone.indicator[0], many.indicator[l])
+        assert torch.equal(alone.indicator[0], many.indicator[l + 2 * ((layers - 1 - l) // 2)])
+        assert torch.equal(alone.hv[0, 0], many.hv[0, l]) and torch.equal(alone.pref[0, 0], many.pref[0, l])
