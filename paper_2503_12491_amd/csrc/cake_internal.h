@@ -53,11 +53,13 @@ struct ScoreLayout {
 ScoreLayout score_layout(const cake_shape& s);
 
 // cake_window_scores (or, with row_lse, cake_window_scores_lse) and cake_layer_preference with the
-// preferences computed beside the pooling; rows of pref_ld preferences and hv_ld (H, V) pairs per sequence
+// preferences computed beside the pooling; rows of pref_ld preferences and hv_ld (H, V) pairs per sequence.
+// `plan` (may be NULL): the plan that follows from them, made in the same launch or behind it
+struct PlanArgs;
 int launch_scores_and_preference(const cake_shape* shape, const cake_params* params, const void* const* q_win,
                                  const void* const* k, const int64_t* q_strides, const int64_t* k_strides,
                                  const float* const* row_lse, float* const* indicator, void* workspace, size_t workspace_bytes,
-                                 double* pref, double* hv, int pref_ld, int hv_ld, hipStream_t stream);
+                                 double* pref, double* hv, int pref_ld, int hv_ld, const PlanArgs* plan, hipStream_t stream);
 
 // ---- ragged per-launch dimensions, passed to kernels by value ----------------------------
 constexpr int kMaxLaunchLayers = 32;
@@ -135,10 +137,6 @@ struct PlanMirror {
   const double* hv;    // device [B, L, 2] or NULL
   uint32_t ticket;
 };
-// cake_plan_eviction with rows of pref_ld preferences per sequence and, on request, the host's copy
-int launch_plan(const cake_shape* shape, const double* pref, int pref_ld, int64_t total_budget, const int32_t* cur_len,
-                void* pool_idx, void* pool_k, void* pool_v, void* pool_ind, void* plan, size_t plan_bytes,
-                int32_t* status, const PlanMirror& mirror, hipStream_t stream);
 // top-k and compaction of all layers with the counts and output places read from a plan
 // max_cur: the longest row to expect; `bounded` if no current length of the plan exceeds it
 int launch_topk_planned(const cake_shape* shape, const float* const* indicator, const PlanView& plan, int64_t max_cur, bool bounded,

@@ -11,8 +11,8 @@
 // too small for the chip and waiting for the one before, and some 2 us between two launches.
 #include <algorithm>
 
-#include "cake_internal.h"
 #include "cake_pass.h"
+#include "plan_device.h"
 
 namespace cake {
 namespace {
@@ -206,11 +206,12 @@ extern "C" int cake_cascade_stage(const cake_cascade* c, int32_t m, const void* 
   const PlanView before = plan_view(c->plan[(m & 1) ^ 1], std::max(m, 1), shape.batch);
   hipLaunchKernelGGL(begin_stage, dim3(1), dim3(kThreads), 0, st, a, before, c->cur, q_win, k, static_cast<void*>(indicator));
   const int L = c->max_layers;
+  PlanArgs plan{};
+  if (int rc = plan_args(&shape, c->pref, L, c->total_budget, c->cur, c->idx, c->k_store, c->v_store, c->ind[m & 1], c->plan[m & 1],
+                         c->plan_bytes, c->status, PlanMirror{}, &plan)) return rc;
   if (int rc = launch_scores_and_preference(&c->shape, &c->params, c->tables + m + 1, c->tables + m + 2, q_strides, kv_strides, nullptr,
                                             reinterpret_cast<float* const*>(c->tables + m), c->workspace, c->workspace_bytes,
-                                            c->pref + m, c->hv + 2 * m, L, L, st)) return rc;
-  if (int rc = launch_plan(&shape, c->pref, L, c->total_budget, c->cur, c->idx, c->k_store, c->v_store, c->ind[m & 1], c->plan[m & 1],
-                           c->plan_bytes, c->status, PlanMirror{}, st)) return rc;
+                                            c->pref + m, c->hv + 2 * m, L, L, &plan, st)) return rc;
   if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(c->tables), a.plan, a.prefix_len, true, st)) return rc;
   const int64_t shares = std::min<int64_t>((a.prefix_len + kThreads) / kThreads, 2048 / ((int64_t)bh * (m + 1)));
   hipLaunchKernelGGL(renew_lists, dim3(bh, m + 1, (unsigned)std::max<int64_t>(shares, 1)), dim3(kThreads), 0, st, a);

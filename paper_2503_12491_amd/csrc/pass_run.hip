@@ -4,8 +4,8 @@
 // compaction instead of after four copies and a stream synchronisation behind them.
 #include <chrono>
 
-#include "cake_internal.h"
 #include "cake_pass.h"
+#include "plan_device.h"
 
 namespace cake {
 namespace {
@@ -43,14 +43,19 @@ extern "C" int cake_pass_launch(const cake_pass* p, int32_t parts, uint32_t tick
   CAKE_REQUIRE(p != nullptr, "pass is NULL");
   if (int rc = check_shape_basic(&p->shape)) return rc;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  PlanArgs plan{};
+  if (parts & CAKE_PASS_EVICT) {
+    const PlanMirror mirror{ticket ? p->mirror : nullptr, p->hv, ticket};
+    if (int rc = plan_args(&p->shape, p->pref, p->shape.n_layers, p->total_budget, nullptr, p->pool_idx, p->pool_k,
+                           p->pool_v, p->pool_ind, p->plan, p->plan_bytes, p->status, mirror, &plan)) return rc;
+  }
   if (parts & CAKE_PASS_SCORES)
     if (int rc = launch_scores_and_preference(&p->shape, &p->params, p->q_win, p->k, p->q_strides, p->kv_strides, p->row_lse,
                                               p->indicator, p->workspace, p->workspace_bytes, p->pref, p->hv,
-                                              p->shape.n_layers, p->shape.n_layers, st)) return rc;
+                                              p->shape.n_layers, p->shape.n_layers, parts & CAKE_PASS_EVICT ? &plan : nullptr, st)) return rc;
   if (parts & CAKE_PASS_EVICT) {
-    const PlanMirror mirror{ticket ? p->mirror : nullptr, p->hv, ticket};
-    if (int rc = launch_plan(&p->shape, p->pref, p->shape.n_layers, p->total_budget, nullptr, p->pool_idx, p->pool_k,
-                             p->pool_v, p->pool_ind, p->plan, p->plan_bytes, p->status, mirror, st)) return rc;
+    if (!(parts & CAKE_PASS_SCORES))
+      if (int rc = launch_plan(plan, st)) return rc;
     // the plan above takes every row at its full length
     return evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, true, stream);
   }

@@ -31,7 +31,7 @@
 #include <cmath>
 #include <type_traits>
 
-#include "cake_internal.h"
+#include "plan_device.h"
 
 namespace cake {
 namespace {
@@ -809,9 +809,23 @@ struct PrefArgs {
 };
 constexpr int kPrefThreads = 256;
 
+// What becomes of an entry's sums.
+__device__ __forceinline__ void store_preference(const PrefArgs& a, int entry, double e, double v) {
+  const int l = entry / a.batch, b = entry % a.batch;
+  const double heads = (double)(a.h_kv * a.group);
+  // Both are non-negative by definition; with nearly one-hot attention the fp32 sums can come
+  // out a rounding error below zero, which the fractional powers below would turn into NaN.
+  const double h_l = fmax(-0.6931471805599453 * e / heads, 0.0);   // sum p*log2 p -> -sum p ln p
+  const double v_l = fmax(v / heads, 0.0);
+  a.pref[(int64_t)b * a.pref_ld + l] = pow(h_l, a.inv_tau1) * pow(v_l, a.inv_tau2);
+  if (a.hv_out) {
+    a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 0] = h_l;
+    a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 1] = v_l;
+  }
+}
+
 __device__ __forceinline__ void preference_of(const PrefArgs& a, int entry) {
   __shared__ double red[2][kPrefThreads / 64];
-  const int l = entry / a.batch, b = entry % a.batch;
   const int tid = threadIdx.x, lane = tid & 63;
   const int count = a.h_kv * a.n_granules_p * a.group;
   const float2* base = reinterpret_cast<const float2*>(a.hv) + (int64_t)entry * count;
@@ -831,17 +845,42 @@ __device__ __forceinline__ void preference_of(const PrefArgs& a, int entry) {
   if (tid == 0) {
 #pragma unroll
     for (int w = 1; w < kPrefThreads / 64; ++w) { e += red[0][w]; v += red[1][w]; }
-    const double heads = (double)(a.h_kv * a.group);
-    // Both are non-negative by definition; with nearly one-hot attention the fp32 sums can come
-    // out a rounding error below zero, which the fractional powers below would turn into NaN.
-    const double h_l = fmax(-0.6931471805599453 * e / heads, 0.0);   // sum p*log2 p -> -sum p ln p
-    const double v_l = fmax(v / heads, 0.0);
-    a.pref[(int64_t)b * a.pref_ld + l] = pow(h_l, a.inv_tau1) * pow(v_l, a.inv_tau2);
-    if (a.hv_out) {
-      a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 0] = h_l;
-      a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 1] = v_l;
-    }
+    store_preference(a, entry, e, v);
   }
+}
+
+// The same sums by one wave, which does the four waves' parts side by side.
+__device__ __forceinline__ void preference_of_wave(const PrefArgs& a, int entry, int lane) {
+  constexpr int kParts = kPrefThreads / 64;
+  const int count = a.h_kv * a.n_granules_p * a.group;
+  const float2* base = reinterpret_cast<const float2*>(a.hv) + (int64_t)entry * count;
+  double e[kParts] = {}, v[kParts] = {};
+  constexpr int kAhead = 4;                 // loads of a part in flight
+  for (int i0 = lane; i0 - lane < count; i0 += kAhead * kPrefThreads) {
+    float2 x[kAhead][kParts];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int w = 0; w < kParts; ++w) x[u][w] = base[min(i0 + u * kPrefThreads + 64 * w, count - 1)];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+#pragma unroll
+      for (int w = 0; w < kParts; ++w)
+        if (i0 + u * kPrefThreads + 64 * w < count) {
+          e[w] += (double)x[u][w].x;
+          v[w] += (double)x[u][w].y;
+        }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1)
+#pragma unroll
+    for (int w = 0; w < kParts; ++w) {
+      e[w] += __shfl_xor(e[w], off);
+      v[w] += __shfl_xor(v[w], off);
+    }
+#pragma unroll
+  for (int w = 1; w < kParts; ++w) { e[0] += e[w]; v[0] += v[w]; }
+  if (lane == 0) store_preference(a, entry, e[0], v[0]);
 }
 
 __global__ __launch_bounds__(kPrefThreads) void layer_preference_kernel(PrefArgs a) { preference_of(a, blockIdx.x); }
@@ -868,19 +907,10 @@ __device__ __forceinline__ float4 pool_quad(const float (&w)[12]) {
   return make_float4(o[0], o[1], o[2], o[3]);
 }
 
-// With kPref the first `pref_rows` rows of the grid compute the layer preferences beside the pooling
-// (both follow pass 2 and neither reads the other): a launch and its latency less.
-template <bool kPref>
-__global__ __launch_bounds__(256) void pool_indicator(ScoreArgs a, PrefArgs pa, int pref_rows) {
-  static_assert(kPrefThreads == 256, "the preference shares the pooling's workgroups");
+// Span blockIdx.x of one slice.
+__device__ __forceinline__ void pool_span(const ScoreArgs& a, int slice) {
   // position j0 + i of the span sits at win[kPoolMaxHalf + i]
   __shared__ __attribute__((aligned(16))) float win[kPoolSpan + 2 * kPoolMaxHalf];
-  if (kPref && (int)blockIdx.y < pref_rows) {
-    const int entry = blockIdx.y * gridDim.x + blockIdx.x;
-    if (entry < pa.n_layers * pa.batch) preference_of(pa, entry);
-    return;
-  }
-  const int slice = blockIdx.y - (kPref ? pref_rows : 0);
   int l, b, g;
   slice_coords(a, slice, l, b, g);
   const int half = a.pool / 2;
@@ -934,6 +964,35 @@ __global__ __launch_bounds__(256) void pool_indicator(ScoreArgs a, PrefArgs pa, 
   }
 }
 
+// With kPref the first `pref_rows` rows of the grid compute the layer preferences beside the pooling
+// (both follow pass 2 and neither reads the other): a launch and its latency less.
+template <bool kPref>
+__global__ __launch_bounds__(256) void pool_indicator(ScoreArgs a, PrefArgs pa, int pref_rows) {
+  static_assert(kPrefThreads == 256, "the preference shares the pooling's workgroups");
+  if (kPref && (int)blockIdx.y < pref_rows) {
+    const int entry = blockIdx.y * gridDim.x + blockIdx.x;
+    if (entry < pa.n_layers * pa.batch) preference_of(pa, entry);
+    return;
+  }
+  pool_span(a, blockIdx.y - (kPref ? pref_rows : 0));
+}
+
+// Pooling, and in the first workgroup the preferences of a few (layer, sequence) entries, a wave each, and the plan
+// that follows from them.
+constexpr int kPoolPlanEntries = 4;
+__global__ __launch_bounds__(256) void pool_and_plan(ScoreArgs a, PrefArgs pa, PlanArgs plan) {
+  static_assert(kPoolPlanEntries == 256 / 64, "a wave per entry");
+  if (blockIdx.y > 0) {
+    pool_span(a, blockIdx.y - 1);
+    return;
+  }
+  if (blockIdx.x > 0) return;
+  for (int entry = threadIdx.x >> 6; entry < pa.n_layers * pa.batch; entry += kPoolPlanEntries) preference_of_wave(pa, entry, threadIdx.x & 63);
+  __threadfence_block();
+  __syncthreads();
+  plan_workgroup(plan, nullptr);
+}
+
 // Optional event timing of the four kernels (diagnostics).  Process-wide and not thread-safe:
 // one set of five events per profiled call, the last kProfileSets calls are kept.
 constexpr int kProfileSets = 64;
@@ -961,7 +1020,7 @@ inline int slices_per_workgroup(int group) { return group == 5 ? 3 : group == 6 
 
 template <typename T, int D, int MB, bool kPivot>
 int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* row_lse, ScoreParts parts, const PrefArgs* pref,
-                  hipStream_t stream) {
+                  const PlanArgs* plan, hipStream_t stream) {
   ScoreArgs a = a_in;
   const bool packing = a_in.pack > 1;
   dim3 block;
@@ -1070,12 +1129,20 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   mark(3, stream);
   const unsigned spans = (a.n_p + kPoolSpan - 1) / kPoolSpan;
   const unsigned pref_rows = pref ? (pref->n_layers * pref->batch + spans - 1) / spans : 0;
-  if (pref && n_slices + pref_rows <= 65535) {
+  // The plan of a few preferences beside the pooling, by the workgroup that computes them: two launches and what they wait
+  // for less (a stage of a cascade of 8192 keys, 8 heads: 16.8 -> 10.3 us behind pass 2).  Each round of kPoolPlanEntries costs it 2 us.
+  const bool with_plan = plan && pref && pref->n_layers * pref->batch <= 2 * kPoolPlanEntries && plan->batch <= kPoolPlanEntries &&
+                         plan->n_layers <= 64 && n_slices < 65535;
+  if (with_plan) {
+    hipLaunchKernelGGL(pool_and_plan, dim3(spans, (unsigned)n_slices + 1), dim3(256), 0, stream, a, *pref, *plan);
+  } else if (pref && n_slices + pref_rows <= 65535) {
     hipLaunchKernelGGL(pool_indicator<true>, dim3(spans, (unsigned)n_slices + pref_rows), dim3(256), 0, stream, a, *pref, (int)pref_rows);
   } else {
     hipLaunchKernelGGL(pool_indicator<false>, dim3(spans, (unsigned)n_slices), dim3(256), 0, stream, a, PrefArgs{}, 0);
     if (pref) hipLaunchKernelGGL(layer_preference_kernel, dim3(pref->n_layers * pref->batch), dim3(kPrefThreads), 0, stream, *pref);
   }
+  if (plan && !with_plan)
+    if (int rc = launch_plan(*plan, stream)) return rc;
   mark(4, stream);
   if (g_profile.enabled && g_profile.created) g_profile.calls += 1;
   CAKE_HIP_TRY(hipGetLastError());
@@ -1127,7 +1194,8 @@ int window_scores_impl(const cake_shape* shape, const cake_params* params,
                        const int64_t* q_strides, const int64_t* k_strides,
                        const float* const* row_lse, float* const* indicator,
                        void* workspace, size_t workspace_bytes, void* stream,
-                       ScoreParts parts = kPartsAll, int key_begin = 0, int key_count = 0, const PrefArgs* pref = nullptr) {
+                       ScoreParts parts = kPartsAll, int key_begin = 0, int key_count = 0, const PrefArgs* pref = nullptr,
+                       const PlanArgs* plan = nullptr) {
   if (int rc = check_shape_scores(shape)) return rc;
   CAKE_REQUIRE(params != nullptr, "params is NULL");
   // what the parts of this call touch: the two finishing steps read neither queries nor keys,
@@ -1200,8 +1268,8 @@ int window_scores_impl(const cake_shape* shape, const cake_params* params,
   // pivoted column sums.  Eq. 11's sum and the plain mean do not need them.
   const bool pivot = mode == CAKE_IND_VAR || mode == CAKE_IND_MEAN_TIMES_VAR;
 #define CAKE_DISPATCH(T, D, MB)                                                         \
-  return pivot ? launch_scores<T, D, MB, true>(a, lay.n_slices, row_lse, parts, pref, st)     \
-               : launch_scores<T, D, MB, false>(a, lay.n_slices, row_lse, parts, pref, st)
+  return pivot ? launch_scores<T, D, MB, true>(a, lay.n_slices, row_lse, parts, pref, plan, st)     \
+               : launch_scores<T, D, MB, false>(a, lay.n_slices, row_lse, parts, pref, plan, st)
   const bool bf = shape->dtype == CAKE_BF16;
   const int d = shape->head_dim, mb = shape->window / 32;
   if (bf && d == 128 && mb == 1) CAKE_DISPATCH(__bf16, 128, 1);
@@ -1293,11 +1361,12 @@ extern "C" int cake_layer_preference(const cake_shape* shape, const cake_params*
 int cake::launch_scores_and_preference(const cake_shape* shape, const cake_params* params, const void* const* q_win,
                                        const void* const* k, const int64_t* q_strides, const int64_t* k_strides,
                                        const float* const* row_lse, float* const* indicator, void* workspace,
-                                       size_t workspace_bytes, double* pref, double* hv, int pref_ld, int hv_ld, hipStream_t stream) {
+                                       size_t workspace_bytes, double* pref, double* hv, int pref_ld, int hv_ld, const PlanArgs* plan,
+                                       hipStream_t stream) {
   PrefArgs a{};
   if (int rc = preference_args(shape, params, workspace, workspace_bytes, pref, hv, &a)) return rc;
   a.pref_ld = pref_ld;
   a.hv_ld = hv_ld;
   return window_scores_impl(shape, params, q_win, k, q_strides, k_strides, row_lse, indicator, workspace, workspace_bytes,
-                            stream, kPartsAll, 0, 0, &a);
+                            stream, kPartsAll, 0, 0, &a, plan);
 }

@@ -239,3 +239,26 @@ def test_layers_evicted_again_from_the_outputs_of_an_earlier_plan(cake):
             at += c
         kept_before[:layers] = keep
     del first
+
+
+@pytest.mark.parametrize("L,B", [(1, 1), (3, 1), (2, 2), (1, 4), (5, 1), (2, 4), (9, 1), (3, 3), (1, 5)])
+def test_plan_beside_the_pooling_equals_the_calls_of_their_own(cake, L, B):
+    """Up to eight (layer, sequence) entries of up to four sequences are planned by the pooling's launch, which also
+    computes their preferences: the same bits as cake_layer_preference, and the host allocator's budgets."""
+    say(f"plan beside the pooling L={L} B={B}")
+    gen = torch.Generator(device=DEV).manual_seed(10 * L + B)
+    mk = lambda h, n: [torch.randn(B, h, n, 64, device=DEV, generator=gen) * (1 + l) for l in range(L)]
+    ev = cake.EvictionPass(mk(4, 32), mk(2, 2500), mk(2, 2500), L * 150)
+    res = ev.run()
+    pref, hv = torch.zeros_like(ev.pref), torch.zeros_like(ev.hv)
+    cake.cake_layer_preference(ev.shape, ev.params, ev.workspace, pref, hv)
+    assert torch.equal(pref, ev.pref) and torch.equal(hv, ev.hv)
+    np.testing.assert_array_equal(res.pref, pref.cpu().numpy())
+    np.testing.assert_array_equal(res.hv, hv.cpu().numpy())
+    np.testing.assert_array_equal(res.budgets, ev.allocate(res.pref))
+    idx, k_out = [t.clone() for t in res.idx], [t.clone() for t in res.k_out]
+    want = ev.run_host_allocated()
+    for l in range(L):
+        for b in range(B):
+            n = int(res.keep[l, b])
+            assert torch.equal(idx[l][b, :, :n], want.idx[l][b, :, :n]) and torch.equal(k_out[l][b, :, :n + 32], want.k_out[l][b, :, :n + 32])
