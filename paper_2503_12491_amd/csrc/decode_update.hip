@@ -198,10 +198,10 @@ typedef cake_decode_buffers StepBuffers;
 struct StepBase {
   const void* q_new; const void* k_new; const void* v_new;
   int64_t qs[3], ns[3];             // element strides of q_new / k_new, v_new: layer, batch, head
-  int32_t batch, h_kv, group, window, pool, n_chunks, rows_max;
+  int32_t batch, h_kv, group, window, pool, n_chunks, rows_max, chunk_rows;
   float c, inv_g;
   float* logits;      // [slice][group][rows_max], rows_max a multiple of 4
-  float* part;        // [slice][n_chunks][kMaxGroup][2]
+  float* part;        // [slice][n_chunks][kMaxGroup][2], chunks of the rows a workgroup of the first kernel takes
   float* amin;        // [slice][n_chunks][2]: (value, logical index as float bits)
 };
 // Arguments of a call for any number of layers: the buffers behind device tables.
@@ -260,18 +260,22 @@ template <int D> struct RowDots<float, D> {
 // v_exp_f32, which returns 0 below 2^-126: for the terms of a sum that is at least 1
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Step kernel 1, one workgroup per 256 rows of a slice: the new row goes to its slot; logits of the G
+// Step kernel 1, one workgroup per 64 rows a wave of a slice: the new row goes to its slot; logits of the G
 // heads for every listed row (kept for what follows) and the chunk's (reference, sum) pairs.
 // Bound by the key bytes: four 16-byte loads per row and lane, all of a wave's 64 rows in flight; the
 // one-row-per-thread form on the vector ALU read its queries from LDS once per row and head and reached
 // 1.1 TB/s (12 layers x 4 sequences x 8 heads of 2K rows: 179 -> 40 us, 5.0 TB/s; one layer of 1K rows
-// per head 18 -> 6 us).
-template <typename T, int D, typename Args>
-__global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
+// per head 18 -> 6 us).  A compute unit gets some 35 bytes a nanosecond, so four waves of one stay for 2 us where the rows
+// would fit compute units of their own: small calls run one-wave workgroups (12 layers of 8 heads of 180 to 2900 rows, called
+// one by one: 10.7 -> 10.3 us a layer, of
+// which the host takes 9; 4 layers of 2 heads, 12 queries and 335 rows at once in fp32: 14.7 -> 12.5 us, with the loads of the
+// second kernel that no longer wait for the state).
+template <typename T, int D, int kStepWaves, typename Args>
+__global__ __launch_bounds__(64 * kStepWaves, 4) void step_logits_kernel(Args a) {
   using Dots = RowDots<T, D>;
   typedef typename Dots::frag frag;
-  constexpr int kElems = 16 / (int)sizeof(T);
-  __shared__ float red_m[kWaves][kMaxGroup], red_l[kWaves][kMaxGroup];
+  constexpr int kElems = 16 / (int)sizeof(T), kRows = 64 * kStepWaves;
+  __shared__ float red_m[kStepWaves][kMaxGroup], red_l[kStepWaves][kMaxGroup];
   const int chunk = blockIdx.x, ll = blockIdx.z;
   const int b = blockIdx.y / a.h_kv, g = blockIdx.y % a.h_kv;
   const int64_t head = (int64_t)b * a.h_kv + g, slice = (int64_t)ll * a.batch * a.h_kv + head;
@@ -289,11 +293,11 @@ __global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
   float* lg = a.logits + slice * a.group * a.rows_max;
 
   // layers of different lengths share a grid: most of the shorter ones' workgroups have no rows
-  if (!std::is_same<Args, StepOneArgs>::value && chunk * kThreads >= n) return;
+  if (!std::is_same<Args, StepOneArgs>::value && chunk * kRows >= n) return;
   // list entries of the lane's rows: for one layer loaded beside the state that says how many there are
   int32_t slot[4];
 #pragma unroll
-  for (int r = 0; r < 4; ++r) slot[r] = order[min(chunk * kThreads + wave * 64 + r * 16 + li, cap + a.window)];
+  for (int r = 0; r < 4; ++r) slot[r] = order[min(chunk * kRows + wave * 64 + r * 16 + li, cap + a.window)];
   frag qf[Dots::kSteps];
 #pragma unroll
   for (int s = 0; s < Dots::kSteps; ++s) {
@@ -302,7 +306,7 @@ __global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
 #pragma unroll
       for (int i = 0; i < kElems; ++i) qf[s][i] = (T)0.f;
   }
-  if (chunk * kThreads >= n) return;
+  if (chunk * kRows >= n) return;
   float m = kMasked, l = 0.f;                             // of head li over the lane's rows
   float t[64 / 16][4];
 #pragma unroll
@@ -310,7 +314,7 @@ __global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
     frag kf[Dots::kBlocks][Dots::kSteps];
 #pragma unroll
     for (int r = 0; r < Dots::kBlocks; ++r) {
-      const int j = chunk * kThreads + wave * 64 + (r0 + r) * 16 + li;
+      const int j = chunk * kRows + wave * 64 + (r0 + r) * 16 + li;
       // the generated token's row comes from the caller; rows past the end repeat it
       const T* row = j < n - 1 ? ks + slot[r0 + r] * tok : kn;
 #pragma unroll
@@ -319,7 +323,7 @@ __global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
 #pragma unroll
     for (int r = 0; r < Dots::kBlocks; ++r) {
       const f32x4 acc = Dots::run(kf[r], qf);
-      const int j0 = chunk * kThreads + wave * 64 + (r0 + r) * 16 + kg * 4;
+      const int j0 = chunk * kRows + wave * 64 + (r0 + r) * 16 + kg * 4;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         t[r0 + r][v] = j0 + v < n ? acc[v] * a.c : kMasked;
@@ -341,22 +345,22 @@ __global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
     m = mn;
   }
   if (lane < a.group) { red_m[wave][lane] = m; red_l[wave][lane] = l; }
-  if (chunk == (n - 1) / kThreads) {                      // the generated token's key and value into the free slot
+  if (chunk == (n - 1) / kRows) {                      // the generated token's key and value into the free slot
     constexpr int kPieces = D * (int)sizeof(T) / 16;
     const T* vn = reinterpret_cast<const T*>(a.v_new) + ll * a.ns[0] + b * a.ns[1] + g * a.ns[2];
     T* vs = reinterpret_cast<T*>(buf.v_slots) + b * a.ss[ll][0] + g * a.ss[ll][1];
-    if (tid < 2 * kPieces) {
-      const int e = (tid % kPieces) * kElems;
-      const T* src = tid < kPieces ? kn : vn;
-      T* dst = (tid < kPieces ? ks : vs) + free_slot * tok;
+    for (int i = tid; i < 2 * kPieces; i += kRows) {
+      const int e = (i % kPieces) * kElems;
+      const T* src = i < kPieces ? kn : vn;
+      T* dst = (i < kPieces ? ks : vs) + free_slot * tok;
       *reinterpret_cast<uint4*>(dst + e) = *reinterpret_cast<const uint4*>(src + e);
     }
   }
   __syncthreads();
   if (tid < a.group) {
     float mm = kMasked, sum = 0.f;
-    for (int w = 0; w < kWaves; ++w) mm = fmaxf(mm, red_m[w][tid]);
-    for (int w = 0; w < kWaves; ++w) sum += red_l[w][tid] * fast_exp2(red_m[w][tid] - mm);
+    for (int w = 0; w < kStepWaves; ++w) mm = fmaxf(mm, red_m[w][tid]);
+    for (int w = 0; w < kStepWaves; ++w) sum += red_l[w][tid] * fast_exp2(red_m[w][tid] - mm);
     float* o = a.part + ((slice * a.n_chunks + chunk) * kMaxGroup + tid) * 2;
     o[0] = mm;
     o[1] = sum;
@@ -373,6 +377,7 @@ __global__ __launch_bounds__(kThreads, 4) void step_logits_kernel(Args a) {
 // 384 heads of 2K.  Letting the last chunk of a slice do this work inside the
 // first kernel (a ticket per slice) was slower, 21 us against 14 for both: making the chunks' logits
 // visible across the dies costs more than the launch.
+constexpr int kStepSmallRows = 4096;       // one-wave workgroups in the first kernel: rows per slice at most
 constexpr int kFinishThreads = 1024, kFinishPer = 8, kFinishRows = kFinishThreads * kFinishPer;
 template <int kGroup, typename Args>
 __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_finish_kernel(Args a) {     // <= 64 registers: two workgroups per compute unit
@@ -391,23 +396,28 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   float* ind = buf.indicator + (int64_t)head * (cap + 1);
   const float* lg = a.logits + (int64_t)slice * a.group * a.rows_max;
   const int group = a.group;
+  // A layer alone is loaded up to what its buffers hold: no load waits for the state to say how much of it is in use.
+  constexpr bool kOne = std::is_same<Args, StepOneArgs>::value;
   int32_t slot[kFinishPer];
   float val[kFinishPer], t[kFinishPer][kGroup];
+  const int last = kOne ? cap + a.window : n - 1;
 #pragma unroll
   for (int i = 0; i < kFinishPer; ++i) {
     const int j = i * kFinishThreads + tid;
-    if (i * kFinishThreads < n) {
-      slot[i] = order[min(j, n - 2)];
-      val[i] = ind[min(j, cur)];
+    if (i * kFinishThreads <= last) {
+      slot[i] = order[min(j, last)];
+      val[i] = ind[min(j, kOne ? cap : cur)];
 #pragma unroll
-      for (int h = 0; h < kGroup; ++h) t[i][h] = lg[min(h, group - 1) * a.rows_max + min(j, n - 1)];
+      for (int h = 0; h < kGroup; ++h) t[i][h] = lg[min(h, group - 1) * a.rows_max + min(j, last)];
     }
   }
   if (wave < group) {
-    const int used = (n + kThreads - 1) / kThreads;
     const float* p = a.part + ((int64_t)slice * a.n_chunks * kMaxGroup + wave) * 2;
-    static_assert(kFinishRows / kThreads <= 64 && kMaxGroup <= kFinishWaves, "a lane per chunk and a wave per head");
-    const float2 x = lane < used ? *reinterpret_cast<const float2*>(p + lane * kMaxGroup * 2) : make_float2(kMasked, 0.f);
+    static_assert(kFinishRows / kThreads <= 64 && kStepSmallRows / 64 <= 64 && kMaxGroup <= kFinishWaves, "a lane per chunk and a wave per head");
+    float2 x = make_float2(kMasked, 0.f);
+    if (kOne) x = *reinterpret_cast<const float2*>(p + min(lane, a.n_chunks - 1) * kMaxGroup * 2);
+    else if (lane * a.chunk_rows < n) x = *reinterpret_cast<const float2*>(p + lane * kMaxGroup * 2);
+    if (lane * a.chunk_rows >= n) x = make_float2(kMasked, 0.f);
     const float m = wave_max(x.x), l = wave_sum(x.y * fast_exp2(x.x - m));
     if (lane == 0) lse[wave] = m + log2f(l);
   }
@@ -743,7 +753,7 @@ extern "C" int cake_decode_step_workspace_bytes(const cake_shape* shape, size_t*
   const size_t slices = (size_t)shape->n_layers * shape->batch * shape->n_kv_heads;
   const size_t n_chunks = ((size_t)shape->seq_len + kThreads - 1) / kThreads;
   *bytes = align_up(sizeof(float) * slices * align_up(shape->seq_len, 4) * kMaxGroup, 256) +
-           align_up(sizeof(float) * slices * n_chunks * kMaxGroup * 2, 256) + align_up(sizeof(float) * slices * n_chunks * 2, 256);
+           align_up(sizeof(float) * slices * n_chunks * (kThreads / 64) * kMaxGroup * 2, 256) + align_up(sizeof(float) * slices * n_chunks * 2, 256);
   return CAKE_OK;
 }
 
@@ -799,22 +809,28 @@ int decode_step_impl(const cake_shape* shape, const cake_params* params,
   a.logits = reinterpret_cast<float*>(ws);
   ws += align_up(sizeof(float) * slices * a.rows_max * kMaxGroup, 256);
   a.part = reinterpret_cast<float*>(ws);
-  ws += align_up(sizeof(float) * slices * a.n_chunks * kMaxGroup * 2, 256);
+  ws += align_up(sizeof(float) * slices * a.n_chunks * (kThreads / 64) * kMaxGroup * 2, 256);
   a.amin = reinterpret_cast<float*>(ws);
   int cap_max = 0;
   for (int l = 0; l < L; ++l) { a.cap[l] = cap[l]; cap_max = std::max(cap_max, cap[l]); }
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int rows = cap_max + shape->window + 1;
   const dim3 grid((rows + kThreads - 1) / kThreads, B * shape->n_kv_heads, L), block(kThreads);
+  // Where workgroups of 256 rows leave compute units idle, four of 64 rows in the place of each.
+  const bool small = (int64_t)grid.x * grid.y * L <= 256 && rows <= kStepSmallRows;
+  const dim3 logits_grid(small ? (rows + 63) / 64 : grid.x, grid.y, L), logits_block(small ? 64 : kThreads);
+  a.chunk_rows = small ? 64 : kThreads;
+  if (small) a.n_chunks *= kThreads / 64;
   const dim3 slices_grid(B * shape->n_kv_heads, L);
   const bool bf = shape->dtype == CAKE_BF16;
   auto launch = [&](const auto& args) -> int {
     using Args = std::decay_t<decltype(args)>;
-    if (bf && shape->head_dim == 128) hipLaunchKernelGGL((step_logits_kernel<__bf16, 128, Args>), grid, block, 0, st, args);
-    else if (bf && shape->head_dim == 64) hipLaunchKernelGGL((step_logits_kernel<__bf16, 64, Args>), grid, block, 0, st, args);
-    else if (!bf && shape->head_dim == 128) hipLaunchKernelGGL((step_logits_kernel<float, 128, Args>), grid, block, 0, st, args);
-    else if (!bf && shape->head_dim == 64) hipLaunchKernelGGL((step_logits_kernel<float, 64, Args>), grid, block, 0, st, args);
-    else return fail(CAKE_ERR_UNSUPPORTED, "no decode kernel for this shape");
+#define CAKE_STEP(T, D)                                                                                               \
+  (small ? step_logits_kernel<T, D, 1, Args> : step_logits_kernel<T, D, kThreads / 64, Args>)
+    const auto logits = bf ? (shape->head_dim == 128 ? CAKE_STEP(__bf16, 128) : CAKE_STEP(__bf16, 64))
+                           : (shape->head_dim == 128 ? CAKE_STEP(float, 128) : CAKE_STEP(float, 64));
+#undef CAKE_STEP
+    hipLaunchKernelGGL(logits, logits_grid, logits_block, 0, st, args);
     if (rows > kFinishRows) return CAKE_OK;
     if (G <= 4) hipLaunchKernelGGL((step_finish_kernel<4, Args>), slices_grid, dim3(kFinishThreads), 0, st, args);
     else hipLaunchKernelGGL((step_finish_kernel<kMaxGroup, Args>), slices_grid, dim3(kFinishThreads), 0, st, args);
