@@ -121,7 +121,7 @@ class cake_cascade(ctypes.Structure):
     """The buffers of a cascade chained on the device (csrc/cake_pass.h)."""
     _fields_ = [("shape", cake_shape), ("params", cake_params), ("max_layers", ctypes.c_int32), ("prefix_rows", ctypes.c_int32),
                 ("total_budget", ctypes.c_int64), ("workspace", _P), ("workspace_bytes", ctypes.c_uint64)] + \
-        [(n, _P) for n in ("pref", "hv", "status", "cur", "tables")] + [("plan", _P * 2), ("plan_bytes", ctypes.c_uint64),
+        [(n, _P) for n in ("pref", "hv", "status", "tables")] + [("plan", _P * 2), ("plan_bytes", ctypes.c_uint64),
          ("idx", _P), ("ind", _P * 2), ("slots", _P * 2)] + [(n, _P) for n in ("free_slots", "k_store", "v_store")]
 
 

@@ -54,12 +54,18 @@ ScoreLayout score_layout(const cake_shape& s);
 
 // cake_window_scores (or, with row_lse, cake_window_scores_lse) and cake_layer_preference with the
 // preferences computed beside the pooling; rows of pref_ld preferences and hv_ld (H, V) pairs per sequence.
-// `plan` (may be NULL): the plan that follows from them, made in the same launch or behind it
+// `plan` (may be NULL): the plan that follows from them, made in the same launch or behind it.
+// `one` (or NULL): the buffers of a call for one layer whose addresses the host knows, instead of the tables.
 struct PlanArgs;
+struct LayerPointers {
+  const void *q, *k;
+  const float* row_lse;          // NULL: the normalisers are computed
+  float* indicator;
+};
 int launch_scores_and_preference(const cake_shape* shape, const cake_params* params, const void* const* q_win,
                                  const void* const* k, const int64_t* q_strides, const int64_t* k_strides,
-                                 const float* const* row_lse, float* const* indicator, void* workspace, size_t workspace_bytes,
-                                 double* pref, double* hv, int pref_ld, int hv_ld, const PlanArgs* plan, hipStream_t stream);
+                                 const float* const* row_lse, float* const* indicator, const LayerPointers* one, void* workspace,
+                                 size_t workspace_bytes, double* pref, double* hv, int pref_ld, int hv_ld, const PlanArgs* plan, hipStream_t stream);
 
 // ---- ragged per-launch dimensions, passed to kernels by value ----------------------------
 constexpr int kMaxLaunchLayers = 32;
@@ -138,8 +144,9 @@ struct PlanMirror {
   uint32_t ticket;
 };
 // top-k and compaction of all layers with the counts and output places read from a plan
-// max_cur: the longest row to expect; `bounded` if no current length of the plan exceeds it
-int launch_topk_planned(const cake_shape* shape, const float* const* indicator, const PlanView& plan, int64_t max_cur, bool bounded,
+// max_cur: the longest row to expect; `bounded` if no current length of the plan exceeds it; `last`: the last layer's rows,
+// which are then not in the table
+int launch_topk_planned(const cake_shape* shape, const float* const* indicator, const float* last, const PlanView& plan, int64_t max_cur, bool bounded,
                         hipStream_t stream);
 // cake_evict_planned; `bounded` if the plan was made with current lengths of at most seq_len - window
 int evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,

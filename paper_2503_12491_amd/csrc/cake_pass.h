@@ -94,8 +94,7 @@ typedef struct {
   uint64_t workspace_bytes;
   double *pref, *hv;               // [B, max_layers], [B, max_layers, 2]
   int32_t* status;                 // [B]
-  int32_t* cur;                    // [max_layers, B] rows held before the stage
-  void** tables;                   // 6 * max_layers + 2 words, then int32 [max_layers, B]
+  void** tables;                   // 5 * max_layers words, then int32 [max_layers, B]
   void* plan[2];                   // even and odd stages, each of cake_plan_bytes at max_layers
   uint64_t plan_bytes;
   // Lists, B * H_kv * (sum over the layers of the largest count of the batch) words each: positions chosen in

@@ -5,10 +5,11 @@
 // stays where it was put when its layer was admitted: a layer is a list of places in a store of B_total
 // rows per head, a stage renews the lists (8 bytes a row), puts the places of the dropped rows on a
 // stack per head and takes the new layer's places from it.  One gather brings the rows into the caches'
-// layout when the caller asks for them.  A stage of 8K keys, d = 128, 8 heads: 55 us of copies and 18 us of
-// ten small ones -> 5.7 us (lists) + 11 us (the new layer's rows) + 2 us; 32 stages with the gather of 55 us:
-// 4595 -> 2600 us, where what is left is the scores (28 us a stage), the plan (8) and the top-k (11), each
-// too small for the chip and waiting for the one before, and some 2 us between two launches.
+// layout when the caller asks for them.  A stage of 8K keys, d = 128, 8 heads is a chain of launches too small for the chip,
+// each waiting for the one before, with some 1.7 us between two: the scores (7 + 9 us), the plan beside the pooling
+// (8.5), the top-k (10), the lists (5) and the new layer's rows (5).  Counts and addresses come from the stage before and from
+// the call, so that nothing has to be written ahead of the scores.  32 stages with the gather of 55 us: 4595 us with
+// copies, 2270 now.
 #include <algorithm>
 
 #include "cake_pass.h"
@@ -23,26 +24,14 @@ constexpr int kLongGap = 8;           // dropped rows in a row that one lane lis
 
 struct StageArgs {
   PlanView plan;                      // of this stage
-  void** tables;                      // [m + 1] the indicators before the stage, then q and k of the new layer
+  void* const* held;                  // [m] the indicators before the stage
+  const float* ind;                   // the new layer's
   const char *ind_old, *ind_new;      // pools the indicators are in; the lists of places have the same layout
   const int32_t* slots_old;
   int32_t* slots_new;
   int32_t* free_slots;
   int32_t m, batch, h_kv, window, prefix_rows, prefix_len;
 };
-
-// Tables and counts of a stage: what the previous stage left, and the new layer's.
-__global__ __launch_bounds__(kThreads) void begin_stage(StageArgs a, PlanView before, int32_t* cur, const void* q, const void* k, void* ind) {
-  const int n_entries = a.m * a.batch;
-  for (int i = threadIdx.x; i < n_entries; i += kThreads) cur[i] = before.keep[i];
-  for (int i = threadIdx.x; i < a.batch; i += kThreads) cur[n_entries + i] = a.prefix_len;
-  for (int l = threadIdx.x; l < a.m; l += kThreads) a.tables[l] = before.ind_out[l];
-  if (threadIdx.x == 0) {
-    a.tables[a.m] = ind;
-    a.tables[a.m + 1] = const_cast<void*>(q);
-    a.tables[a.m + 2] = const_cast<void*>(k);
-  }
-}
 
 // Sum over the layers before l of keep (or of cur - keep) of sequence b, by one wave.
 __device__ __forceinline__ int32_t rows_before(const StageArgs& a, int l, int b, bool dropped, int lane) {
@@ -67,7 +56,7 @@ __global__ __launch_bounds__(kThreads) void renew_lists(StageArgs a) {
   const int32_t* idx = static_cast<const int32_t*>(a.plan.idx[l]) + at;
   float* ind_out = static_cast<float*>(a.plan.ind_out[l]) + at;
   const int64_t from = (int64_t)head * a.plan.cap_cur[l];
-  const float* ind_in = static_cast<const float*>(a.tables[l]) + from;
+  const float* ind_in = (l == a.m ? a.ind : static_cast<const float*>(a.held[l])) + from;
   if (l == a.m) {                     // the new layer gets its places in fill_rows
     for (int r = tid; r < keep; r += all) ind_out[r] = ind_in[min(max(idx[r], 0), cur - 1)];
     return;
@@ -174,9 +163,10 @@ __global__ __launch_bounds__(kThreads) void gather_tables(StageArgs a, int n_lay
   for (int i = threadIdx.x; i < n_layers * a.batch; i += kThreads) window_at[i] = a.prefix_rows + i / a.batch * a.window;
 }
 
-StageArgs stage_args(const cake_cascade* c, int m) {
+StageArgs stage_args(const cake_cascade* c, int m, const float* ind) {
   const cake_shape& s = c->shape;
-  return StageArgs{plan_view(c->plan[m & 1], m + 1, s.batch), c->tables, reinterpret_cast<const char*>(c->ind[(m & 1) ^ 1]),
+  const PlanView before = plan_view(c->plan[(m & 1) ^ 1], std::max(m, 1), s.batch);
+  return StageArgs{plan_view(c->plan[m & 1], m + 1, s.batch), before.ind_out, ind, reinterpret_cast<const char*>(c->ind[(m & 1) ^ 1]),
                    reinterpret_cast<const char*>(c->ind[m & 1]), c->slots[(m & 1) ^ 1], c->slots[m & 1], c->free_slots, m, s.batch,
                    s.n_kv_heads, s.window, c->prefix_rows, s.seq_len - s.window};
 }
@@ -202,17 +192,20 @@ extern "C" int cake_cascade_stage(const cake_cascade* c, int32_t m, const void* 
     CAKE_REQUIRE((kv_strides[j] * eb) % 16 == 0, "strides must be multiples of 16 bytes");
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const StageArgs a = stage_args(c, m);
-  const PlanView before = plan_view(c->plan[(m & 1) ^ 1], std::max(m, 1), shape.batch);
-  hipLaunchKernelGGL(begin_stage, dim3(1), dim3(kThreads), 0, st, a, before, c->cur, q_win, k, static_cast<void*>(indicator));
+  const StageArgs a = stage_args(c, m, indicator);
   const int L = c->max_layers;
+  // the rows held before the stage: what the stage before kept, and the new layer whole
   PlanArgs plan{};
-  if (int rc = plan_args(&shape, c->pref, L, c->total_budget, c->cur, c->idx, c->k_store, c->v_store, c->ind[m & 1], c->plan[m & 1],
+  if (int rc = plan_args(&shape, c->pref, L, c->total_budget, nullptr, c->idx, c->k_store, c->v_store, c->ind[m & 1], c->plan[m & 1],
                          c->plan_bytes, c->status, PlanMirror{}, &plan)) return rc;
-  if (int rc = launch_scores_and_preference(&c->shape, &c->params, c->tables + m + 1, c->tables + m + 2, q_strides, kv_strides, nullptr,
-                                            reinterpret_cast<float* const*>(c->tables + m), c->workspace, c->workspace_bytes,
-                                            c->pref + m, c->hv + 2 * m, L, L, &plan, st)) return rc;
-  if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(c->tables), a.plan, a.prefix_len, true, st)) return rc;
+  if (m > 0) {
+    plan.cur_len = plan_view(c->plan[(m & 1) ^ 1], m, shape.batch).keep;
+    plan.cur_known = m * shape.batch;
+  }
+  const LayerPointers one{q_win, k, nullptr, indicator};
+  if (int rc = launch_scores_and_preference(&c->shape, &c->params, nullptr, nullptr, q_strides, kv_strides, nullptr, nullptr, &one,
+                                            c->workspace, c->workspace_bytes, c->pref + m, c->hv + 2 * m, L, L, &plan, st)) return rc;
+  if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(a.held), indicator, a.plan, a.prefix_len, true, st)) return rc;
   const int64_t shares = std::min<int64_t>((a.prefix_len + kThreads) / kThreads, 2048 / ((int64_t)bh * (m + 1)));
   hipLaunchKernelGGL(renew_lists, dim3(bh, m + 1, (unsigned)std::max<int64_t>(shares, 1)), dim3(kThreads), 0, st, a);
   // as many workgroups as the most rows the layer can keep fill, up to four for each compute unit
@@ -233,9 +226,8 @@ extern "C" int cake_cascade_gather(const cake_cascade* c, int32_t n_layers, void
   hipStream_t st = static_cast<hipStream_t>(stream);
   cake_shape shape = c->shape;
   shape.n_layers = n_layers;
-  const StageArgs a = stage_args(c, n_layers - 1);
-  // the stage tables come first (the next stage reads none of them); these follow
-  void** tables = c->tables + c->max_layers + 2;
+  const StageArgs a = stage_args(c, n_layers - 1, nullptr);
+  void** tables = c->tables;
   int32_t* window_at = reinterpret_cast<int32_t*>(tables + 5 * (size_t)c->max_layers);
   hipLaunchKernelGGL(gather_tables, dim3(1), dim3(kThreads), 0, st, a, n_layers, c->k_store, c->v_store, static_cast<char*>(pool_k),
                      static_cast<char*>(pool_v), tables, window_at);

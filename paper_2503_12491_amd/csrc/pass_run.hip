@@ -51,7 +51,7 @@ extern "C" int cake_pass_launch(const cake_pass* p, int32_t parts, uint32_t tick
   }
   if (parts & CAKE_PASS_SCORES)
     if (int rc = launch_scores_and_preference(&p->shape, &p->params, p->q_win, p->k, p->q_strides, p->kv_strides, p->row_lse,
-                                              p->indicator, p->workspace, p->workspace_bytes, p->pref, p->hv,
+                                              p->indicator, nullptr, p->workspace, p->workspace_bytes, p->pref, p->hv,
                                               p->shape.n_layers, p->shape.n_layers, parts & CAKE_PASS_EVICT ? &plan : nullptr, st)) return rc;
   if (parts & CAKE_PASS_EVICT) {
     if (!(parts & CAKE_PASS_SCORES))

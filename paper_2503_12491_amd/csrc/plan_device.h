@@ -61,7 +61,8 @@ struct PlanArgs {
   const double* pref;         // [B] rows of pref_ld
   int32_t pref_ld, n_layers, batch, h_kv, window, seq_len, row_bytes;
   int64_t total_budget;
-  const int32_t* cur_len;     // [L*B] or NULL: seq_len - window
+  const int32_t* cur_len;     // of the first cur_known of the [L*B] entries; the others': seq_len - window
+  int32_t cur_known;
   int32_t *budgets, *keep, *cur, *cap_keep, *cap_cur, *copy_blocks, *status;
   char *pool_idx, *pool_k, *pool_v, *pool_ind;
   void **idx_tbl, **k_tbl, **v_tbl, **ind_tbl;
@@ -232,7 +233,7 @@ __device__ void allocate_sequence(const PlanArgs& a, int b, int lane, double* p_
   }
   for (int l = lane; l < n_layers; l += 64) {
     const int64_t e = (int64_t)l * a.batch + b;
-    const int cur = a.cur_len ? a.cur_len[e] : seq_len - window;
+    const int cur = e < a.cur_known ? a.cur_len[e] : seq_len - window;
     a.budgets[e] = bud[l];
     a.keep[e] = min(max(bud[l] - window, 0), cur);
     a.cur[e] = cur;

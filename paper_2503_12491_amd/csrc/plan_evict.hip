@@ -76,7 +76,7 @@ int cake::plan_args(const cake_shape* shape, const double* pref, int pref_ld, in
   a.pref = pref; a.pref_ld = pref_ld;
   a.n_layers = L; a.batch = shape->batch; a.h_kv = shape->n_kv_heads; a.window = shape->window; a.seq_len = shape->seq_len;
   a.row_bytes = (int32_t)(shape->head_dim * elem_bytes(shape->dtype));
-  a.total_budget = total_budget; a.cur_len = cur_len;
+  a.total_budget = total_budget; a.cur_len = cur_len; a.cur_known = cur_len ? L * shape->batch : 0;
   a.budgets = reinterpret_cast<int32_t*>(b + lay.off_budgets);
   a.keep = reinterpret_cast<int32_t*>(b + lay.off_keep);
   a.cur = reinterpret_cast<int32_t*>(b + lay.off_cur);
@@ -155,7 +155,7 @@ int cake::evict_planned(const cake_shape* shape, const float* const* indicator, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   // without a length in the shape the kernel for any length serves
   const int64_t max_cur = shape->seq_len > shape->window ? shape->seq_len - shape->window : 0x7fffffff;
-  if (int rc = launch_topk_planned(shape, indicator, view, max_cur, bounded, st)) return rc;
+  if (int rc = launch_topk_planned(shape, indicator, nullptr, view, max_cur, bounded, st)) return rc;
   return launch_compact_planned(shape, k_in, v_in, kv_strides, compacted, indicator, view, st);
 }
 

@@ -32,6 +32,7 @@ constexpr int kMaxWaves = 16;
 
 struct TopkArgs {
   const float* const* indicator;
+  const float* last;          // of the last layer; NULL: in the table as well
   int32_t* const* idx;
   int32_t batch, h_kv;
   int32_t cap_cur[kMaxLaunchLayers];
@@ -340,7 +341,8 @@ __device__ __forceinline__ RowTask row_task(const TopkArgs& a, const RaggedDims&
   const int cap_keep = kPlanned ? plan.cap_keep[ll] : a.cap_keep[ll];
   RowTask t;
   t.keep = kPlanned ? plan.keep[e] : dims.keep[e];
-  t.row.init(a.indicator[ll] + ((int64_t)b * a.h_kv + h) * cap_cur, cur);
+  const float* indicator = a.last != nullptr && ll == (int)gridDim.y - 1 ? a.last : a.indicator[ll];
+  t.row.init(indicator + ((int64_t)b * a.h_kv + h) * cap_cur, cur);
   t.out = a.idx[ll] + ((int64_t)b * a.h_kv + h) * cap_keep;
   return t;
 }
@@ -593,10 +595,11 @@ int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs& a, const 
 }  // namespace
 }  // namespace cake
 
-int cake::launch_topk_planned(const cake_shape* shape, const float* const* indicator, const PlanView& plan, int64_t max_cur,
+int cake::launch_topk_planned(const cake_shape* shape, const float* const* indicator, const float* last, const PlanView& plan, int64_t max_cur,
                               bool bounded, hipStream_t stream) {
   TopkArgs a{};
   a.indicator = indicator;
+  a.last = last;
   a.idx = reinterpret_cast<int32_t* const*>(plan.idx);
   a.batch = shape->batch;
   a.h_kv = shape->n_kv_heads;

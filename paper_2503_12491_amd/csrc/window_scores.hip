@@ -102,6 +102,7 @@ struct ScoreArgs {
   const void* const* q_win;
   const void* const* k;
   float* const* indicator;
+  LayerPointers one;         // one layer's, where there are no tables
   int64_t qs[3], ks[3];      // element strides: batch, head, token
   int32_t batch, h_kv, group, n, n_p, chunk, wg_keys, granule, n_granules, n_granules_p, pool;   // wg_keys: keys per workgroup, granules each
   int32_t key_lo, key_hi;    // keys [key_lo, key_hi) are behind the k pointers (row 0 = key key_lo); the whole layer: 0, n
@@ -308,10 +309,10 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass1(ScoreArgs a) 
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
-  const T* q = reinterpret_cast<const T*>(a.q_win[l]) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
+  const T* q = reinterpret_cast<const T*>(a.q_win ? a.q_win[l] : a.one.q) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
   const int64_t tok_bytes = a.ks[2] * (int64_t)sizeof(T);
   // address of key 0 of the slice (keys below key_lo are not behind the pointer and never touched)
-  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k[l]) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
+  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k ? a.k[l] : a.one.k) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
                       (int64_t)a.key_lo * tok_bytes;
 
   const int key0 = a.key0 + blockIdx.x * a.wg_keys;
@@ -530,7 +531,7 @@ __global__ __launch_bounds__(256) void scores_combine(ScoreArgs a, int rows_per_
 __global__ void scores_import_lse(ScoreArgs a, const float* const* row_lse, int64_t per_layer, int64_t total) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
-  a.lse[i] = row_lse[i / per_layer][i % per_layer] * 1.4426950408889634f;
+  a.lse[i] = (row_lse ? row_lse[i / per_layer] : a.one.row_lse)[i % per_layer] * 1.4426950408889634f;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -660,10 +661,10 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
-  const T* q = reinterpret_cast<const T*>(a.q_win[l]) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
+  const T* q = reinterpret_cast<const T*>(a.q_win ? a.q_win[l] : a.one.q) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
   const int64_t tok_bytes = a.ks[2] * (int64_t)sizeof(T);
   // address of key 0 of the slice (keys below key_lo are not behind the pointer and never touched)
-  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k[l]) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
+  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k ? a.k[l] : a.one.k) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
                       (int64_t)a.key_lo * tok_bytes;
 
   const int key0 = a.key0 + blockIdx.x * a.wg_keys;
@@ -917,7 +918,7 @@ __device__ __forceinline__ void pool_span(const ScoreArgs& a, int slice) {
   const int j0 = blockIdx.x * kPoolSpan;
   const int span = min(kPoolSpan, a.n_p - j0);
   const float* raw = a.raw + (int64_t)slice * a.n_p;
-  float* out = a.indicator[l] + ((int64_t)b * a.h_kv + g) * a.n_p;
+  float* out = (a.indicator ? a.indicator[l] : a.one.indicator) + ((int64_t)b * a.h_kv + g) * a.n_p;
   // Rows of a multiple of four positions at 16-byte aligned addresses, windows of at most nine:
   // 16-byte loads and stores, four outputs per lane from three 16-byte LDS reads.
   const bool quads = a.n_p % 4 == 0 && half <= kPoolQuadHalf &&
@@ -1109,7 +1110,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   }
   mark(0, stream);
   bool combine = false;
-  if (row_lse == nullptr) {
+  if (row_lse == nullptr && a.one.row_lse == nullptr) {
     CAKE_HIP_TRY(run_pass1(0, a.n));
     mark(1, stream);
     // every workgroup of pass 2 reads its slice's pairs where it combines them itself: at most 16 MB in all
@@ -1195,7 +1196,7 @@ int window_scores_impl(const cake_shape* shape, const cake_params* params,
                        const float* const* row_lse, float* const* indicator,
                        void* workspace, size_t workspace_bytes, void* stream,
                        ScoreParts parts = kPartsAll, int key_begin = 0, int key_count = 0, const PrefArgs* pref = nullptr,
-                       const PlanArgs* plan = nullptr) {
+                       const PlanArgs* plan = nullptr, const LayerPointers* one = nullptr) {
   if (int rc = check_shape_scores(shape)) return rc;
   CAKE_REQUIRE(params != nullptr, "params is NULL");
   // what the parts of this call touch: the two finishing steps read neither queries nor keys,
@@ -1203,10 +1204,10 @@ int window_scores_impl(const cake_shape* shape, const cake_params* params,
   const bool reads_keys = parts == kPartsAll || parts == kPartsPass1Segment || parts == kPartsPass2Segment;
   const bool writes_indicator = parts == kPartsAll || parts == kPartsPool;
   if (reads_keys) {
-    CAKE_REQUIRE(q_win && k, "q_win or k table is NULL");
+    CAKE_REQUIRE((q_win && k) || one, "q_win or k table is NULL");
     CAKE_REQUIRE(q_strides && k_strides, "q_strides or k_strides is NULL");
   }
-  CAKE_REQUIRE(!writes_indicator || indicator, "indicator table is NULL");
+  CAKE_REQUIRE(!writes_indicator || indicator || one, "indicator table is NULL");
   CAKE_REQUIRE(params->pool_kernel >= 1 && params->pool_kernel % 2 == 1 && params->pool_kernel <= 2 * kPoolMaxHalf + 1,
                "pool_kernel %d must be odd and within [1, %d]", params->pool_kernel, 2 * kPoolMaxHalf + 1);
   CAKE_REQUIRE(params->indicator_mode >= CAKE_IND_MEAN_PLUS_VAR && params->indicator_mode <= CAKE_IND_CUMULATIVE,
@@ -1231,6 +1232,7 @@ int window_scores_impl(const cake_shape* shape, const cake_params* params,
 
   ScoreArgs a{};
   a.q_win = q_win; a.k = k; a.indicator = indicator;
+  if (one) a.one = *one;
   if (reads_keys)
     for (int i = 0; i < 3; ++i) { a.qs[i] = q_strides[i]; a.ks[i] = k_strides[i]; }
   a.batch = shape->batch; a.h_kv = shape->n_kv_heads; a.group = shape->n_q_heads / shape->n_kv_heads;
@@ -1360,13 +1362,13 @@ extern "C" int cake_layer_preference(const cake_shape* shape, const cake_params*
 
 int cake::launch_scores_and_preference(const cake_shape* shape, const cake_params* params, const void* const* q_win,
                                        const void* const* k, const int64_t* q_strides, const int64_t* k_strides,
-                                       const float* const* row_lse, float* const* indicator, void* workspace,
-                                       size_t workspace_bytes, double* pref, double* hv, int pref_ld, int hv_ld, const PlanArgs* plan,
+                                       const float* const* row_lse, float* const* indicator, const LayerPointers* one,
+                                       void* workspace, size_t workspace_bytes, double* pref, double* hv, int pref_ld, int hv_ld, const PlanArgs* plan,
                                        hipStream_t stream) {
   PrefArgs a{};
   if (int rc = preference_args(shape, params, workspace, workspace_bytes, pref, hv, &a)) return rc;
   a.pref_ld = pref_ld;
   a.hv_ld = hv_ld;
   return window_scores_impl(shape, params, q_win, k, q_strides, k_strides, row_lse, indicator, workspace, workspace_bytes,
-                            stream, kPartsAll, 0, 0, &a, plan);
+                            stream, kPartsAll, 0, 0, &a, plan, one);
 }
