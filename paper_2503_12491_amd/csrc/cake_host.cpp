@@ -93,16 +93,18 @@ extern "C" int cake_workspace_bytes(const cake_shape* shape, size_t* bytes) {
 }
 
 // Number of seat counts s in [window, n-1] whose priority p/(s + 1/2) is strictly above lam.
-// The quotient never increases with s, so the boundary is found by bisection on s with the
+// The quotient never increases with s, so the last such s is found from a closed-form guess, corrected with the
 // same fp64 division the award loop uses.
 static int64_t seats_above(double p, double lam, int32_t window, int32_t n) {
   if (!(p / (window + 0.5) > lam)) return 0;
-  int64_t lo = window, hi = n - 1;          // invariant: quotient(lo) > lam
-  while (lo < hi) {
-    int64_t mid = lo + (hi - lo + 1) / 2;
-    if (p / ((double)mid + 0.5) > lam) lo = mid; else hi = mid - 1;
+  int64_t s = n - 1;
+  if (lam > 0.0) {
+    const double guess = std::floor(p / lam - 0.5);
+    s = guess >= (double)(n - 1) ? n - 1 : guess <= (double)window ? window : (int64_t)guess;
   }
-  return lo - window + 1;
+  while (s < n - 1 && p / ((double)s + 1.5) > lam) ++s;
+  while (s > window && !(p / ((double)s + 0.5) > lam)) --s;
+  return s - window + 1;
 }
 
 extern "C" int cake_keep_counts(const int32_t* budgets, const int32_t* cur_len, int32_t n, int32_t window, int32_t* keep) {
@@ -150,10 +152,27 @@ extern "C" int cake_cascade_allocate(const double* pref, int32_t n_seen, int64_t
   if (taken_above(lo) <= r_total) {
     hi = lo;
   } else {
-    for (int it = 0; it < 80; ++it) {
-      double mid = 0.5 * (lo + hi);
-      if (!(mid > lo && mid < hi)) break;
-      if (taken_above(mid) <= r_total) hi = mid; else lo = mid;
+    // Any such level will do, and one that leaves the loop a seat per layer is soon found: the layers that are neither
+    // at their floor nor full hold p/lam - window seats each, give or take one.  (A search that has not ended after six
+    // of these steps halves the bracket at every other one.)
+    double sum_p = 0.0;
+    for (double x : p) sum_p += x;
+    double lam = sum_p / ((double)total_budget + 0.5 * n_seen);
+    for (int it = 0; it < 160; ++it) {
+      if (!(lam > lo && lam < hi)) lam = 0.5 * (lo + hi);
+      if (!(lam > lo && lam < hi)) break;
+      int64_t taken = 0;
+      double active_p = 0.0;
+      for (int l = 0; l < n_seen; ++l) {
+        const int64_t s = seats_above(p[l], lam, window, seq_len);
+        taken += s;
+        if (s > 0 && s < seq_len - window) active_p += p[l];
+      }
+      if (taken <= r_total) hi = lam; else lo = lam;
+      const int64_t left = r_total - taken;
+      if (left >= 0 && left <= n_seen) break;
+      const double seats = active_p / lam + (double)left - 0.5 * n_seen;
+      lam = active_p > 0.0 && seats > 0.0 && (it < 6 || (it & 1)) ? active_p / seats : 0.5 * (lo + hi);
     }
   }
   std::vector<int64_t> b(n_seen);
