@@ -70,13 +70,6 @@ _SIGNATURES = {
     "cake_profile_read": (ctypes.c_int, [ctypes.POINTER(ctypes.c_float)]),
 }
 
-# calls that are not part of the public ABI (csrc/cake_pass.h)
-_INTERNAL = {
-    "cake_compact_kv_positions": (ctypes.c_int, [ctypes.POINTER(cake_shape), _P, _P, ctypes.POINTER(ctypes.c_int64),
-                                                 ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32), _P, _P,
-                                                 _P, _P, _P, _P, _P, _P]),
-}
-
 _lib = None
 
 
@@ -89,7 +82,7 @@ def load() -> ctypes.CDLL:
                 f"{LIB_PATH} is missing: build it with `python -m paper_2503_12491_amd.build` "
                 "(hipcc, gfx950).  This package has no CPU or PyTorch fallback.")
         lib = ctypes.CDLL(LIB_PATH)
-        for name, (res, args) in {**_SIGNATURES, **_INTERNAL}.items():
+        for name, (res, args) in _SIGNATURES.items():
             fn = getattr(lib, name)
             fn.restype, fn.argtypes = res, args
         _lib = lib
@@ -123,6 +116,14 @@ class cake_cascade(ctypes.Structure):
                 ("total_budget", ctypes.c_int64), ("workspace", _P), ("workspace_bytes", ctypes.c_uint64)] + \
         [(n, _P) for n in ("pref", "hv", "status", "tables")] + [("plan", _P * 2), ("plan_bytes", ctypes.c_uint64),
          ("idx", _P), ("ind", _P * 2), ("slots", _P * 2)] + [(n, _P) for n in ("free_slots", "k_store", "v_store")]
+
+
+class cake_session(ctypes.Structure):
+    """A cascade whose allocation is the host's (csrc/cake_pass.h)."""
+    _fields_ = [("shape", cake_shape), ("params", cake_params), ("max_layers", ctypes.c_int32), ("track_positions", ctypes.c_int32),
+                ("total_budget", ctypes.c_int64), ("workspace", _P), ("workspace_bytes", ctypes.c_uint64)] + \
+        [(n, _P) for n in ("mirror", "tables", "pref", "hv", "cur_len", "k", "v", "ind", "pos", "strides", "cap", "off_kv", "off_i",
+                           "budgets")]
 
 
 PASS_SCORES, PASS_EVICT = 1, 2

@@ -221,15 +221,6 @@ def cake_compact_kv(shape, k_in, v_in, kv_strides, cur_len, k, idx, ind_in, k_ou
                                   _stream(stream)))
 
 
-def cake_compact_kv_positions(shape, k_in, v_in, kv_strides, cur_len, k, idx, ind_in, k_out, v_out, ind_out, pos_in, pos_out,
-                              stream=None) -> None:
-    """cake_compact_kv that also carries the rows' positions in the prompt (csrc/cake_pass.h)."""
-    flat = [s for layer in kv_strides for s in layer]
-    _check(load().cake_compact_kv_positions(ctypes.byref(shape), _ptr(k_in), _ptr(v_in), _i64(flat), _i32(cur_len), _i32(k),
-                                            _ptr(idx), _ptr(ind_in), _ptr(k_out), _ptr(v_out), _ptr(ind_out), _ptr(pos_in),
-                                            _ptr(pos_out), _stream(stream)))
-
-
 def cake_quantize_kv(shape, bits, k_hat, v_hat, kv_strides, keep, k_codes, k_scale, k_zero, v_codes, v_scale, v_zero,
                      stream=None) -> None:
     flat = [s for layer in kv_strides for s in layer]

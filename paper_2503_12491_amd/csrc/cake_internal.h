@@ -61,6 +61,8 @@ struct LayerPointers {
   const void *q, *k;
   const float* row_lse;          // NULL: the normalisers are computed
   float* indicator;
+  uint32_t* flags;               // or NULL: `ticket` goes to flags[b] once sequence b's preference and (H, V) are written
+  uint32_t ticket;
 };
 int launch_scores_and_preference(const cake_shape* shape, const cake_params* params, const void* const* q_win,
                                  const void* const* k, const int64_t* q_strides, const int64_t* k_strides,

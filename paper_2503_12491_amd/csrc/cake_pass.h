@@ -57,6 +57,32 @@ int cake_compact_kv_positions(const cake_shape* shape, const void* const* k_in, 
                               const float* const* ind_in, void* const* k_out, void* const* v_out, float* const* ind_out,
                               const int32_t* const* pos_in, int32_t* const* pos_out, void* stream);
 
+// Alg. 1 with the allocation on the host (CascadeSession).  The session's own arrays are host memory; what is
+// indexed by layer has room for max_layers.
+typedef struct {
+  cake_shape shape;                // of one layer
+  cake_params params;
+  int32_t max_layers, track_positions;
+  int64_t total_budget;
+  void* workspace;                 // of cake_workspace_bytes(shape)
+  uint64_t workspace_bytes;
+  void* mirror;                    // pinned: double pref[B], hv[B][2], then uint32 flags[B]
+  void** tables;                   // device [9 * max_layers]
+  double *pref, *hv;               // [B][max_layers], [B][max_layers][2]
+  int64_t* cur_len;                // [max_layers][B] prefix rows held
+  int64_t *k, *v, *ind, *pos;      // addresses of the layers' rows; pos 0: row r is position r of the prompt
+  int64_t *strides, *cap;          // [max_layers][3] of K and V, row capacity
+  int64_t *off_kv, *off_i;         // element offsets in the slabs, -1: the caller's own tensors
+  int64_t* budgets;                // [max_layers][B] of the last stage
+} cake_session;
+// Scores of one layer and its preferences into the mirror; the flags take `ticket`.
+int cake_session_scores(const cake_session* s, const void* q_win, const void* k, const float* row_lse, float* indicator,
+                        const int64_t* q_strides, const int64_t* kv_strides, uint32_t ticket, void* stream);
+// Returns when the mirror holds what the scores of `ticket` wrote.
+int cake_session_wait(const cake_session* s, uint32_t ticket, void* stream);
+// n words to device memory, as kernel arguments: nothing of the caller's is read after the call.
+int cake_write_words(void* dst, const uint64_t* words, int32_t n, void* stream);
+
 // The buffers of an in-place decode step (cake_decode_step) at up to 32 layers, described once.
 #define CAKE_DECODE_LAYERS 32
 typedef struct {

@@ -202,7 +202,7 @@ extern "C" int cake_cascade_stage(const cake_cascade* c, int32_t m, const void* 
     plan.cur_len = plan_view(c->plan[(m & 1) ^ 1], m, shape.batch).keep;
     plan.cur_known = m * shape.batch;
   }
-  const LayerPointers one{q_win, k, nullptr, indicator};
+  const LayerPointers one{q_win, k, nullptr, indicator, nullptr, 0};
   if (int rc = launch_scores_and_preference(&c->shape, &c->params, nullptr, nullptr, q_strides, kv_strides, nullptr, nullptr, &one,
                                             c->workspace, c->workspace_bytes, c->pref + m, c->hv + 2 * m, L, L, &plan, st)) return rc;
   if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(a.held), indicator, a.plan, a.prefix_len, true, st)) return rc;

@@ -28,6 +28,31 @@ __global__ __launch_bounds__(kPlaceLayers) void place_outputs(PlaceArgs a) {
   a.tables[3 * a.n_layers + l] = a.ind + before * a.row_i;
 }
 
+constexpr int kWords = 448;                  // per launch: 3.5 KiB of arguments
+struct WordArgs {
+  uint64_t* dst;
+  int32_t n;
+  uint64_t w[kWords];
+};
+__global__ __launch_bounds__(kWords) void write_words(WordArgs a) {
+  if ((int)threadIdx.x < a.n) a.dst[threadIdx.x] = a.w[threadIdx.x];
+}
+
+// Until `flag` holds the ticket.  A watched flag is seen within a microsecond; a stream that is this slow or broken is
+// left to the runtime.
+int wait_flag(const uint32_t* flag, uint32_t ticket, void* stream) {
+  const auto arrived = [&] { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == ticket; };
+  const auto t0 = std::chrono::steady_clock::now();
+  for (uint32_t i = 1; !arrived(); ++i) {
+    __builtin_ia32_pause();
+    if ((i & 1023) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(200)) {
+      if (int rc = cake_stream_wait(stream)) return rc;
+      CAKE_REQUIRE(arrived(), "the plan did not arrive");
+    }
+  }
+  return CAKE_OK;
+}
+
 }  // namespace
 }  // namespace cake
 
@@ -91,16 +116,39 @@ extern "C" int cake_stream_wait(void* stream) {
 
 extern "C" int cake_pass_wait_plan(const void* mirror, uint32_t ticket, void* stream) {
   CAKE_REQUIRE(mirror != nullptr && ticket != 0, "no mirror to wait on");
-  const uint32_t* flag = static_cast<const uint32_t*>(mirror);
-  const auto arrived = [&] { return __atomic_load_n(flag, __ATOMIC_ACQUIRE) == ticket; };
-  // A watched flag is seen within a microsecond; a stream that is this slow or broken is left to the runtime.
-  const auto t0 = std::chrono::steady_clock::now();
-  for (uint32_t i = 1; !arrived(); ++i) {
-    __builtin_ia32_pause();
-    if ((i & 1023) == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::milliseconds(200)) {
-      if (int rc = cake_stream_wait(stream)) return rc;
-      CAKE_REQUIRE(arrived(), "the plan did not arrive");
-    }
+  return wait_flag(static_cast<const uint32_t*>(mirror), ticket, stream);
+}
+
+extern "C" int cake_session_scores(const cake_session* s, const void* q_win, const void* k, const float* row_lse, float* indicator,
+                                   const int64_t* q_strides, const int64_t* kv_strides, uint32_t ticket, void* stream) {
+  CAKE_REQUIRE(s && q_win && k && indicator && q_strides && kv_strides && s->mirror && ticket != 0, "a required argument is NULL");
+  if (int rc = check_shape_scores(&s->shape)) return rc;
+  CAKE_REQUIRE(s->shape.n_layers == 1, "the scores of one layer, not of %d", s->shape.n_layers);
+  double* pref = static_cast<double*>(s->mirror);
+  const int B = s->shape.batch;
+  const LayerPointers one{q_win, k, row_lse, indicator, reinterpret_cast<uint32_t*>(pref + 3 * B), ticket};
+  return launch_scores_and_preference(&s->shape, &s->params, nullptr, nullptr, q_strides, kv_strides, nullptr, nullptr, &one, s->workspace,
+                                      s->workspace_bytes, pref, pref + B, 1, 1, nullptr, static_cast<hipStream_t>(stream));
+}
+
+extern "C" int cake_session_wait(const cake_session* s, uint32_t ticket, void* stream) {
+  CAKE_REQUIRE(s && s->mirror && ticket != 0, "no mirror to wait on");
+  const int B = s->shape.batch;
+  const uint32_t* flags = reinterpret_cast<const uint32_t*>(static_cast<const double*>(s->mirror) + 3 * B);
+  for (int b = 0; b < B; ++b)
+    if (int rc = wait_flag(flags + b, ticket, stream)) return rc;
+  return CAKE_OK;
+}
+
+extern "C" int cake_write_words(void* dst, const uint64_t* words, int32_t n, void* stream) {
+  CAKE_REQUIRE(dst && words && n >= 0, "a pointer argument is NULL");
+  WordArgs a{};
+  for (int at = 0; at < n; at += kWords) {
+    a.dst = static_cast<uint64_t*>(dst) + at;
+    a.n = n - at < kWords ? n - at : kWords;
+    for (int i = 0; i < a.n; ++i) a.w[i] = words[at + i];
+    hipLaunchKernelGGL(write_words, dim3(1), dim3(kWords), 0, static_cast<hipStream_t>(stream), a);
   }
+  CAKE_HIP_TRY(hipGetLastError());
   return CAKE_OK;
 }

@@ -807,6 +807,8 @@ struct PrefArgs {
   double* pref;                // [B] rows of pref_ld
   double* hv_out;              // [B, n_layers, 2] or NULL
   int32_t pref_ld, hv_ld;
+  uint32_t* flags;             // of a layer alone, or NULL (LayerPointers)
+  uint32_t ticket;
 };
 constexpr int kPrefThreads = 256;
 
@@ -822,6 +824,10 @@ __device__ __forceinline__ void store_preference(const PrefArgs& a, int entry, d
   if (a.hv_out) {
     a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 0] = h_l;
     a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 1] = v_l;
+  }
+  if (a.flags) {                // a host that watches the flag finds the preference in its memory
+    __threadfence_system();
+    __hip_atomic_store(a.flags + b, a.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 
@@ -1344,7 +1350,7 @@ int preference_args(const cake_shape* shape, const cake_params* params, const vo
     return fail(CAKE_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, lay.total);
   *out = PrefArgs{reinterpret_cast<const float*>(static_cast<const char*>(workspace) + lay.off_hv), shape->n_layers, shape->batch,
                   shape->n_kv_heads, shape->n_q_heads / shape->n_kv_heads, lay.n_granules_p, 1.0 / (double)params->tau1,
-                  1.0 / (double)params->tau2, pref, hv, shape->n_layers, shape->n_layers};
+                  1.0 / (double)params->tau2, pref, hv, shape->n_layers, shape->n_layers, nullptr, 0};
   return CAKE_OK;
 }
 }  // namespace
@@ -1369,6 +1375,7 @@ int cake::launch_scores_and_preference(const cake_shape* shape, const cake_param
   if (int rc = preference_args(shape, params, workspace, workspace_bytes, pref, hv, &a)) return rc;
   a.pref_ld = pref_ld;
   a.hv_ld = hv_ld;
+  if (one) { a.flags = one->flags; a.ticket = one->ticket; }
   return window_scores_impl(shape, params, q_win, k, q_strides, k_strides, row_lse, indicator, workspace, workspace_bytes,
                             stream, kPartsAll, 0, 0, &a, plan, one);
 }

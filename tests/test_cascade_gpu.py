@@ -155,3 +155,58 @@ def test_device_cascade_equals_host_cascade_and_one_shot(cake, name):
                 assert torch.equal(a[l][s_, :, : n_k + cfg.window], c[l][s_, :, : n_k + cfg.window]), (l, s_, "vs one-shot")
             assert torch.equal(got.ind_out[l][s_, :, :n_k], want.ind_out[l][s_, :, :n_k])
             assert torch.equal(got.ind_out[l][s_, :, :n_k], shot.ind_out[l][s_, :, :n_k])
+
+
+@pytest.mark.parametrize("L,B,H_q,H_kv,d,N,S_w,total,lse", [
+    (6, 1, 8, 2, 64, 700, 32, 3 * 700 + 40, False),     # three layers fit, the fourth makes them shrink
+    (5, 3, 10, 2, 128, 999, 64, 5 * 70, True),          # ragged batch, hardly more than the windows, normalisers handed over
+    (4, 2, 4, 4, 64, 130, 64, 4 * 130, False),          # nothing is ever dropped: the caller's own tensors
+    (3, 1, 4, 2, 128, 257, 32, 3 * 32, False),          # windows only
+])
+def test_session_stages_against_the_one_shot_pass_of_the_layers_seen(cake, L, B, H_q, H_kv, d, N, S_w, total, lse):
+    """After every stage a session's caches, positions and budgets are those of a one-shot pass over the layers seen so
+    far (Thm. 2), and a result stays what it was when later stages run."""
+    from gpu_util import torch_row_lse
+    say(f"session stages L={L} B={B} N={N} total={total}")
+    gen = torch.Generator(device=DEV).manual_seed(N + L)
+    mk = lambda h, n, t: [(torch.randn(B, h, n, d, device=DEV, generator=gen) * t).to(torch.bfloat16) for _ in range(L)]
+    q, k, v = mk(H_q, S_w, 1.5), mk(H_kv, N, 1.0), mk(H_kv, N, 1.0)
+    rows = [torch_row_lse(a, b) for a, b in zip(q, k)] if lse else None
+    session = cake.CascadeSession(L, total)
+    early = kept = None
+    for m in range(L):
+        got = session.admit(q[m], k[m], v[m], None if rows is None else rows[m])
+        shot = cake.EvictionPass(q[:m + 1], k[:m + 1], v[:m + 1], total, row_lse=None if rows is None else rows[:m + 1]).run()
+        res = session.result()
+        np.testing.assert_array_equal(got, shot.budgets)
+        np.testing.assert_array_equal(res.budgets, shot.budgets)
+        np.testing.assert_array_equal(res.keep, shot.keep)
+        np.testing.assert_array_equal(res.pref, shot.pref)
+        np.testing.assert_array_equal(res.hv, shot.hv)
+        assert session.rows_held() == int((shot.keep.max(axis=1) + S_w).sum()) and len(res.stage_budgets) == m + 1
+        for l in range(m + 1):
+            cap = int(shot.keep[l].max())
+            assert res.idx[l].shape == (B, H_kv, cap) and res.k_out[l].shape == (B, H_kv, cap + S_w, d)
+            for b in range(B):
+                n = int(shot.keep[l, b])
+                assert torch.equal(res.idx[l][b, :, :n], shot.idx[l][b, :, :n])
+                assert torch.equal(res.ind_out[l][b, :, :n], shot.ind_out[l][b, :, :n])
+                for x, y in ((res.k_out, shot.k_out), (res.v_out, shot.v_out)):
+                    assert torch.equal(x[l][b, :, :n + S_w], y[l][b, :, :n + S_w])
+        if m == L // 2:
+            early, kept = res, [t.clone() for t in res.k_out + res.v_out + res.ind_out + res.idx]
+    for a, b in zip(early.k_out + early.v_out + early.ind_out + early.idx, kept, strict=True):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+def test_session_takes_its_budget_at_the_stage_and_reports_one_that_is_too_small(cake):
+    say("session: budgets that change")
+    gen = torch.Generator(device=DEV).manual_seed(3)
+    mk = lambda h, n: torch.randn(1, h, n, 64, device=DEV, generator=gen)
+    session = cake.CascadeSession(3, 3 * 60)
+    session.admit(mk(4, 32), mk(2, 300), mk(2, 300))
+    session.total_budget = 63                            # below the two layers' windows
+    with pytest.raises(cake.CakeError):
+        session.admit(mk(4, 32), mk(2, 300), mk(2, 300))
+    session.total_budget = 150
+    assert session.admit(mk(4, 32), mk(2, 300), mk(2, 300)).sum() == 150 and session.rows_held() == 150

@@ -100,3 +100,19 @@ else:
     assert r.returncode == 0, (r.returncode, r.stderr[-400:])
     if kind != "fake":                       # a fake tensor's address is 0, which the library refuses where it reads it
         assert r.stdout.startswith("raised")
+
+
+def test_a_session_stage_that_is_refused_gives_its_return_code(host):
+    calls, keep = _calls(host)
+    shape, params, _ = keep
+    session = _ffi.cake_session(shape, params, 1)
+    y = torch.zeros(1, 2, 32, 64)
+    stage = lambda: host.session_stage(ctypes.addressof(session), 0, y, y, y, None, y, 1, 0)
+    assert stage()[0] == 0 and stage()[1] < 0 and stage()[2:] == (None,) * 5
+    with pytest.raises(ValueError):
+        host.session_stage(ctypes.addressof(session), 1, y, y, y, None, y, 1, 0)
+    with pytest.raises(AssertionError):
+        host.session_stage(ctypes.addressof(session), 0, y, y, y[:, :, :, ::2], None, y, 1, 0)
+    with pytest.raises(ValueError):
+        host.slab_views(torch.zeros(10), [4], [(2, 4)])
+    assert [t.tolist() for t in host.slab_views(torch.arange(10), [4, 0], [(2, 3), (0, 5)])] == [[[4, 5, 6], [7, 8, 9]], []]
