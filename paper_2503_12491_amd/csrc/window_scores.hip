@@ -820,7 +820,9 @@ __device__ __forceinline__ void store_preference(const PrefArgs& a, int entry, d
   // out a rounding error below zero, which the fractional powers below would turn into NaN.
   const double h_l = fmax(-0.6931471805599453 * e / heads, 0.0);   // sum p*log2 p -> -sum p ln p
   const double v_l = fmax(v / heads, 0.0);
-  a.pref[(int64_t)b * a.pref_ld + l] = pow(h_l, a.inv_tau1) * pow(v_l, a.inv_tau2);
+  // (a power costs half a microsecond of a chain that the plan waits for, and the usual one is the first)
+  const double h_pow = a.inv_tau1 == 1.0 ? h_l : pow(h_l, a.inv_tau1), v_pow = a.inv_tau2 == 1.0 ? v_l : pow(v_l, a.inv_tau2);
+  a.pref[(int64_t)b * a.pref_ld + l] = h_pow * v_pow;
   if (a.hv_out) {
     a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 0] = h_l;
     a.hv_out[((int64_t)b * a.hv_ld + l) * 2 + 1] = v_l;
@@ -842,11 +844,8 @@ __device__ __forceinline__ void preference_of(const PrefArgs& a, int entry) {
     e += (double)x.x;
     v += (double)x.y;
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    e += __shfl_xor(e, off);
-    v += __shfl_xor(v, off);
-  }
+  e = wave_sum(e);
+  v = wave_sum(v);
   if (lane == 0) { red[0][tid >> 6] = e; red[1][tid >> 6] = v; }
   __syncthreads();
   if (tid == 0) {
@@ -879,12 +878,10 @@ __device__ __forceinline__ void preference_of_wave(const PrefArgs& a, int entry,
         }
   }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1)
-#pragma unroll
-    for (int w = 0; w < kParts; ++w) {
-      e[w] += __shfl_xor(e[w], off);
-      v[w] += __shfl_xor(v[w], off);
-    }
+  for (int w = 0; w < kParts; ++w) {
+    e[w] = wave_sum(e[w]);
+    v[w] = wave_sum(v[w]);
+  }
 #pragma unroll
   for (int w = 1; w < kParts; ++w) { e[0] += e[w]; v[0] += v[w]; }
   if (lane == 0) store_preference(a, entry, e[0], v[0]);
