@@ -140,19 +140,22 @@ __host__ __device__ inline PlanMirrorLayout plan_mirror_layout(int n_layers, int
   p.total = p.off_hv + lb * 16;
   return p;
 }
-struct PlanMirror {
-  void* host;          // NULL: no copy
-  const double* hv;    // device [B, L, 2] or NULL
+struct PlanMirror {            // device addresses of what is copied
+  void* host;                  // NULL: no copy
+  const int32_t *budgets, *keep, *status;
+  const double *pref, *hv;     // [B, L], [B, L, 2] or NULL
+  int32_t n_layers, batch;
   uint32_t ticket;
 };
 // top-k and compaction of all layers with the counts and output places read from a plan
 // max_cur: the longest row to expect; `bounded` if no current length of the plan exceeds it; `last`: the last layer's rows,
-// which are then not in the table
+// which are then not in the table; `mirror`: a workgroup more writes the host's copy of the plan meanwhile
 int launch_topk_planned(const cake_shape* shape, const float* const* indicator, const float* last, const PlanView& plan, int64_t max_cur, bool bounded,
-                        hipStream_t stream);
+                        const PlanMirror& mirror, hipStream_t stream);
 // cake_evict_planned; `bounded` if the plan was made with current lengths of at most seq_len - window
 int evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,
-                  const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded, void* stream);
+                  const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded, const PlanMirror& mirror,
+                  void* stream);
 constexpr int kPlanMaskWords = 32;       // one bit per layer, n_layers <= 1024
 int launch_compact_planned(const cake_shape* shape, const void* const* k_in, const void* const* v_in,
                            const int64_t* kv_strides, const uint8_t* compacted, const float* const* ind_in,

@@ -197,7 +197,7 @@ extern "C" int cake_cascade_stage(const cake_cascade* c, int32_t m, const void* 
   // the rows held before the stage: what the stage before kept, and the new layer whole
   PlanArgs plan{};
   if (int rc = plan_args(&shape, c->pref, L, c->total_budget, nullptr, c->idx, c->k_store, c->v_store, c->ind[m & 1], c->plan[m & 1],
-                         c->plan_bytes, c->status, PlanMirror{}, &plan)) return rc;
+                         c->plan_bytes, c->status, &plan)) return rc;
   if (m > 0) {
     plan.cur_len = plan_view(c->plan[(m & 1) ^ 1], m, shape.batch).keep;
     plan.cur_known = m * shape.batch;
@@ -205,7 +205,7 @@ extern "C" int cake_cascade_stage(const cake_cascade* c, int32_t m, const void* 
   const LayerPointers one{q_win, k, nullptr, indicator, nullptr, 0};
   if (int rc = launch_scores_and_preference(&c->shape, &c->params, nullptr, nullptr, q_strides, kv_strides, nullptr, nullptr, &one,
                                             c->workspace, c->workspace_bytes, c->pref + m, c->hv + 2 * m, L, L, &plan, st)) return rc;
-  if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(a.held), indicator, a.plan, a.prefix_len, true, st)) return rc;
+  if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(a.held), indicator, a.plan, a.prefix_len, true, PlanMirror{}, st)) return rc;
   const int64_t shares = std::min<int64_t>((a.prefix_len + kThreads) / kThreads, 2048 / ((int64_t)bh * (m + 1)));
   hipLaunchKernelGGL(renew_lists, dim3(bh, m + 1, (unsigned)std::max<int64_t>(shares, 1)), dim3(kThreads), 0, st, a);
   // as many workgroups as the most rows the layer can keep fill, up to four for each compute unit

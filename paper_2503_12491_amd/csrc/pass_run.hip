@@ -70,9 +70,8 @@ extern "C" int cake_pass_launch(const cake_pass* p, int32_t parts, uint32_t tick
   hipStream_t st = static_cast<hipStream_t>(stream);
   PlanArgs plan{};
   if (parts & CAKE_PASS_EVICT) {
-    const PlanMirror mirror{ticket ? p->mirror : nullptr, p->hv, ticket};
     if (int rc = plan_args(&p->shape, p->pref, p->shape.n_layers, p->total_budget, nullptr, p->pool_idx, p->pool_k,
-                           p->pool_v, p->pool_ind, p->plan, p->plan_bytes, p->status, mirror, &plan)) return rc;
+                           p->pool_v, p->pool_ind, p->plan, p->plan_bytes, p->status, &plan)) return rc;
   }
   if (parts & CAKE_PASS_SCORES)
     if (int rc = launch_scores_and_preference(&p->shape, &p->params, p->q_win, p->k, p->q_strides, p->kv_strides, p->row_lse,
@@ -82,7 +81,9 @@ extern "C" int cake_pass_launch(const cake_pass* p, int32_t parts, uint32_t tick
     if (!(parts & CAKE_PASS_SCORES))
       if (int rc = launch_plan(plan, st)) return rc;
     // the plan above takes every row at its full length
-    return evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, true, stream);
+    const PlanMirror mirror{ticket ? p->mirror : nullptr, plan.budgets, plan.keep, plan.status, p->pref, p->hv, p->shape.n_layers,
+                            p->shape.batch, ticket};
+    return evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, true, mirror, stream);
   }
   return CAKE_OK;
 }

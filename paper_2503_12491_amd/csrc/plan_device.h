@@ -66,7 +66,6 @@ struct PlanArgs {
   int32_t *budgets, *keep, *cur, *cap_keep, *cap_cur, *copy_blocks, *status;
   char *pool_idx, *pool_k, *pool_v, *pool_ind;
   void **idx_tbl, **k_tbl, **v_tbl, **ind_tbl;
-  PlanMirror mirror;
   bool allocated;             // budgets, keep and cur are there already (allocate_kernel)
 };
 
@@ -242,8 +241,7 @@ __device__ void allocate_sequence(const PlanArgs& a, int b, int lane, double* p_
 
 // The whole plan in one workgroup: budgets and keep counts (a wave per sequence), row capacities of
 // every layer (the largest count over the batch), the places of the layers' outputs, one after the
-// other, in the four pools, the compaction's work list, and on request a copy of what the host wants
-// to know in pinned host memory.
+// other, in the four pools, and the compaction's work list.
 __device__ __forceinline__ void plan_workgroup(const PlanArgs& a, char* plan_lds /* kPlanLdsPerLayer bytes per wave and layer beyond 64 layers */) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
   const int n_layers = a.n_layers, batch = a.batch;
@@ -318,33 +316,12 @@ __device__ __forceinline__ void plan_workgroup(const PlanArgs& a, char* plan_lds
     }
     if (lane == 63) a.copy_blocks[n] = (int32_t)before;     // the last lane's run ends the list
   }
-  if (a.mirror.host != nullptr) {
-    // Plain stores over the bus, then one flag once they are all out: a host that watches the flag
-    // knows the plan while the top-k and the compaction are still running.
-    const PlanMirrorLayout lay = plan_mirror_layout(n_layers, batch);
-    char* h = static_cast<char*>(a.mirror.host);
-    const int n = n_layers * batch;
-    for (int i = tid; i < n; i += blockDim.x) {
-      reinterpret_cast<int32_t*>(h + lay.off_budgets)[i] = a.budgets[i];
-      reinterpret_cast<int32_t*>(h + lay.off_keep)[i] = a.keep[i];
-      reinterpret_cast<double*>(h + lay.off_pref)[i] = a.pref[(int64_t)(i / n_layers) * a.pref_ld + i % n_layers];
-      if (a.mirror.hv != nullptr) {
-        reinterpret_cast<double*>(h + lay.off_hv)[2 * i] = a.mirror.hv[2 * i];
-        reinterpret_cast<double*>(h + lay.off_hv)[2 * i + 1] = a.mirror.hv[2 * i + 1];
-      }
-    }
-    for (int b = tid; b < batch; b += blockDim.x) reinterpret_cast<int32_t*>(h + lay.off_status)[b] = a.status[b];
-    __threadfence_system();
-    __syncthreads();
-    if (tid == 0) __hip_atomic_store(reinterpret_cast<uint32_t*>(h), a.mirror.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-  }
 }
 
-// The arguments of cake_plan_eviction (with rows of pref_ld preferences per sequence and, on request, the host's copy),
-// checked.
+// The arguments of cake_plan_eviction (with rows of pref_ld preferences per sequence), checked.
 int plan_args(const cake_shape* shape, const double* pref, int pref_ld, int64_t total_budget, const int32_t* cur_len,
               void* pool_idx, void* pool_k, void* pool_v, void* pool_ind, void* plan, size_t plan_bytes,
-              int32_t* status, const PlanMirror& mirror, PlanArgs* out);
+              int32_t* status, PlanArgs* out);
 int launch_plan(const PlanArgs& args, hipStream_t stream);
 
 }  // namespace cake

@@ -59,7 +59,7 @@ extern "C" int cake_plan_bytes(const cake_shape* shape, size_t* bytes) {
 
 int cake::plan_args(const cake_shape* shape, const double* pref, int pref_ld, int64_t total_budget, const int32_t* cur_len,
                     void* pool_idx, void* pool_k, void* pool_v, void* pool_ind, void* plan, size_t plan_bytes,
-                    int32_t* status, const PlanMirror& mirror, PlanArgs* out) {
+                    int32_t* status, PlanArgs* out) {
   CAKE_REQUIRE(pref && pool_idx && pool_k && pool_v && pool_ind && plan && status, "a pointer argument is NULL");
   CAKE_REQUIRE(shape->seq_len > shape->window, "seq_len %d must exceed window %d", shape->seq_len, shape->window);
   CAKE_REQUIRE(total_budget >= (int64_t)shape->n_layers * shape->window,
@@ -88,7 +88,6 @@ int cake::plan_args(const cake_shape* shape, const double* pref, int pref_ld, in
   a.pool_v = static_cast<char*>(pool_v); a.pool_ind = static_cast<char*>(pool_ind);
   void** tables = reinterpret_cast<void**>(b + lay.off_tables);
   a.idx_tbl = tables; a.k_tbl = tables + L; a.v_tbl = tables + 2 * L; a.ind_tbl = tables + 3 * L;
-  a.mirror = mirror;
   *out = a;
   return CAKE_OK;
 }
@@ -122,7 +121,7 @@ extern "C" int cake_plan_eviction(const cake_shape* shape, const double* pref, i
   if (int rc = check_shape_basic(shape)) return rc;
   PlanArgs a{};
   if (int rc = plan_args(shape, pref, shape->n_layers, total_budget, cur_len, pool_idx, pool_k, pool_v, pool_ind, plan, plan_bytes,
-                         status, PlanMirror{}, &a)) return rc;
+                         status, &a)) return rc;
   return launch_plan(a, static_cast<hipStream_t>(stream));
 }
 
@@ -139,7 +138,7 @@ extern "C" int cake_plan_layout(const cake_shape* shape, size_t* offsets) {
 
 int cake::evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,
                         const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded,
-                        void* stream) {
+                        const PlanMirror& mirror, void* stream) {
   if (int rc = check_shape_basic(shape)) return rc;
   CAKE_REQUIRE(indicator && k_in && v_in && kv_strides && plan, "a pointer argument is NULL");
   CAKE_REQUIRE((int64_t)shape->n_layers * shape->batch * shape->n_kv_heads <= 65535 * 64,
@@ -155,7 +154,7 @@ int cake::evict_planned(const cake_shape* shape, const float* const* indicator, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   // without a length in the shape the kernel for any length serves
   const int64_t max_cur = shape->seq_len > shape->window ? shape->seq_len - shape->window : 0x7fffffff;
-  if (int rc = launch_topk_planned(shape, indicator, nullptr, view, max_cur, bounded, st)) return rc;
+  if (int rc = launch_topk_planned(shape, indicator, nullptr, view, max_cur, bounded, mirror, st)) return rc;
   return launch_compact_planned(shape, k_in, v_in, kv_strides, compacted, indicator, view, st);
 }
 
@@ -165,5 +164,5 @@ extern "C" int cake_evict_planned(const cake_shape* shape, const float* const* i
                                   const void* const* k_in, const void* const* v_in, const int64_t* kv_strides,
                                   const uint8_t* compacted,
                                   const void* plan, size_t plan_bytes, void* stream) {
-  return evict_planned(shape, indicator, k_in, v_in, kv_strides, compacted, plan, plan_bytes, false, stream);
+  return evict_planned(shape, indicator, k_in, v_in, kv_strides, compacted, plan, plan_bytes, false, PlanMirror{}, stream);
 }

@@ -44,6 +44,8 @@ struct TopkPlan {
   const int32_t* keep;        // [L*B]
   const int32_t* cap_cur;     // [L]
   const int32_t* cap_keep;    // [L]
+  int32_t n_layers;
+  PlanMirror mirror;          // where its host is not NULL, row n_layers of the grid writes it
   int32_t served_slots;       // the kernel for any length leaves rows of up to so many slots to the register kernel launched before it
 };
 
@@ -325,6 +327,30 @@ __device__ __forceinline__ void find_threshold(uint32_t (&key)[kSlots][4], int n
   last = s.last;
 }
 
+// The host's copy of the plan, by the last row's first workgroup of a launch: plain stores over the bus, then one flag
+// once they are all out, so that a host that watches the flag knows the plan while the top-k and the compaction are
+// still running.  The plan's own kernel would wait for the bus before the top-k may begin (1.5 us).
+template <int kThreads>
+__device__ __forceinline__ void write_mirror(const PlanMirror& a) {
+  if (blockIdx.x > 0) return;
+  const PlanMirrorLayout lay = plan_mirror_layout(a.n_layers, a.batch);
+  char* h = static_cast<char*>(a.host);
+  const int n = a.n_layers * a.batch, tid = threadIdx.x;
+  for (int i = tid; i < n; i += kThreads) {
+    reinterpret_cast<int32_t*>(h + lay.off_budgets)[i] = a.budgets[i];
+    reinterpret_cast<int32_t*>(h + lay.off_keep)[i] = a.keep[i];
+    reinterpret_cast<double*>(h + lay.off_pref)[i] = a.pref[i];
+    if (a.hv != nullptr) {
+      reinterpret_cast<double*>(h + lay.off_hv)[2 * i] = a.hv[2 * i];
+      reinterpret_cast<double*>(h + lay.off_hv)[2 * i + 1] = a.hv[2 * i + 1];
+    }
+  }
+  for (int b = tid; b < a.batch; b += kThreads) reinterpret_cast<int32_t*>(h + lay.off_status)[b] = a.status[b];
+  __threadfence_system();
+  __syncthreads();
+  if (tid == 0) __hip_atomic_store(reinterpret_cast<uint32_t*>(h), a.ticket, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // A workgroup's row and output.
 struct RowTask {
   Row row;
@@ -341,7 +367,7 @@ __device__ __forceinline__ RowTask row_task(const TopkArgs& a, const RaggedDims&
   const int cap_keep = kPlanned ? plan.cap_keep[ll] : a.cap_keep[ll];
   RowTask t;
   t.keep = kPlanned ? plan.keep[e] : dims.keep[e];
-  const float* indicator = a.last != nullptr && ll == (int)gridDim.y - 1 ? a.last : a.indicator[ll];
+  const float* indicator = a.last != nullptr && ll == plan.n_layers - 1 ? a.last : a.indicator[ll];
   t.row.init(indicator + ((int64_t)b * a.h_kv + h) * cap_cur, cur);
   t.out = a.idx[ll] + ((int64_t)b * a.h_kv + h) * cap_keep;
   return t;
@@ -351,6 +377,7 @@ __device__ __forceinline__ RowTask row_task(const TopkArgs& a, const RaggedDims&
 template <bool kPlanned, int kThreads, int kSlots>
 __global__ __launch_bounds__(kThreads) void select_topk_kernel(TopkArgs a, RaggedDims dims, TopkPlan plan) {
   __shared__ __attribute__((aligned(16))) SelectLds lds;
+  if (kPlanned && (int)blockIdx.y == plan.n_layers) return write_mirror<kThreads>(plan.mirror);
   const RowTask t = row_task<kPlanned>(a, dims, plan);
   if (t.keep <= 0) return;
   if (kPlanned && t.row.n_slots > kThreads * kSlots) return;       // a plan's row longer than the caller's shape says: the next launch's
@@ -392,6 +419,7 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
   extern __shared__ __attribute__((aligned(16))) char long_lds[];
   LongLds& lds = *reinterpret_cast<LongLds*>(long_lds);
   SelectLds& s = lds.sel;
+  if (kPlanned && (int)blockIdx.y == plan.n_layers) return write_mirror<kLongThreads>(plan.mirror);
   const RowTask t = row_task<kPlanned>(a, dims, plan);
   if (t.keep <= 0) return;
   const Row& row = t.row;
@@ -585,6 +613,7 @@ int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs& a, const 
     auto kern = select_topk_long_kernel<kPlanned>;
     CAKE_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)sizeof(LongLds)));
+    if (kPlanned) grid.y = plan.n_layers + (plan.served_slots == 0 && plan.mirror.host != nullptr ? 1 : 0);     // once
     hipLaunchKernelGGL(kern, grid, dim3(kLongThreads), sizeof(LongLds), stream, a, dims, plan);
   }
 #undef CAKE_TOPK
@@ -596,15 +625,15 @@ int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs& a, const 
 }  // namespace cake
 
 int cake::launch_topk_planned(const cake_shape* shape, const float* const* indicator, const float* last, const PlanView& plan, int64_t max_cur,
-                              bool bounded, hipStream_t stream) {
+                              bool bounded, const PlanMirror& mirror, hipStream_t stream) {
   TopkArgs a{};
   a.indicator = indicator;
   a.last = last;
   a.idx = reinterpret_cast<int32_t* const*>(plan.idx);
   a.batch = shape->batch;
   a.h_kv = shape->n_kv_heads;
-  const TopkPlan tp{plan.cur_len, plan.keep, plan.cap_cur, plan.cap_keep, 0};
-  return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers), max_cur, bounded, a, RaggedDims{}, tp, stream);
+  const TopkPlan tp{plan.cur_len, plan.keep, plan.cap_cur, plan.cap_keep, shape->n_layers, mirror, 0};
+  return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers + (mirror.host != nullptr ? 1 : 0)), max_cur, bounded, a, RaggedDims{}, tp, stream);
 }
 
 using namespace cake;
