@@ -6,6 +6,7 @@
 #include <cstdarg>
 #include <cstddef>
 #include <cstdint>
+#include <type_traits>
 
 #include "cake.h"
 
@@ -80,6 +81,13 @@ struct RaggedDims {
 struct LayerStrides {
   int64_t s[kMaxLaunchLayers][3];
 };
+// Kernels that read their dimensions from a plan do without those arguments: a launch copies them to device memory (the
+// top-k's and the compaction's were 2.5 and 3.5 KB; 0.3 KB cost 0.8 us of host and device against none).
+struct NoArgs {};
+template <bool kPlanned> using DimsArg = typename std::conditional<kPlanned, NoArgs, RaggedDims>::type;
+template <bool kPlanned> using StridesArg = typename std::conditional<kPlanned, NoArgs, LayerStrides>::type;
+template <bool kPlanned> struct CapsArg { int32_t cur[kMaxLaunchLayers], keep[kMaxLaunchLayers]; };      // row capacities
+template <> struct CapsArg<true> {};
 
 // ---- device-resident eviction plan (cake_plan_eviction writes it, cake_evict_planned reads it) ----
 // int32 budgets[L*B], keep[L*B], cur_len[L*B], cap_keep[L], cap_cur[L], copy_blocks[L*B + 1];

@@ -13,6 +13,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kUnroll = 4;   // pieces per thread
 
+template <bool kPlanned>
 struct CompactArgs {
   const void* const* k_in;
   const void* const* v_in;
@@ -25,8 +26,7 @@ struct CompactArgs {
   int32_t* const* pos_out;               // NULL: not carried along
   int32_t batch, h_kv, window, pieces;   // pieces: 16-byte pieces per row
   int32_t elem_bytes;
-  int32_t cap_cur[kMaxLaunchLayers];
-  int32_t cap_keep[kMaxLaunchLayers];
+  CapsArg<kPlanned> cap;
 };
 
 // The same dimensions when they live in device memory (an eviction plan); the strides are then
@@ -52,11 +52,13 @@ constexpr int kListLds = 4096;       // work-list entries searched from LDS (lon
 // the plan's work list, the blocks of all (layer, sequence) entries in one sequence, head by
 // blockIdx.y: the entry of a block is found by bisection of the running counts.
 template <bool kPlanned>
-__global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a, RaggedDims dims, LayerStrides st, CompactPlan plan) {
+__global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned> a, DimsArg<kPlanned> dims, StridesArg<kPlanned> st,
+                                                          typename std::conditional<kPlanned, CompactPlan, NoArgs>::type plan) {
   __shared__ int32_t list[kPlanned ? kListLds + 1 : 1];
-  const int32_t* blocks = plan.copy_blocks;
+  const int32_t* blocks = nullptr;
   int32_t n_blocks = 1;
-  if (kPlanned) {
+  if constexpr (kPlanned) {
+    blocks = plan.copy_blocks;
     if (plan.n_entries <= kListLds) {
       for (int i = threadIdx.x; i <= plan.n_entries; i += kThreads) list[i] = plan.copy_blocks[i];
       __syncthreads();
@@ -68,7 +70,7 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a, Ragged
   for (int32_t blk = blockIdx.x; blk < blk_end; blk += gridDim.x) {
   int ll, b, h;
   int64_t first;
-  if (kPlanned) {
+  if constexpr (kPlanned) {
     int lo = 0, hi = plan.n_entries;          // largest e with blocks[e] <= blk (entries without blocks share a count)
     while (hi - lo > 1) {
       const int mid = (lo + hi) >> 1;
@@ -80,16 +82,25 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs a, Ragged
     ll = blockIdx.z; b = blockIdx.y / a.h_kv; h = blockIdx.y % a.h_kv;
     first = (int64_t)blockIdx.x * (kThreads * kUnroll);
   }
-  const int cur = kPlanned ? plan.cur_len[ll * a.batch + b] : dims.cur_len[ll * a.batch + b];
-  const int keep = kPlanned ? plan.keep[ll * a.batch + b] : dims.keep[ll * a.batch + b];
-  const int cap_cur = kPlanned ? plan.cap_cur[ll] : a.cap_cur[ll];
-  const int cap_keep = kPlanned ? plan.cap_keep[ll] : a.cap_keep[ll];
-  int64_t s0 = kPlanned ? plan.s[0] : st.s[ll][0], s1 = kPlanned ? plan.s[1] : st.s[ll][1],
-          s2 = kPlanned ? plan.s[2] : st.s[ll][2];
-  if (kPlanned && (plan.compacted[ll >> 5] >> (ll & 31) & 1u)) {
-    s2 = (int64_t)a.pieces * 16 / a.elem_bytes;
-    s1 = (int64_t)(cap_cur + a.window) * s2;
-    s0 = (int64_t)a.h_kv * s1;
+  int cur, keep, cap_cur, cap_keep;
+  int64_t s0, s1, s2;
+  if constexpr (kPlanned) {
+    cur = plan.cur_len[ll * a.batch + b];
+    keep = plan.keep[ll * a.batch + b];
+    cap_cur = plan.cap_cur[ll];
+    cap_keep = plan.cap_keep[ll];
+    s0 = plan.s[0]; s1 = plan.s[1]; s2 = plan.s[2];
+    if (plan.compacted[ll >> 5] >> (ll & 31) & 1u) {
+      s2 = (int64_t)a.pieces * 16 / a.elem_bytes;
+      s1 = (int64_t)(cap_cur + a.window) * s2;
+      s0 = (int64_t)a.h_kv * s1;
+    }
+  } else {
+    cur = dims.cur_len[ll * a.batch + b];
+    keep = dims.keep[ll * a.batch + b];
+    cap_cur = a.cap.cur[ll];
+    cap_keep = a.cap.keep[ll];
+    s0 = st.s[ll][0]; s1 = st.s[ll][1]; s2 = st.s[ll][2];
   }
   const int rows_out = keep + a.window;
   const int64_t total = (int64_t)rows_out * a.pieces;
@@ -160,7 +171,7 @@ int cake::launch_compact_planned(const cake_shape* shape, const void* const* k_i
                                  const int64_t* kv_strides, const uint8_t* compacted, const float* const* ind_in,
                                  const PlanView& plan, hipStream_t stream) {
   const int eb = (int)elem_bytes(shape->dtype);
-  CompactArgs a{};
+  CompactArgs<true> a{};
   a.k_in = k_in; a.v_in = v_in;
   a.idx = reinterpret_cast<const int32_t* const*>(plan.idx);
   a.ind_in = ind_in;
@@ -177,7 +188,7 @@ int cake::launch_compact_planned(const cake_shape* shape, const void* const* k_i
   // 8192 workgroups in all (a few rounds of what the chip holds at once), striding over the work list
   const unsigned gx = (unsigned)std::max(1, 8192 / shape->n_kv_heads);
   hipLaunchKernelGGL(compact_kernel<true>, dim3(gx, shape->n_kv_heads), dim3(kThreads), 0,
-                     stream, a, RaggedDims{}, LayerStrides{}, cp);
+                     stream, a, NoArgs{}, NoArgs{}, cp);
   CAKE_HIP_TRY(hipGetLastError());
   return CAKE_OK;
 }
@@ -220,7 +231,7 @@ extern "C" int cake_compact_kv_positions(const cake_shape* shape,
   hipStream_t st = static_cast<hipStream_t>(stream);
   for (int l0 = 0; l0 < L;) {
     const int nl = launch_layers(L - l0, B);
-    CompactArgs a{};
+    CompactArgs<false> a{};
     RaggedDims dims{};
     LayerStrides ls{};
     a.k_in = k_in + l0; a.v_in = v_in + l0; a.idx = idx + l0;
@@ -242,14 +253,14 @@ extern "C" int cake_compact_kv_positions(const cake_shape* shape,
         cc = std::max(cc, cur_len[i]);
         ck = std::max(ck, k[i]);
       }
-      a.cap_cur[ll] = cc;
-      a.cap_keep[ll] = ck;
+      a.cap.cur[ll] = cc;
+      a.cap.keep[ll] = ck;
       max_rows = std::max(max_rows, ck + shape->window);
       for (int j = 0; j < 3; ++j) ls.s[ll][j] = kv_strides[(l0 + ll) * 3 + j];
     }
     const int64_t pieces_total = (int64_t)max_rows * a.pieces;
     const unsigned gx = (unsigned)((pieces_total + kThreads * kUnroll - 1) / (kThreads * kUnroll));
-    hipLaunchKernelGGL(compact_kernel<false>, dim3(gx, B * shape->n_kv_heads, nl), dim3(kThreads), 0, st, a, dims, ls, CompactPlan{});
+    hipLaunchKernelGGL(compact_kernel<false>, dim3(gx, B * shape->n_kv_heads, nl), dim3(kThreads), 0, st, a, dims, ls, NoArgs{});
     l0 += nl;
   }
   CAKE_HIP_TRY(hipGetLastError());

@@ -30,13 +30,13 @@ constexpr int kCopies = 2;          // histogram copies, chosen by lane: fewer l
 constexpr int kFewKeys = 128;       // keys ranked by comparison with each other
 constexpr int kMaxWaves = 16;
 
+template <bool kPlanned>
 struct TopkArgs {
   const float* const* indicator;
   const float* last;          // of the last layer; NULL: in the table as well
   int32_t* const* idx;
   int32_t batch, h_kv;
-  int32_t cap_cur[kMaxLaunchLayers];
-  int32_t cap_keep[kMaxLaunchLayers];
+  CapsArg<kPlanned> cap;
 };
 // The same dimensions when they live in device memory (an eviction plan).
 struct TopkPlan {
@@ -358,16 +358,28 @@ struct RowTask {
   int keep;
 };
 template <bool kPlanned>
-__device__ __forceinline__ RowTask row_task(const TopkArgs& a, const RaggedDims& dims, const TopkPlan& plan) {
+using PlanArg = typename std::conditional<kPlanned, TopkPlan, NoArgs>::type;
+template <bool kPlanned>
+__device__ __forceinline__ RowTask row_task(const TopkArgs<kPlanned>& a, const DimsArg<kPlanned>& dims, const PlanArg<kPlanned>& plan) {
   const int ll = blockIdx.y;                           // layer within this launch
   const int b = blockIdx.x / a.h_kv, h = blockIdx.x % a.h_kv;
   const int e = ll * a.batch + b;
-  const int cur = kPlanned ? plan.cur_len[e] : dims.cur_len[e];
-  const int cap_cur = kPlanned ? plan.cap_cur[ll] : a.cap_cur[ll];
-  const int cap_keep = kPlanned ? plan.cap_keep[ll] : a.cap_keep[ll];
+  int cur, cap_cur, cap_keep;
   RowTask t;
-  t.keep = kPlanned ? plan.keep[e] : dims.keep[e];
-  const float* indicator = a.last != nullptr && ll == plan.n_layers - 1 ? a.last : a.indicator[ll];
+  const float* indicator;
+  if constexpr (kPlanned) {
+    cur = plan.cur_len[e];
+    cap_cur = plan.cap_cur[ll];
+    cap_keep = plan.cap_keep[ll];
+    t.keep = plan.keep[e];
+    indicator = a.last != nullptr && ll == plan.n_layers - 1 ? a.last : a.indicator[ll];
+  } else {
+    cur = dims.cur_len[e];
+    cap_cur = a.cap.cur[ll];
+    cap_keep = a.cap.keep[ll];
+    t.keep = dims.keep[e];
+    indicator = a.indicator[ll];
+  }
   t.row.init(indicator + ((int64_t)b * a.h_kv + h) * cap_cur, cur);
   t.out = a.idx[ll] + ((int64_t)b * a.h_kv + h) * cap_keep;
   return t;
@@ -375,9 +387,10 @@ __device__ __forceinline__ RowTask row_task(const TopkArgs& a, const RaggedDims&
 
 // Rows that fit the workgroup's registers: kThreads * kSlots * 4 entries, up to three of them absent.
 template <bool kPlanned, int kThreads, int kSlots>
-__global__ __launch_bounds__(kThreads) void select_topk_kernel(TopkArgs a, RaggedDims dims, TopkPlan plan) {
+__global__ __launch_bounds__(kThreads) void select_topk_kernel(TopkArgs<kPlanned> a, DimsArg<kPlanned> dims, PlanArg<kPlanned> plan) {
   __shared__ __attribute__((aligned(16))) SelectLds lds;
-  if (kPlanned && (int)blockIdx.y == plan.n_layers) return write_mirror<kThreads>(plan.mirror);
+  if constexpr (kPlanned)
+    if ((int)blockIdx.y == plan.n_layers) return write_mirror<kThreads>(plan.mirror);
   const RowTask t = row_task<kPlanned>(a, dims, plan);
   if (t.keep <= 0) return;
   if (kPlanned && t.row.n_slots > kThreads * kSlots) return;       // a plan's row longer than the caller's shape says: the next launch's
@@ -415,15 +428,17 @@ static_assert(offsetof(SelectLds, hist) % 16 == 0 && offsetof(SelectLds, few) % 
               "read in 16-byte pieces from a 16-byte aligned block");
 
 template <bool kPlanned>
-__global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs a, RaggedDims dims, TopkPlan plan) {
+__global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs<kPlanned> a, DimsArg<kPlanned> dims, PlanArg<kPlanned> plan) {
   extern __shared__ __attribute__((aligned(16))) char long_lds[];
   LongLds& lds = *reinterpret_cast<LongLds*>(long_lds);
   SelectLds& s = lds.sel;
-  if (kPlanned && (int)blockIdx.y == plan.n_layers) return write_mirror<kLongThreads>(plan.mirror);
+  if constexpr (kPlanned)
+    if ((int)blockIdx.y == plan.n_layers) return write_mirror<kLongThreads>(plan.mirror);
   const RowTask t = row_task<kPlanned>(a, dims, plan);
   if (t.keep <= 0) return;
   const Row& row = t.row;
-  if (kPlanned && row.n_slots <= plan.served_slots) return;
+  if constexpr (kPlanned)
+    if (row.n_slots <= plan.served_slots) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, copy = lane & (kCopies - 1);
   if (t.keep >= row.cur) {
     for (int i = tid; i < row.cur; i += kLongThreads) t.out[i] = i;
@@ -597,23 +612,27 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
 // what the caller's shape suggests (!bounded: the lengths are device data), rows that do not fit it are left out
 // by that kernel and served by the one for any length, launched behind it.
 template <bool kPlanned>
-int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs& a, const RaggedDims& dims, TopkPlan plan, hipStream_t stream) {
+int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs<kPlanned>& a, const DimsArg<kPlanned>& dims, PlanArg<kPlanned> plan,
+                hipStream_t stream) {
   const int64_t need = most + 3;                       // up to three absent entries in front
-  plan.served_slots = 0;
+  int32_t served_slots = 0;
 #define CAKE_TOPK(T, S)                                                                                    \
   do {                                                                                                     \
     hipLaunchKernelGGL((select_topk_kernel<kPlanned, T, S>), grid, dim3(T), 0, stream, a, dims, plan);     \
-    plan.served_slots = T * S;                                                                             \
+    served_slots = T * S;                                                                                  \
   } while (0)
   if (need <= 256 * 4 * 4) CAKE_TOPK(256, 4);
   else if (need <= 512 * 8 * 4) CAKE_TOPK(512, 8);
   else if (need <= 1024 * 8 * 4) CAKE_TOPK(1024, 8);
   else if (need <= 1024 * 16 * 4) CAKE_TOPK(1024, 16);
-  if (plan.served_slots == 0 || !bounded) {
+  if (served_slots == 0 || !bounded) {
     auto kern = select_topk_long_kernel<kPlanned>;
     CAKE_HIP_TRY(hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                      (int)sizeof(LongLds)));
-    if (kPlanned) grid.y = plan.n_layers + (plan.served_slots == 0 && plan.mirror.host != nullptr ? 1 : 0);     // once
+    if constexpr (kPlanned) {
+      plan.served_slots = served_slots;
+      grid.y = plan.n_layers + (served_slots == 0 && plan.mirror.host != nullptr ? 1 : 0);     // the copy is made once
+    }
     hipLaunchKernelGGL(kern, grid, dim3(kLongThreads), sizeof(LongLds), stream, a, dims, plan);
   }
 #undef CAKE_TOPK
@@ -626,14 +645,14 @@ int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs& a, const 
 
 int cake::launch_topk_planned(const cake_shape* shape, const float* const* indicator, const float* last, const PlanView& plan, int64_t max_cur,
                               bool bounded, const PlanMirror& mirror, hipStream_t stream) {
-  TopkArgs a{};
+  TopkArgs<true> a{};
   a.indicator = indicator;
   a.last = last;
   a.idx = reinterpret_cast<int32_t* const*>(plan.idx);
   a.batch = shape->batch;
   a.h_kv = shape->n_kv_heads;
   const TopkPlan tp{plan.cur_len, plan.keep, plan.cap_cur, plan.cap_keep, shape->n_layers, mirror, 0};
-  return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers + (mirror.host != nullptr ? 1 : 0)), max_cur, bounded, a, RaggedDims{}, tp, stream);
+  return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers + (mirror.host != nullptr ? 1 : 0)), max_cur, bounded, a, NoArgs{}, tp, stream);
 }
 
 using namespace cake;
@@ -653,7 +672,7 @@ extern "C" int cake_select_topk(const cake_shape* shape, const float* const* ind
   hipStream_t st = static_cast<hipStream_t>(stream);
   for (int l0 = 0; l0 < L;) {
     const int nl = launch_layers(L - l0, B);
-    TopkArgs a{};
+    TopkArgs<false> a{};
     RaggedDims dims{};
     a.indicator = indicator + l0;
     a.idx = idx + l0;
@@ -669,13 +688,13 @@ extern "C" int cake_select_topk(const cake_shape* shape, const float* const* ind
         cc = std::max(cc, cur_len[i]);
         ck = std::max(ck, k[i]);
       }
-      a.cap_cur[ll] = cc;
-      a.cap_keep[ll] = ck;
+      a.cap.cur[ll] = cc;
+      a.cap.keep[ll] = ck;
       most = std::max(most, cc);
       rows = std::max(rows, ck);
     }
     if (rows > 0)
-      if (int rc = launch_topk<false>(dim3(B * shape->n_kv_heads, nl), most, true, a, dims, TopkPlan{}, st)) return rc;
+      if (int rc = launch_topk<false>(dim3(B * shape->n_kv_heads, nl), most, true, a, dims, NoArgs{}, st)) return rc;
     l0 += nl;
   }
   return CAKE_OK;
