@@ -164,6 +164,23 @@ int launch_topk_planned(const cake_shape* shape, const float* const* indicator, 
 int evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,
                   const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded, const PlanMirror& mirror,
                   void* stream);
+// What a stage of the device-chained cascade (cascade_stage.hip) does to its lists.
+struct StageArgs {
+  PlanView plan;                      // of this stage
+  void* const* held;                  // [m] the indicators before the stage
+  const float* ind;                   // the new layer's
+  const char *ind_old, *ind_new;      // pools the indicators are in; the lists of places have the same layout
+  const int32_t* slots_old;
+  int32_t* slots_new;
+  int32_t* free_slots;
+  int32_t m, batch, h_kv, window, prefix_rows, prefix_len;
+};
+// The top-k of the stage's rows and the lists after it in one launch, for rows of at most kStageMaxCur entries.  A stage of 8
+// key heads with the lists in a launch of their own, and in this one: 35.2 and 31.9 us at 1500 keys (16 layers, 200 rows
+// kept), 55.3 and 53.1 at 8192 (32 layers, 1024), 68.0 and 67.7 at 16000 (16 layers, 1000).  Beyond, the 1024 threads the
+// row takes have no registers left for the places (30000 keys: 97.8 and 99.6; 60000: 121 and 125).
+constexpr int kStageMaxCur = 512 * 8 * 4 - 3;
+int launch_topk_stage(const StageArgs& a, hipStream_t stream);
 constexpr int kPlanMaskWords = 32;       // one bit per layer, n_layers <= 1024
 int launch_compact_planned(const cake_shape* shape, const void* const* k_in, const void* const* v_in,
                            const int64_t* kv_strides, const uint8_t* compacted, const float* const* ind_in,
@@ -234,6 +251,15 @@ __device__ __forceinline__ float wave_max(float x) {
   x = fmaxf(x, dpp_step<0x142, 0xa, true>(x));
   x = fmaxf(x, dpp_step<0x143, 0xc, true>(x));
   return from_lane(x, 63);
+}
+// Sum over the layers before l of keep (or of cur - keep) of sequence b, by one wave.
+__device__ __forceinline__ int32_t rows_before(const StageArgs& a, int l, int b, bool dropped, int lane) {
+  uint32_t t = 0;
+  for (int i = lane; i < l; i += 64) {
+    const int e = i * a.batch + b;
+    t += (uint32_t)(dropped ? a.plan.cur_len[e] - a.plan.keep[e] : a.plan.keep[e]);
+  }
+  return (int32_t)wave_sum(t);
 }
 #endif
 

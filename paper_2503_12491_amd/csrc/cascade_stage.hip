@@ -6,10 +6,10 @@
 // rows per head, a stage renews the lists (8 bytes a row), puts the places of the dropped rows on a
 // stack per head and takes the new layer's places from it.  One gather brings the rows into the caches'
 // layout when the caller asks for them.  A stage of 8K keys, d = 128, 8 heads is a chain of launches too small for the chip,
-// each waiting for the one before, with some 1.7 us between two: the scores (7 + 9 us), the plan beside the pooling
-// (8.5), the top-k (10), the lists (5) and the new layer's rows (5).  Counts and addresses come from the stage before and from
-// the call, so that nothing has to be written ahead of the scores.  32 stages with the gather of 55 us: 4595 us with
-// copies, 2270 now.
+// each waiting for the one before, with some 1.7 us between two: the scores (9 + 11 us), the plan beside the pooling
+// (8), the top-k with the lists (14; apart 11 + 6) and the new layer's rows (4 to 20).  Counts and addresses come from the stage
+// before and from the call, so that nothing has to be written ahead of the scores.  32 stages with the gather of 55 us: 4595 us
+// with copies, 2150 now.
 #include <algorithm>
 
 #include "cake_pass.h"
@@ -22,28 +22,8 @@ constexpr int kThreads = 256;
 constexpr int kUnroll = 2;            // 16-byte pieces a thread moves per step
 constexpr int kLongGap = 8;           // dropped rows in a row that one lane lists alone
 
-struct StageArgs {
-  PlanView plan;                      // of this stage
-  void* const* held;                  // [m] the indicators before the stage
-  const float* ind;                   // the new layer's
-  const char *ind_old, *ind_new;      // pools the indicators are in; the lists of places have the same layout
-  const int32_t* slots_old;
-  int32_t* slots_new;
-  int32_t* free_slots;
-  int32_t m, batch, h_kv, window, prefix_rows, prefix_len;
-};
-
-// Sum over the layers before l of keep (or of cur - keep) of sequence b, by one wave.
-__device__ __forceinline__ int32_t rows_before(const StageArgs& a, int l, int b, bool dropped, int lane) {
-  uint32_t t = 0;
-  for (int i = lane; i < l; i += 64) {
-    const int e = i * a.batch + b;
-    t += (uint32_t)(dropped ? a.plan.cur_len[e] - a.plan.keep[e] : a.plan.keep[e]);
-  }
-  return (int32_t)wave_sum(t);
-}
-
-// Lists of one (layer, sequence, head) after the stage, and the places its dropped rows leave free.  Bound by
+// Lists of one held (layer, sequence, head) after the stage, and the places its dropped rows leave free, where the row is too
+// long for the top-k that does both.  Bound by
 // the latency of its chain of loads (counts, position, entry), some 3 us a turn, so a list is shared out
 // over as many workgroups (blockIdx.z) as the chip has room for: no entry needs another's.
 __global__ __launch_bounds__(kThreads) void renew_lists(StageArgs a) {
@@ -56,11 +36,7 @@ __global__ __launch_bounds__(kThreads) void renew_lists(StageArgs a) {
   const int32_t* idx = static_cast<const int32_t*>(a.plan.idx[l]) + at;
   float* ind_out = static_cast<float*>(a.plan.ind_out[l]) + at;
   const int64_t from = (int64_t)head * a.plan.cap_cur[l];
-  const float* ind_in = (l == a.m ? a.ind : static_cast<const float*>(a.held[l])) + from;
-  if (l == a.m) {                     // the new layer gets its places in fill_rows
-    for (int r = tid; r < keep; r += all) ind_out[r] = ind_in[min(max(idx[r], 0), cur - 1)];
-    return;
-  }
+  const float* ind_in = static_cast<const float*>(a.held[l]) + from;
   const int32_t* old = a.slots_old + (reinterpret_cast<const char*>(ind_in) - a.ind_old) / 4;
   int32_t* renewed = a.slots_new + (reinterpret_cast<const char*>(ind_out) - a.ind_new) / 4;
   if (keep == cur) {
@@ -102,7 +78,7 @@ __global__ __launch_bounds__(kThreads) void renew_lists(StageArgs a) {
 }
 
 // Rows of the new layer into the store: the kept prefix rows to the places on top of the free stack, the
-// window rows to the layer's own.  Workgroups stride over the rows, whose number only the device knows.
+// window rows to the layer's own; and the kept rows' indicators and places into the layer's lists.  Workgroups stride over the rows, whose number only the device knows.
 __global__ __launch_bounds__(kThreads) void fill_rows(StageArgs a, const char* k, const char* v, char* k_store, char* v_store,
                                                      int64_t s0, int64_t s1, int64_t s2 /* bytes */, int64_t head_rows, int32_t pieces) {
   const int head = blockIdx.y, b = head / a.h_kv, h = head % a.h_kv;
@@ -113,6 +89,8 @@ __global__ __launch_bounds__(kThreads) void fill_rows(StageArgs a, const char* k
   const int32_t top = a.prefix_rows - rows_before(a, a.m, b, false, threadIdx.x & 63);
   const int64_t at = (int64_t)head * a.plan.cap_keep[a.m];
   const int32_t* idx = static_cast<const int32_t*>(a.plan.idx[a.m]) + at;
+  const float* ind_in = a.ind + (int64_t)head * a.plan.cap_cur[a.m];
+  float* ind_out = static_cast<float*>(a.plan.ind_out[a.m]) + at;
   int32_t* slots = a.slots_new + (static_cast<const char*>(a.plan.ind_out[a.m]) - a.ind_new) / 4 + at;
   const int32_t* freed = a.free_slots + (int64_t)head * a.prefix_rows;
   const char* kin = k + b * s0 + h * s1;
@@ -133,7 +111,10 @@ __global__ __launch_bounds__(kThreads) void fill_rows(StageArgs a, const char* k
         if (r < keep) {
           src = min(max(idx[r], 0), cur - 1);
           slot = min(max(freed[min(max(top - 1 - r, 0), a.prefix_rows - 1)], 0), a.prefix_rows - 1);
-          if (piece == 0) slots[r] = slot;
+          if (piece == 0) {
+            slots[r] = slot;
+            ind_out[r] = ind_in[src];
+          }
         }
         kv[u] = *reinterpret_cast<const uint4*>(kin + src * s2 + piece * 16);
         vv[u] = *reinterpret_cast<const uint4*>(vin + src * s2 + piece * 16);
@@ -205,9 +186,15 @@ extern "C" int cake_cascade_stage(const cake_cascade* c, int32_t m, const void* 
   const LayerPointers one{q_win, k, nullptr, indicator, nullptr, 0};
   if (int rc = launch_scores_and_preference(&c->shape, &c->params, nullptr, nullptr, q_strides, kv_strides, nullptr, nullptr, &one,
                                             c->workspace, c->workspace_bytes, c->pref + m, c->hv + 2 * m, L, L, &plan, st)) return rc;
-  if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(a.held), indicator, a.plan, a.prefix_len, true, PlanMirror{}, st)) return rc;
-  const int64_t shares = std::min<int64_t>((a.prefix_len + kThreads) / kThreads, 2048 / ((int64_t)bh * (m + 1)));
-  hipLaunchKernelGGL(renew_lists, dim3(bh, m + 1, (unsigned)std::max<int64_t>(shares, 1)), dim3(kThreads), 0, st, a);
+  if (a.prefix_len <= kStageMaxCur) {
+    if (int rc = launch_topk_stage(a, st)) return rc;
+  } else {
+    if (int rc = launch_topk_planned(&shape, reinterpret_cast<const float* const*>(a.held), indicator, a.plan, a.prefix_len, true, PlanMirror{}, st)) return rc;
+    if (m > 0) {
+      const int64_t shares = std::min<int64_t>((a.prefix_len + kThreads) / kThreads, 2048 / ((int64_t)bh * m));
+      hipLaunchKernelGGL(renew_lists, dim3(bh, m, (unsigned)std::max<int64_t>(shares, 1)), dim3(kThreads), 0, st, a);
+    }
+  }
   // as many workgroups as the most rows the layer can keep fill, up to four for each compute unit
   const int32_t pieces = shape.head_dim * eb / 16;
   const int64_t most = std::min<int64_t>(shape.seq_len, c->total_budget - (int64_t)m * shape.window);

@@ -157,12 +157,18 @@ __device__ __forceinline__ void find_interval(uint32_t need, SelectLds& s) {
   __syncthreads();
 }
 
-// The keys that satisfy `pick`, in order: store(rank, u, j).  Wave w holds a contiguous run of groups,
+struct LeaveOut {
+  __device__ __forceinline__ void operator()(uint32_t, int, int) const {}
+  __device__ __forceinline__ void operator()(int) const {}
+};
+
+// The keys that satisfy `pick`, in order: store(rank, u, j); the others: other(how many picked ones come before, u, j); ahead
+// of group u's: begin(u).  Wave w holds a contiguous run of groups,
 // group u of it in the lanes' slots u.  `before` counts the keys of earlier calls; a call alternates
 // between two sets of wave totals, so that one barrier per call is enough.
-template <int kThreads, int kSlots, typename Pick, typename Store>
+template <int kThreads, int kSlots, typename Pick, typename Store, typename Other = LeaveOut, typename Begin = LeaveOut>
 __device__ __forceinline__ void write_picked(uint32_t (&key)[kSlots][4], int n_u, Pick pick, uint32_t (&wave_sel)[kMaxWaves],
-                                             uint32_t& before, Store store) {
+                                             uint32_t& before, Store store, Other other = LeaveOut{}, Begin begin = LeaveOut{}) {
   constexpr int kWaves = kThreads / 64;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   uint32_t n = 0;
@@ -184,6 +190,7 @@ __device__ __forceinline__ void write_picked(uint32_t (&key)[kSlots][4], int n_u
 #pragma unroll
   for (int u = 0; u < kSlots; ++u) {
     if (u >= n_u) continue;
+    begin(u);
     uint32_t rank = n;
     bool p[4];
 #pragma unroll
@@ -196,6 +203,7 @@ __device__ __forceinline__ void write_picked(uint32_t (&key)[kSlots][4], int n_u
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (p[j]) store(rank, u, j);
+      else other(rank, u, j);
       rank += p[j] ? 1u : 0u;
     }
   }
@@ -410,6 +418,101 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(TopkArgs<kPlanned
   find_threshold<kThreads, kSlots>(key, n_u, (uint32_t)t.keep, position, lds, thr, last);
   write_picked<kThreads, kSlots>(key, n_u, [&](uint32_t x, int u, int j) { return x > thr - (position(u, j) <= last ? 1u : 0u); },
                                  lds.wave_sel[1], before, [&](uint32_t rank, int u, int j) { t.out[rank] = position(u, j); });
+}
+
+// The same for a stage of the cascade (cascade_stage.hip), one workgroup per (layer, sequence, head): the list of a layer held
+// before is renewed where the places of its rows are known anyway, with the number of kept rows before each.  The kept
+// rows' indicators and places go to the new lists, the places of the dropped ones to the head's free stack.  Of the new layer,
+// whose rows get their places afterwards, the kept positions are written.
+template <int kThreads, int kSlots>
+__global__ __launch_bounds__(kThreads) void select_stage_kernel(StageArgs a) {
+  __shared__ __attribute__((aligned(16))) SelectLds lds;
+  const int l = blockIdx.y, head = blockIdx.x, b = head / a.h_kv, e = l * a.batch + b;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cur = a.plan.cur_len[e], keep = a.plan.keep[e];
+  const bool held = l < a.m;
+  const int64_t at = (int64_t)head * a.plan.cap_keep[l];
+  int32_t* idx = static_cast<int32_t*>(a.plan.idx[l]) + at;
+  float* ind_out = static_cast<float*>(a.plan.ind_out[l]) + at;
+  const float* ind_in = (held ? static_cast<const float*>(a.held[l]) : a.ind) + (int64_t)head * a.plan.cap_cur[l];
+  const int32_t* old = a.slots_old + (reinterpret_cast<const char*>(ind_in) - a.ind_old) / 4;
+  int32_t* renewed = a.slots_new + (reinterpret_cast<const char*>(ind_out) - a.ind_new) / 4;
+  int32_t* freed = a.free_slots + (int64_t)head * a.prefix_rows;
+  // counts of the layers before, for the places the dropped ones go to (more than 64 layers: added up below)
+  const int le = min(lane, max(a.m - 1, 0)) * a.batch + b;
+  const int32_t cur_le = a.plan.cur_len[le], keep_le = a.plan.keep[le];
+  int top = 0;
+  auto stack_height = [&] {
+    if (!held || keep >= cur) return;
+    uint32_t t = (lane < l ? (uint32_t)(cur_le - keep_le) : 0u) - (lane < a.m ? (uint32_t)cur_le : 0u);
+    for (int i = lane + 64; i < a.m; i += 64) {
+      const int32_t c = a.plan.cur_len[i * a.batch + b];
+      t += (i < l ? (uint32_t)(c - a.plan.keep[i * a.batch + b]) : 0u) - (uint32_t)c;
+    }
+    top = a.prefix_rows + (int32_t)wave_sum(t);
+  };
+  auto stays = [&](int r, int p, float value, int32_t place) {
+    if (held) {
+      ind_out[r] = value;
+      renewed[r] = place;
+    } else {
+      idx[r] = p;
+    }
+  };
+  auto goes = [&](int r, int p, int32_t place) {
+    const int to = top + p - r;
+    if (held && to >= 0 && to < a.prefix_rows) freed[to] = place;
+  };
+  if (keep >= cur || keep <= 0) {
+    stack_height();
+    constexpr int kCopied = 8;                         // a thread's, in flight together
+    for (int p0 = tid; p0 < cur; p0 += kThreads * kCopied) {
+      float x[kCopied];
+      int32_t o[kCopied];
+#pragma unroll
+      for (int i = 0; i < kCopied; ++i) {
+        const int p = min(p0 + i * kThreads, cur - 1);
+        x[i] = held ? ind_in[p] : 0.f;
+        o[i] = held ? old[p] : 0;
+      }
+#pragma unroll
+      for (int i = 0; i < kCopied; ++i) {
+        const int p = p0 + i * kThreads;
+        if (p < cur && keep > 0) stays(p, p, x[i], o[i]);
+        else if (p < cur) goes(0, p, o[i]);
+      }
+    }
+    return;
+  }
+  Row row;
+  row.init(ind_in, cur);
+  const int n_u = (row.n_slots + kThreads - 1) / kThreads;
+  const int s0 = wave * 64 * n_u + lane;
+  uint32_t key[kSlots][4];
+  row.load(n_u, [&](int u) { return s0 + 64 * u; }, key);
+  auto position = [&](int u, int j) { return 4 * (s0 + 64 * u) - row.pad + j; };
+  // values and places of the group at hand and the next one's: the first ones arrive while the threshold is found
+  float value[2][4];
+  int32_t place[2][4];
+  auto fetch = [&](int u) {
+    if (!held) return;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int p = min(max(position(u, j), 0), cur - 1);
+      value[u & 1][j] = ind_in[p];
+      place[u & 1][j] = old[p];
+    }
+  };
+  fetch(0);
+  uint32_t thr, before = 0;
+  int last;
+  find_threshold<kThreads, kSlots>(key, n_u, (uint32_t)keep, position, lds, thr, last);
+  stack_height();
+  write_picked<kThreads, kSlots>(key, n_u, [&](uint32_t x, int u, int j) { return x > thr - (position(u, j) <= last ? 1u : 0u); },
+                                 lds.wave_sel[1], before,
+                                 [&](uint32_t rank, int u, int j) { stays(rank, position(u, j), value[u & 1][j], place[u & 1][j]); },
+                                 [&](uint32_t rank, int u, int j) { if (key[u][j] != 0u) goes(rank, position(u, j), place[u & 1][j]); },
+                                 [&](int u) { if (u + 1 < kSlots && u + 1 < n_u) fetch(u + 1); });
 }
 
 // Longer rows.
@@ -653,6 +756,14 @@ int cake::launch_topk_planned(const cake_shape* shape, const float* const* indic
   a.h_kv = shape->n_kv_heads;
   const TopkPlan tp{plan.cur_len, plan.keep, plan.cap_cur, plan.cap_keep, shape->n_layers, mirror, 0};
   return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers + (mirror.host != nullptr ? 1 : 0)), max_cur, bounded, a, NoArgs{}, tp, stream);
+}
+
+int cake::launch_topk_stage(const StageArgs& a, hipStream_t stream) {
+  const dim3 grid(a.batch * a.h_kv, a.m + 1);
+  if (a.prefix_len + 3 <= 256 * 4 * 4) hipLaunchKernelGGL((select_stage_kernel<256, 4>), grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL((select_stage_kernel<512, 8>), grid, dim3(512), 0, stream, a);
+  CAKE_HIP_TRY(hipGetLastError());
+  return CAKE_OK;
 }
 
 using namespace cake;

@@ -157,6 +157,40 @@ def test_device_cascade_equals_host_cascade_and_one_shot(cake, name):
             assert torch.equal(got.ind_out[l][s_, :, :n_k], shot.ind_out[l][s_, :, :n_k])
 
 
+@pytest.mark.parametrize("L,B,N,total", [
+    (5, 1, 4093 + 32, 5 * 300),            # rows of 4093 scored keys are the longest of the smaller list kernel,
+    (5, 2, 4094 + 32, 4094 + 2 * 700),     # one more (a layer that stays whole at first, two sequences),
+    (4, 1, 16381 + 32, 16381 + 500),       # the longest of the larger one,
+    (4, 1, 16382 + 32, 16381 + 500),       # and lists in a launch of their own
+    (70, 1, 130, 70 * 36),                 # more held layers than a wave has lanes
+    (9, 3, 601, 9 * 32 + 5),               # layers that lose their last row
+])
+def test_device_cascade_lists_at_the_edges_of_their_kernels(cake, L, B, N, total):
+    """After every second stage the same positions' rows and indicators, bit for bit, as the one-shot pass of the layers seen."""
+    say(f"device cascade lists L{L} B{B} N{N} total {total}")
+    S_w, d, H_kv = 32, 64, 2
+    g = torch.Generator(device=DEV).manual_seed(L * N)
+    rand = lambda *s: torch.randn(*s, generator=g, device=DEV, dtype=torch.float32).to(torch.bfloat16)
+    q = [rand(B, 2 * H_kv, S_w, d) * (1 + l % 5) for l in range(L)]
+    k, v = ([rand(B, H_kv, N, d) for _ in range(L)] for _ in range(2))
+    dev = cake.DeviceCascade(L, total)
+    for m in range(1, L + 1):
+        dev.admit(q[m - 1], k[m - 1], v[m - 1])
+        if m != L and (m % 2 or m > 8):
+            continue
+        got = dev.result()
+        want = cake.EvictionPass(q[:m], k[:m], v[:m], total).run()
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(got.budgets, want.budgets)
+        np.testing.assert_array_equal(got.keep, want.keep)
+        for l in range(m):
+            for b in range(B):
+                n_k = int(want.keep[l, b])
+                assert torch.equal(got.ind_out[l][b, :, :n_k], want.ind_out[l][b, :, :n_k]), (m, l, b)
+                for x, y in ((got.k_out, want.k_out), (got.v_out, want.v_out)):
+                    assert torch.equal(x[l][b, :, : n_k + S_w], y[l][b, :, : n_k + S_w]), (m, l, b)
+
+
 @pytest.mark.parametrize("L,B,H_q,H_kv,d,N,S_w,total,lse", [
     (6, 1, 8, 2, 64, 700, 32, 3 * 700 + 40, False),     # three layers fit, the fourth makes them shrink
     (5, 3, 10, 2, 128, 999, 64, 5 * 70, True),          # ragged batch, hardly more than the windows, normalisers handed over
