@@ -260,6 +260,18 @@ template <int D> struct RowDots<float, D> {
 // v_exp_f32, which returns 0 below 2^-126: for the terms of a sum that is at least 1
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// The (reference, sum) pairs of 64 rows each, in the rows' order, as one pair.  Both forms of the step merge the same runs of
+// 256 rows this way, so that a step's result depends on neither the other layers nor the other sequences of the call.
+template <int kPairs>
+__device__ __forceinline__ float2 merge_pairs(const float (&m)[kPairs], const float (&l)[kPairs]) {
+  float mm = kMasked, sum = 0.f;
+#pragma unroll
+  for (int i = 0; i < kPairs; ++i) mm = fmaxf(mm, m[i]);
+#pragma unroll
+  for (int i = 0; i < kPairs; ++i) sum = fmaf(l[i], fast_exp2(m[i] - mm), sum);
+  return make_float2(mm, sum);
+}
+
 // Step kernel 1, one workgroup per 64 rows a wave of a slice: the new row goes to its slot; logits of the G
 // heads for every listed row (kept for what follows) and the chunk's (reference, sum) pairs.
 // Bound by the key bytes: four 16-byte loads per row and lane, all of a wave's 64 rows in flight; the
@@ -358,12 +370,10 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void step_logits_kernel(Args a)
   }
   __syncthreads();
   if (tid < a.group) {
-    float mm = kMasked, sum = 0.f;
-    for (int w = 0; w < kStepWaves; ++w) mm = fmaxf(mm, red_m[w][tid]);
-    for (int w = 0; w < kStepWaves; ++w) sum += red_l[w][tid] * fast_exp2(red_m[w][tid] - mm);
-    float* o = a.part + ((slice * a.n_chunks + chunk) * kMaxGroup + tid) * 2;
-    o[0] = mm;
-    o[1] = sum;
+    float rm[kStepWaves], rl[kStepWaves];
+#pragma unroll
+    for (int w = 0; w < kStepWaves; ++w) { rm[w] = red_m[w][tid]; rl[w] = red_l[w][tid]; }
+    *reinterpret_cast<float2*>(a.part + ((slice * a.n_chunks + chunk) * kMaxGroup + tid) * 2) = merge_pairs(rm, rl);
   }
 }
 
@@ -413,11 +423,27 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   }
   if (wave < group) {
     const float* p = a.part + ((int64_t)slice * a.n_chunks * kMaxGroup + wave) * 2;
-    static_assert(kFinishRows / kThreads <= 64 && kStepSmallRows / 64 <= 64 && kMaxGroup <= kFinishWaves, "a lane per chunk and a wave per head");
-    float2 x = make_float2(kMasked, 0.f);
-    if (kOne) x = *reinterpret_cast<const float2*>(p + min(lane, a.n_chunks - 1) * kMaxGroup * 2);
-    else if (lane * a.chunk_rows < n) x = *reinterpret_cast<const float2*>(p + lane * kMaxGroup * 2);
-    if (lane * a.chunk_rows >= n) x = make_float2(kMasked, 0.f);
+    static_assert(kFinishRows / kThreads <= 64 && kMaxGroup <= kFinishWaves, "a lane per 256 rows and a wave per head");
+    auto pair = [&](int chunk) {            // (masked where the chunk has no rows)
+      float2 x = make_float2(kMasked, 0.f);
+      if (kOne) x = *reinterpret_cast<const float2*>(p + min(chunk, a.n_chunks - 1) * kMaxGroup * 2);
+      else if (chunk * a.chunk_rows < n) x = *reinterpret_cast<const float2*>(p + chunk * kMaxGroup * 2);
+      if (chunk * a.chunk_rows >= n) x = make_float2(kMasked, 0.f);
+      return x;
+    };
+    float2 x;
+    if (a.chunk_rows == kThreads) {
+      x = pair(lane);
+    } else {                                // pairs of 64 rows: four are what a workgroup of 256 rows writes
+      float rm[kWaves], rl[kWaves];
+#pragma unroll
+      for (int w = 0; w < kWaves; ++w) {
+        const float2 y = pair(lane * kWaves + w);
+        rm[w] = y.x;
+        rl[w] = y.y;
+      }
+      x = merge_pairs(rm, rl);
+    }
     const float m = wave_max(x.x), l = wave_sum(x.y * fast_exp2(x.x - m));
     if (lane == 0) lse[wave] = m + log2f(l);
   }

@@ -113,3 +113,43 @@ def test_queries_may_start_at_any_element(cake, dtype):
         torch.cuda.synchronize()
         for name in ("k", "v", "ind", "order", "state"):
             assert torch.equal(getattr(got, name)[0], getattr(want, name)[0]), (off, name)
+
+
+@pytest.mark.parametrize("L,B,H_kv,G,d,S_w,dtype,cap", [
+    (12, 1, 8, 4, 128, 32, "bf16", 1000),      # one call for all layers is large, a layer is not
+    (3, 16, 4, 1, 64, 64, "bf16", 767),        # a layer's call is large too, a sequence alone is not
+    (3, 5, 8, 6, 64, 32, "f32", 1400),
+    (2, 2, 8, 8, 128, 32, "bf16", 4063)])      # 4096 rows: the longest lists of the small form
+def test_a_step_is_the_same_whatever_else_the_call_holds(cake, L, B, H_kv, G, d, S_w, dtype, cap):
+    """Every buffer of a call for all layers equals that of calls layer by layer, and every sequence's rows those of a
+    batch of one, bit for bit: calls of more than 256 workgroups of 256 rows, and calls of fewer, which take 64 rows each."""
+    say(f"decode step alone and among others: L={L} B={B} H_kv={H_kv} G={G} d={d} S_w={S_w} {dtype} {cap} rows")
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    workgroups = lambda layers, batch: -(-(cap + S_w + 1) // 256) * layers * batch * H_kv
+    assert workgroups(L, B) > 256 >= workgroups(1, 1)
+    gen = torch.Generator().manual_seed(cap + L)
+    keep = np.array([[max(cap - 90 * l - 7 * b, 1) for b in range(B)] for l in range(L)])
+    mk = lambda l: torch.randn(B, H_kv, int(keep[l].max()) + S_w, d, generator=gen).to(dt).to(DEV)
+    k, v = [mk(l) for l in range(L)], [mk(l) for l in range(L)]
+    ind = [torch.exp(torch.randn(B, H_kv, int(keep[l].max()), generator=gen) - 6.0).to(DEV) for l in range(L)]
+
+    def slots(b=slice(None)):
+        kept = keep[:, b]
+        cut = lambda t, extra: [x[b, :, : int(kept[l].max()) + extra] for l, x in enumerate(t)]
+        return cake.DecodeSlots(cake.PassResult(kept + S_w, kept, None, None, [], [], cut(k, S_w), cut(v, S_w), cut(ind, 0)), G * H_kv, S_w)
+
+    together, by_layer, alone = slots(), slots(), [slots(slice(b, b + 1)) for b in range(B)]
+    for step in range(3):
+        qn = (torch.randn(L, B, G * H_kv, d, generator=gen) * 2).to(dt).to(DEV)
+        kn, vn = (torch.randn(L, B, H_kv, d, generator=gen).to(dt).to(DEV) for _ in range(2))
+        together.step_all(qn, kn, vn)
+        for l in range(L):
+            by_layer.step(l, qn[l], kn[l], vn[l])
+            for b in range(B):
+                alone[b].step(l, qn[l, b:b + 1], kn[l, b:b + 1], vn[l, b:b + 1])
+        for l in range(L):
+            for name in ("k", "v", "ind", "order", "state"):
+                assert torch.equal(getattr(together, name)[l], getattr(by_layer, name)[l]), (step, l, name)
+            for b in range(B):
+                for x, y in zip(by_layer.logical(l, b), alone[b].logical(l, 0)):
+                    assert np.array_equal(x, y) if isinstance(x, np.ndarray) else torch.equal(x, y), (step, l, b)
