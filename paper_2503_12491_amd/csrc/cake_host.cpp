@@ -93,18 +93,22 @@ extern "C" int cake_workspace_bytes(const cake_shape* shape, size_t* bytes) {
 }
 
 // Number of seat counts s in [window, n-1] whose priority p/(s + 1/2) is strictly above lam.
-// The quotient never increases with s, so the last such s is found from a closed-form guess, corrected with the
-// same fp64 division the award loop uses.
+// The quotient never increases with s, so the last such s is searched from a closed-form guess with the
+// same fp64 division the award loop uses.  The guess is a seat off at most, unless the quotients are subnormal: they
+// are then rounded so coarsely that it can be off by a large share of n, and what is left is halved.
 static int64_t seats_above(double p, double lam, int32_t window, int32_t n) {
   if (!(p / (window + 0.5) > lam)) return 0;
-  int64_t s = n - 1;
+  int64_t lo = window, hi = n - 1, s = hi;  // above lam at lo, not above it beyond hi
   if (lam > 0.0) {
     const double guess = std::floor(p / lam - 0.5);
-    s = guess >= (double)(n - 1) ? n - 1 : guess <= (double)window ? window : (int64_t)guess;
+    s = guess >= (double)hi ? hi : guess <= (double)lo ? lo : (int64_t)guess;
   }
-  while (s < n - 1 && p / ((double)s + 1.5) > lam) ++s;
-  while (s > window && !(p / ((double)s + 0.5) > lam)) --s;
-  return s - window + 1;
+  for (int tries = 1; lo < hi; ++tries) {
+    const bool above = p / ((double)s + 0.5) > lam;
+    if (above) lo = s; else hi = s - 1;
+    s = tries >= 4 ? lo + (hi - lo + 1) / 2 : above ? lo + 1 : hi;
+  }
+  return lo - window + 1;
 }
 
 extern "C" int cake_keep_counts(const int32_t* budgets, const int32_t* cur_len, int32_t n, int32_t window, int32_t* keep) {

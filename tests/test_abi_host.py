@@ -3,6 +3,7 @@ arguments before touching the GPU, and its allocator equals the oracle's exactly
 import ctypes
 import os
 import re
+import time
 
 import numpy as np
 import pytest
@@ -71,6 +72,24 @@ def test_allocator_paper_scale(cake):
         if prev is not None:
             assert all(c <= p for c, p in zip(cur, prev))
         prev = cur
+
+
+def test_allocator_subnormal_preferences(cake):
+    """Quotients among the subnormal numbers are rounded by up to a half of themselves, so that no closed form finds a layer's
+    seats: the same budgets as the oracle's, and no search seat by seat (5 ms are ten times what halving takes and a
+    quarter of what that took)."""
+    rng = np.random.default_rng(102)
+    for exponent in (300, 308, 310, 314, 318, 320, 322, 323):
+        for total, n in ((40 * 300, 3000), (40 * 2900, 3000), (40 * 34, 200)):
+            pref = np.array([float(f"{x:.6f}e-{exponent}") for x in 1.0 + 9.0 * rng.random(40)])
+            assert cake.cake_cascade_allocate(pref, total, 32, n) == co.cascade_allocate(pref, total, 32, n), (exponent, total, n)
+    pref = [float(f"{x:.6f}e-318") for x in rng.random(32)]
+    took = []
+    for _ in range(5):
+        t0 = time.perf_counter()
+        cake.cake_cascade_allocate(pref, 32 * 8192, 32, 131072)
+        took.append(time.perf_counter() - t0)
+    assert min(took) < 5e-3, took
 
 
 def test_allocator_errors(cake):
