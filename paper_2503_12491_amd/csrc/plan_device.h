@@ -28,18 +28,22 @@ __device__ __forceinline__ double approx_rcp(double x) {
 }
 
 // Number of seat counts s in [window, n-1] with p/(s + 1/2) > lam.  The quotient never increases
-// with s, so the count is fixed by the last s that passes; a closed-form guess is corrected with
-// the exact predicate.
+// with s, so the count is fixed by the last s that passes; it is searched from a closed-form guess with
+// the exact predicate.  The guess is a seat off at most, unless the quotients are subnormal: they are then rounded so
+// coarsely that it can be off by a large share of n, and what is left after four tries is halved.
 __device__ int64_t seats_above(double p, double lam, int window, int n) {
   if (!seat_above(p, lam, window)) return 0;
-  int64_t s = n - 1;
+  int64_t lo = window, hi = n - 1, s = hi;        // above lam at lo, not above it beyond hi
   if (lam > 0.0) {
     const double guess = floor(p / lam - 0.5);
-    s = guess >= (double)(n - 1) ? (int64_t)(n - 1) : guess <= (double)window ? (int64_t)window : (int64_t)guess;
+    s = guess >= (double)hi ? hi : guess <= (double)lo ? lo : (int64_t)guess;
   }
-  while (s < n - 1 && seat_above(p, lam, s + 1)) ++s;
-  while (s > window && !seat_above(p, lam, s)) --s;
-  return s - window + 1;
+  for (int tries = 1; lo < hi; ++tries) {
+    const bool above = seat_above(p, lam, s);
+    if (above) lo = s; else hi = s - 1;
+    s = tries >= 4 ? lo + (hi - lo + 1) / 2 : above ? lo + 1 : hi;
+  }
+  return lo - window + 1;
 }
 
 // The largest value, of several equal ones the lowest layer; the wave's answer in every lane.

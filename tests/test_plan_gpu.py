@@ -66,6 +66,38 @@ def test_device_budgets_equal_the_oracle_allocator(cake):
     say(f"device allocation: {cases} sequences identical to the oracle allocator")
 
 
+def test_device_budgets_of_subnormal_preferences(cake):
+    """Quotients among the subnormal numbers are rounded by up to a half of themselves, so that no closed form finds a layer's
+    seats: the same budgets as the oracle's, and no search seat by seat.  (Of 131072 seats with quotients of 0 the search
+    that halves takes 19 divisions in a row and one seat by seat 131030, each longer than 10 ns at any clock of this chip: 0.5 ms
+    are below the half of those.)"""
+    from paper_2503_12491_amd import binding as C
+    say("device allocation: subnormal preferences")
+    rng = np.random.default_rng(102)
+    for exponent in (300, 308, 314, 318, 320, 322, 323):
+        for total, n in ((40 * 300, 3000), (40 * 2900, 3000), (40 * 34, 200)):
+            pref = np.array([float(f"{x:.6f}e-{exponent}") for x in 1.0 + 9.0 * rng.random(40)])
+            budgets, _, _, status = _plan(cake, pref[None], total, 32, n)
+            assert status[0] == 0 and list(budgets[:, 0]) == co.cascade_allocate(pref, total, 32, n), (exponent, total, n)
+    L, window, seq_len, total = 32, 32, 131072, 32 * 8192
+    pref = np.array([[float(f"{1 + l % 9}e-322") for l in range(L)]])
+    budgets, _, _, _ = _plan(cake, pref, total, window, seq_len)
+    assert list(budgets[:, 0]) == cake.cake_cascade_allocate(pref[0], total, window, seq_len)
+    shape = C.make_shape(1, L, 2, 2, 64, seq_len, window, torch.float32)
+    plan = torch.zeros(C.cake_plan_bytes(shape), dtype=torch.uint8, device=DEV)
+    status, pool, p = torch.zeros(1, dtype=torch.int32, device=DEV), torch.zeros(64, dtype=torch.uint8, device=DEV), torch.tensor(pref, device=DEV)
+    took = []
+    for _ in range(5):
+        begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        begin.record()
+        C.cake_plan_eviction(shape, p, total, None, pool, pool, pool, pool, plan, status)
+        end.record()
+        torch.cuda.synchronize()
+        took.append(begin.elapsed_time(end))
+    say(f"plan of preferences around 1e-322: {min(took):.3f} ms")
+    assert min(took) < 0.5, took
+
+
 @pytest.mark.parametrize("L,B", [(3, 12), (3, 13), (64, 13), (65, 12), (65, 13), (300, 10), (300, 11), (1024, 3), (1024, 4), (2, 64), (2, 65), (5, 256)])
 def test_plans_of_batches_of_every_size(cake, L, B):
     """Few sequences are allocated in the plan's workgroup, more by workgroups of their own, and the row capacities are
