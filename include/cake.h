@@ -433,8 +433,9 @@ int cake_decode_update_static(const cake_shape* shape, const cake_params* params
  * kernels (a few microseconds of overhead).  cake_profile_read waits for the last recorded
  * event and returns milliseconds averaged over the calls since cake_profile_enable(1) (at most
  * the 64 most recent): ms[0] pass 1 (row normalisers), ms[1] combine, ms[2] pass 2 (column
- * statistics), ms[3] pooling.  Process-wide state, not thread-safe; events are created by
- * cake_profile_enable(1) and destroyed by cake_profile_enable(0).
+ * statistics), ms[3] pooling (in a whole pass with what shares the pooling's launch: the layer
+ * preferences, and the plan where only a few follow from them).  Process-wide state, not
+ * thread-safe; events are created by cake_profile_enable(1) and destroyed by cake_profile_enable(0).
  */
 int cake_profile_enable(int enable);
 int cake_profile_read(float* ms /* host [4], out */);

@@ -294,3 +294,31 @@ def test_plan_beside_the_pooling_equals_the_calls_of_their_own(cake, L, B):
         for b in range(B):
             n = int(res.keep[l, b])
             assert torch.equal(idx[l][b, :, :n], want.idx[l][b, :, :n]) and torch.equal(k_out[l][b, :, :n + 32], want.k_out[l][b, :, :n + 32])
+
+
+def test_a_plan_in_a_launch_of_its_own_is_not_timed_as_pooling(cake):
+    """The timed pooling of a whole pass ends before the plan's launch: 1024 equal preferences leave the plan a thousand
+    seats to award one by one, some hundred times what their few positions take to be pooled."""
+    say("profile of a pass with a long plan")
+    L, S_w, N = 1024, 32, 97
+    gen = torch.Generator(device=DEV).manual_seed(5)
+    q, k, v = (torch.randn(1, h, n, 64, device=DEV, generator=gen) for h, n in ((2, S_w), (1, N), (1, N)))
+    ev = cake.EvictionPass([q] * L, [k] * L, [v] * L, L * S_w + L * 9 + 1000)
+    pooled = []
+    for call in (ev.scores, ev.run):
+        call()
+        cake.cake_profile_enable(True)
+        try:
+            for _ in range(5):
+                call()
+            pooled.append(cake.cake_profile_read()[3])
+        finally:
+            cake.cake_profile_enable(False)
+    begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    begin.record()
+    cake.cake_plan_eviction(ev.shape, ev.pref, ev.total_budget, None, ev.pool_idx, ev.pool_k, ev.pool_v, ev.pool_ind, ev.plan, ev.status)
+    end.record()
+    torch.cuda.synchronize()
+    plan = begin.elapsed_time(end)
+    say(f"pooling alone {pooled[0]:.4f} ms, in the pass {pooled[1]:.4f} ms, plan {plan:.4f} ms")
+    assert pooled[1] < pooled[0] + 0.25 * plan
