@@ -391,8 +391,8 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass1(ScoreArgs a) 
 // Combine the granules' pairs of a window row into lse2 = log2 sum_j 2^(t_j).  Four chains share
 // a row: each folds every fourth granule into a running (reference, sum) pair in one sweep, the four
 // pairs are merged in a fixed order, so that the result does not depend on how the chains are dealt to lanes: kChains
-// of a lane's own (4, 2 or 1), the others' from `partner`, which returns another lane's value and whether that lane's
-// chains come first.  p: the row's first pair; chain0: the lane's first chain; all of a row's lanes get the result.
+// of a lane's own (4, 2 or 1), merged by then into one pair; `partner` folds into it, in place, the pairs of the other lanes of the
+// row, the pair of the earlier chains first.  p: the row's first pair; chain0: the lane's first chain; all of a row's lanes get the result.
 // Bound by latency: a chain of loads, then of fp64 additions.  With four lanes a row and 16 rows a turn, pass 2 of one layer of
 // 8192 keys waited 5.6 us for its first tile (8 x 4 heads of 128; 16.5 us in all, now 12.6).
 constexpr int kCombineAhead = 8;          // pairs in flight per chain
@@ -710,8 +710,8 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
   // Two accumulator sets (logits of even / odd sub-tiles) let one sub-tile's MFMAs overlap the
   // previous one's statistics.  Measured, this pays for bf16 with two row blocks per wave
   // (S_w = 64); with one row block the periods are too short and the plain order is faster, and
-  // the fp32 kernels hold four times the query fragments and would spill.  Those run the two
-  // phases of a sub-tile one after the other on a single set.
+  // the fp32 kernels hold twice the query registers (128 of them at two row blocks of 128) and would spill.  Those run
+  // the two phases of a sub-tile one after the other on a single set.
   constexpr bool kPipelined = kPipelinedForm<T, MB>;
   f32x16 acc_a[MB], acc_b[MB];
   ColSums cs0{}, cs1{};

@@ -34,24 +34,47 @@ def test_fp32_scores_against_the_oracle(d, window, n):
     assert_close(hv[0, 0, 1], want["V"], "V", rtol=1e-4)
 
 
+def _granules(n, window):
+    """(chunk, granule) in keys of a layer of n keys."""
+    chunk = 2048 if n >= 32768 else 1024 if n >= 8192 else 512 if n >= 2048 else 256
+    return chunk, 2048 if n >= 65536 else 1024 if n >= 16384 else 256 if n >= 2048 else 128 if window > 32 else 64
+
+
+def _combines(slices, dtype, window, group, n):
+    """Whether pass 2 combines the pairs of pass 1 by itself in a call of so many slices: None where that hangs on how many
+    granules a workgroup takes (one at least, a chunk at most)."""
+    chunk, granule = _granules(n, window)
+    n_p = n - window
+    if dtype == torch.bfloat16 and window == 32 and group in (5, 6) and slices * -(-n_p // granule) > 512:
+        return False                               # packed workgroups do not
+    pairs = group * window * -(-n // granule) * 8
+    piped = dtype == torch.bfloat16 and window == 64
+    fits = lambda workgroups: workgroups * pairs <= 16 << 20 and (not piped or workgroups <= 256)
+    fewest, most = fits(slices * -(-n_p // chunk)), fits(slices * -(-n_p // granule))
+    return fewest if fewest == most else None
+
+
 @pytest.mark.parametrize("peak", [1.0, 12.0])      # references all 0; references of their own
-@pytest.mark.parametrize("dtype,window,group,d,n", [
-    (torch.bfloat16, 32, 4, 128, 160),             # 3 granules of 64
-    (torch.bfloat16, 32, 5, 64, 32 * 64),          # 8 granules of 256, packed where there are many
-    (torch.bfloat16, 32, 6, 128, 33 * 256 - 7),    # 33 granules: one more than a sweep of the pairs
-    (torch.bfloat16, 32, 1, 128, 8192),            # 32 granules: one sweep
-    (torch.bfloat16, 64, 4, 128, 31 * 256 + 1),    # 32 granules of the software-pipelined form, one key in the last
-    (torch.float32, 64, 3, 64, 1999),              # 16 granules of 128
-    (torch.float32, 32, 2, 128, 2100),
+@pytest.mark.parametrize("dtype,window,group,d,n,layers", [
+    (torch.bfloat16, 32, 4, 128, 160, 700),        # 3 granules of 64
+    (torch.bfloat16, 32, 5, 64, 32 * 64, 160),     # 8 granules of 256, packed where there are many
+    (torch.bfloat16, 32, 6, 128, 33 * 256 - 7, 60),    # 33 granules: one more than a sweep of the pairs
+    (torch.bfloat16, 32, 1, 128, 8192, 70),        # 32 granules: one sweep
+    (torch.bfloat16, 64, 4, 128, 31 * 256 + 1, 64),    # 32 granules of the software-pipelined form, one key in the last
+    (torch.float32, 64, 3, 64, 1999, 160),         # 16 granules of 128
+    (torch.float32, 32, 2, 128, 2100, 100),
 ])
-def test_a_layer_alone_scores_to_the_same_bits_as_among_many(dtype, window, group, d, n, peak):
+def test_a_layer_alone_scores_to_the_same_bits_as_among_many(dtype, window, group, d, n, layers, peak):
+    """A layer alone has its pairs combined inside pass 2, among many by the kernel in between."""
     cake = load_cake()
     say(f"scores alone and among many {dtype} S_w={window} G={group} d={d} N={n} peak={peak}")
-    h_kv, layers = 2, 1 + 4096 // (2 * (-(-n // 256)) + 1)
-    layers = min(layers, 160)
+    h_kv = 8
+    assert _combines(h_kv, dtype, window, group, n) is True
+    assert _combines(h_kv * layers, dtype, window, group, n) is False
     q, k, v = _inputs(2, h_kv * group, h_kv, d, n, window, dtype, n, peak)
     many = cake.EvictionPass([q[i % 2] for i in range(layers)], [k[i % 2] for i in range(layers)], [v[i % 2] for i in range(layers)],
                              layers * window)
+    assert cake.cake_scores_chunk_keys(many.shape) == _granules(n, window)[0]
     many.scores()
     for l in range(2):
         alone = cake.EvictionPass(q[l:l + 1], k[l:l + 1], v[l:l + 1], window)
