@@ -198,7 +198,7 @@ typedef cake_decode_buffers StepBuffers;
 struct StepBase {
   const void* q_new; const void* k_new; const void* v_new;
   int64_t qs[3], ns[3];             // element strides of q_new / k_new, v_new: layer, batch, head
-  int32_t batch, h_kv, group, window, pool, n_chunks, rows_max, chunk_rows;
+  int32_t batch, h_kv, group, window, pool, n_chunks, rows_max;
   float c, inv_g;
   float* logits;      // [slice][group][rows_max], rows_max a multiple of 4
   float* part;        // [slice][n_chunks][kMaxGroup][2], chunks of the rows a workgroup of the first kernel takes
@@ -388,10 +388,12 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void step_logits_kernel(Args a)
 // first kernel (a ticket per slice) was slower, 21 us against 14 for both: making the chunks' logits
 // visible across the dies costs more than the launch.
 constexpr int kStepSmallRows = 4096;       // one-wave workgroups in the first kernel: rows per slice at most
-constexpr int kFinishThreads = 1024, kFinishPer = 8, kFinishRows = kFinishThreads * kFinishPer;
-template <int kGroup, typename Args>
+constexpr int kFinishThreads = 1024, kFinishRows = 8 * kFinishThreads;
+// kSmall: the first kernel's workgroups took 64 rows each, of kStepSmallRows at most.  (One kernel that merged the pairs of
+// either had registers of the four-head form spilled: 384 heads of 2K rows 11.1 -> 12.5 us.)
+template <int kGroup, bool kSmall, typename Args>
 __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_finish_kernel(Args a) {     // <= 64 registers: two workgroups per compute unit
-  constexpr int kFinishWaves = kFinishThreads / 64;
+  constexpr int kFinishWaves = kFinishThreads / 64, kPer = (kSmall ? kStepSmallRows : kFinishRows) / kFinishThreads;
   __shared__ float obs[kFinishRows + 2 * kMaxHalf];      // group-mean weights between two clipped edges
   __shared__ float lse[kMaxGroup];
   __shared__ uint64_t cand[kFinishWaves];
@@ -408,11 +410,11 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   const int group = a.group;
   // A layer alone is loaded up to what its buffers hold: no load waits for the state to say how much of it is in use.
   constexpr bool kOne = std::is_same<Args, StepOneArgs>::value;
-  int32_t slot[kFinishPer];
-  float val[kFinishPer], t[kFinishPer][kGroup];
+  int32_t slot[kPer];
+  float val[kPer], t[kPer][kGroup];
   const int last = kOne ? cap + a.window : n - 1;
 #pragma unroll
-  for (int i = 0; i < kFinishPer; ++i) {
+  for (int i = 0; i < kPer; ++i) {
     const int j = i * kFinishThreads + tid;
     if (i * kFinishThreads <= last) {
       slot[i] = order[min(j, last)];
@@ -424,17 +426,16 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   if (wave < group) {
     const float* p = a.part + ((int64_t)slice * a.n_chunks * kMaxGroup + wave) * 2;
     static_assert(kFinishRows / kThreads <= 64 && kMaxGroup <= kFinishWaves, "a lane per 256 rows and a wave per head");
+    constexpr int kChunkRows = kSmall ? 64 : kThreads;
     auto pair = [&](int chunk) {            // (masked where the chunk has no rows)
       float2 x = make_float2(kMasked, 0.f);
       if (kOne) x = *reinterpret_cast<const float2*>(p + min(chunk, a.n_chunks - 1) * kMaxGroup * 2);
-      else if (chunk * a.chunk_rows < n) x = *reinterpret_cast<const float2*>(p + chunk * kMaxGroup * 2);
-      if (chunk * a.chunk_rows >= n) x = make_float2(kMasked, 0.f);
+      else if (chunk * kChunkRows < n) x = *reinterpret_cast<const float2*>(p + chunk * kMaxGroup * 2);
+      if (chunk * kChunkRows >= n) x = make_float2(kMasked, 0.f);
       return x;
     };
     float2 x;
-    if (a.chunk_rows == kThreads) {
-      x = pair(lane);
-    } else {                                // pairs of 64 rows: four are what a workgroup of 256 rows writes
+    if constexpr (kSmall) {                 // pairs of 64 rows: four are what a workgroup of 256 rows writes
       float rm[kWaves], rl[kWaves];
 #pragma unroll
       for (int w = 0; w < kWaves; ++w) {
@@ -443,6 +444,8 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
         rl[w] = y.y;
       }
       x = merge_pairs(rm, rl);
+    } else {
+      x = pair(lane);
     }
     const float m = wave_max(x.x), l = wave_sum(x.y * fast_exp2(x.x - m));
     if (lane == 0) lse[wave] = m + log2f(l);
@@ -450,7 +453,7 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   for (int i = tid; i < half; i += kFinishThreads) obs[i] = obs[half + cur1 + i] = -INFINITY;      // clipped edges never win the max
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < kFinishPer; ++i) {
+  for (int i = 0; i < kPer; ++i) {
     const int j = i * kFinishThreads + tid;
     if (i * kFinishThreads < cur1 && j < cur1) {
       float s = 0.f;
@@ -472,7 +475,7 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   __syncthreads();
   uint64_t best = 0;                                     // largest complement of (order-preserving key of the value, complement of the index)
 #pragma unroll
-  for (int i = 0; i < kFinishPer; ++i) {
+  for (int i = 0; i < kPer; ++i) {
     const int j = i * kFinishThreads + tid;
     if (i * kFinishThreads < cur1 && j < cur1) {
       float mx = obs[half + j];
@@ -489,7 +492,7 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   for (int w = 0; w < kFinishWaves; ++w) best = max(best, cand[w]);
   const int e = (int)(uint32_t)best;
 #pragma unroll
-  for (int i = 0; i < kFinishPer; ++i) {
+  for (int i = 0; i < kPer; ++i) {
     const int j = i * kFinishThreads + tid;
     if (i * kFinishThreads >= n || j >= n) continue;
     if (j == n - 1) slot[i] = free_slot;
@@ -845,7 +848,6 @@ int decode_step_impl(const cake_shape* shape, const cake_params* params,
   // Where workgroups of 256 rows leave compute units idle, four of 64 rows in the place of each.
   const bool small = (int64_t)grid.x * grid.y * L <= 256 && rows <= kStepSmallRows;
   const dim3 logits_grid(small ? (rows + 63) / 64 : grid.x, grid.y, L), logits_block(small ? 64 : kThreads);
-  a.chunk_rows = small ? 64 : kThreads;
   if (small) a.n_chunks *= kThreads / 64;
   const dim3 slices_grid(B * shape->n_kv_heads, L);
   const bool bf = shape->dtype == CAKE_BF16;
@@ -858,8 +860,9 @@ int decode_step_impl(const cake_shape* shape, const cake_params* params,
 #undef CAKE_STEP
     hipLaunchKernelGGL(logits, logits_grid, logits_block, 0, st, args);
     if (rows > kFinishRows) return CAKE_OK;
-    if (G <= 4) hipLaunchKernelGGL((step_finish_kernel<4, Args>), slices_grid, dim3(kFinishThreads), 0, st, args);
-    else hipLaunchKernelGGL((step_finish_kernel<kMaxGroup, Args>), slices_grid, dim3(kFinishThreads), 0, st, args);
+    const auto finish = G <= 4 ? (small ? step_finish_kernel<4, true, Args> : step_finish_kernel<4, false, Args>)
+                               : (small ? step_finish_kernel<kMaxGroup, true, Args> : step_finish_kernel<kMaxGroup, false, Args>);
+    hipLaunchKernelGGL(finish, slices_grid, dim3(kFinishThreads), 0, st, args);
     return CAKE_OK;
   };
   if (L == 1 && buffers != nullptr && rows <= kFinishRows) {
