@@ -260,8 +260,8 @@ template <int D> struct RowDots<float, D> {
 // v_exp_f32, which returns 0 below 2^-126: for the terms of a sum that is at least 1
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// The (reference, sum) pairs of 64 rows each, in the rows' order, as one pair.  Both forms of the step merge the same runs of
-// 256 rows this way, so that a step's result depends on neither the other layers nor the other sequences of the call.
+// What all forms of the step share, so that a head's result depends on neither the other layers nor the other sequences of the
+// call: the (reference, sum) pairs of 64 rows each, in the rows' order, as one pair (runs of 256 rows);
 template <int kPairs>
 __device__ __forceinline__ float2 merge_pairs(const float (&m)[kPairs], const float (&l)[kPairs]) {
   float mm = kMasked, sum = 0.f;
@@ -270,6 +270,38 @@ __device__ __forceinline__ float2 merge_pairs(const float (&m)[kPairs], const fl
 #pragma unroll
   for (int i = 0; i < kPairs; ++i) sum = fmaf(l[i], fast_exp2(m[i] - mm), sum);
   return make_float2(mm, sum);
+}
+
+// the normaliser, log2 of the sum that the lanes' pairs stand for;
+__device__ __forceinline__ float wave_normaliser(float2 x) {
+  const float m = wave_max(x.x), e = fast_exp2(x.x - m);
+  // (which of the sum's products are rounded is written out: it must not hang on the kernel)
+  float l = fmaf(x.y, e, dpp_step<0x111, 0xf, false>(x.y * e));
+  l += dpp_step<0x112, 0xf, false>(l);
+  l += dpp_step<0x114, 0xf, false>(l);
+  l += dpp_step<0x118, 0xf, false>(l);
+  l += dpp_step<0x142, 0xa, false>(l);
+  l += dpp_step<0x143, 0xc, false>(l);
+  return m + log2f(from_lane(l, 63));
+}
+
+// and the sum of a row's weights over the heads.  Weights below 2^-126 too: they order rows whose indicators are still 0.  Beside
+// a sum from 2^-90 on the up to eight terms that came out as 0 are less than half its last place, so the sum is the
+// same to the bit; taking exp2f for all terms cost up to 7 % of a step (32 heads of 6000 rows and 8 queries 26.1 -> 28.1 us a
+// layer, so 26.3).
+template <int kGroup>
+__device__ __forceinline__ float weight_sum(const float (&t)[kGroup], const float* lse, int group) {
+  float s = 0.f;
+#pragma unroll
+  for (int h = 0; h < kGroup; ++h)
+    if (h < group) s += fast_exp2(t[h] - lse[h]);
+  if (s < 0x1p-90f) {
+    s = 0.f;
+#pragma unroll
+    for (int h = 0; h < kGroup; ++h)
+      if (h < group) s += exp2f(t[h] - lse[h]);
+  }
+  return s;
 }
 
 // Step kernel 1, one workgroup per 64 rows a wave of a slice: the new row goes to its slot; logits of the G
@@ -447,8 +479,8 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
     } else {
       x = pair(lane);
     }
-    const float m = wave_max(x.x), l = wave_sum(x.y * fast_exp2(x.x - m));
-    if (lane == 0) lse[wave] = m + log2f(l);
+    const float norm = wave_normaliser(x);
+    if (lane == 0) lse[wave] = norm;
   }
   for (int i = tid; i < half; i += kFinishThreads) obs[i] = obs[half + cur1 + i] = -INFINITY;      // clipped edges never win the max
   __syncthreads();
@@ -456,20 +488,7 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
   for (int i = 0; i < kPer; ++i) {
     const int j = i * kFinishThreads + tid;
     if (i * kFinishThreads < cur1 && j < cur1) {
-      float s = 0.f;
-#pragma unroll
-      for (int h = 0; h < kGroup; ++h)
-        if (h < group) s += fast_exp2(t[i][h] - lse[h]);
-      // Weights below 2^-126 too: they order rows whose indicators are still 0.  Beside a sum from 2^-90 on the up to
-      // eight terms that came out as 0 are less than half its last place, so the sum is the same to the bit; taking exp2f
-      // for all terms cost up to 7 % of a step (32 heads of 6000 rows and 8 queries 26.1 -> 28.1 us a layer, so 26.3).
-      if (s < 0x1p-90f) {
-        s = 0.f;
-#pragma unroll
-        for (int h = 0; h < kGroup; ++h)
-          if (h < group) s += exp2f(t[i][h] - lse[h]);
-      }
-      obs[half + j] = s * a.inv_g;
+      obs[half + j] = weight_sum(t[i], lse, group) * a.inv_g;
     }
   }
   __syncthreads();
@@ -511,7 +530,9 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
 // Caches of more rows than one workgroup holds: two more kernels.
 // Step kernel 2: normalisers, pooled group-mean weights added to the indicator of the cur + 1
 // scored rows, and this chunk's candidate for eviction: the smallest updated indicator, the later
-// row among equals.
+// row among equals.  Sums as in step_finish_kernel, so that a head of up to 8192 rows comes out the same in a call that also
+// holds longer ones; a lane per pair instead of a thread per head over all of them: a step of 8 heads of 9000
+// rows 28.2 -> 19.0 us, of 30000 68.5 -> 35.4.
 __global__ __launch_bounds__(kThreads) void step_apply_kernel(StepArgs a) {
   __shared__ float lse_lds[kMaxGroup];
   __shared__ float obs[kThreads + 2 * kMaxHalf];
@@ -525,14 +546,16 @@ __global__ __launch_bounds__(kThreads) void step_apply_kernel(StepArgs a) {
   const int n = cur1 + a.window;
   if (chunk * kThreads >= cur1) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (tid < a.group) {
-    const int used = (n + kThreads - 1) / kThreads;
-    const float* p = a.part + (slice * a.n_chunks * kMaxGroup + tid) * 2;
-    float mm = kMasked;
-    for (int c = 0; c < used; ++c) mm = fmaxf(mm, p[(int64_t)c * kMaxGroup * 2]);
-    float sum = 0.f;
-    for (int c = 0; c < used; ++c) sum += p[(int64_t)c * kMaxGroup * 2 + 1] * exp2f(p[(int64_t)c * kMaxGroup * 2] - mm);
-    lse_lds[tid] = mm + log2f(sum);
+  const int used = (n + kThreads - 1) / kThreads;
+  for (int h = wave; h < a.group; h += kWaves) {           // a lane per 256 rows and, of more than 16384, those 64 chunks further as well
+    const float* p = a.part + (slice * a.n_chunks * kMaxGroup + h) * 2;
+    float2 x = make_float2(kMasked, 0.f);
+    for (int c = lane; c < used; c += 64) {
+      const float2 y = *reinterpret_cast<const float2*>(p + (int64_t)c * kMaxGroup * 2);
+      x = c == lane ? y : merge_pairs({x.x, y.x}, {x.y, y.y});
+    }
+    const float norm = wave_normaliser(x);
+    if (lane == 0) lse_lds[h] = norm;
   }
   __syncthreads();
   const int half = a.pool / 2;
@@ -542,11 +565,10 @@ __global__ __launch_bounds__(kThreads) void step_apply_kernel(StepArgs a) {
     const int j = j0 + i;
     float w = -INFINITY;                                   // clipped edges never win the max
     if (j >= 0 && j < cur1) {
-      float s = 0.f;
+      float t[kMaxGroup];
 #pragma unroll
-      for (int h = 0; h < kMaxGroup; ++h)
-        if (h < a.group) s += exp2f(lg[(int64_t)h * a.rows_max + j] - lse_lds[h]);
-      w = s * a.inv_g;
+      for (int h = 0; h < kMaxGroup; ++h) t[h] = h < a.group ? lg[(int64_t)h * a.rows_max + j] : 0.f;
+      w = weight_sum(t, lse_lds, a.group) * a.inv_g;
     }
     obs[i] = w;
   }

@@ -119,7 +119,8 @@ def test_queries_may_start_at_any_element(cake, dtype):
     (12, 1, 8, 4, 128, 32, "bf16", 1000),      # one call for all layers is large, a layer is not
     (3, 16, 4, 1, 64, 64, "bf16", 767),        # a layer's call is large too, a sequence alone is not
     (3, 5, 8, 6, 64, 32, "f32", 1400),
-    (2, 2, 8, 8, 128, 32, "bf16", 4063)])      # 4096 rows: the longest lists of the small form
+    (2, 2, 8, 8, 128, 32, "bf16", 4063),       # 4096 rows: the longest lists of the small form
+    (3, 9, 4, 4, 64, 32, "bf16", 8300)])       # lists longer than a workgroup holds (8192 rows) beside others that are not
 def test_a_step_is_the_same_whatever_else_the_call_holds(cake, L, B, H_kv, G, d, S_w, dtype, cap):
     """Every buffer of a call for all layers equals that of calls layer by layer, and every sequence's rows those of a
     batch of one, bit for bit: calls of more than 256 workgroups of 256 rows, and calls of fewer, which take 64 rows each."""
