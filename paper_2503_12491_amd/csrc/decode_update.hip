@@ -308,12 +308,12 @@ __device__ __forceinline__ float weight_sum(const float (&t)[kGroup], const floa
 // heads for every listed row (kept for what follows) and the chunk's (reference, sum) pairs.
 // Bound by the key bytes: four 16-byte loads per row and lane, all of a wave's 64 rows in flight; the
 // one-row-per-thread form on the vector ALU read its queries from LDS once per row and head and reached
-// 1.1 TB/s (12 layers x 4 sequences x 8 heads of 2K rows: 179 -> 40 us, 5.0 TB/s; one layer of 1K rows
-// per head 18 -> 6 us).  A compute unit gets some 35 bytes a nanosecond, so four waves of one stay for 2 us where the rows
-// would fit compute units of their own: small calls run one-wave workgroups (12 layers of 8 heads of 180 to 2900 rows, called
-// one by one: 10.7 -> 10.3 us a layer, of
-// which the host takes 9; 4 layers of 2 heads, 12 queries and 335 rows at once in fp32: 14.7 -> 12.5 us, with the loads of the
-// second kernel that no longer wait for the state).
+// 1.1 TB/s (12 layers x 4 sequences x 8 heads of 2K rows: 179 us; now 50, 4.2 TB/s, or 39 where the keys still lie in the
+// last-level cache from the token before; one layer of 1K rows per head 18 -> 6 us).  A compute unit gets some 35 bytes a nanosecond,
+// so four waves of one stay for 2 us where the rows would fit compute units of their own: small calls run one-wave workgroups
+// (4 layers of 2 heads, 12 queries and 335 rows at once in fp32: 14.7 -> 12.5 us, with the loads of the second kernel that no longer
+// wait for the state).  12 layers of 8 heads of 180 to 2900 rows called one by one gain nothing: the kernels
+// take 4.6 and 5.0 us a layer, and the host as long to launch them.
 template <typename T, int D, int kStepWaves, typename Args>
 __global__ __launch_bounds__(64 * kStepWaves, 4) void step_logits_kernel(Args a) {
   using Dots = RowDots<T, D>;
