@@ -13,7 +13,7 @@ CSRC = os.path.join(PKG, "csrc")
 OBJ_DIR = os.path.join(ROOT, "_build")
 LIB_PATH = os.path.join(PKG, "libcake.so")
 
-SOURCES = ["cake_host.cpp", "window_scores.hip", "select_topk.hip", "compact_kv.hip", "decode_update.hip", "plan_evict.hip",
+SOURCES = ["cake_host.cpp", "window_scores.hip", "scores_stream.hip", "select_topk.hip", "compact_kv.hip", "decode_update.hip", "plan_evict.hip",
            "quantize_kv.hip", "pass_run.hip", "cascade_stage.hip"]
 # the package's host module: Python and torch headers, no device code, linked to libcake.so beside it
 HOST_SRC = os.path.join(CSRC, "host_module.cpp")

@@ -21,101 +21,18 @@
 //   pref    fixed-order fp64 reduction of the per-granule entropy/variance sums    -> P_l, H_l, V_l
 //
 // One workgroup = G wavefronts = one or more granules of keys of one slice; wave w serves query head
-// g*G + w.  K tiles of 64 keys go from global memory straight into LDS (global_load_lds, 16
+// g*G + w (large launches of some group sizes: scores_stream.hip, to the same bits).  K tiles of 64 keys go from global memory straight into LDS (global_load_lds, 16
 // bytes per lane), double-buffered so that tile t+1 is in flight while tile t is consumed, and
 // are shared by the G waves.  Rows are stored unpadded with their 16-byte pieces XOR-swizzled by
 // the row index so that the MFMA operand reads spread over the banks.
 // With the row normalisers supplied by the caller (cake_window_scores_lse) pass 1 and the
 // combine give way to a kernel that converts them to the log2 domain.
 // Everything is deterministic: no float atomics, fixed reduction orders.
-#include <cmath>
-#include <type_traits>
-
 #include "plan_device.h"
+#include "score_device.h"
 
 namespace cake {
 namespace {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(1))) const void* global_cptr;
-typedef __attribute__((address_space(3))) void* lds_ptr;
-
-constexpr int kTileKeys = 64;        // keys staged per LDS tile (two 32-key MFMA sub-tiles)
-constexpr float kMasked = -1.0e30f;  // stands for -inf without producing NaN in differences
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }  // v_exp_f32
-
-template <typename T, int D>
-struct Tile {
-  static constexpr int kRowBytes = D * (int)sizeof(T);
-  static constexpr int kPieces = kRowBytes / 16;         // 16-byte pieces per key row (power of two)
-  static constexpr int kBytes = kTileKeys * kRowBytes;
-  static constexpr int kGroups = kBytes / 1024;          // one wave-wide 1 KiB transfer each
-  // LDS byte offset of piece q of row r: pieces are permuted within the row by r.
-  static __device__ __forceinline__ int offset(int r, int q) { return r * kRowBytes + ((q ^ (r & (kPieces - 1))) << 4); }
-};
-
-// MFMA operand fragments.  For both the A and the B operand of the 32x32 instructions lane
-// (c32, hh) supplies, for its row/column c32, a group of consecutive reduction elements chosen
-// by hh; A and B use the same element order, so the dot products come out complete.
-template <typename T> struct Frag;
-template <> struct Frag<__bf16> {
-  using type = bf16x8;
-  static constexpr int kElems = 16;  // reduction elements per MFMA
-  static __device__ __forceinline__ type load_global(const __bf16* row, int step, int hh) {
-    return *reinterpret_cast<const bf16x8*>(row + step * 16 + hh * 8);
-  }
-  template <typename TL>
-  static __device__ __forceinline__ type load_lds(const char* tile, int r, int step, int hh) {
-    return *reinterpret_cast<const bf16x8*>(tile + TL::offset(r, 2 * step + hh));
-  }
-  static __device__ __forceinline__ f32x16 mfma(type a, type b, f32x16 c) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
-  }
-};
-// Four 32x32x2 products in a row: a lane's share of eight reduction elements is one 16-byte piece, read at once.  (With a
-// 4-byte read per product the addresses of all pieces took 16 to 32 registers: 900 bytes a lane were spilled at two row blocks
-// of 128, and one row block ran two waves per SIMD instead of three.  8 layers of 6000 keys, 8 x 4 heads, 64 rows of 128:
-// pass 1 322 -> 217 us, pass 2 446 -> 223; 32 rows of 64: 69 -> 61 and 74 -> 68; one layer of 1024 keys, 8 x 4 heads, 32 rows of
-// 128: 17 -> 11 and 19 -> 13.)
-template <> struct Frag<float> {
-  using type = f32x4;
-  typedef float loose __attribute__((ext_vector_type(4), aligned(4)));
-  static constexpr int kElems = 8;
-  static __device__ __forceinline__ type load_global(const float* row, int step, int hh) {
-    return *reinterpret_cast<const loose*>(row + step * 8 + hh * 4);
-  }
-  template <typename TL>
-  static __device__ __forceinline__ type load_lds(const char* tile, int r, int step, int hh) {
-    return *reinterpret_cast<const f32x4*>(tile + TL::offset(r, 2 * step + hh));
-  }
-  static __device__ __forceinline__ f32x16 mfma(type a, type b, f32x16 c) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[i], c, 0, 0, 0);
-    return c;
-  }
-};
-
-struct ScoreArgs {
-  const void* const* q_win;
-  const void* const* k;
-  float* const* indicator;
-  LayerPointers one;         // one layer's, where there are no tables
-  int64_t qs[3], ks[3];      // element strides: batch, head, token
-  int32_t batch, h_kv, group, n, n_p, chunk, wg_keys, granule, n_granules, n_granules_p, pool;   // wg_keys: keys per workgroup, granules each
-  int32_t key_lo, key_hi;    // keys [key_lo, key_hi) are behind the k pointers (row 0 = key key_lo); the whole layer: 0, n
-  int32_t key0;              // first key of the first workgroup of a launch
-  int32_t n_slices, pack;    // slices in all; slices that share a workgroup (packed kernels), else 1
-  float c;                   // scale * log2(e): logits are handled in the log2 domain
-  float inv_sw, inv_swc, inv_g;
-  float w_mean, w_var, w_prod;   // I_q = w_mean*Mean + w_var*Var + w_prod*Mean*Var (Eq. 11 and the ablation's variants)
-  float* lse;                // [slice][G*S_w]
-  float* part;               // [slice][n_granules][G*S_w][2]
-  float* hv;                 // [slice][n_granules_p][G][2]
-  float* raw;                // [slice][n_p]
-};
 
 // Transfer of keys [t0, t0+64) of one slice into an LDS tile.  The tile is moved as 1 KiB
 // groups, one wave-wide instruction each, group i by wave i mod G.  Lane j of a group fills LDS
@@ -126,12 +43,6 @@ struct ScoreArgs {
 // once per kernel; per transfer there remain a scalar base, one XOR and one add, and no branch.
 // Rows past the last key are clamped to it (their logits are masked later), so every access
 // stays inside the slice.
-// Cache-policy bits of the tile transfers: non-temporal.  Every key byte is used once per pass
-// and the whole K of a pass is far larger than the caches, so the tiles should not displace the
-// small arrays that are reused (partial sums, normalisers, the un-pooled indicator); measured
-// 5-12 % faster on the 32K-context shapes, neutral at 128K.
-constexpr int kStreamPolicy = 2;
-
 template <typename T, int D>
 struct TileMover {
   using TL = Tile<T, D>;
@@ -170,12 +81,6 @@ struct TileMover {
 
 // All of this wave's outstanding vector-memory operations (the tile transfers) have landed.
 __device__ __forceinline__ void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
-
-__device__ __forceinline__ void slice_coords(const ScoreArgs& a, int slice, int& l, int& b, int& g) {
-  g = slice % a.h_kv;
-  b = (slice / a.h_kv) % a.batch;
-  l = slice / (a.h_kv * a.batch);
-}
 
 template <typename T, int D, int MB>
 __device__ __forceinline__ void load_q(typename Frag<T>::type (&qf)[MB][D / Frag<T>::kElems], const T* q,
@@ -219,13 +124,6 @@ __device__ __forceinline__ void pass1_logits(const char* tile, int sub,
 // The finished logits of a sub-tile (first key kb) folded into the rows' running
 // (reference, sum) pairs.  Key j is visible to window row r iff j <= n_p + r (and j < n);
 // kTail: some key of the sub-tile may be hidden or lie past the end.
-// A row starts from reference 0 and keeps it while its sum stays within 2^-24 .. 2^24, as it does in most
-// layers.  Outside (a logit outran the reference, all of them lie far below it, inf or NaN) the block is redone with
-// a reference of its own.  The bounds are narrow because an exponent is rounded at its distance from the
-// reference: with 2^-60 .. 2^100 rows whose largest logit exceeds some 35 (log2 units) got normalisers up to a quarter
-// further off than with references of their own from the first block on (2.85e-6 rms against 2.40e-6 at 72; 2.22e-6
-// with these bounds, which nowhere between logits of 2 and 92 are worse).
-constexpr uint32_t kSumLow = (127u - 24u) << 23, kSumHigh = (127u + 24u) << 23;      // the two bounds as float bits
 template <int MB, bool kTail>
 __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, float (&mref)[MB], float (&lsum)[MB],
                                            float cv, int n, int n_p, int c32, int hh) {
@@ -240,72 +138,23 @@ __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, floa
       if (v < 2) bsum[v] = e;
       else bsum[v & 1] += e;
     }
-    float sum = lsum[nb] + (bsum[0] + bsum[1]);
-    if (__float_as_uint(sum) - kSumLow > kSumHigh - kSumLow) {
-      float rmax = kMasked;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) rmax = fmaxf(rmax, hidden(v) ? kMasked : acc[nb][v] * cv);
-      if (rmax > kMasked) {               // (no key of the block is visible: nothing to refer to)
-        // the earlier terms, a half wave's share of a granule, are at most 2^10: some of them are as large as their
-        // sum by that, which the block's own largest logit need not be
-        if (lsum[nb] != 0.f) rmax = fmaxf(rmax, mref[nb] + (float)(__builtin_amdgcn_frexp_expf(lsum[nb]) - 10));
-        sum = lsum[nb] == 0.f ? 0.f : lsum[nb] * fast_exp2(mref[nb] - rmax);      // (0 * 2^(mref - rmax) would be NaN from 2^128 on)
-        mref[nb] = rmax;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) sum += hidden(v) ? 0.f : fast_exp2(fmaf(acc[nb][v], cv, -rmax));      // not from the rounded products
-      } else {
-        sum = lsum[nb];
-      }
-    }
-    lsum[nb] = sum;
+    add_block_sum(acc[nb], bsum[0] + bsum[1], mref[nb], lsum[nb], cv, hidden);
   }
 }
 
-// Packed kernels (kPack): a.pack slices share a workgroup, G waves each, every slice with its own
-// tile buffers.  A workgroup's waves are dealt over the compute unit's four SIMDs in turn, so a
-// group of 5 or 6 heads alone leaves two waves on one SIMD and one on the others, and the
-// barriers make every wave wait for the doubled SIMD; three slices of 5 waves (or two of 6) fill
-// the SIMDs almost evenly.  Slices past the last one (the final workgroup) repeat the last
-// slice's work and store nothing.
-extern __shared__ __attribute__((aligned(1024))) char packed_lds[];
-
-struct WaveRole {
-  int slice, w;      // the wave's slice and its head within the group
-  int first_wave;    // index of the slice's first wave in the workgroup
-  bool live;         // false: a repeat of the last slice, stores nothing
-};
-template <bool kPack>
-__device__ __forceinline__ WaveRole wave_role(const ScoreArgs& a) {
-  const int w_all = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave index, known uniform
-  WaveRole r;
-  if (kPack) {
-    const int hg = w_all / a.group;
-    const int slice = blockIdx.y * a.pack + hg;
-    r.live = slice < a.n_slices;
-    r.slice = min(slice, a.n_slices - 1);
-    r.first_wave = hg * a.group;
-    r.w = w_all - r.first_wave;
-  } else {
-    r.slice = blockIdx.y; r.w = w_all; r.first_wave = 0; r.live = true;
-  }
-  return r;
-}
-
-template <typename T, int D, int MB, bool kPack>
-__global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass1(ScoreArgs a) {
+template <typename T, int D, int MB>
+__global__ __launch_bounds__(512) void scores_pass1(ScoreArgs a) {
   using F = Frag<T>;
   using TL = Tile<T, D>;
   constexpr int kSteps = D / F::kElems;
   // double buffer: tile t+1 is in flight while tile t is consumed (rings of three and four tiles
-  // measured no faster, and 4 % slower in the packed kernels)
-  __shared__ __attribute__((aligned(1024))) char own_tiles[kPack ? 1024 : 2 * TL::kBytes];
+  // measured no faster, with waits for the oldest tile alone as well)
+  __shared__ __attribute__((aligned(1024))) char tiles[2 * TL::kBytes];
 
-  const WaveRole role = wave_role<kPack>(a);
-  const int slice = role.slice;
+  const int slice = blockIdx.y;
   int l, b, g;
   slice_coords(a, slice, l, b, g);
-  const int w = role.w;
-  char* tiles = kPack ? packed_lds + (role.first_wave / a.group) * (2 * TL::kBytes) : own_tiles;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);       // wave index, known uniform
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
@@ -343,14 +192,8 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass1(ScoreArgs a) 
     float* o = out + (int64_t)((key0 + t * kTileKeys) >> granule_shift) * (a.group * s_w) * 2;
 #pragma unroll
     for (int nb = 0; nb < MB; ++nb) {
-      // both halves' values in every lane: the lower half's first
-      // (a half that has seen no key is masked: its reference 0 may lie far above the row's logits)
-      const uint32_t ref = __float_as_uint(lsum[nb] == 0.f ? kMasked : mref[nb]);
-      const auto rm = __builtin_amdgcn_permlane32_swap(ref, ref, false, false);
-      const auto rl = __builtin_amdgcn_permlane32_swap(__float_as_uint(lsum[nb]), __float_as_uint(lsum[nb]), false, false);
-      const float m0 = __uint_as_float(rm[0]), m1 = __uint_as_float(rm[1]), m = fmaxf(m0, m1);
-      const float s = __uint_as_float(rl[0]) * fast_exp2(m0 - m) + __uint_as_float(rl[1]) * fast_exp2(m1 - m);
-      if (hh == 0 && role.live) *reinterpret_cast<float2*>(o + (nb * 32 + c32) * 2) = make_float2(m, s);
+      const float2 pair = merge_halves(mref[nb], lsum[nb]);
+      if (hh == 0) *reinterpret_cast<float2*>(o + (nb * 32 + c32) * 2) = pair;
       mref[nb] = 0.f;
       lsum[nb] = 0.f;
     }
@@ -537,12 +380,6 @@ __global__ void scores_import_lse(ScoreArgs a, const float* const* row_lse, int6
 // ------------------------------------------------------------------------------------------
 // Pass 2: normalised weights on the prefix columns; column Mean/Var, entropy, group mean.
 // ------------------------------------------------------------------------------------------
-// Column sums of one finished sub-tile, still split over the two lane halves.
-struct ColSums {
-  float sp, sp2;     // sum of (p - pivot), sum of (p - pivot)^2 over this half's window rows
-  float pivot;       // 0 unless the pivoted form is used
-};
-
 // One period of pass 2.  kMfma: the MFMAs of sub-tile `sub` of `tile` accumulate into `dst`,
 // starting from `init`, which holds -lse2/c of the lane's window rows, so that the accumulator
 // times c is already the log2 of the weight.  kValu: the finished accumulators in `src` are
@@ -614,50 +451,27 @@ __device__ __forceinline__ void pass2_period(const char* tile, int sub,
   }
 }
 
-// Statistics of the 64 key columns of one tile from the half sums of its two sub-tiles.  One
-// swap of lane halves per quantity leaves lanes 0-31 with the complete sums of sub-tile 0's
-// columns and lanes 32-63 with those of sub-tile 1's: lane L ends up owning key L of the tile.
-template <bool kPivot>
-__device__ __forceinline__ void pass2_tile_stats(const ColSums& s0, const ColSums& s1, const ScoreArgs& a, int hh,
-                                                 float& var_acc, float* iq_row /* [64], this wave's */, int lane) {
-  auto r1 = __builtin_amdgcn_permlane32_swap(__float_as_uint(s0.sp), __float_as_uint(s1.sp), false, false);
-  auto r2 = __builtin_amdgcn_permlane32_swap(__float_as_uint(s0.sp2), __float_as_uint(s1.sp2), false, false);
-  const float sp = __uint_as_float(r1[0]) + __uint_as_float(r1[1]);
-  const float sp2 = __uint_as_float(r2[0]) + __uint_as_float(r2[1]);
-  const float dmean = sp * a.inv_sw;                               // mean of (p - pivot)
-  const float var = fmaxf((sp2 - sp * dmean) * a.inv_swc, 0.f);    // the variance does not see the pivot
-  const float mean = kPivot ? dmean + (hh ? s1.pivot : s0.pivot) : dmean;
-  var_acc += var;
-  iq_row[lane] = fmaf(a.w_prod * mean, var, fmaf(a.w_var, var, a.w_mean * mean));
-}
-
-constexpr int kPackMaxWaves = 16;      // waves of a packed workgroup
 // Pass 2 comes with and without the code to combine the pairs of pass 1 by itself (kCombine).  The software-pipelined form has
 // it for a workgroup per compute unit only (its registers are full): 8192 keys of one layer, 8 x 4 heads, scores of 64 rows
 // 32.4 -> 29.7 us with it, 512 workgroups of 8 layers of 1000 keys 32.9 -> 33.9.
 template <typename T, int MB> constexpr bool kPipelinedForm = sizeof(T) == 2 && MB == 2;
 
-template <typename T, int D, int MB, bool kPivot, bool kPack, bool kCombine>
-__global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) {
+template <typename T, int D, int MB, bool kPivot, bool kCombine>
+__global__ __launch_bounds__(512) void scores_pass2(ScoreArgs a) {
   using F = Frag<T>;
   using TL = Tile<T, D>;
   constexpr int kSteps = D / F::kElems;
   // double buffer: tile t+1 is in flight while tile t is consumed (deeper rings measured no faster)
-  __shared__ __attribute__((aligned(1024))) char own_tiles[kPack ? 1024 : 2 * TL::kBytes];
+  __shared__ __attribute__((aligned(1024))) char tiles[2 * TL::kBytes];
   // I_q of the G heads for two tiles in turn: the flush of one tile reads one buffer in the
   // stage in which the other is written, and a barrier separates the stages
-  __shared__ float own_iq[kPack ? 1 : 2 * 8 * kTileKeys];
+  __shared__ float iq_lds[2][8][kTileKeys];
 
-  const WaveRole role = wave_role<kPack>(a);
-  const int slice = role.slice;
+  const int slice = blockIdx.y;
   int l, b, g;
   slice_coords(a, slice, l, b, g);
-  const int w = role.w;
-  char* tiles = kPack ? packed_lds + (role.first_wave / a.group) * (2 * TL::kBytes) : own_tiles;
-  constexpr int kIqWaves = kPack ? kPackMaxWaves : 8;
-  // [2][kIqWaves][64]; the packed kernels keep it behind the slices' tile buffers
-  float* iq_lds = kPack ? reinterpret_cast<float*>(packed_lds + a.pack * (2 * TL::kBytes)) : own_iq;
-  auto iq_row = [&](int buf, int wave) { return iq_lds + (buf * kIqWaves + role.first_wave + wave) * kTileKeys; };
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);       // wave index, known uniform
+  auto iq_row = [&](int buf, int wave) { return iq_lds[buf][wave]; };
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
@@ -723,14 +537,14 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
     const int key = key0 + t * kTileKeys + lane;
     float s = 0.f;
     for (int ww = 0; ww < a.group; ++ww) s += iq_row(t & 1, ww)[lane];
-    if (key < key_end && role.live) raw[key] = s * a.inv_g;
+    if (key < key_end) raw[key] = s * a.inv_g;
   };
   // Entropy and variance sums of the granule that ends with tile t.
   const int granule_shift = __builtin_ctz(a.granule), granule_tiles = a.granule / kTileKeys;      // powers of two
   auto finish = [&](int t) {
     const float ent = wave_sum((entv[0] + entv[1]) * cv), var = wave_sum(var_acc);
     const int64_t granule = (key0 + t * kTileKeys) >> granule_shift;
-    if (lane == 0 && role.live)
+    if (lane == 0)
       *reinterpret_cast<float2*>(a.hv + (((int64_t)slice * a.n_granules_p + granule) * a.group + w) * 2) = make_float2(ent, var);
     entv[0] = entv[1] = var_acc = 0.f;
   };
@@ -757,7 +571,7 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
       } else {
         // statistics of tile t-1's second sub-tile: never a tail, tile t-1 is not the last
         pass2_period<T, D, MB, true, true, false, kPivot>(cur, 0, qf, init, acc_a, acc_b, cv, true, entv, cs1, c32, hh);
-        pass2_tile_stats<kPivot>(cs0, cs1, a, hh, var_acc, iq_row((t - 1) & 1, w), lane);
+        iq_row((t - 1) & 1, w)[lane] = pass2_tile_stats<kPivot>(cs0, cs1, a, hh, var_acc);
         if (kSlot == 0 && (t & (granule_tiles - 1)) == 0) finish(t - 1);      // granules of S_w = 64 are an even number of tiles
       }
       pass2_period<T, D, MB, true, true, kTail, kPivot>(cur, 1, qf, init, acc_b, acc_a, cv, v0, entv, cs0, c32, hh);
@@ -766,7 +580,7 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
       pass2_period<T, D, MB, false, true, kTail, kPivot>(cur, 0, qf, init, acc_a, acc_a, cv, v0, entv, cs0, c32, hh);
       pass2_period<T, D, MB, true, false, false, kPivot>(cur, 1, qf, init, acc_a, acc_a, cv, true, entv, cs1, c32, hh);
       pass2_period<T, D, MB, false, true, kTail, kPivot>(cur, 1, qf, init, acc_a, acc_a, cv, v1, entv, cs1, c32, hh);
-      pass2_tile_stats<kPivot>(cs0, cs1, a, hh, var_acc, iq_row(t & 1, w), lane);
+      iq_row(t & 1, w)[lane] = pass2_tile_stats<kPivot>(cs0, cs1, a, hh, var_acc);
       if (((t + 1) & (granule_tiles - 1)) == 0 || t + 1 == n_tiles) finish(t);
     }
   };
@@ -789,7 +603,7 @@ __global__ __launch_bounds__(kPack ? 1024 : 512) void scores_pass2(ScoreArgs a) 
       pass2_period<T, D, MB, false, true, true, kPivot>(tiles, 0, qf, init, acc_a, acc_b, cv, v1, entv, cs1, c32, hh);
     else
       pass2_period<T, D, MB, false, true, false, kPivot>(tiles, 0, qf, init, acc_a, acc_b, cv, true, entv, cs1, c32, hh);
-    pass2_tile_stats<kPivot>(cs0, cs1, a, hh, var_acc, iq_row((n_tiles - 1) & 1, w), lane);
+    iq_row((n_tiles - 1) & 1, w)[lane] = pass2_tile_stats<kPivot>(cs0, cs1, a, hh, var_acc);
     finish(n_tiles - 1);
   }
   __syncthreads();
@@ -1015,30 +829,12 @@ inline void mark(int i, hipStream_t stream) {
 // four steps of the segment-wise form (keys handed over a range at a time).
 enum ScoreParts { kPartsAll, kPartsPass1Segment, kPartsCombine, kPartsPass2Segment, kPartsPool };
 
-// Slices per workgroup: group sizes whose waves would load the four SIMDs unevenly share a
-// workgroup (3 x 5 or 2 x 6 waves).  Only the kernels that fit 16 waves on a compute unit
-// (bf16, one row block) have a packed form.
-template <typename T, int MB>
-constexpr bool can_pack() { return sizeof(T) == 2 && MB == 1; }
-inline int slices_per_workgroup(int group) { return group == 5 ? 3 : group == 6 ? 2 : 1; }
-
 template <typename T, int D, int MB, bool kPivot>
 int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* row_lse, ScoreParts parts, const PrefArgs* pref,
                   const PlanArgs* plan, hipStream_t stream) {
   ScoreArgs a = a_in;
-  const bool packing = a_in.pack > 1;
-  dim3 block;
-  unsigned gy;
-  size_t packed_bytes;
-  // A launch of few workgroups of one granule each packs none: its slices' chunks on compute units of their own are done
-  // sooner (one layer of 8192 keys, 8 x 5 heads of 128: pass 1 16.0 -> 12.4 us, pass 2 27 -> 17.6; of 16384 37 -> 27 and 50 -> 35).
-  auto set_pack = [&](int lo, int hi) {
-    const bool few = n_slices * ((hi - lo + a_in.granule - 1) / a_in.granule) <= 512;
-    a.pack = packing && !few ? slices_per_workgroup(a.group) : 1;
-    block = dim3(64 * a.group * a.pack);
-    gy = (unsigned)((n_slices + a.pack - 1) / a.pack);
-    packed_bytes = a.pack > 1 ? (size_t)a.pack * 2 * Tile<T, D>::kBytes + sizeof(float) * 2 * kPackMaxWaves * kTileKeys : 0;
-  };
+  const dim3 block(64 * a.group);
+  const unsigned gy = (unsigned)n_slices;
   // Keys per workgroup: the chunk's granules, or a half or quarter of them where that shortens the rounds of workgroups
   // over the chip.  A workgroup's prologue (its queries, the first tile's way from memory) counts as a tile of keys.  A
   // compute unit holds as many workgroups as LDS and the registers of the pass allow; those of five and more heads of 64
@@ -1055,7 +851,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     constexpr int kWaves2 = kWide ? 2 : kF32 ? (kSmall ? 4 : 3) : (kSmall ? 5 : 4);      // waves per SIMD
     constexpr int kLds = 2 * Tile<T, D>::kBytes + (int)sizeof(float) * 2 * 8 * kTileKeys;
     const int by_waves = 4 * (pass == 1 ? kWaves1 : kWaves2) / a.group;
-    const bool alone = a.pack > 1 || a.group > (kF32 ? (kSmall && !kWide ? 5 : 2) : kWide ? 4 : 8);
+    const bool alone = a.group > (kF32 ? (kSmall && !kWide ? 5 : 2) : kWide ? 4 : 8);
     const int64_t slots = 256 * (alone ? 1 : std::max(1, std::min(160 * 1024 / kLds, by_waves)));
     int64_t least = INT64_MAX;
     int best = 1;
@@ -1072,27 +868,34 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     a.wg_keys = best * a.granule;
     return (unsigned)((hi - lo + a.wg_keys - 1) / a.wg_keys);
   };
-  auto run = [&](auto kern, unsigned chunks) -> hipError_t {
-    if (packed_bytes > 0)
-      if (hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                             (int)packed_bytes); e != hipSuccess) return e;
-    hipLaunchKernelGGL(kern, dim3(chunks, gy), block, packed_bytes, stream, a);
-    return hipSuccess;
+  // Launches with enough keys for each of the 2048 waves that the chip holds of them take the streaming kernels (stream_min_keys),
+  // a whole number of granules a wave, at most 4096 keys: as many as leave the fewest keys in the longest place, where a
+  // workgroup's prologue counts as 96.  (4 x 5 heads of 32749 keys, 16 layers: 830 + 1010 us with 1024 or 2048 keys a wave,
+  // 815 + 980 with 4096, 825 + 1010 with 8192 in a single round.)
+  auto set_stream = [&](int pass, int lo, int hi) -> unsigned {
+    const int waves = sizeof(T) == 2 ? stream_waves(pass, D, MB, a.group) : 0;
+    if (waves == 0 || n_slices * (hi - lo) < 2048 * (int64_t)stream_min_keys(MB, a.group)) return 0;
+    const int64_t granules = (hi - lo + a.granule - 1) / a.granule, slots = 2048 / std::max(waves, 1);
+    int64_t least = INT64_MAX, best = 1;
+    for (int64_t per = 1; per <= granules && per * a.granule <= 4096; ++per) {
+      const int64_t workgroups = n_slices * ((granules + waves * per - 1) / (waves * per));
+      const int64_t cost = (workgroups + slots - 1) / slots * (per * a.granule + 96);
+      if (cost < least) { least = cost; best = per; }
+    }
+    a.key0 = lo;
+    a.wg_keys = (int)(best * a.granule);
+    return (unsigned)((granules + waves * best - 1) / (waves * best));
   };
-  auto run_pass1 = [&](int lo, int hi) -> hipError_t {
-    set_pack(lo, hi);
+  auto run_pass1 = [&](int lo, int hi) {
+    if (const unsigned gx = set_stream(1, lo, hi)) return launch_stream_pass1(a, D, MB, gx, stream);
     const unsigned chunks = set_span(1, lo, hi);
-    if constexpr (can_pack<T, MB>())
-      if (a.pack > 1) return run(scores_pass1<T, D, MB, true>, chunks);
-    return run(scores_pass1<T, D, MB, false>, chunks);
+    hipLaunchKernelGGL((scores_pass1<T, D, MB>), dim3(chunks, gy), block, 0, stream, a);
   };
-  auto run_pass2 = [&](int lo, int hi, bool combine) -> hipError_t {
-    set_pack(lo, hi);
+  auto run_pass2 = [&](int lo, int hi, bool combine) {
+    if (const unsigned gx = set_stream(2, lo, hi)) return launch_stream_pass2(a, D, MB, kPivot, gx, stream);
     const unsigned chunks = set_span(2, lo, hi);
-    if constexpr (can_pack<T, MB>())
-      if (a.pack > 1) return run(scores_pass2<T, D, MB, kPivot, true, false>, chunks);
-    if (combine) return run(scores_pass2<T, D, MB, kPivot, false, true>, chunks);
-    return run(scores_pass2<T, D, MB, kPivot, false, false>, chunks);
+    if (combine) hipLaunchKernelGGL((scores_pass2<T, D, MB, kPivot, true>), dim3(chunks, gy), block, 0, stream, a);
+    else hipLaunchKernelGGL((scores_pass2<T, D, MB, kPivot, false>), dim3(chunks, gy), block, 0, stream, a);
   };
   const int rows = a.group * MB * 32;
   const int64_t total_rows = n_slices * rows;
@@ -1100,11 +903,11 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     // the keys of this launch: those of [key_lo, key_hi) (pass 2: below n_p as well)
     const int hi1 = min(a.n, a.key_hi), hi2 = min(a.n_p, a.key_hi);
     if (parts == kPartsPass1Segment)
-      CAKE_HIP_TRY(run_pass1(a.key_lo, hi1));
+      run_pass1(a.key_lo, hi1);
     else if (parts == kPartsCombine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
     else if (parts == kPartsPass2Segment && hi2 > a.key_lo)
-      CAKE_HIP_TRY(run_pass2(a.key_lo, hi2, false));
+      run_pass2(a.key_lo, hi2, false);
     else if (parts == kPartsPool)
       hipLaunchKernelGGL(pool_indicator<false>, dim3((a.n_p + kPoolSpan - 1) / kPoolSpan, (unsigned)n_slices), dim3(256), 0,
                          stream, a, PrefArgs{}, 0);
@@ -1114,12 +917,11 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   mark(0, stream);
   bool combine = false;
   if (row_lse == nullptr && a.one.row_lse == nullptr) {
-    CAKE_HIP_TRY(run_pass1(0, a.n));
+    run_pass1(0, a.n);
     mark(1, stream);
     // every workgroup of pass 2 reads its slice's pairs where it combines them itself: at most 16 MB in all
-    set_pack(0, a.n_p);
     const int64_t workgroups = (int64_t)gy * set_span(2, 0, a.n_p);
-    combine = a.pack == 1 && workgroups * rows * a.n_granules * 8 <= 16 << 20 && (!kPipelinedForm<T, MB> || workgroups <= 256);
+    combine = !set_stream(2, 0, a.n_p) && workgroups * rows * a.n_granules * 8 <= 16 << 20 && (!kPipelinedForm<T, MB> || workgroups <= 256);
     if (!combine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
   } else {
@@ -1129,7 +931,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     mark(1, stream);
   }
   mark(2, stream);
-  CAKE_HIP_TRY(run_pass2(0, a.n_p, combine));
+  run_pass2(0, a.n_p, combine);
   mark(3, stream);
   const unsigned spans = (a.n_p + kPoolSpan - 1) / kPoolSpan;
   const unsigned pref_rows = pref ? (pref->n_layers * pref->batch + spans - 1) / spans : 0;
@@ -1243,7 +1045,6 @@ int window_scores_impl(const cake_shape* shape, const cake_params* params,
   a.chunk = lay.chunk; a.granule = lay.granule; a.n_granules = lay.n_granules; a.n_granules_p = lay.n_granules_p; a.pool = params->pool_kernel;
   a.key_lo = 0; a.key_hi = a.n;
   a.n_slices = (int32_t)lay.n_slices;
-  a.pack = (shape->dtype == CAKE_BF16 && shape->window == 32) ? slices_per_workgroup(a.group) : 1;
   if (parts == kPartsPass1Segment || parts == kPartsPass2Segment) {
     CAKE_REQUIRE(key_begin >= 0 && key_count > 0 && (int64_t)key_begin + key_count <= a.n,
                  "segment [%d, %d + %d) outside [0, seq_len = %d)", key_begin, key_begin, key_count, a.n);

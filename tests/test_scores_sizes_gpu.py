@@ -1,5 +1,5 @@
 """The score passes at the sizes where their forms change: element types and row blocks, and launches of a few
-workgroups (which combine pass 1's pairs inside pass 2 and pack no slices) against launches of many."""
+workgroups (which combine pass 1's pairs inside pass 2) against launches of many (some of which stream)."""
 import pytest
 import torch
 
@@ -45,8 +45,8 @@ def _combines(slices, dtype, window, group, n):
     granules a workgroup takes (one at least, a chunk at most)."""
     chunk, granule = _granules(n, window)
     n_p = n - window
-    if dtype == torch.bfloat16 and window == 32 and group in (5, 6) and slices * -(-n_p // granule) > 512:
-        return False                               # packed workgroups do not
+    if dtype == torch.bfloat16 and window == 32 and group in (5, 6) and slices * n_p >= 2048 * 256:
+        return False                               # waves that stream do not
     pairs = group * window * -(-n // granule) * 8
     piped = dtype == torch.bfloat16 and window == 64
     fits = lambda workgroups: workgroups * pairs <= 16 << 20 and (not piped or workgroups <= 256)
@@ -57,7 +57,7 @@ def _combines(slices, dtype, window, group, n):
 @pytest.mark.parametrize("peak", [1.0, 12.0])      # references all 0; references of their own
 @pytest.mark.parametrize("dtype,window,group,d,n,layers", [
     (torch.bfloat16, 32, 4, 128, 160, 700),        # 3 granules of 64
-    (torch.bfloat16, 32, 5, 64, 32 * 64, 160),     # 8 granules of 256, packed where there are many
+    (torch.bfloat16, 32, 5, 64, 32 * 64, 160),     # 8 granules of 256, streaming where there are many
     (torch.bfloat16, 32, 6, 128, 33 * 256 - 7, 60),    # 33 granules: one more than a sweep of the pairs
     (torch.bfloat16, 32, 1, 128, 8192, 70),        # 32 granules: one sweep
     (torch.bfloat16, 64, 4, 128, 31 * 256 + 1, 64),    # 32 granules of the software-pipelined form, one key in the last
@@ -82,3 +82,52 @@ def test_a_layer_alone_scores_to_the_same_bits_as_among_many(dtype, window, grou
         assert torch.equal(alone.indicator[0], many.indicator[l])
         assert torch.equal(alone.indicator[0], many.indicator[l + 2 * ((layers - 1 - l) // 2)])
         assert torch.equal(alone.hv[0, 0], many.hv[0, l]) and torch.equal(alone.pref[0, 0], many.pref[0, l])
+
+
+@pytest.mark.parametrize("mode", [0, 2])            # sums of the weights; about a pivot
+@pytest.mark.parametrize("window,group,d,n,layers", [
+    (32, 4, 128, 1000, 545),       # 8 x 545 x 968 keys: where groups of four begin to stream
+    (32, 5, 128, 32 + 97, 1010),   # a tile with one key in its second half, keys past the prefix in the same one
+    (32, 5, 128, 4093, 34),        # whole granules of 256 and a ragged one
+    (32, 6, 128, 16384 + 31, 6),   # granules of 1024
+    (32, 5, 64, 193, 700),
+    (32, 6, 64, 2048, 66),
+    (64, 3, 128, 2100, 70),        # pass 2 alone streams
+    (64, 4, 64, 193 + 64, 820),
+])
+def test_waves_that_stream_give_the_bits_of_a_layer_alone(window, group, d, n, layers, mode):
+    """Launches beyond the line of the streaming kernels against one layer, which is below it."""
+    cake = load_cake()
+    say(f"streaming scores S_w={window} G={group} d={d} N={n} layers={layers} mode={mode}")
+    h_kv, n_p = 8, n - window
+    line = 2048 * (512 if window == 64 else 2048 if group == 4 else 256)
+    assert h_kv * n < line <= h_kv * layers * n_p
+    q, k, v = _inputs(2, h_kv * group, h_kv, d, n, window, torch.bfloat16, n + group, 6.0)
+    params = cake.make_params(indicator_mode=mode)
+    many = cake.EvictionPass([q[i % 2] for i in range(layers)], [k[i % 2] for i in range(layers)], [v[i % 2] for i in range(layers)],
+                             layers * window, params)
+    many.scores()
+    for l in range(2):
+        alone = cake.EvictionPass(q[l:l + 1], k[l:l + 1], v[l:l + 1], window, params)
+        alone.scores()
+        assert torch.equal(alone.indicator[0], many.indicator[l])
+        assert torch.equal(alone.indicator[0], many.indicator[l + 2 * ((layers - 1 - l) // 2)])
+        assert torch.equal(alone.hv[0, 0], many.hv[0, l]) and torch.equal(alone.pref[0, 0], many.pref[0, l])
+
+
+def test_streamed_segments_give_the_bits_of_the_resident_call():
+    """Key segments long enough to stream, against the whole layer at once."""
+    cake = load_cake()
+    layers, h_kv, group, d, n, window = 16, 8, 5, 128, 3 * 8192 + 77, 32
+    say(f"streamed segments {layers} layers of {n} keys")
+    q, k, v = _inputs(1, h_kv * group, h_kv, d, n, window, torch.bfloat16, 5, 3.0)
+    ev = cake.EvictionPass(q * layers, k * layers, v * layers, layers * window)
+    assert layers * h_kv * 8192 >= 2048 * 256
+    ev.scores()
+    torch.cuda.synchronize()
+    want, want_hv = ev.indicator.clone(), ev.hv.clone()
+    ev.workspace.fill_(0xFF)
+    ev.indicator.fill_(float("nan"))
+    ev.scores_segmented(8192)
+    torch.cuda.synchronize()
+    assert torch.equal(ev.indicator, want) and torch.equal(ev.hv, want_hv)
