@@ -33,10 +33,10 @@ __global__ __launch_bounds__(kThreads) void renew_lists(StageArgs a) {
   const int cur = a.plan.cur_len[e], keep = a.plan.keep[e];
   if ((int)(blockIdx.z * kThreads) > keep) return;
   const int64_t at = (int64_t)head * a.plan.cap_keep[l];
-  const int32_t* idx = static_cast<const int32_t*>(a.plan.idx[l]) + at;
-  float* ind_out = static_cast<float*>(a.plan.ind_out[l]) + at;
+  const int32_t* idx = in_global(static_cast<const int32_t*>(a.plan.idx[l])) + at;
+  float* ind_out = in_global(static_cast<float*>(a.plan.ind_out[l])) + at;
   const int64_t from = (int64_t)head * a.plan.cap_cur[l];
-  const float* ind_in = static_cast<const float*>(a.held[l]) + from;
+  const float* ind_in = in_global(static_cast<const float*>(a.held[l])) + from;
   const int32_t* old = a.slots_old + (reinterpret_cast<const char*>(ind_in) - a.ind_old) / 4;
   int32_t* renewed = a.slots_new + (reinterpret_cast<const char*>(ind_out) - a.ind_new) / 4;
   if (keep == cur) {
@@ -88,9 +88,9 @@ __global__ __launch_bounds__(kThreads) void fill_rows(StageArgs a, const char* k
   if ((int64_t)blockIdx.x * kThreads * kUnroll >= total) return;
   const int32_t top = a.prefix_rows - rows_before(a, a.m, b, false, threadIdx.x & 63);
   const int64_t at = (int64_t)head * a.plan.cap_keep[a.m];
-  const int32_t* idx = static_cast<const int32_t*>(a.plan.idx[a.m]) + at;
+  const int32_t* idx = in_global(static_cast<const int32_t*>(a.plan.idx[a.m])) + at;
   const float* ind_in = a.ind + (int64_t)head * a.plan.cap_cur[a.m];
-  float* ind_out = static_cast<float*>(a.plan.ind_out[a.m]) + at;
+  float* ind_out = in_global(static_cast<float*>(a.plan.ind_out[a.m])) + at;
   int32_t* slots = a.slots_new + (static_cast<const char*>(a.plan.ind_out[a.m]) - a.ind_new) / 4 + at;
   const int32_t* freed = a.free_slots + (int64_t)head * a.prefix_rows;
   const char* kin = k + b * s0 + h * s1;

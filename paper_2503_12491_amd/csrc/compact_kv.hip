@@ -109,11 +109,11 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
   const int64_t in_row = s2 * a.elem_bytes;
   const int64_t out_row = (int64_t)a.pieces * 16;
   const int64_t out_off = ((int64_t)b * a.h_kv + h) * (cap_keep + a.window) * out_row;
-  const char* kin = static_cast<const char*>(a.k_in[ll]) + in_off;
-  const char* vin = static_cast<const char*>(a.v_in[ll]) + in_off;
-  char* kout = static_cast<char*>(a.k_out[ll]) + out_off;
-  char* vout = static_cast<char*>(a.v_out[ll]) + out_off;
-  const int32_t* idx = a.idx[ll] + ((int64_t)b * a.h_kv + h) * cap_keep;
+  const char* kin = in_global(static_cast<const char*>(a.k_in[ll])) + in_off;
+  const char* vin = in_global(static_cast<const char*>(a.v_in[ll])) + in_off;
+  char* kout = in_global(static_cast<char*>(a.k_out[ll])) + out_off;
+  char* vout = in_global(static_cast<char*>(a.v_out[ll])) + out_off;
+  const int32_t* idx = in_global(a.idx[ll]) + ((int64_t)b * a.h_kv + h) * cap_keep;
 
   if (first >= total) { if (kPlanned) continue; else return; }
   uint4 kv[kUnroll], vv[kUnroll];
@@ -146,10 +146,10 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
   // per layer and stage took a session of 16 layers of 6K keys two launches each.
   if (a.ind_in != nullptr) {
     const int64_t head = (int64_t)b * a.h_kv + h;
-    const float* iin = a.ind_in[ll] + head * cap_cur;
-    float* iout = a.ind_out[ll] + head * cap_keep;
-    const int32_t* pin = a.pos_out != nullptr ? a.pos_in[ll] : nullptr;
-    int32_t* pout = a.pos_out != nullptr ? a.pos_out[ll] + head * cap_keep : nullptr;
+    const float* iin = in_global(a.ind_in[ll]) + head * cap_cur;
+    float* iout = in_global(a.ind_out[ll]) + head * cap_keep;
+    const int32_t* pin = a.pos_out != nullptr ? in_global(a.pos_in[ll]) : nullptr;
+    int32_t* pout = a.pos_out != nullptr ? in_global(a.pos_out[ll]) + head * cap_keep : nullptr;
     if (pin != nullptr) pin += head * cap_cur;
     const int64_t r0 = first / a.pieces;                               // rows this block touches
     const int64_t r1 = min((first + kThreads * kUnroll + a.pieces - 1) / a.pieces, (int64_t)keep);

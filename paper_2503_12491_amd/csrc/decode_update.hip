@@ -93,8 +93,8 @@ __global__ __launch_bounds__(kThreads) void decode_partials_kernel(DecodeArgs a,
   const int n = dims.cur_len[ll * a.batch + b] + a.window;       // rows the new query sees
   if (chunk * kThreads >= n) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const T* q = reinterpret_cast<const T*>(a.q_new[ll]) + b * a.qs[0] + (int64_t)(g * a.group) * a.qs[1];
-  const T* k = reinterpret_cast<const T*>(a.k_cache[ll]) + b * ks.s[ll][0] + g * ks.s[ll][1];
+  const T* q = in_global(reinterpret_cast<const T*>(a.q_new[ll])) + b * a.qs[0] + (int64_t)(g * a.group) * a.qs[1];
+  const T* k = in_global(reinterpret_cast<const T*>(a.k_cache[ll])) + b * ks.s[ll][0] + g * ks.s[ll][1];
   for (int i = tid; i < a.group * D; i += kThreads) q_lds[i] = (float)q[(i / D) * a.qs[1] + (i % D)];
   __syncthreads();
 
@@ -143,8 +143,8 @@ __global__ __launch_bounds__(kThreads) void decode_apply_kernel(DecodeArgs a, Ra
   const int n = cur + a.window;
   if (chunk * kThreads >= cur) return;
   const int tid = threadIdx.x;
-  const T* q = reinterpret_cast<const T*>(a.q_new[ll]) + b * a.qs[0] + (int64_t)(g * a.group) * a.qs[1];
-  const T* k = reinterpret_cast<const T*>(a.k_cache[ll]) + b * ks.s[ll][0] + g * ks.s[ll][1];
+  const T* q = in_global(reinterpret_cast<const T*>(a.q_new[ll])) + b * a.qs[0] + (int64_t)(g * a.group) * a.qs[1];
+  const T* k = in_global(reinterpret_cast<const T*>(a.k_cache[ll])) + b * ks.s[ll][0] + g * ks.s[ll][1];
   for (int i = tid; i < a.group * D; i += kThreads) q_lds[i] = (float)q[(i / D) * a.qs[1] + (i % D)];
   if (tid < a.group) {
     const int used = (n + kThreads - 1) / kThreads;               // chunks that hold rows
@@ -178,7 +178,7 @@ __global__ __launch_bounds__(kThreads) void decode_apply_kernel(DecodeArgs a, Ra
   if (j < cur) {
     float mx = obs[tid + half];
     for (int d = 1; d <= half; ++d) mx = fmaxf(mx, fmaxf(obs[tid + half - d], obs[tid + half + d]));
-    float* ind = a.indicator[ll] + ((int64_t)b * a.h_kv + g) * a.cap_cur[ll];
+    float* ind = in_global(a.indicator[ll]) + ((int64_t)b * a.h_kv + g) * a.cap_cur[ll];
     ind[j] += mx;
   }
 }
@@ -211,7 +211,7 @@ struct StepArgs : StepBase {
   int64_t ss[kMaxLaunchLayers][3];  // element strides of every layer's slots: batch, head, slot
   int32_t cap[kMaxLaunchLayers];
   __device__ __forceinline__ StepBuffers buffers(int ll) const {
-    return StepBuffers{k_slots[ll], v_slots[ll], indicator[ll], order[ll], state[ll]};
+    return StepBuffers{in_global(k_slots[ll]), in_global(v_slots[ll]), in_global(indicator[ll]), in_global(order[ll]), in_global(state[ll])};
   }
 };
 // Arguments of a call for one layer whose buffers the host knows: a quarter of a kilobyte and no table
@@ -541,7 +541,7 @@ __global__ __launch_bounds__(kThreads) void step_apply_kernel(StepArgs a) {
   const int chunk = blockIdx.x, ll = blockIdx.z;
   const int b = blockIdx.y / a.h_kv, g = blockIdx.y % a.h_kv;
   const int64_t slice = ((int64_t)ll * a.batch + b) * a.h_kv + g;
-  const int32_t* st = a.state[ll] + ((int64_t)b * a.h_kv + g) * 4;
+  const int32_t* st = in_global(a.state[ll]) + ((int64_t)b * a.h_kv + g) * 4;
   const int cur1 = st[0] + 1;                              // scored rows, the newcomer included
   const int n = cur1 + a.window;
   if (chunk * kThreads >= cur1) return;
@@ -579,7 +579,7 @@ __global__ __launch_bounds__(kThreads) void step_apply_kernel(StepArgs a) {
   if (j < cur1) {
     float mx = obs[tid + half];
     for (int d = 1; d <= half; ++d) mx = fmaxf(mx, fmaxf(obs[tid + half - d], obs[tid + half + d]));
-    float* ind = a.indicator[ll] + ((int64_t)b * a.h_kv + g) * (a.cap[ll] + 1);
+    float* ind = in_global(a.indicator[ll]) + ((int64_t)b * a.h_kv + g) * (a.cap[ll] + 1);
     val = (j < cur1 - 1 ? ind[j] : 0.f) + mx;               // the row that has just left the window starts at 0
     ind[j] = val;
     best = j;
@@ -608,12 +608,12 @@ __global__ __launch_bounds__(kThreads) void step_evict_kernel(StepArgs a) {
   const int ll = blockIdx.y;
   const int b = blockIdx.x / a.h_kv, g = blockIdx.x % a.h_kv;
   const int64_t slice = ((int64_t)ll * a.batch + b) * a.h_kv + g;
-  int32_t* st = a.state[ll] + ((int64_t)b * a.h_kv + g) * 4;
+  int32_t* st = in_global(a.state[ll]) + ((int64_t)b * a.h_kv + g) * 4;
   const int cur = st[0], cur1 = cur + 1, n = cur1 + a.window;
   const int cap = a.cap[ll];
   const int tid = threadIdx.x;
-  int32_t* order = a.order[ll] + ((int64_t)b * a.h_kv + g) * (cap + a.window + 1);
-  float* ind = a.indicator[ll] + ((int64_t)b * a.h_kv + g) * (cap + 1);
+  int32_t* order = in_global(a.order[ll]) + ((int64_t)b * a.h_kv + g) * (cap + a.window + 1);
+  float* ind = in_global(a.indicator[ll]) + ((int64_t)b * a.h_kv + g) * (cap + 1);
   if (tid == 0) {
     const int used = (cur1 + kThreads - 1) / kThreads;
     const float* p = a.amin + slice * a.n_chunks * 2;

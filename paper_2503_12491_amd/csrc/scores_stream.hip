@@ -93,7 +93,7 @@ __device__ __forceinline__ WaveSpan wave_span(const ScoreArgs& a, int w, int n_w
   return s;
 }
 __device__ __forceinline__ const char* key_base(const ScoreArgs& a, const WaveSpan& s) {
-  return reinterpret_cast<const char*>(reinterpret_cast<const __bf16*>(a.k ? a.k[s.l] : a.one.k) + s.b * a.ks[0] + (int64_t)s.g * a.ks[1]) -
+  return reinterpret_cast<const char*>(in_global(reinterpret_cast<const __bf16*>(a.k ? a.k[s.l] : a.one.k)) + s.b * a.ks[0] + (int64_t)s.g * a.ks[1]) -
          (int64_t)a.key_lo * a.ks[2] * 2;
 }
 
@@ -111,7 +111,7 @@ struct Queries {
   uint32_t first;              // see read_keys
 
   static __device__ __forceinline__ const __bf16* row(const ScoreArgs& a, const WaveSpan& s, int r) {      // r: head * S_w + window row
-    const __bf16* q = reinterpret_cast<const __bf16*>(a.q_win ? a.q_win[s.l] : a.one.q) + s.b * a.qs[0] + (int64_t)s.g * G * a.qs[1];
+    const __bf16* q = in_global(reinterpret_cast<const __bf16*>(a.q_win ? a.q_win[s.l] : a.one.q)) + s.b * a.qs[0] + (int64_t)s.g * G * a.qs[1];
     return q + (int64_t)(r / (MB * 32)) * a.qs[1] + (int64_t)(r % (MB * 32)) * a.qs[2];
   }
   // by the whole workgroup, a barrier follows

@@ -388,8 +388,8 @@ __device__ __forceinline__ RowTask row_task(const TopkArgs<kPlanned>& a, const D
     t.keep = dims.keep[e];
     indicator = a.indicator[ll];
   }
-  t.row.init(indicator + ((int64_t)b * a.h_kv + h) * cap_cur, cur);
-  t.out = a.idx[ll] + ((int64_t)b * a.h_kv + h) * cap_keep;
+  t.row.init(in_global(indicator) + ((int64_t)b * a.h_kv + h) * cap_cur, cur);
+  t.out = in_global(a.idx[ll]) + ((int64_t)b * a.h_kv + h) * cap_keep;
   return t;
 }
 
@@ -432,9 +432,9 @@ __global__ __launch_bounds__(kThreads) void select_stage_kernel(StageArgs a) {
   const int cur = a.plan.cur_len[e], keep = a.plan.keep[e];
   const bool held = l < a.m;
   const int64_t at = (int64_t)head * a.plan.cap_keep[l];
-  int32_t* idx = static_cast<int32_t*>(a.plan.idx[l]) + at;
-  float* ind_out = static_cast<float*>(a.plan.ind_out[l]) + at;
-  const float* ind_in = (held ? static_cast<const float*>(a.held[l]) : a.ind) + (int64_t)head * a.plan.cap_cur[l];
+  int32_t* idx = in_global(static_cast<int32_t*>(a.plan.idx[l])) + at;
+  float* ind_out = in_global(static_cast<float*>(a.plan.ind_out[l])) + at;
+  const float* ind_in = in_global(held ? static_cast<const float*>(a.held[l]) : a.ind) + (int64_t)head * a.plan.cap_cur[l];
   const int32_t* old = a.slots_old + (reinterpret_cast<const char*>(ind_in) - a.ind_old) / 4;
   int32_t* renewed = a.slots_new + (reinterpret_cast<const char*>(ind_out) - a.ind_new) / 4;
   int32_t* freed = a.free_slots + (int64_t)head * a.prefix_rows;

@@ -158,10 +158,10 @@ __global__ __launch_bounds__(512) void scores_pass1(ScoreArgs a) {
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
-  const T* q = reinterpret_cast<const T*>(a.q_win ? a.q_win[l] : a.one.q) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
+  const T* q = in_global(reinterpret_cast<const T*>(a.q_win ? a.q_win[l] : a.one.q)) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
   const int64_t tok_bytes = a.ks[2] * (int64_t)sizeof(T);
   // address of key 0 of the slice (keys below key_lo are not behind the pointer and never touched)
-  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k ? a.k[l] : a.one.k) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
+  const char* kbase = reinterpret_cast<const char*>(in_global(reinterpret_cast<const T*>(a.k ? a.k[l] : a.one.k)) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
                       (int64_t)a.key_lo * tok_bytes;
 
   const int key0 = a.key0 + blockIdx.x * a.wg_keys;
@@ -374,7 +374,7 @@ __global__ __launch_bounds__(256) void scores_combine(ScoreArgs a, int rows_per_
 __global__ void scores_import_lse(ScoreArgs a, const float* const* row_lse, int64_t per_layer, int64_t total) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= total) return;
-  a.lse[i] = (row_lse ? row_lse[i / per_layer] : a.one.row_lse)[i % per_layer] * 1.4426950408889634f;
+  a.lse[i] = in_global(row_lse ? row_lse[i / per_layer] : a.one.row_lse)[i % per_layer] * 1.4426950408889634f;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -475,10 +475,10 @@ __global__ __launch_bounds__(512) void scores_pass2(ScoreArgs a) {
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
-  const T* q = reinterpret_cast<const T*>(a.q_win ? a.q_win[l] : a.one.q) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
+  const T* q = in_global(reinterpret_cast<const T*>(a.q_win ? a.q_win[l] : a.one.q)) + b * a.qs[0] + (int64_t)(g * a.group + w) * a.qs[1];
   const int64_t tok_bytes = a.ks[2] * (int64_t)sizeof(T);
   // address of key 0 of the slice (keys below key_lo are not behind the pointer and never touched)
-  const char* kbase = reinterpret_cast<const char*>(reinterpret_cast<const T*>(a.k ? a.k[l] : a.one.k) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
+  const char* kbase = reinterpret_cast<const char*>(in_global(reinterpret_cast<const T*>(a.k ? a.k[l] : a.one.k)) + b * a.ks[0] + (int64_t)g * a.ks[1]) -
                       (int64_t)a.key_lo * tok_bytes;
 
   const int key0 = a.key0 + blockIdx.x * a.wg_keys;
@@ -735,7 +735,7 @@ __device__ __forceinline__ void pool_span(const ScoreArgs& a, int slice) {
   const int j0 = blockIdx.x * kPoolSpan;
   const int span = min(kPoolSpan, a.n_p - j0);
   const float* raw = a.raw + (int64_t)slice * a.n_p;
-  float* out = (a.indicator ? a.indicator[l] : a.one.indicator) + ((int64_t)b * a.h_kv + g) * a.n_p;
+  float* out = in_global(a.indicator ? a.indicator[l] : a.one.indicator) + ((int64_t)b * a.h_kv + g) * a.n_p;
   // Rows of a multiple of four positions at 16-byte aligned addresses, windows of at most nine:
   // 16-byte loads and stores, four outputs per lane from three 16-byte LDS reads.
   const bool quads = a.n_p % 4 == 0 && half <= kPoolQuadHalf &&
