@@ -246,6 +246,8 @@ __device__ void allocate_sequence(const PlanArgs& a, int b, int lane, double* p_
 // The whole plan in one workgroup: budgets and keep counts (a wave per sequence), row capacities of
 // every layer (the largest count over the batch), the places of the layers' outputs, one after the
 // other, in the four pools, and the compaction's work list.
+// kAtMost64: no plan of more layers than that gets here (the code for them is nearly half of the kernel).
+template <bool kAtMost64 = false>
 __device__ __forceinline__ void plan_workgroup(const PlanArgs& a, char* plan_lds /* kPlanLdsPerLayer bytes per wave and layer beyond 64 layers */) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n_waves = blockDim.x >> 6;
   const int n_layers = a.n_layers, batch = a.batch;
@@ -253,7 +255,7 @@ __device__ __forceinline__ void plan_workgroup(const PlanArgs& a, char* plan_lds
     double* p = reinterpret_cast<double*>(plan_lds) + (size_t)wave * 2 * n_layers;
     int32_t* bud = reinterpret_cast<int32_t*>(plan_lds + (size_t)n_waves * n_layers * 2 * sizeof(double)) + (size_t)wave * n_layers;
     for (int b = wave; b < batch; b += n_waves) {
-      if (n_layers <= 64) allocate_sequence<true>(a, b, lane, nullptr, nullptr, nullptr);
+      if (kAtMost64 || n_layers <= 64) allocate_sequence<true>(a, b, lane, nullptr, nullptr, nullptr);
       else allocate_sequence<false>(a, b, lane, p, p + n_layers, bud);
     }
   }

@@ -808,7 +808,7 @@ __global__ __launch_bounds__(256) void pool_and_plan(ScoreArgs a, PrefArgs pa, P
   for (int entry = threadIdx.x >> 6; entry < pa.n_layers * pa.batch; entry += kPoolPlanEntries) preference_of_wave(pa, entry, threadIdx.x & 63);
   __threadfence_block();
   __syncthreads();
-  plan_workgroup(plan, nullptr);
+  plan_workgroup<true>(plan, nullptr);
 }
 
 // Optional event timing of the four kernels (diagnostics).  Process-wide and not thread-safe:
