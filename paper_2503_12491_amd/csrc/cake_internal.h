@@ -176,7 +176,7 @@ struct StageArgs {
   int32_t m, batch, h_kv, window, prefix_rows, prefix_len;
 };
 // The top-k of the stage's rows and the lists after it in one launch, for rows of at most kStageMaxCur entries.  A stage of 8
-// key heads with the lists in a launch of their own, and in this one: 35.2 and 31.9 us at 1500 keys (16 layers, 200 rows
+// key heads with the lists in a launch of their own, and in this one, of 512 threads with eight slots throughout: 35.2 and 31.9 us at 1500 keys (16 layers, 200 rows
 // kept), 55.3 and 53.1 at 8192 (32 layers, 1024), 68.0 and 67.7 at 16000 (16 layers, 1000).  Beyond, the 1024 threads the
 // row takes have no registers left for the places (30000 keys: 97.8 and 99.6; 60000: 121 and 125).
 constexpr int kStageMaxCur = 512 * 8 * 4 - 3;

@@ -7,9 +7,9 @@
 // stack per head and takes the new layer's places from it.  One gather brings the rows into the caches'
 // layout when the caller asks for them.  A stage of 8K keys, d = 128, 8 heads is a chain of launches too small for the chip,
 // each waiting for the one before, with some 1.7 us between two: the scores (9 + 11 us), the plan beside the pooling
-// (8), the top-k with the lists (14; apart 11 + 6) and the new layer's rows (4 to 20).  Counts and addresses come from the stage
+// (7), the top-k with the lists (12; apart 11 + 6) and the new layer's rows (4 to 20).  Counts and addresses come from the stage
 // before and from the call, so that nothing has to be written ahead of the scores.  32 stages with the gather of 55 us: 4595 us
-// with copies, 2150 now.
+// with copies, 2025 now.
 #include <algorithm>
 
 #include "cake_pass.h"

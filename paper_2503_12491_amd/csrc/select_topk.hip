@@ -13,8 +13,8 @@
 // entry above the threshold and the first `need` entries equal to it: the total order (value
 // descending, position ascending).
 //
-// What bounds it is latency, a chain of barriers and LDS round trips: 992 entries 19 -> 5.9 us, 1024
-// rows of 4061 89 -> 15 us, 256 rows of 32736 38 -> 21 us and of 131008 106 -> 71 us (where reading the
+// What bounds it is latency, a chain of barriers and LDS round trips: 992 entries 19 -> 5.0 us, 1024
+// rows of 4061 89 -> 13 us, 256 rows of 32736 38 -> 21 us and of 131008 106 -> 71 us (where reading the
 // row twice at the 35 bytes/ns a compute unit gets is most of it), against four sweeps of the row with a
 // one-wave search of every histogram.
 #include <algorithm>
@@ -710,10 +710,19 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
   sweep([&](uint32_t x, int pos) { return x > thr - (pos <= last ? 1u : 0u); }, [&](uint32_t rank, uint32_t, int pos) { t.out[rank] = pos; });
 }
 
-// The kernel for rows of up to `most` entries.  A short row in a large workgroup would leave its waves
-// idle at every barrier, and small workgroups let several rows share a compute unit.  Where `most` is only
-// what the caller's shape suggests (!bounded: the lengths are device data), rows that do not fit it are left out
-// by that kernel and served by the one for any length, launched behind it.
+// The kernel for rows of up to `most` entries, with as few slots a thread as hold them (a slot that no row has costs its tests:
+// 992 entries 5.9 us with four of 256 threads, 5.0 with one; 8160 in 256 rows of a pass 13.5 with eight of 512, 12.2 with four).
+// More threads leave a thread less to do in a row, but idle at its barriers, and fewer rows share a compute unit.  Us at 8, 256
+// and 1024 rows:
+//   entries   256 threads          512                 1024
+//    1000     4.8   5.1   7.6      4.8   5.2  11.8     5.5   5.9  24.2
+//    2000     5.6   6.2   9.9      4.8   5.3  11.9     5.4   6.1  24.9
+//    4000     7.4   8.5  13.8      5.9   6.8  13.3     5.8   6.6  23.4
+//    6000     9.7  10.0            7.4   7.9           7.7   8.1
+//    8100    11.4  11.8  19.9      8.5   9.1  19.2     8.0   8.5  29.8
+//   16300                         12.0  15.5          10.3  13.0        (in a pass of 256 rows 512 threads are the faster)
+// Where `most` is only what the caller's shape suggests (!bounded: the lengths are device data), rows that do not fit it are
+// left out by that kernel and served by the one for any length, launched behind it.
 template <bool kPlanned>
 int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs<kPlanned>& a, const DimsArg<kPlanned>& dims, PlanArg<kPlanned> plan,
                 hipStream_t stream) {
@@ -724,7 +733,14 @@ int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs<kPlanned>&
     hipLaunchKernelGGL((select_topk_kernel<kPlanned, T, S>), grid, dim3(T), 0, stream, a, dims, plan);     \
     served_slots = T * S;                                                                                  \
   } while (0)
-  if (need <= 256 * 4 * 4) CAKE_TOPK(256, 4);
+  const int64_t rows = (int64_t)grid.x * grid.y;
+  if (need <= 256 * 1 * 4) CAKE_TOPK(256, 1);
+  else if (need <= 256 * 2 * 4 && rows > 256) CAKE_TOPK(256, 2);
+  else if (need <= 512 * 1 * 4) CAKE_TOPK(512, 1);
+  else if (need <= 512 * 2 * 4) CAKE_TOPK(512, 2);
+  else if (need <= 512 * 3 * 4) CAKE_TOPK(512, 3);
+  else if (need <= 512 * 4 * 4) CAKE_TOPK(512, 4);
+  else if (need <= 1024 * 4 * 4 && rows <= 128) CAKE_TOPK(1024, 4);
   else if (need <= 512 * 8 * 4) CAKE_TOPK(512, 8);
   else if (need <= 1024 * 8 * 4) CAKE_TOPK(1024, 8);
   else if (need <= 1024 * 16 * 4) CAKE_TOPK(1024, 16);
@@ -758,10 +774,23 @@ int cake::launch_topk_planned(const cake_shape* shape, const float* const* indic
   return launch_topk<true>(dim3(shape->batch * shape->n_kv_heads, shape->n_layers + (mirror.host != nullptr ? 1 : 0)), max_cur, bounded, a, NoArgs{}, tp, stream);
 }
 
+// As many threads as leave a row the fewest slots each, while a row has a compute unit to itself: averages over the stages of
+// 32 layers of 8 heads (256 to 264 rows in the last), us with 256, 512 and 1024 threads: 1000 keys 6.8, 6.7, 7.4; 2000 7.6, 6.7, 7.5;
+// 4000 10.7, 8.3, 7.9; 6000 14.4, 11.3, 10.4; 8192 (512 threads with eight slots 13.2) 12.4, 11.3 for the last two; 15000 (16
+// layers) 17.6, 14.7.  64 layers of 8192 keys: 12.1, 13.4.
 int cake::launch_topk_stage(const StageArgs& a, hipStream_t stream) {
   const dim3 grid(a.batch * a.h_kv, a.m + 1);
-  if (a.prefix_len + 3 <= 256 * 4 * 4) hipLaunchKernelGGL((select_stage_kernel<256, 4>), grid, dim3(256), 0, stream, a);
-  else hipLaunchKernelGGL((select_stage_kernel<512, 8>), grid, dim3(512), 0, stream, a);
+  const int need = a.prefix_len + 3;
+  const bool few = (int64_t)grid.x * grid.y <= 272;
+  auto run = [&](auto kern, int threads) { hipLaunchKernelGGL(kern, grid, dim3(threads), 0, stream, a); };
+  if (need <= 256 * 1 * 4) run(select_stage_kernel<256, 1>, 256);
+  else if (need <= 512 * 1 * 4) run(select_stage_kernel<512, 1>, 512);
+  else if (need <= 1024 * 1 * 4 && few) run(select_stage_kernel<1024, 1>, 1024);
+  else if (need <= 512 * 2 * 4) run(select_stage_kernel<512, 2>, 512);
+  else if (need <= 1024 * 2 * 4 && few) run(select_stage_kernel<1024, 2>, 1024);
+  else if (need <= 512 * 4 * 4) run(select_stage_kernel<512, 4>, 512);
+  else if (few) run(select_stage_kernel<1024, 4>, 1024);
+  else run(select_stage_kernel<512, 8>, 512);
   CAKE_HIP_TRY(hipGetLastError());
   return CAKE_OK;
 }

@@ -56,3 +56,20 @@ def test_rows_of_the_store_are_those_of_the_copying_cascade(name):
     _same(dev.result(), host.result(), S_w)
     for a, b in zip(early.k_out + early.v_out + early.ind_out, kept, strict=True):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+# rows at the edges of the stage's kernels; the last with more rows than compute units
+@pytest.mark.parametrize("N,H_kv,L", [(1021 + 32, 2, 3), (1022 + 32, 2, 3), (2045 + 32, 2, 3), (2046 + 32, 2, 3), (4094 + 32, 2, 3),
+                                      (8189 + 32, 1, 3), (8190 + 32, 1, 3), (16381 + 32, 1, 3), (4093 + 32, 46, 7), (8189 + 32, 46, 7)])
+def test_kernels_of_a_stage(N, H_kv, L):
+    cake = load_cake()
+    say(f"cascade stage: {L} layers of {H_kv} heads of {N} keys")
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    total = L * N // 6
+    dev, host = cake.DeviceCascade(L, total), cake.CascadeSession(L, total, track_positions=False)
+    for l in range(L):
+        q = (torch.randn(1, H_kv, 32, 64, device=DEV, generator=gen) * (0.5 + l % 3)).bfloat16()
+        k, v = [torch.randn(1, H_kv, N, 64, device=DEV, generator=gen).bfloat16() for _ in range(2)]
+        dev.admit(q, k, v)
+        host.admit(q, k, v)
+    _same(dev.result(), host.result(), 32)

@@ -92,3 +92,28 @@ def test_rows_of_the_largest_key(cake, n):
             for h in range(2):
                 want = co.select_topk(np.where(np.isnan(vals[h]), 1e30, vals[h]).astype(np.float64), k)
                 np.testing.assert_array_equal(idx[0, h].cpu().numpy(), want, err_msg=f"m={m} k={k} row {h}")
+
+
+# the edges between the kernels of up to 16381 entries, which hang on the number of rows as well
+@pytest.mark.parametrize("n,layers", [(1021, 1), (1022, 1), (1022, 32), (2045, 1), (2045, 32), (2046, 32), (4094, 2), (6141, 1), (6142, 1),
+                                      (8189, 2), (8190, 2), (8190, 17), (16381, 17)])
+def test_kernels_of_short_rows(cake, n, layers):
+    say(f"top-k of {layers} layers of rows of {n}")
+    heads, batch = 3, 3                                           # 9 rows a layer: at most 32 layers, 288 rows, a launch
+    rng = np.random.default_rng(n + layers)
+    few = min(layers, 2)
+    vals = [np.stack([_values(kind, heads, n, rng) for kind in ("pooled", "few", "wide")]).astype(np.float32) for _ in range(few)]
+    ind = [torch.tensor(x, device=DEV) for x in vals]
+    for k in (1, n // 5, n - 1):
+        idx = torch.full((layers, batch, heads, k), -1, dtype=torch.int32, device=DEV)
+        shape = cake.make_shape(batch, layers, heads, heads, 64, n + 32, 32, torch.float32)
+        cake.cake_select_topk(shape, cake.ptr_table([ind[l % few] for l in range(layers)]), [n] * layers * batch, [k] * layers * batch,
+                              cake.ptr_table(list(idx)))
+        torch.cuda.synchronize()
+        for l in range(few):
+            for b in range(batch):
+                for h in range(heads):
+                    want = co.select_topk(vals[l][b, h].astype(np.float64), k)
+                    np.testing.assert_array_equal(idx[l, b, h].cpu().numpy(), want, err_msg=f"n={n} k={k} layer {l} row {b} {h}")
+            for again in range(l + few, layers, few):
+                assert torch.equal(idx[again], idx[l]), (n, k, again)
