@@ -110,8 +110,11 @@ __device__ __forceinline__ void slice_coords(const ScoreArgs& a, int slice, int&
 // with these bounds, which nowhere between logits of 2 and 92 are worse).
 constexpr uint32_t kSumLow = (127u - 24u) << 23, kSumHigh = (127u + 24u) << 23;      // the two bounds as float bits
 __device__ __forceinline__ bool block_sum_outside(float sum) { return __float_as_uint(sum) - kSumLow > kSumHigh - kSumLow; }
-template <typename Hidden>
-__device__ __forceinline__ void add_block_sum(const f32x16& acc, float block, float& mref, float& lsum, float cv, Hidden hidden) {
+// kTail: keys of the block from position `last` + 1 on (counted as the lane's registers hold them) are hidden from the row.  (As a
+// callable argument the test for them cost pass 1 ten registers and a wave a SIMD, also where nothing is hidden.)
+template <bool kTail>
+__device__ __forceinline__ void add_block_sum(const f32x16& acc, float block, float& mref, float& lsum, float cv, int last) {
+  auto hidden = [&](int v) { return kTail && 8 * (v / 4) + (v % 4) > last; };
   float sum = lsum + block;
   if (block_sum_outside(sum)) {
     float rmax = kMasked;

@@ -187,7 +187,7 @@ __device__ __forceinline__ void period1(Q& q, int nb, const KeyFrags<D>& kf, f32
     if (kMfma && kValu) __builtin_amdgcn_sched_barrier(0);
   }
   if (kValu) {
-    if (__ballot(redo)) add_block_sum(src, bsum[0], mref, lsum, cv, [](int) { return false; });
+    if (__ballot(redo)) add_block_sum<false>(src, bsum[0], mref, lsum, cv, 0);
     else lsum += bsum[0];
   }
 }
@@ -266,8 +266,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void stream_pass1(ScoreArgs a) {
 #pragma unroll
     for (int nb = 0; nb < kBlocks; ++nb) {
       period1<D, true, false>(q, nb, kf, acc[0], acc[1], mref[nb], lsum[nb], cv);
-      const int last_visible = min(a.n_p + nb % MB * 32 + c32, a.n - 1);
-      auto hidden = [&](int v) { return kb + 8 * (v / 4) + 4 * hh + (v % 4) > last_visible; };
+      const int last = min(a.n_p + nb % MB * 32 + c32, a.n - 1) - kb - 4 * hh;
+      auto hidden = [&](int v) { return 8 * (v / 4) + (v % 4) > last; };
       float bsum[2];
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void stream_pass1(ScoreArgs a) {
         if (v < 2) bsum[v] = e;
         else bsum[v & 1] += e;
       }
-      add_block_sum(acc[0], bsum[0] + bsum[1], mref[nb], lsum[nb], cv, hidden);
+      add_block_sum<true>(acc[0], bsum[0] + bsum[1], mref[nb], lsum[nb], cv, last);
       __builtin_amdgcn_sched_barrier(0);
     }
     if (((t + 1) & (granule_subs - 1)) == 0 || t + 1 == sp.n_sub) finish(t);

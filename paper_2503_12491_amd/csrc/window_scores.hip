@@ -129,8 +129,8 @@ __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, floa
                                            float cv, int n, int n_p, int c32, int hh) {
 #pragma unroll
   for (int nb = 0; nb < MB; ++nb) {
-    const int last_visible = min(n_p + nb * 32 + c32, n - 1);
-    auto hidden = [&](int v) { return kTail && kb + 8 * (v / 4) + 4 * hh + (v % 4) > last_visible; };
+    const int last = min(n_p + nb * 32 + c32, n - 1) - kb - 4 * hh;
+    auto hidden = [&](int v) { return kTail && 8 * (v / 4) + (v % 4) > last; };
     float bsum[2];                        // two chains: consecutive additions do not wait on each other
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -138,7 +138,7 @@ __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, floa
       if (v < 2) bsum[v] = e;
       else bsum[v & 1] += e;
     }
-    add_block_sum(acc[nb], bsum[0] + bsum[1], mref[nb], lsum[nb], cv, hidden);
+    add_block_sum<kTail>(acc[nb], bsum[0] + bsum[1], mref[nb], lsum[nb], cv, last);
   }
 }
 
