@@ -160,10 +160,11 @@ struct PlanMirror {            // device addresses of what is copied
 // which are then not in the table; `mirror`: a workgroup more writes the host's copy of the plan meanwhile
 int launch_topk_planned(const cake_shape* shape, const float* const* indicator, const float* last, const PlanView& plan, int64_t max_cur, bool bounded,
                         const PlanMirror& mirror, hipStream_t stream);
-// cake_evict_planned; `bounded` if the plan was made with current lengths of at most seq_len - window
+// cake_evict_planned; `bounded` if the plan was made with current lengths of at most seq_len - window; most_rows: see
+// launch_compact_planned
 int evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,
                   const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded, const PlanMirror& mirror,
-                  void* stream);
+                  int64_t most_rows, void* stream);
 // What a stage of the device-chained cascade (cascade_stage.hip) does to its lists.
 struct StageArgs {
   PlanView plan;                      // of this stage
@@ -182,9 +183,10 @@ struct StageArgs {
 constexpr int kStageMaxCur = 512 * 8 * 4 - 3;
 int launch_topk_stage(const StageArgs& a, hipStream_t stream);
 constexpr int kPlanMaskWords = 32;       // one bit per layer, n_layers <= 1024
+// most_rows: rows that a head of a sequence keeps in all layers together at most, windows included; 0: not known
 int launch_compact_planned(const cake_shape* shape, const void* const* k_in, const void* const* v_in,
                            const int64_t* kv_strides, const uint8_t* compacted, const float* const* ind_in,
-                           const PlanView& plan, hipStream_t stream);
+                           const PlanView& plan, int64_t most_rows, hipStream_t stream);
 
 #ifdef __HIPCC__
 // The pointer, known to point to global memory (cast by way of an integer: a pair of pointer casts is folded away).  Where the

@@ -225,5 +225,6 @@ extern "C" int cake_cascade_gather(const cake_cascade* c, int32_t n_layers, void
   view.v_out = tables + 4 * n_layers;
   const int64_t rows = store_rows(c), d = shape.head_dim;
   const int64_t strides[3] = {shape.n_kv_heads * rows * d, rows * d, d};
-  return launch_compact_planned(&shape, tables, tables + n_layers, strides, nullptr, nullptr, view, st);
+  return launch_compact_planned(&shape, tables, tables + n_layers, strides, nullptr, nullptr, view,
+                                std::min<int64_t>(c->total_budget, (int64_t)n_layers * shape.seq_len), st);
 }

@@ -3,6 +3,7 @@
 // of head_dim elements, copied as 16-byte pieces with consecutive lanes on consecutive pieces,
 // so a 256-byte bf16 row is one coalesced access of 16 lanes.
 #include <algorithm>
+#include <cstdint>
 
 #include "cake_internal.h"
 #include "cake_pass.h"
@@ -45,21 +46,33 @@ struct CompactPlan {
 };
 static_assert(kThreads * kUnroll == kCopyBlockPieces, "a workgroup step is one block of the plan's work list");
 constexpr int kListLds = 4096;       // work-list entries searched from LDS (longer lists are searched in memory)
+constexpr int kListWave = 64;        // entries that a wave holds, one a lane
 
 // A workgroup moves kThreads*kUnroll pieces of one (layer, sequence, head) slice per step.
 // Launches that know the row counts on the host give every slice the blocks it needs.  Planned
 // launches (counts known only on the device) run a fixed number of workgroups that stride over
 // the plan's work list, the blocks of all (layer, sequence) entries in one sequence, head by
-// blockIdx.y: the entry of a block is found by bisection of the running counts.
+// blockIdx.y: the entry of a block is found by counting, in a wave's lanes, the running counts not above it, or
+// in a long list by bisection.
+//
+// Large calls are bound by the bytes of the rows (5 TB/s), small ones by the chain of loads that leads to them: list, counts and
+// addresses, index, row.  A block's index loads go out together and its row loads behind them, without a branch about either (in
+// branches each of the four waited for the rows of the one before), the indicator's entries beside the rows instead of behind
+// their stores; the work list of a small plan is searched without LDS and its barrier, and a call that knows how long the list can
+// be brings no more workgroups.  Passes of 2 layers of 1024 keys 42.9 -> 42.0 us, of 2 layers of 4000 55.4 -> 50.9, of 8 layers of
+// 2000 70.0 -> 67.2; the eviction of 32 layers of 32768 keys 80.3 -> 78.2.
 template <bool kPlanned>
 __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned> a, DimsArg<kPlanned> dims, StridesArg<kPlanned> st,
                                                           typename std::conditional<kPlanned, CompactPlan, NoArgs>::type plan) {
   __shared__ int32_t list[kPlanned ? kListLds + 1 : 1];
   const int32_t* blocks = nullptr;
-  int32_t n_blocks = 1;
+  int32_t n_blocks = 1, begins = 0;
   if constexpr (kPlanned) {
     blocks = plan.copy_blocks;
-    if (plan.n_entries <= kListLds) {
+    if (plan.n_entries <= kListWave) {
+      const int e = threadIdx.x & 63;
+      begins = e < plan.n_entries ? plan.copy_blocks[e] : 0x7fffffff;
+    } else if (plan.n_entries <= kListLds) {
       for (int i = threadIdx.x; i <= plan.n_entries; i += kThreads) list[i] = plan.copy_blocks[i];
       __syncthreads();
       blocks = list;
@@ -72,9 +85,14 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
   int64_t first;
   if constexpr (kPlanned) {
     int lo = 0, hi = plan.n_entries;          // largest e with blocks[e] <= blk (entries without blocks share a count)
-    while (hi - lo > 1) {
-      const int mid = (lo + hi) >> 1;
-      if (blocks[mid] <= blk) lo = mid; else hi = mid;
+    if (hi <= kListWave) {
+      lo = __popcll(__ballot(begins <= blk)) - 1;                 // the counts ascend, from 0
+    } else {
+      while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (blocks[mid] <= blk) lo = mid; else hi = mid;
+      }
+      lo = __builtin_amdgcn_readfirstlane(lo);
     }
     ll = lo / a.batch; b = lo % a.batch; h = blockIdx.y;
     first = (int64_t)(blk - blocks[lo]) * (kThreads * kUnroll);
@@ -116,51 +134,79 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
   const int32_t* idx = in_global(a.idx[ll]) + ((int64_t)b * a.h_kv + h) * cap_keep;
 
   if (first >= total) { if (kPlanned) continue; else return; }
-  uint4 kv[kUnroll], vv[kUnroll];
-  int64_t dst[kUnroll];
+  // Indicator entries of the retained prefix rows and, where the caller tracks them, their positions in
+  // the prompt: composing the positions here takes the kernel no measurable time, a gather of its own
+  // per layer and stage took a session of 16 layers of 6K keys two launches each.  A row split between two blocks is
+  // written by the block that holds its piece 0.
+  const bool entries = a.ind_in != nullptr, positions = a.pos_out != nullptr;
+  const int64_t head = (int64_t)b * a.h_kv + h;
+  const float* iin = nullptr;
+  float* iout = nullptr;
+  const int32_t* pin = nullptr;
+  int32_t* pout = nullptr;
+  if (entries) {
+    iin = in_global(a.ind_in[ll]) + head * cap_cur;
+    iout = in_global(a.ind_out[ll]) + head * cap_keep;
+    if (positions) {
+      if (a.pos_in[ll] != nullptr) pin = in_global(a.pos_in[ll]) + head * cap_cur;
+      pout = in_global(a.pos_out[ll]) + head * cap_keep;
+    }
+  }
+  const int64_t row0 = first / a.pieces;                               // of the block's first piece
+  const uint32_t piece0 = (uint32_t)(first - row0 * a.pieces), pieces = (uint32_t)a.pieces;
+  const int64_t r_first = row0 + (piece0 > 0 ? 1 : 0);                  // rows that begin in the block
+  const int64_t r_end = min((first + kThreads * kUnroll + a.pieces - 1) / a.pieces, (int64_t)keep);
+  const int64_t own = r_first + threadIdx.x;
+  const bool has_entry = entries && own < r_end;
+  int own_src = 0;
+  if (has_entry) own_src = min(max(idx[own], 0), cur - 1);
+  const int64_t at = first + threadIdx.x;                              // the thread's first piece, here and in the output
+  // Pieces past the end repeat the last one: with no branch about them the loads of a block are in flight together, the
+  // indexes first and then the rows.
+  const uint32_t last = (uint32_t)min(total - 1 - first, (int64_t)(kThreads * kUnroll - 1)) + piece0;
+  int64_t src[kUnroll];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
-    const int64_t p = first + (int64_t)u * kThreads + threadIdx.x;
-    dst[u] = -1;
-    if (p < total) {
-      const int r = (int)(p / a.pieces), piece = (int)(p % a.pieces);
-      // selected prefix rows first, then the window rows that follow the cur prefix rows
-      int src = r < keep ? min(max(idx[r], 0), cur - 1) : cur + (r - keep);
-      const int64_t so = (int64_t)src * in_row + piece * 16;
-      kv[u] = *reinterpret_cast<const uint4*>(kin + so);
-      vv[u] = *reinterpret_cast<const uint4*>(vin + so);
-      dst[u] = (int64_t)r * out_row + piece * 16;
+    const uint32_t q = min(piece0 + u * kThreads + threadIdx.x, last), down = q / pieces, piece = q - down * pieces;
+    const int r = (int)row0 + (int)down;
+    // selected prefix rows first, then the window rows that follow the cur prefix rows
+    int from = cur + (r - keep);
+    if (keep > 0) {
+      const int chosen = min(max(idx[min(r, keep - 1)], 0), cur - 1);
+      from = r < keep ? chosen : from;
     }
+    src[u] = (int64_t)from * in_row + piece * 16;
+  }
+  float own_ind = 0.f;
+  int own_pos = own_src;
+  if (has_entry) {
+    own_ind = iin[own_src];
+    if (pin != nullptr) own_pos = pin[own_src];
+  }
+  uint4 kv[kUnroll], vv[kUnroll];
+#pragma unroll
+  for (int u = 0; u < kUnroll; ++u) {
+    kv[u] = *reinterpret_cast<const uint4*>(kin + src[u]);
+    vv[u] = *reinterpret_cast<const uint4*>(vin + src[u]);
+  }
+  if (has_entry) {
+    iout[own] = own_ind;
+    if (pout != nullptr) pout[own] = own_pos;
   }
   // Streaming stores: the compacted rows are not read again by this pass, and plain stores were
   // measured to cost twice their bytes in memory writes (the rows pass through the cache first).
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u)
-    if (dst[u] >= 0) {
-      store_streaming(kout + dst[u], kv[u]);
-      store_streaming(vout + dst[u], vv[u]);
+    if (at + u * kThreads < total) {
+      store_streaming(kout + (at + u * kThreads) * 16, kv[u]);
+      store_streaming(vout + (at + u * kThreads) * 16, vv[u]);
     }
-
-  // Indicator entries of the retained prefix rows and, where the caller tracks them, their positions in
-  // the prompt: composing the positions here takes the kernel no measurable time, a gather of its own
-  // per layer and stage took a session of 16 layers of 6K keys two launches each.
-  if (a.ind_in != nullptr) {
-    const int64_t head = (int64_t)b * a.h_kv + h;
-    const float* iin = in_global(a.ind_in[ll]) + head * cap_cur;
-    float* iout = in_global(a.ind_out[ll]) + head * cap_keep;
-    const int32_t* pin = a.pos_out != nullptr ? in_global(a.pos_in[ll]) : nullptr;
-    int32_t* pout = a.pos_out != nullptr ? in_global(a.pos_out[ll]) + head * cap_keep : nullptr;
-    if (pin != nullptr) pin += head * cap_cur;
-    const int64_t r0 = first / a.pieces;                               // rows this block touches
-    const int64_t r1 = min((first + kThreads * kUnroll + a.pieces - 1) / a.pieces, (int64_t)keep);
-    // a row split between two blocks is written by the block that holds its piece 0
-    for (int64_t r = r0 + threadIdx.x; r < r1; r += kThreads)
-      if (r * a.pieces >= first) {
-        const int src = min(max(idx[r], 0), cur - 1);
-        iout[r] = iin[src];
-        if (pout != nullptr) pout[r] = pin != nullptr ? pin[src] : src;
-      }
-  }
+  if (entries)                                                        // a block of more rows than threads: rows of fewer than five pieces
+    for (int64_t r = own + kThreads; r < r_end; r += kThreads) {
+      const int from = min(max(idx[r], 0), cur - 1);
+      iout[r] = iin[from];
+      if (pout != nullptr) pout[r] = pin != nullptr ? pin[from] : from;
+    }
   }
 }
 
@@ -169,7 +215,7 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
 
 int cake::launch_compact_planned(const cake_shape* shape, const void* const* k_in, const void* const* v_in,
                                  const int64_t* kv_strides, const uint8_t* compacted, const float* const* ind_in,
-                                 const PlanView& plan, hipStream_t stream) {
+                                 const PlanView& plan, int64_t most_rows, hipStream_t stream) {
   const int eb = (int)elem_bytes(shape->dtype);
   CompactArgs<true> a{};
   a.k_in = k_in; a.v_in = v_in;
@@ -185,8 +231,11 @@ int cake::launch_compact_planned(const cake_shape* shape, const void* const* k_i
   if (compacted != nullptr)
     for (int l = 0; l < shape->n_layers; ++l)
       if (compacted[l]) cp.compacted[l >> 5] |= 1u << (l & 31);
-  // 8192 workgroups in all (a few rounds of what the chip holds at once), striding over the work list
-  const unsigned gx = (unsigned)std::max(1, 8192 / shape->n_kv_heads);
+  // 8192 workgroups in all (a few rounds of what the chip holds at once), striding over the work list, or as many as the list
+  // can be long
+  const int64_t entries = (int64_t)shape->n_layers * shape->batch;
+  const int64_t longest = most_rows > 0 ? most_rows * shape->batch * a.pieces / kCopyBlockPieces + entries : INT32_MAX;
+  const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(8192 / shape->n_kv_heads, longest));
   hipLaunchKernelGGL(compact_kernel<true>, dim3(gx, shape->n_kv_heads), dim3(kThreads), 0,
                      stream, a, NoArgs{}, NoArgs{}, cp);
   CAKE_HIP_TRY(hipGetLastError());

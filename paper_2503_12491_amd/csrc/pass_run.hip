@@ -2,6 +2,7 @@
 // launches are made back to back from here, and the host learns the plan from pinned memory as soon
 // as the plan kernel has run, so that it prepares the caller's results beside the top-k and the
 // compaction instead of after four copies and a stream synchronisation behind them.
+#include <algorithm>
 #include <chrono>
 
 #include "cake_pass.h"
@@ -83,7 +84,8 @@ extern "C" int cake_pass_launch(const cake_pass* p, int32_t parts, uint32_t tick
     // the plan above takes every row at its full length
     const PlanMirror mirror{ticket ? p->mirror : nullptr, plan.budgets, plan.keep, plan.status, p->pref, p->hv, p->shape.n_layers,
                             p->shape.batch, ticket};
-    return evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, true, mirror, stream);
+    return evict_planned(&p->shape, p->indicator, p->k, p->v, p->kv_strides, nullptr, p->plan, p->plan_bytes, true, mirror,
+                         std::min<int64_t>(p->total_budget, (int64_t)p->shape.n_layers * p->shape.seq_len), stream);
   }
   return CAKE_OK;
 }

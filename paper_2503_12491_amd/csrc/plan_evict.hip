@@ -138,7 +138,7 @@ extern "C" int cake_plan_layout(const cake_shape* shape, size_t* offsets) {
 
 int cake::evict_planned(const cake_shape* shape, const float* const* indicator, const void* const* k_in, const void* const* v_in,
                         const int64_t* kv_strides, const uint8_t* compacted, const void* plan, size_t plan_bytes, bool bounded,
-                        const PlanMirror& mirror, void* stream) {
+                        const PlanMirror& mirror, int64_t most_rows, void* stream) {
   if (int rc = check_shape_basic(shape)) return rc;
   CAKE_REQUIRE(indicator && k_in && v_in && kv_strides && plan, "a pointer argument is NULL");
   CAKE_REQUIRE((int64_t)shape->n_layers * shape->batch * shape->n_kv_heads <= 65535 * 64,
@@ -155,7 +155,7 @@ int cake::evict_planned(const cake_shape* shape, const float* const* indicator, 
   // without a length in the shape the kernel for any length serves
   const int64_t max_cur = shape->seq_len > shape->window ? shape->seq_len - shape->window : 0x7fffffff;
   if (int rc = launch_topk_planned(shape, indicator, nullptr, view, max_cur, bounded, mirror, st)) return rc;
-  return launch_compact_planned(shape, k_in, v_in, kv_strides, compacted, indicator, view, st);
+  return launch_compact_planned(shape, k_in, v_in, kv_strides, compacted, indicator, view, most_rows, st);
 }
 
 // The lengths are the plan's, device data that this call cannot look at: the shape's length only says which rows
@@ -164,5 +164,5 @@ extern "C" int cake_evict_planned(const cake_shape* shape, const float* const* i
                                   const void* const* k_in, const void* const* v_in, const int64_t* kv_strides,
                                   const uint8_t* compacted,
                                   const void* plan, size_t plan_bytes, void* stream) {
-  return evict_planned(shape, indicator, k_in, v_in, kv_strides, compacted, plan, plan_bytes, false, PlanMirror{}, stream);
+  return evict_planned(shape, indicator, k_in, v_in, kv_strides, compacted, plan, plan_bytes, false, PlanMirror{}, 0, stream);
 }

@@ -322,3 +322,49 @@ def test_a_plan_in_a_launch_of_its_own_is_not_timed_as_pooling(cake):
     plan = begin.elapsed_time(end)
     say(f"pooling alone {pooled[0]:.4f} ms, in the pass {pooled[1]:.4f} ms, plan {plan:.4f} ms")
     assert pooled[1] < pooled[0] + 0.25 * plan
+
+
+@pytest.mark.parametrize("L,B,H,d,dtype", [(1, 1, 1, 8, torch.bfloat16), (2, 1, 2, 24, torch.bfloat16), (63, 1, 1, 56, torch.bfloat16),
+                                           (32, 2, 2, 64, torch.float32), (65, 1, 2, 12, torch.float32), (13, 5, 2, 128, torch.bfloat16)])
+def test_planned_rows_of_any_width_and_lists_around_a_waves_lanes(cake, L, B, H, d, dtype):
+    """The compaction's work list of up to 64 (layer, sequence) entries is searched in a wave's lanes, a longer one by bisection;
+    rows of 1, 3, 7 and 16 pieces straddle its blocks of 1024 pieces, and blocks of one-piece rows hold more rows than threads."""
+    from paper_2503_12491_amd import binding as C
+    say(f"planned compaction: {L} layers x {B} sequences x {H} heads, rows of {d}")
+    S_w, n = 3, 1500
+    rng = np.random.default_rng(L * B + d)
+    cur = rng.integers(1, n + 1, size=(L, B))
+    cur[0] = n
+    if L > 2:
+        cur[1] = 0                                                    # a layer of windows alone
+    caps = cur.max(axis=1)
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    k, v = ([torch.randn(B, H, n + S_w, d, device=DEV, generator=gen).to(dtype) for _ in range(L)] for _ in range(2))
+    ind = [torch.rand(B, H, max(int(c), 1), device=DEV, generator=gen) for c in caps]
+    shape = C.make_shape(B, L, H, H, d, n + S_w, S_w, dtype)
+    pref = torch.from_numpy(np.exp(rng.standard_normal((B, L)))).to(DEV)
+    total = L * 700 if L < 3 else L * 90
+    rows = L * n
+    mk = lambda count, t: torch.zeros(count, dtype=t, device=DEV)
+    pools = [mk(B * H * rows, torch.int32), mk(B * H * (rows + L * S_w) * d, dtype), mk(B * H * (rows + L * S_w) * d, dtype), mk(B * H * rows, torch.float32)]
+    plan, status = mk(C.cake_plan_bytes(shape), torch.uint8), mk(B, torch.int32)
+    C.cake_plan_eviction(shape, pref, total, torch.tensor(cur.reshape(-1), dtype=torch.int32, device=DEV), *pools, plan, status)
+    C.cake_evict_planned(shape, C.ptr_table(ind), C.ptr_table(k), C.ptr_table(v), [k[0].stride(i) for i in range(3)], plan)
+    torch.cuda.synchronize()
+    _, keep, _, cap_keep = C.plan_fields(plan.cpu(), L, B)
+    before = 0
+    for l in range(L):
+        c = int(cap_keep[l])
+        idx, i_out = (p[B * H * before: B * H * (before + c)].view(B, H, c).cpu() for p in (pools[0], pools[3]))
+        at = B * H * (before + l * S_w) * d
+        k_out, v_out = (p[at: at + B * H * (c + S_w) * d].view(B, H, c + S_w, d).cpu() for p in pools[1:3])
+        k_in, v_in, i_in = k[l].cpu(), v[l].cpu(), ind[l].cpu()
+        for b in range(B):
+            m, full = int(keep[l, b]), int(cur[l, b])
+            for h in range(H):
+                want = torch.from_numpy(co.select_topk(i_in[b, h, :full].double().numpy(), m)).long()
+                src = torch.cat([want, torch.arange(full, full + S_w)])
+                assert torch.equal(idx[b, h, :m].long(), want), (l, b, h)
+                assert torch.equal(i_out[b, h, :m], i_in[b, h][want]), (l, b, h)
+                assert torch.equal(k_out[b, h, : m + S_w], k_in[b, h][src]) and torch.equal(v_out[b, h, : m + S_w], v_in[b, h][src]), (l, b, h)
+        before += c
