@@ -304,6 +304,81 @@ __device__ __forceinline__ float weight_sum(const float (&t)[kGroup], const floa
   return s;
 }
 
+template <typename T, int D> using StepFrags = typename RowDots<T, D>::frag[RowDots<T, D>::kSteps];
+// The new query rows of a group as operands: head li's piece kg of every step.
+template <typename T, int D>
+__device__ __forceinline__ void load_queries(StepFrags<T, D>& qf, const T* q, int li, int kg, int group) {
+  using Dots = RowDots<T, D>;
+  constexpr int kElems = 16 / (int)sizeof(T);
+#pragma unroll
+  for (int s = 0; s < Dots::kSteps; ++s) {
+    qf[s] = *reinterpret_cast<const typename Dots::loose*>(q + s * 4 * kElems + kg * kElems);     // q_new may start at any element
+    if (li >= group)
+#pragma unroll
+      for (int i = 0; i < kElems; ++i) qf[s][i] = (T)0.f;
+  }
+}
+
+// A wave's 64 rows from row0 on, whose slots lane li knows (16 apart): logits of head li, four rows at a time, to `keep`; returns
+// the rows' (reference, sum) of head li.
+template <typename T, int D, typename Keep>
+__device__ __forceinline__ float2 wave_rows(const StepFrags<T, D>& qf, const int32_t (&slot)[4], const T* ks,
+                                            const T* kn, int64_t tok, int row0, int n, float c, int li, int kg, Keep keep) {
+  using Dots = RowDots<T, D>;
+  typedef typename Dots::frag frag;
+  constexpr int kElems = 16 / (int)sizeof(T);
+  float m = kMasked, l = 0.f;                             // of head li over the lane's rows
+  float t[64 / 16][4];
+#pragma unroll
+  for (int r0 = 0; r0 < 4; r0 += Dots::kBlocks) {
+    frag kf[Dots::kBlocks][Dots::kSteps];
+#pragma unroll
+    for (int r = 0; r < Dots::kBlocks; ++r) {
+      const int j = row0 + (r0 + r) * 16 + li;
+      // the generated token's row comes from the caller; rows past the end repeat it
+      const T* row = j < n - 1 ? ks + slot[r0 + r] * tok : kn;
+#pragma unroll
+      for (int s = 0; s < Dots::kSteps; ++s) kf[r][s] = *reinterpret_cast<const frag*>(row + s * 4 * kElems + kg * kElems);
+    }
+#pragma unroll
+    for (int r = 0; r < Dots::kBlocks; ++r) {
+      const f32x4 acc = Dots::run(kf[r], qf);
+      const int j0 = row0 + (r0 + r) * 16 + kg * 4;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        t[r0 + r][v] = j0 + v < n ? acc[v] * c : kMasked;
+        m = fmaxf(m, t[r0 + r][v]);
+      }
+      keep(j0, make_float4(acc[0] * c, acc[1] * c, acc[2] * c, acc[3] * c));
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) l += fast_exp2(t[r][v] - m);
+  if (m == kMasked) l = 0.f;                              // none of the lane's rows exists
+#pragma unroll
+  for (int off = 16; off <= 32; off <<= 1) {
+    const float om = __shfl_xor(m, off), ol = __shfl_xor(l, off), mn = fmaxf(m, om);
+    l = l * fast_exp2(m - mn) + ol * fast_exp2(om - mn);
+    m = mn;
+  }
+  return make_float2(m, l);
+}
+
+// The generated token's key and value into the free slot.
+template <typename T, int D>
+__device__ __forceinline__ void store_new_row(const void* v_new, int64_t v_at, const T* kn, T* ks, T* vs, int64_t to, int tid, int threads) {
+  constexpr int kElems = 16 / (int)sizeof(T), kPieces = D / kElems;
+  const T* vn = reinterpret_cast<const T*>(v_new) + v_at;
+  for (int i = tid; i < 2 * kPieces; i += threads) {
+    const int e = (i % kPieces) * kElems;
+    const T* src = i < kPieces ? kn : vn;
+    T* dst = (i < kPieces ? ks : vs) + to;
+    *reinterpret_cast<uint4*>(dst + e) = *reinterpret_cast<const uint4*>(src + e);
+  }
+}
+
 // Step kernel 1, one workgroup per 64 rows a wave of a slice: the new row goes to its slot; logits of the G
 // heads for every listed row (kept for what follows) and the chunk's (reference, sum) pairs.
 // Bound by the key bytes: four 16-byte loads per row and lane, all of a wave's 64 rows in flight; the
@@ -343,63 +418,15 @@ __global__ __launch_bounds__(64 * kStepWaves, 4) void step_logits_kernel(Args a)
 #pragma unroll
   for (int r = 0; r < 4; ++r) slot[r] = order[min(chunk * kRows + wave * 64 + r * 16 + li, cap + a.window)];
   frag qf[Dots::kSteps];
-#pragma unroll
-  for (int s = 0; s < Dots::kSteps; ++s) {
-    qf[s] = *reinterpret_cast<const typename Dots::loose*>(q + s * 4 * kElems + kg * kElems);     // q_new may start at any element
-    if (li >= a.group)
-#pragma unroll
-      for (int i = 0; i < kElems; ++i) qf[s][i] = (T)0.f;
-  }
+  load_queries<T, D>(qf, q, li, kg, a.group);
   if (chunk * kRows >= n) return;
-  float m = kMasked, l = 0.f;                             // of head li over the lane's rows
-  float t[64 / 16][4];
-#pragma unroll
-  for (int r0 = 0; r0 < 4; r0 += Dots::kBlocks) {
-    frag kf[Dots::kBlocks][Dots::kSteps];
-#pragma unroll
-    for (int r = 0; r < Dots::kBlocks; ++r) {
-      const int j = chunk * kRows + wave * 64 + (r0 + r) * 16 + li;
-      // the generated token's row comes from the caller; rows past the end repeat it
-      const T* row = j < n - 1 ? ks + slot[r0 + r] * tok : kn;
-#pragma unroll
-      for (int s = 0; s < Dots::kSteps; ++s) kf[r][s] = *reinterpret_cast<const frag*>(row + s * 4 * kElems + kg * kElems);
-    }
-#pragma unroll
-    for (int r = 0; r < Dots::kBlocks; ++r) {
-      const f32x4 acc = Dots::run(kf[r], qf);
-      const int j0 = chunk * kRows + wave * 64 + (r0 + r) * 16 + kg * 4;
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        t[r0 + r][v] = j0 + v < n ? acc[v] * a.c : kMasked;
-        m = fmaxf(m, t[r0 + r][v]);
-      }
-      if (li < a.group && j0 < n) *reinterpret_cast<float4*>(lg + (int64_t)li * a.rows_max + j0) =
-          make_float4(acc[0] * a.c, acc[1] * a.c, acc[2] * a.c, acc[3] * a.c);
-    }
-  }
-#pragma unroll
-  for (int r = 0; r < 4; ++r)
-#pragma unroll
-    for (int v = 0; v < 4; ++v) l += fast_exp2(t[r][v] - m);
-  if (m == kMasked) l = 0.f;                              // none of the lane's rows exists
-#pragma unroll
-  for (int off = 16; off <= 32; off <<= 1) {
-    const float om = __shfl_xor(m, off), ol = __shfl_xor(l, off), mn = fmaxf(m, om);
-    l = l * fast_exp2(m - mn) + ol * fast_exp2(om - mn);
-    m = mn;
-  }
-  if (lane < a.group) { red_m[wave][lane] = m; red_l[wave][lane] = l; }
-  if (chunk == (n - 1) / kRows) {                      // the generated token's key and value into the free slot
-    constexpr int kPieces = D * (int)sizeof(T) / 16;
-    const T* vn = reinterpret_cast<const T*>(a.v_new) + ll * a.ns[0] + b * a.ns[1] + g * a.ns[2];
-    T* vs = reinterpret_cast<T*>(buf.v_slots) + b * a.ss[ll][0] + g * a.ss[ll][1];
-    for (int i = tid; i < 2 * kPieces; i += kRows) {
-      const int e = (i % kPieces) * kElems;
-      const T* src = i < kPieces ? kn : vn;
-      T* dst = (i < kPieces ? ks : vs) + free_slot * tok;
-      *reinterpret_cast<uint4*>(dst + e) = *reinterpret_cast<const uint4*>(src + e);
-    }
-  }
+  const float2 own = wave_rows<T, D>(qf, slot, ks, kn, tok, chunk * kRows + wave * 64, n, a.c, li, kg, [&](int j0, const float4& x) {
+    if (li < a.group && j0 < n) *reinterpret_cast<float4*>(lg + (int64_t)li * a.rows_max + j0) = x;
+  });
+  if (lane < a.group) { red_m[wave][lane] = own.x; red_l[wave][lane] = own.y; }
+  if (chunk == (n - 1) / kRows)
+    store_new_row<T, D>(a.v_new, ll * a.ns[0] + b * a.ns[1] + g * a.ns[2], kn, ks, reinterpret_cast<T*>(buf.v_slots) + b * a.ss[ll][0] + g * a.ss[ll][1],
+                        free_slot * tok, tid, kRows);
   __syncthreads();
   if (tid < a.group) {
     float rm[kStepWaves], rl[kStepWaves];
@@ -525,6 +552,99 @@ __global__ __launch_bounds__(kFinishThreads, kGroup <= 4 ? 8 : 4) void step_fini
     if (j == n - 1) order[j] = free_slot;
     if (j == cur) ind[j] = val[i];
   }
+}
+
+// Both steps of a head of few rows in one launch: a workgroup with a wave per 64 rows, logits and pairs in LDS; the same sums in the
+// same order as by the two kernels.  Bound by the chain state, list, keys, then by the one compute unit that takes in the head's
+// keys, some 35 bytes a nanosecond; but nothing goes through memory and waits for a second launch, which the host has to
+// make as well.  Heads of at most kStepWholeBytes of keys take it (all layers of a call, so that the longest decides).  Us of two launches and of
+// one, 8 layers of 8 heads called one by one: 100 to 350 rows of 128 in bf16 86 and 62, 470 86 and 68, 700 85 and 88, 980 86 and
+// 108; 220 rows in fp32 88 and 71, 470 87 and 102; 980 rows of 64 with 8 queries 86 and 79.  384 heads at once: up to 470 rows 21.8 and
+// 18.3, 980 30.2 and 29.3; 8 heads at once: 220 rows 10.5 and 7.2, 470 10.7 and 8.9, 980 10.5 and 13.8.
+constexpr int kStepOneThreads = 1024;
+constexpr int64_t kStepWholeBytes = 128 << 10;
+template <typename T, int D, int kGroup, typename Args>
+__global__ __launch_bounds__(kStepOneThreads) void step_whole_kernel(Args a) {
+  using Dots = RowDots<T, D>;
+  constexpr int kLd = kStepOneThreads + 4;               // logits of a head: the heads' rows start in banks of their own
+  __shared__ __attribute__((aligned(16))) float lg[kGroup * kLd];
+  __shared__ float2 red[kStepOneThreads / 64][kMaxGroup];
+  __shared__ float obs[kStepOneThreads + 2 * kMaxHalf];
+  __shared__ float lse[kMaxGroup];
+  __shared__ uint64_t cand[kStepOneThreads / 64];
+  const int ll = blockIdx.y, b = blockIdx.x / a.h_kv, g = blockIdx.x % a.h_kv;
+  const int threads = blockDim.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, kg = lane >> 4;
+  const int64_t head = blockIdx.x;
+  const StepBuffers buf = a.buffers(ll);
+  int32_t* st = buf.state + head * 4;
+  const int cur = st[0], free_slot = st[1], cur1 = cur + 1, n = cur1 + a.window, cap = a.cap[ll], half = a.pool / 2;
+  int32_t* order = buf.order + head * (cap + a.window + 1);
+  float* ind = buf.indicator + head * (cap + 1);
+  const T* q = reinterpret_cast<const T*>(a.q_new) + ll * a.qs[0] + b * a.qs[1] + (int64_t)(g * a.group + min(li, a.group - 1)) * a.qs[2];
+  const T* kn = reinterpret_cast<const T*>(a.k_new) + ll * a.ns[0] + b * a.ns[1] + g * a.ns[2];
+  T* ks = reinterpret_cast<T*>(buf.k_slots) + b * a.ss[ll][0] + g * a.ss[ll][1];
+  const int64_t tok = a.ss[ll][2];
+  // loaded up to what the buffers hold: no load waits for the state to say how much of it is in use
+  int32_t rows[4];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) rows[r] = order[min(wave * 64 + r * 16 + li, cap + a.window)];
+  StepFrags<T, D> qf;
+  load_queries<T, D>(qf, q, li, kg, a.group);
+  int32_t slot = order[min(tid, cap + a.window)], last_free = free_slot;
+  float val = ind[min(tid, cap)];
+  if (wave * 64 < n) {
+    const float2 own = wave_rows<T, D>(qf, rows, ks, kn, tok, wave * 64, n, a.c, li, kg, [&](int j0, const float4& x) {
+      if (li < a.group) *reinterpret_cast<float4*>(lg + li * kLd + j0) = x;
+    });
+    if (lane < a.group) red[wave][lane] = own;
+  }
+  if (wave == 0)
+    store_new_row<T, D>(a.v_new, ll * a.ns[0] + b * a.ns[1] + g * a.ns[2], kn, ks, reinterpret_cast<T*>(buf.v_slots) + b * a.ss[ll][0] + g * a.ss[ll][1],
+                        free_slot * tok, lane, 64);
+  asm volatile("" : "+v"(slot), "+v"(val), "+v"(last_free));       // have arrived: other waves write their places behind the barriers
+  __syncthreads();
+  for (int h = wave; h < a.group; h += threads >> 6) {   // a lane per 256 rows, as in step_finish_kernel
+    float rm[kWaves], rl[kWaves];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+      const int chunk = lane * kWaves + w;
+      const float2 y = chunk * 64 < n ? red[chunk][h] : make_float2(kMasked, 0.f);
+      rm[w] = y.x;
+      rl[w] = y.y;
+    }
+    const float norm = wave_normaliser(merge_pairs(rm, rl));
+    if (lane == 0) lse[h] = norm;
+  }
+  for (int i = tid; i < half; i += threads) obs[i] = obs[half + cur1 + i] = -INFINITY;      // clipped edges never win the max
+  float t[kGroup];
+#pragma unroll
+  for (int h = 0; h < kGroup; ++h) t[h] = lg[min(h, a.group - 1) * kLd + tid];
+  __syncthreads();
+  if (tid < cur1) obs[half + tid] = weight_sum(t, lse, a.group) * a.inv_g;
+  __syncthreads();
+  uint64_t best = 0;                                     // as in step_finish_kernel, from here on
+  if (tid < cur1) {
+    float mx = obs[half + tid];
+    for (int d = 1; d <= half; ++d) mx = fmaxf(mx, fmaxf(obs[half + tid - d], obs[half + tid + d]));
+    val = (tid < cur ? val : 0.f) + mx;
+    const uint32_t u = __float_as_uint(val + 0.f), key = u & 0x80000000u ? ~u : u | 0x80000000u;
+    best = (uint64_t)~key << 32 | (uint32_t)tid;
+  }
+  best = wave_scan(best, [](uint64_t x, uint64_t y) { return max(x, y); });
+  if (lane == 63) cand[wave] = best;
+  __syncthreads();
+  for (int w = 0; w < threads >> 6; ++w) best = max(best, cand[w]);
+  const int e = (int)(uint32_t)best;
+  if (tid >= n) return;
+  if (tid == n - 1) slot = last_free;
+  if (tid > e) order[tid - 1] = slot;
+  if (tid < cur1 && tid != e) ind[tid - (tid > e ? 1 : 0)] = val;
+  if (tid == e) {
+    st[1] = slot;
+    st[2] = e;
+  }
+  if (tid == n - 1) order[tid] = last_free;
+  if (tid == cur) ind[tid] = val;
 }
 
 // Caches of more rows than one workgroup holds: two more kernels.
@@ -873,8 +993,17 @@ int decode_step_impl(const cake_shape* shape, const cake_params* params,
   if (small) a.n_chunks *= kThreads / 64;
   const dim3 slices_grid(B * shape->n_kv_heads, L);
   const bool bf = shape->dtype == CAKE_BF16;
+  const bool whole = (int64_t)rows * shape->head_dim * eb <= kStepWholeBytes && rows <= kStepOneThreads;
   auto launch = [&](const auto& args) -> int {
     using Args = std::decay_t<decltype(args)>;
+    if (whole) {
+#define CAKE_WHOLE(T, D) (G <= 4 ? step_whole_kernel<T, D, 4, Args> : step_whole_kernel<T, D, kMaxGroup, Args>)
+      const auto one = bf ? (shape->head_dim == 128 ? CAKE_WHOLE(__bf16, 128) : CAKE_WHOLE(__bf16, 64))
+                          : (shape->head_dim == 128 ? CAKE_WHOLE(float, 128) : CAKE_WHOLE(float, 64));
+#undef CAKE_WHOLE
+      hipLaunchKernelGGL(one, slices_grid, dim3((rows + 63) / 64 * 64), 0, st, args);
+      return CAKE_OK;
+    }
 #define CAKE_STEP(T, D)                                                                                               \
   (small ? step_logits_kernel<T, D, 1, Args> : step_logits_kernel<T, D, kThreads / 64, Args>)
     const auto logits = bf ? (shape->head_dim == 128 ? CAKE_STEP(__bf16, 128) : CAKE_STEP(__bf16, 64))

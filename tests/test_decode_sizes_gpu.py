@@ -11,6 +11,7 @@ from gpu_util import assert_close, host64, load_cake, oracle_params, say
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
+STEP_WHOLE_BYTES = 128 << 10      # keys of a head that one workgroup takes in
 
 
 @pytest.fixture(scope="module")
@@ -154,3 +155,32 @@ def test_a_step_is_the_same_whatever_else_the_call_holds(cake, L, B, H_kv, G, d,
             for b in range(B):
                 for x, y in zip(by_layer.logical(l, b), alone[b].logical(l, 0)):
                     assert np.array_equal(x, y) if isinstance(x, np.ndarray) else torch.equal(x, y), (step, l, b)
+
+
+@pytest.mark.parametrize("G,d,S_w,dtype,B,pool", [(4, 128, 32, "bf16", 1, 7), (5, 128, 64, "bf16", 2, 129), (8, 64, 32, "bf16", 3, 13),
+                                                  (1, 128, 32, "f32", 1, 7), (7, 64, 64, "f32", 2, 1)])
+def test_short_lists_in_one_launch_equal_two(cake, G, d, S_w, dtype, B, pool):
+    """A call whose longest list is short does the step in one launch, beside a longer list in two: the same bits in every
+    buffer, at the edges of a wave's 64 rows, of 256 and of the longest list the one launch takes (counted with the window and the new row)."""
+    dt, eb = (torch.bfloat16, 2) if dtype == "bf16" else (torch.float32, 4)
+    longest = min(STEP_WHOLE_BYTES // (d * eb), 1024)
+    rows = [S_w + 1, S_w + 2, 127, 128, 129, 256, 257, longest - 1, longest, longest + 1, longest + 700]
+    caps = sorted({r - S_w - 1 for r in rows if r > S_w})
+    say(f"decode step in one launch and in two: G={G} d={d} S_w={S_w} {dtype} batch {B}, rows {rows}")
+    gen = torch.Generator().manual_seed(G + d)
+    H_kv, L = 2, len(caps)
+    keep = np.array([[max(c - 5 * b, 0) for b in range(B)] for c in caps])
+    mk = lambda c: torch.randn(B, H_kv, c + S_w, d, generator=gen).to(dt).to(DEV)
+    res = cake.PassResult(keep + S_w, keep, None, None, [], [], [mk(c) for c in caps], [mk(c) for c in caps],
+                          [torch.exp(torch.randn(B, H_kv, c, generator=gen) - 6.0).to(DEV) for c in caps])
+    together, by_layer = (cake.DecodeSlots(res, G * H_kv, S_w, cake.make_params(pool_kernel=pool)) for _ in range(2))
+    for step in range(4):
+        qn = (torch.randn(L, B, G * H_kv, d, generator=gen) * 2).to(dt).to(DEV)
+        kn, vn = (torch.randn(L, B, H_kv, d, generator=gen).to(dt).to(DEV) for _ in range(2))
+        together.step_all(qn, kn, vn)
+        for l in range(L):
+            by_layer.step(l, qn[l], kn[l], vn[l])
+        torch.cuda.synchronize()
+        for l in range(L):
+            for name in ("k", "v", "ind", "order", "state"):
+                assert torch.equal(getattr(together, name)[l], getattr(by_layer, name)[l]), (step, caps[l], name)
