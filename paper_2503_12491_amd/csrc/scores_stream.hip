@@ -21,6 +21,7 @@ constexpr int kSubKeys = 32;         // keys of a transfer, one MFMA sub-tile
 
 // A wave's ring of two transfers in LDS.  The transfers are written in assembly because the compiler takes any read of LDS for
 // one of a transfer in flight and waits for all of them; here a read waits for its own tile alone, and the one behind it stays under way.
+// Their place in LDS is an operand in m0: the compiler writes the register and knows it (the no-op keeps its write apart from its use).
 // Same layout and swizzle as the tiles of window_scores.hip.
 template <int D>
 struct KeyRing {
@@ -47,8 +48,8 @@ struct KeyRing {
 #pragma unroll
       for (int i = 0; i < kGroups; ++i) {
         const uint32_t off = row_off + (piece_off ^ (uint32_t)(((i * kRows) & (TL::kPieces - 1)) << 4));
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
-                     :: "s"(to + i * 1024), "v"(off), "s"(base + (int64_t)i * kRows * tok_bytes) : "memory");
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                     :: "{m0}"(to + i * 1024), "v"(off), "s"(base + (int64_t)i * kRows * tok_bytes) : "memory");
       }
     } else {                                     // rows past the last key are clamped to it
       int lane = this->lane;
@@ -57,7 +58,7 @@ struct KeyRing {
       for (int i = 0; i < kGroups; ++i) {
         const int off = i * 1024 + lane * 16, r = off / TL::kRowBytes, q = ((off % TL::kRowBytes) >> 4) ^ (r & (TL::kPieces - 1));
         const char* src = kbase + (int64_t)min(t0 + r, last_key) * tok_bytes + q * 16;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" :: "s"(to + i * 1024), "v"(src) : "memory");
+        asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" :: "{m0}"(to + i * 1024), "v"(src) : "memory");
       }
     }
   }
