@@ -193,8 +193,9 @@ constexpr int stream_waves(int pass, int head_dim, int mb, int group) {
 // 8 layers 46 + 54 and 44 + 47; 3 heads of 64 rows, pass 2, 8 layers 48 and 50, 16 layers 92 and 84; 4 heads, 16 layers 57 + 58 and
 // 70 + 67, 32 layers 107 + 121 and 109 + 116.
 constexpr int stream_min_keys(int mb, int group) { return mb == 2 ? 512 : group == 4 ? 2048 : 256; }
-void launch_stream_pass1(const ScoreArgs& a, int head_dim, int mb, unsigned gx, hipStream_t stream);
-void launch_stream_pass2(const ScoreArgs& a, int head_dim, int mb, bool pivot, unsigned gx, hipStream_t stream);
+constexpr int kStreamMaxGroup = 6;
+int launch_stream_pass1(const ScoreArgs& a, int head_dim, int mb, unsigned gx, hipStream_t stream);
+int launch_stream_pass2(const ScoreArgs& a, int head_dim, int mb, bool pivot, unsigned gx, hipStream_t stream);
 
 }  // namespace cake
 #endif

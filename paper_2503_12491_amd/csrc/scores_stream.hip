@@ -488,39 +488,36 @@ __global__ __launch_bounds__(64 * kWaves, 2) void stream_pass2(ScoreArgs a) {
 template <int D, int MB, int G>
 constexpr int held_blocks() { return G * MB < 512 / D ? G * MB : 512 / D; }      // row blocks in 128 registers
 
-template <int D, int MB, int G>
-void run_pass1(const ScoreArgs& a, unsigned gx, hipStream_t stream) {
-  constexpr int W = stream_waves(1, D, MB, G);
-  hipLaunchKernelGGL((stream_pass1<D, MB, G, held_blocks<D, MB, G>(), W>), dim3(gx, a.n_slices), dim3(64 * W), 0, stream, a);
+// The kernel of the group's size, where stream_waves says that there is one: no second list of sizes.
+template <int kPass, int D, int MB, bool kPivot, int G = 1>
+int run_group(const ScoreArgs& a, unsigned gx, hipStream_t stream) {
+  if constexpr (G > kStreamMaxGroup) {
+    return fail(CAKE_ERR_UNSUPPORTED, "no streaming score kernel for groups of %d", a.group);
+  } else {
+    if (a.group != G) return run_group<kPass, D, MB, kPivot, G + 1>(a, gx, stream);
+    constexpr int W = stream_waves(kPass, D, MB, G), H = held_blocks<D, MB, G>();
+    if constexpr (W == 0) {
+      return fail(CAKE_ERR_UNSUPPORTED, "no streaming kernel of pass %d for groups of %d, %d rows of %d", kPass, G, MB * 32, D);
+    } else {
+      if constexpr (kPass == 1) hipLaunchKernelGGL((stream_pass1<D, MB, G, H, W>), dim3(gx, a.n_slices), dim3(64 * W), 0, stream, a);
+      else hipLaunchKernelGGL((stream_pass2<D, MB, G, H, W, kPivot>), dim3(gx, a.n_slices), dim3(64 * W), 0, stream, a);
+      return CAKE_OK;
+    }
+  }
 }
-template <int D, int MB, int G>
-void run_pass2(const ScoreArgs& a, bool pivot, unsigned gx, hipStream_t stream) {
-  constexpr int W = stream_waves(2, D, MB, G), H = held_blocks<D, MB, G>();
-  if (pivot) hipLaunchKernelGGL((stream_pass2<D, MB, G, H, W, true>), dim3(gx, a.n_slices), dim3(64 * W), 0, stream, a);
-  else hipLaunchKernelGGL((stream_pass2<D, MB, G, H, W, false>), dim3(gx, a.n_slices), dim3(64 * W), 0, stream, a);
+template <int kPass, bool kPivot>
+int run_rows(const ScoreArgs& a, int head_dim, int mb, unsigned gx, hipStream_t stream) {
+  if (head_dim == 128) return mb == 1 ? run_group<kPass, 128, 1, kPivot>(a, gx, stream) : run_group<kPass, 128, 2, kPivot>(a, gx, stream);
+  return mb == 1 ? run_group<kPass, 64, 1, kPivot>(a, gx, stream) : run_group<kPass, 64, 2, kPivot>(a, gx, stream);
 }
 
 }  // namespace
 
-void launch_stream_pass1(const ScoreArgs& a, int head_dim, int mb, unsigned gx, hipStream_t stream) {
-  switch (head_dim * 100 + mb * 10 + a.group) {
-    case 12814: return run_pass1<128, 1, 4>(a, gx, stream);
-    case 12815: return run_pass1<128, 1, 5>(a, gx, stream);
-    case 12816: return run_pass1<128, 1, 6>(a, gx, stream);
-    case 6415: return run_pass1<64, 1, 5>(a, gx, stream);
-    case 6416: return run_pass1<64, 1, 6>(a, gx, stream);
-  }
+int launch_stream_pass1(const ScoreArgs& a, int head_dim, int mb, unsigned gx, hipStream_t stream) {
+  return run_rows<1, false>(a, head_dim, mb, gx, stream);
 }
-void launch_stream_pass2(const ScoreArgs& a, int head_dim, int mb, bool pivot, unsigned gx, hipStream_t stream) {
-  switch (head_dim * 100 + mb * 10 + a.group) {
-    case 12814: return run_pass2<128, 1, 4>(a, pivot, gx, stream);
-    case 12815: return run_pass2<128, 1, 5>(a, pivot, gx, stream);
-    case 12816: return run_pass2<128, 1, 6>(a, pivot, gx, stream);
-    case 12823: return run_pass2<128, 2, 3>(a, pivot, gx, stream);
-    case 6415: return run_pass2<64, 1, 5>(a, pivot, gx, stream);
-    case 6416: return run_pass2<64, 1, 6>(a, pivot, gx, stream);
-    case 6424: return run_pass2<64, 2, 4>(a, pivot, gx, stream);
-  }
+int launch_stream_pass2(const ScoreArgs& a, int head_dim, int mb, bool pivot, unsigned gx, hipStream_t stream) {
+  return pivot ? run_rows<2, true>(a, head_dim, mb, gx, stream) : run_rows<2, false>(a, head_dim, mb, gx, stream);
 }
 
 }  // namespace cake

@@ -886,29 +886,31 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     a.wg_keys = (int)(best * a.granule);
     return (unsigned)((granules + waves * best - 1) / (waves * best));
   };
-  auto run_pass1 = [&](int lo, int hi) {
+  auto run_pass1 = [&](int lo, int hi) -> int {
     if (const unsigned gx = set_stream(1, lo, hi)) return launch_stream_pass1(a, D, MB, gx, stream);
     const unsigned chunks = set_span(1, lo, hi);
     hipLaunchKernelGGL((scores_pass1<T, D, MB>), dim3(chunks, gy), block, 0, stream, a);
+    return CAKE_OK;
   };
-  auto run_pass2 = [&](int lo, int hi, bool combine) {
+  auto run_pass2 = [&](int lo, int hi, bool combine) -> int {
     if (const unsigned gx = set_stream(2, lo, hi)) return launch_stream_pass2(a, D, MB, kPivot, gx, stream);
     const unsigned chunks = set_span(2, lo, hi);
     if (combine) hipLaunchKernelGGL((scores_pass2<T, D, MB, kPivot, true>), dim3(chunks, gy), block, 0, stream, a);
     else hipLaunchKernelGGL((scores_pass2<T, D, MB, kPivot, false>), dim3(chunks, gy), block, 0, stream, a);
+    return CAKE_OK;
   };
   const int rows = a.group * MB * 32;
   const int64_t total_rows = n_slices * rows;
   if (parts != kPartsAll) {
     // the keys of this launch: those of [key_lo, key_hi) (pass 2: below n_p as well)
     const int hi1 = min(a.n, a.key_hi), hi2 = min(a.n_p, a.key_hi);
-    if (parts == kPartsPass1Segment)
-      run_pass1(a.key_lo, hi1);
-    else if (parts == kPartsCombine)
+    if (parts == kPartsPass1Segment) {
+      if (int rc = run_pass1(a.key_lo, hi1)) return rc;
+    } else if (parts == kPartsCombine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
-    else if (parts == kPartsPass2Segment && hi2 > a.key_lo)
-      run_pass2(a.key_lo, hi2, false);
-    else if (parts == kPartsPool)
+    else if (parts == kPartsPass2Segment && hi2 > a.key_lo) {
+      if (int rc = run_pass2(a.key_lo, hi2, false)) return rc;
+    } else if (parts == kPartsPool)
       hipLaunchKernelGGL(pool_indicator<false>, dim3((a.n_p + kPoolSpan - 1) / kPoolSpan, (unsigned)n_slices), dim3(256), 0,
                          stream, a, PrefArgs{}, 0);
     CAKE_HIP_TRY(hipGetLastError());
@@ -917,7 +919,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   mark(0, stream);
   bool combine = false;
   if (row_lse == nullptr && a.one.row_lse == nullptr) {
-    run_pass1(0, a.n);
+    if (int rc = run_pass1(0, a.n)) return rc;
     mark(1, stream);
     // every workgroup of pass 2 reads its slice's pairs where it combines them itself: at most 16 MB in all
     const int64_t workgroups = (int64_t)gy * set_span(2, 0, a.n_p);
@@ -931,7 +933,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     mark(1, stream);
   }
   mark(2, stream);
-  run_pass2(0, a.n_p, combine);
+  if (int rc = run_pass2(0, a.n_p, combine)) return rc;
   mark(3, stream);
   const unsigned spans = (a.n_p + kPoolSpan - 1) / kPoolSpan;
   const unsigned pref_rows = pref ? (pref->n_layers * pref->batch + spans - 1) / spans : 0;
