@@ -88,8 +88,9 @@ __device__ __forceinline__ WaveSpan wave_span(const ScoreArgs& a, int w, int n_w
   WaveSpan s;
   s.slice = blockIdx.y;
   slice_coords(a, s.slice, s.l, s.b, s.g);
-  s.key0 = a.key0 + (blockIdx.x * n_waves + w) * a.wg_keys;
-  s.key_end = min(s.key0 + a.wg_keys, end);
+  const int64_t at = a.key0 + ((int64_t)blockIdx.x * n_waves + w) * a.wg_keys;      // behind a layer of nearly 2^31 keys: beyond an int
+  s.key0 = (int)min(at, (int64_t)end);
+  s.key_end = (int)min(at + a.wg_keys, (int64_t)end);
   s.n_sub = (s.key_end - s.key0 + kSubKeys - 1) / kSubKeys;
   return s;
 }

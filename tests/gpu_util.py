@@ -95,3 +95,14 @@ def torch_row_lse(q_win_l: torch.Tensor, k_l: torch.Tensor, scale=None) -> torch
     hidden = torch.arange(N, device=s.device)[None, :] > pos_q[:, None]
     s = s.masked_fill(hidden, float("-inf"))
     return torch.logsumexp(s, dim=-1).view(B, H_q, S_w).float().contiguous()
+
+
+def kernels_of(call):
+    """Names of the kernels that `call` launches, in their order."""
+    from torch.profiler import ProfilerActivity, profile
+    torch.cuda.synchronize()
+    with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA], acc_events=True) as prof:
+        call()
+        torch.cuda.synchronize()
+    on_device = [e for e in prof.events() if e.device_type != torch.autograd.DeviceType.CPU]
+    return [e.name for e in sorted(on_device, key=lambda e: e.time_range.start) if not e.name.startswith(("Memcpy", "Memset"))]

@@ -3,7 +3,7 @@ workgroups (which combine pass 1's pairs inside pass 2) against launches of many
 import pytest
 import torch
 
-from gpu_util import assert_close, load_cake, oracle_layer, say
+from gpu_util import assert_close, kernels_of, load_cake, oracle_layer, say
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -131,3 +131,34 @@ def test_streamed_segments_give_the_bits_of_the_resident_call():
     ev.scores_segmented(8192)
     torch.cuda.synchronize()
     assert torch.equal(ev.indicator, want) and torch.equal(ev.hv, want_hv)
+
+
+def test_streamed_end_of_the_longest_layer():
+    """The last segment of a layer of nearly 2^31 keys, whose last workgroup has waves beyond them: the sums of the same keys in
+    short segments, and nothing written behind the last granule."""
+    from paper_2503_12491_amd import binding as C
+    cake = load_cake()
+    n, window, group, d = 2**31 - 2048 - 31, 32, 5, 64
+    lo, short = 2**31 - 4098 * 2048, 128 * 2048
+    say(f"streamed segment [{lo}, {n})")
+    q, k, _ = _inputs(1, group, 1, d, n - lo, window, torch.bfloat16, 3, 3.0)
+    k = k[0]
+    shape, params = C.make_shape(1, 1, group, 1, d, n, window, torch.bfloat16), cake.make_params()
+    assert C.cake_scores_chunk_keys(shape) == 2048
+    strides = lambda x: [x.stride(i) for i in range(3)]
+    ws = [torch.zeros(C.cake_workspace_bytes(shape), dtype=torch.uint8, device=DEV) for _ in range(2)]
+
+    def run(pass_, begin, end, to):
+        part = k[:, :, begin - lo:end - lo]
+        C.cake_window_scores_segment(shape, params, pass_, begin, end - begin, C.ptr_table(q), C.ptr_table([part]), strides(q[0]), strides(part), to)
+
+    for pass_ in (1, 2):
+        names = kernels_of(lambda: run(pass_, lo, n, ws[0]))
+        assert len(names) == 1 and f"stream_pass{pass_}" in names[0], names
+        for begin in range(lo, n, short):
+            run(pass_, begin, min(begin + short, n), ws[1])
+        torch.cuda.synchronize()
+        assert torch.equal(ws[0], ws[1]), pass_
+        if pass_ == 1:
+            for w in ws:
+                C.cake_window_scores_finish(shape, params, 1, None, w)
