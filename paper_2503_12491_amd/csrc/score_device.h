@@ -172,27 +172,48 @@ __device__ __forceinline__ float pass2_tile_stats(const ColSums& s0, const ColSu
   return column_indicator<kPivot>(sp, sp2, hh ? s1.pivot : s0.pivot, a, var_acc);
 }
 
-// The streaming kernels (scores_stream.hip): waves of a workgroup, 0 where there is no such kernel.  There is one where it is
-// faster than a wave per head: groups that leave the four SIMDs of a compute unit unevenly loaded, and by less a group of four
-// heads of 32 rows.  Us of pass 1 + pass 2, a wave per head (groups of 5 and 6: three or two slices a workgroup to even them
-// out) and streaming, 16 layers of 4 x 8 key heads of 32749 keys:
-//   32 rows of 128  4 heads 755 + 911, 728 + 861    5 heads 978 + 1190, 816 + 1004    6 heads 1147 + 1383, 970 + 1195
-//                   3 heads 673 + 820, 696 + 787    2 heads 639 + 744, 662 + 765      1 head  624 + 734, 641 + 752
-//   32 rows of 64   4 heads 432 + 628, 461 + 634    5 heads 678 + 868, 526 + 723      6 heads 615 + 1045, 623 + 837
-//   64 rows of 128  3 heads 947 + 1430, 1001 + 1213    4 heads (32 layers of 8 x 131072 keys) pass 1 2187, 2450
-//   64 rows of 64   4 heads (likewise) 1466 + 2297, 1510 + 2038
+// Three forms of a pass over bf16 keys, to the same bits: a wave per head of a group, the group a workgroup; slices packed three
+// (groups of 5) or two (of 6) to a workgroup, which loads the four SIMDs of a compute unit evenly; waves that stream keys of their
+// own through all heads (scores_stream.hip), which do that too, without barriers, but take whole granules of keys each: 2048 waves
+// fill the chip.  Groups of other sizes load the SIMDs evenly with a wave per head and have no other form; streaming was
+// slower there, in pass 2 of two sizes of 64 rows apart (32 rows of 128, 4 heads, 12 to 33 million keys: pass 1 0.98-1.11 and pass 2 0.93-1.06 of a
+// wave per head; 64 of 128, 4 heads, pass 1 2450 us for 2187).
+//
+// Waves of a streaming workgroup, 0 where there is no such kernel.
 constexpr int stream_waves(int pass, int head_dim, int mb, int group) {
-  if (head_dim == 128 && mb == 1) return group == 4 || group == 5 ? 4 : group == 6 ? 8 : 0;
+  if (head_dim == 128 && mb == 1) return group == 5 ? 4 : group == 6 ? 8 : 0;
   if (head_dim == 64 && mb == 1) return group == 5 || group == 6 ? 4 : 0;
   if (pass == 2 && head_dim == 128) return group == 3 ? 8 : 0;
   if (pass == 2 && head_dim == 64) return group == 4 ? 4 : 0;
   return 0;
 }
-// Keys that each of 2048 waves has to have: below, a wave that does all heads of its keys takes longer than a workgroup that
-// does them side by side.  Layers of 8 x 8192 keys, wave per head and streaming, us: 5 heads of 128, 4 layers 28 + 24 and 26 + 29,
-// 8 layers 46 + 54 and 44 + 47; 3 heads of 64 rows, pass 2, 8 layers 48 and 50, 16 layers 92 and 84; 4 heads, 16 layers 57 + 58 and
-// 70 + 67, 32 layers 107 + 121 and 109 + 116.
-constexpr int stream_min_keys(int mb, int group) { return mb == 2 ? 512 : group == 4 ? 2048 : 256; }
+// What a launch takes: nanoseconds per key of a workgroup (streaming: of a wave) in a round that has up to 1, 2 or 3 workgroups a
+// compute unit (packed: one; streaming: as many as make 4 or 8 waves); 0: no such kernel.  Fitted, to 6-13 %, to launches of each form
+// with all its spans over 140 thousand to 8.4 million keys (a call's slices together) in layers of 1100 to 131072.  The shape of it: a key
+// costs by the fullest SIMD, so that a second workgroup of 5 or 6 waves comes at half the price of the first, and streaming pays from
+// half the chip's waves on.  Us of pass 1 + pass 2 packed and streaming, slices x keys: 5 heads of 128, 367 x 32749 697 + 842, 591 + 728,
+// but 21 x 32749 45 + 52, 54 + 68; 6 heads, 367 x 32749 817 + 968, 691 + 850, but 43 x 16424 66 + 78, 91 + 114; pass 2 of 5 heads,
+// 127 x 2100: 30 packed, 37 with a wave per head.  Chosen so, a launch takes 1.004 to 1.03 times the fastest form's time on
+// average over those sizes.  Streaming counts 6 % more than it takes, for what the fit is off.  Pass 1 of 5 heads has no packed
+// kernel: of three slices at a few sizes the fastest by up to 7 %, but at more of them, under the same rule, the slower choice.
+struct FormRates {
+  int per_head[3], packed, stream[2];
+};
+constexpr FormRates form_rates(int pass, int head_dim, int mb, int group) {
+  if (mb == 1 && head_dim == 128) {
+    if (group == 5) return pass == 1 ? FormRates{{18, 26, 34}, 0, {41, 76}} : FormRates{{23, 34, 49}, 42, {53, 88}};
+    if (group == 6) return pass == 1 ? FormRates{{18, 29, 39}, 26, {79, 0}} : FormRates{{24, 38, 55}, 34, {100, 0}};
+  }
+  if (mb == 1 && head_dim == 64) {
+    if (group == 5) return pass == 1 ? FormRates{{13, 18, 19}, 0, {31, 46}} : FormRates{{19, 27, 31}, 30, {44, 59}};
+    if (group == 6) return pass == 1 ? FormRates{{13, 21, 22}, 14, {36, 53}} : FormRates{{19, 30, 40}, 25, {50, 68}};
+  }
+  if (pass == 2 && mb == 2 && head_dim == 128 && group == 3) return FormRates{{24, 36, 50}, 0, {104, 0}};
+  if (pass == 2 && mb == 2 && head_dim == 64 && group == 4) return FormRates{{21, 31, 40}, 0, {63, 90}};
+  return FormRates{};
+}
+// A workgroup's prologue (its queries, the first tile's way from memory) in keys.
+constexpr int kFormPrologue = 128, kStreamPrologue = 192;
 constexpr int kStreamMaxGroup = 6;
 int launch_stream_pass1(const ScoreArgs& a, int head_dim, int mb, unsigned gx, hipStream_t stream);
 int launch_stream_pass2(const ScoreArgs& a, int head_dim, int mb, bool pivot, unsigned gx, hipStream_t stream);

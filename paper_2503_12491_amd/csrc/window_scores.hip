@@ -21,7 +21,8 @@
 //   pref    fixed-order fp64 reduction of the per-granule entropy/variance sums    -> P_l, H_l, V_l
 //
 // One workgroup = G wavefronts = one or more granules of keys of one slice; wave w serves query head
-// g*G + w (large launches of some group sizes: scores_stream.hip, to the same bits).  K tiles of 64 keys go from global memory straight into LDS (global_load_lds, 16
+// g*G + w (packed kernels: several slices a workgroup; large launches of some group sizes: scores_stream.hip; all to the same
+// bits).  K tiles of 64 keys go from global memory straight into LDS (global_load_lds, 16
 // bytes per lane), double-buffered so that tile t+1 is in flight while tile t is consumed, and
 // are shared by the G waves.  Rows are stored unpadded with their 16-byte pieces XOR-swizzled by
 // the row index so that the MFMA operand reads spread over the banks.
@@ -142,19 +143,37 @@ __device__ __forceinline__ void pass1_sums(const f32x16 (&acc)[MB], int kb, floa
   }
 }
 
-template <typename T, int D, int MB>
-__global__ __launch_bounds__(512) void scores_pass1(ScoreArgs a) {
+// Packed kernels (kSlices > 1): as many slices share a workgroup, G waves each, every slice with tile buffers of its own.  A
+// workgroup's waves are dealt over the compute unit's four SIMDs in turn, so that a group of 5 or 6 heads alone leaves two waves on
+// one SIMD and one on the others, and the barriers make every wave wait for the doubled SIMD; three slices of 5 waves (or two of
+// 6) fill the SIMDs almost evenly.  Slices past the last one (the final workgroup) repeat the last slice's work and store nothing.
+struct WaveRole {
+  int slice, w;      // the wave's slice and its head within the group
+  int sub;           // the slice's place in the workgroup
+  bool live;         // false: a repeat of the last slice, stores nothing
+};
+template <int kSlices>
+__device__ __forceinline__ WaveRole wave_role(const ScoreArgs& a) {
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);       // wave index, known uniform
+  if (kSlices == 1) return WaveRole{(int)blockIdx.y, w, 0, true};
+  const int sub = w / a.group, slice = blockIdx.y * kSlices + sub;
+  return WaveRole{min(slice, a.n_slices - 1), w - sub * a.group, sub, slice < a.n_slices};
+}
+
+template <typename T, int D, int MB, int kSlices = 1>
+__global__ __launch_bounds__(kSlices > 1 ? 1024 : 512) void scores_pass1(ScoreArgs a) {
   using F = Frag<T>;
   using TL = Tile<T, D>;
   constexpr int kSteps = D / F::kElems;
   // double buffer: tile t+1 is in flight while tile t is consumed (rings of three and four tiles
   // measured no faster, with waits for the oldest tile alone as well)
-  __shared__ __attribute__((aligned(1024))) char tiles[2 * TL::kBytes];
+  __shared__ __attribute__((aligned(1024))) char all_tiles[kSlices * 2 * TL::kBytes];
 
-  const int slice = blockIdx.y;
+  const WaveRole role = wave_role<kSlices>(a);
+  const int slice = role.slice, w = role.w;
   int l, b, g;
   slice_coords(a, slice, l, b, g);
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);       // wave index, known uniform
+  char* tiles = all_tiles + role.sub * (2 * TL::kBytes);
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
@@ -193,7 +212,7 @@ __global__ __launch_bounds__(512) void scores_pass1(ScoreArgs a) {
 #pragma unroll
     for (int nb = 0; nb < MB; ++nb) {
       const float2 pair = merge_halves(mref[nb], lsum[nb]);
-      if (hh == 0) *reinterpret_cast<float2*>(o + (nb * 32 + c32) * 2) = pair;
+      if (hh == 0 && role.live) *reinterpret_cast<float2*>(o + (nb * 32 + c32) * 2) = pair;
       mref[nb] = 0.f;
       lsum[nb] = 0.f;
     }
@@ -456,22 +475,23 @@ __device__ __forceinline__ void pass2_period(const char* tile, int sub,
 // 32.4 -> 29.7 us with it, 512 workgroups of 8 layers of 1000 keys 32.9 -> 33.9.
 template <typename T, int MB> constexpr bool kPipelinedForm = sizeof(T) == 2 && MB == 2;
 
-template <typename T, int D, int MB, bool kPivot, bool kCombine>
-__global__ __launch_bounds__(512) void scores_pass2(ScoreArgs a) {
+template <typename T, int D, int MB, bool kPivot, bool kCombine, int kSlices = 1>
+__global__ __launch_bounds__(kSlices > 1 ? 1024 : 512) void scores_pass2(ScoreArgs a) {
   using F = Frag<T>;
   using TL = Tile<T, D>;
   constexpr int kSteps = D / F::kElems;
   // double buffer: tile t+1 is in flight while tile t is consumed (deeper rings measured no faster)
-  __shared__ __attribute__((aligned(1024))) char tiles[2 * TL::kBytes];
+  __shared__ __attribute__((aligned(1024))) char all_tiles[kSlices * 2 * TL::kBytes];
   // I_q of the G heads for two tiles in turn: the flush of one tile reads one buffer in the
   // stage in which the other is written, and a barrier separates the stages
-  __shared__ float iq_lds[2][8][kTileKeys];
+  __shared__ float iq_lds[2][kSlices > 1 ? 16 : 8][kTileKeys];
 
-  const int slice = blockIdx.y;
+  const WaveRole role = wave_role<kSlices>(a);
+  const int slice = role.slice, w = role.w;
   int l, b, g;
   slice_coords(a, slice, l, b, g);
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);       // wave index, known uniform
-  auto iq_row = [&](int buf, int wave) { return iq_lds[buf][wave]; };
+  char* tiles = all_tiles + role.sub * (2 * TL::kBytes);
+  auto iq_row = [&](int buf, int wave) { return iq_lds[buf][role.sub * a.group + wave]; };
   const int lane = threadIdx.x & 63, c32 = lane & 31, hh = lane >> 5;
   const int n_waves = a.group;
   constexpr int s_w = MB * 32;
@@ -537,14 +557,14 @@ __global__ __launch_bounds__(512) void scores_pass2(ScoreArgs a) {
     const int key = key0 + t * kTileKeys + lane;
     float s = 0.f;
     for (int ww = 0; ww < a.group; ++ww) s += iq_row(t & 1, ww)[lane];
-    if (key < key_end) raw[key] = s * a.inv_g;
+    if (key < key_end && role.live) raw[key] = s * a.inv_g;
   };
   // Entropy and variance sums of the granule that ends with tile t.
   const int granule_shift = __builtin_ctz(a.granule), granule_tiles = a.granule / kTileKeys;      // powers of two
   auto finish = [&](int t) {
     const float ent = wave_sum((entv[0] + entv[1]) * cv), var = wave_sum(var_acc);
     const int64_t granule = (key0 + t * kTileKeys) >> granule_shift;
-    if (lane == 0)
+    if (lane == 0 && role.live)
       *reinterpret_cast<float2*>(a.hv + (((int64_t)slice * a.n_granules_p + granule) * a.group + w) * 2) = make_float2(ent, var);
     entv[0] = entv[1] = var_acc = 0.f;
   };
@@ -868,35 +888,71 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     a.wg_keys = best * a.granule;
     return (unsigned)((hi - lo + a.wg_keys - 1) / a.wg_keys);
   };
-  // Launches with enough keys for each of the 2048 waves that the chip holds of them take the streaming kernels (stream_min_keys),
-  // a whole number of granules a wave, at most 4096 keys: as many as leave the fewest keys in the longest place, where a
-  // workgroup's prologue counts as 96.  (4 x 5 heads of 32749 keys, 16 layers: 830 + 1010 us with 1024 or 2048 keys a wave,
-  // 815 + 980 with 4096, 825 + 1010 with 8192 in a single round.)
-  auto set_stream = [&](int pass, int lo, int hi) -> unsigned {
-    const int waves = sizeof(T) == 2 ? stream_waves(pass, D, MB, a.group) : 0;
-    if (waves == 0 || n_slices * (hi - lo) < 2048 * (int64_t)stream_min_keys(MB, a.group)) return 0;
-    const int64_t granules = (hi - lo + a.granule - 1) / a.granule, slots = 2048 / std::max(waves, 1);
-    int64_t least = INT64_MAX, best = 1;
-    for (int64_t per = 1; per <= granules && per * a.granule <= 4096; ++per) {
-      const int64_t workgroups = n_slices * ((granules + waves * per - 1) / (waves * per));
-      const int64_t cost = (workgroups + slots - 1) / slots * (per * a.granule + 96);
-      if (cost < least) { least = cost; best = per; }
-    }
-    a.key0 = lo;
-    a.wg_keys = (int)(best * a.granule);
-    return (unsigned)((granules + waves * best - 1) / (waves * best));
+  // The form of a launch and its keys per workgroup (per wave where waves stream): the cheapest by form_rates where the group
+  // has more than one.  Launches of few granules take a wave per head: their granules on compute units of their own are done
+  // sooner than packed ones (8 x 8192 keys, 5 heads of 128: pass 1 16.0 -> 12.4 us, pass 2 27 -> 17.6; 16384 keys 37 -> 27
+  // and 50 -> 35), pass 2 may combine the pairs by itself, and of fewer granules than a quarter of the streaming waves streaming never was the fastest.
+  enum Form { kPerHead, kPacked, kStreaming };
+  struct Launch {
+    Form form;
+    unsigned gx;
+    int key0, wg_keys;
   };
-  auto run_pass1 = [&](int lo, int hi) -> int {
-    if (const unsigned gx = set_stream(1, lo, hi)) return launch_stream_pass1(a, D, MB, gx, stream);
-    const unsigned chunks = set_span(1, lo, hi);
-    hipLaunchKernelGGL((scores_pass1<T, D, MB>), dim3(chunks, gy), block, 0, stream, a);
+  const int pack = a.group == 5 ? 3 : 2;          // slices of a packed workgroup
+  auto choose = [&](int pass, int lo, int hi) -> Launch {
+    const FormRates rates = sizeof(T) == 2 ? form_rates(pass, D, MB, a.group) : FormRates{};
+    const int64_t granules = ((int64_t)hi - lo + a.granule - 1) / a.granule;
+    if (rates.per_head[0] == 0 || n_slices * granules <= 512) {
+      const unsigned gx = set_span(pass, lo, hi);
+      return Launch{kPerHead, gx, a.key0, a.wg_keys};
+    }
+    int64_t least = INT64_MAX;
+    Launch best{};
+    auto consider = [&](Form form, int64_t per, int64_t gx, int64_t rows, const int* rate, int places, int prologue) {
+      const int64_t slots = 256 * places, whole = gx * rows / slots, left = gx * rows % slots;
+      const int64_t cost = (per * a.granule + prologue) * (whole * rate[places - 1] + (left ? rate[(left + 255) / 256 - 1] : 0));
+      if (cost >= least) return;
+      least = cost;
+      best = Launch{form, (unsigned)gx, lo, (int)(per * a.granule)};
+    };
+    for (int per = a.chunk / a.granule; per >= 1; per >>= 1) {
+      const int64_t gx = (granules + per - 1) / per;
+      consider(kPerHead, per, gx, n_slices, rates.per_head, 3, kFormPrologue);
+      if (rates.packed) consider(kPacked, per, gx, (n_slices + pack - 1) / pack, &rates.packed, 1, kFormPrologue);
+    }
+    const int waves = stream_waves(pass, D, MB, a.group);
+    if (waves > 0)
+      for (int64_t per = 1; per <= granules && per * a.granule <= 4096; ++per)
+        consider(kStreaming, per, (granules + waves * per - 1) / (waves * per), n_slices, rates.stream, 8 / waves, kStreamPrologue);
+    return best;
+  };
+  // packed3, packed2: kernels of three and two slices a workgroup.
+  auto run = [&](const Launch& launch, auto per_head, auto packed3, auto packed2) {
+    a.key0 = launch.key0;
+    a.wg_keys = launch.wg_keys;
+    if (launch.form == kPacked)
+      hipLaunchKernelGGL(pack == 3 ? packed3 : packed2, dim3(launch.gx, (gy + pack - 1) / pack), dim3(64 * a.group * pack), 0, stream, a);
+    else
+      hipLaunchKernelGGL(per_head, dim3(launch.gx, gy), block, 0, stream, a);
+  };
+  constexpr bool kPacks = sizeof(T) == 2 && MB == 1;      // (where no rates pack, the kernel of one slice stands in for the others)
+  auto run_pass1 = [&](const Launch& launch) -> int {
+    if (launch.form == kStreaming) {
+      a.key0 = launch.key0;
+      a.wg_keys = launch.wg_keys;
+      return launch_stream_pass1(a, D, MB, launch.gx, stream);
+    }
+    run(launch, scores_pass1<T, D, MB, 1>, scores_pass1<T, D, MB, 1>, scores_pass1<T, D, MB, kPacks ? 2 : 1>);
     return CAKE_OK;
   };
-  auto run_pass2 = [&](int lo, int hi, bool combine) -> int {
-    if (const unsigned gx = set_stream(2, lo, hi)) return launch_stream_pass2(a, D, MB, kPivot, gx, stream);
-    const unsigned chunks = set_span(2, lo, hi);
-    if (combine) hipLaunchKernelGGL((scores_pass2<T, D, MB, kPivot, true>), dim3(chunks, gy), block, 0, stream, a);
-    else hipLaunchKernelGGL((scores_pass2<T, D, MB, kPivot, false>), dim3(chunks, gy), block, 0, stream, a);
+  auto run_pass2 = [&](const Launch& launch, bool combine) -> int {
+    if (launch.form == kStreaming) {
+      a.key0 = launch.key0;
+      a.wg_keys = launch.wg_keys;
+      return launch_stream_pass2(a, D, MB, kPivot, launch.gx, stream);
+    }
+    run(launch, combine ? scores_pass2<T, D, MB, kPivot, true, 1> : scores_pass2<T, D, MB, kPivot, false, 1>,
+        scores_pass2<T, D, MB, kPivot, false, kPacks ? 3 : 1>, scores_pass2<T, D, MB, kPivot, false, kPacks ? 2 : 1>);
     return CAKE_OK;
   };
   const int rows = a.group * MB * 32;
@@ -905,11 +961,11 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     // the keys of this launch: those of [key_lo, key_hi) (pass 2: below n_p as well)
     const int hi1 = min(a.n, a.key_hi), hi2 = min(a.n_p, a.key_hi);
     if (parts == kPartsPass1Segment) {
-      if (int rc = run_pass1(a.key_lo, hi1)) return rc;
+      if (int rc = run_pass1(choose(1, a.key_lo, hi1))) return rc;
     } else if (parts == kPartsCombine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
     else if (parts == kPartsPass2Segment && hi2 > a.key_lo) {
-      if (int rc = run_pass2(a.key_lo, hi2, false)) return rc;
+      if (int rc = run_pass2(choose(2, a.key_lo, hi2), false)) return rc;
     } else if (parts == kPartsPool)
       hipLaunchKernelGGL(pool_indicator<false>, dim3((a.n_p + kPoolSpan - 1) / kPoolSpan, (unsigned)n_slices), dim3(256), 0,
                          stream, a, PrefArgs{}, 0);
@@ -917,13 +973,14 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     return CAKE_OK;
   }
   mark(0, stream);
+  const Launch second = choose(2, 0, a.n_p);
   bool combine = false;
   if (row_lse == nullptr && a.one.row_lse == nullptr) {
-    if (int rc = run_pass1(0, a.n)) return rc;
+    if (int rc = run_pass1(choose(1, 0, a.n))) return rc;
     mark(1, stream);
     // every workgroup of pass 2 reads its slice's pairs where it combines them itself: at most 16 MB in all
-    const int64_t workgroups = (int64_t)gy * set_span(2, 0, a.n_p);
-    combine = !set_stream(2, 0, a.n_p) && workgroups * rows * a.n_granules * 8 <= 16 << 20 && (!kPipelinedForm<T, MB> || workgroups <= 256);
+    const int64_t workgroups = (int64_t)gy * second.gx;
+    combine = second.form == kPerHead && workgroups * rows * a.n_granules * 8 <= 16 << 20 && (!kPipelinedForm<T, MB> || workgroups <= 256);
     if (!combine)
       hipLaunchKernelGGL(scores_combine, dim3((unsigned)((total_rows * 4 + 255) / 256)), dim3(256), 0, stream, a, rows, total_rows);
   } else {
@@ -933,7 +990,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     mark(1, stream);
   }
   mark(2, stream);
-  if (int rc = run_pass2(0, a.n_p, combine)) return rc;
+  if (int rc = run_pass2(second, combine)) return rc;
   mark(3, stream);
   const unsigned spans = (a.n_p + kPoolSpan - 1) / kPoolSpan;
   const unsigned pref_rows = pref ? (pref->n_layers * pref->batch + spans - 1) / spans : 0;

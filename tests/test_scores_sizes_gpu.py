@@ -1,5 +1,7 @@
 """The score passes at the sizes where their forms change: element types and row blocks, and launches of a few
 workgroups (which combine pass 1's pairs inside pass 2) against launches of many (some of which stream)."""
+import re
+
 import pytest
 import torch
 
@@ -46,7 +48,7 @@ def _combines(slices, dtype, window, group, n):
     chunk, granule = _granules(n, window)
     n_p = n - window
     if dtype == torch.bfloat16 and window == 32 and group in (5, 6) and slices * n_p >= 2048 * 256:
-        return False                               # waves that stream do not
+        return False                               # packed slices and waves that stream do not
     pairs = group * window * -(-n // granule) * 8
     piped = dtype == torch.bfloat16 and window == 64
     fits = lambda workgroups: workgroups * pairs <= 16 << 20 and (not piped or workgroups <= 256)
@@ -84,35 +86,57 @@ def test_a_layer_alone_scores_to_the_same_bits_as_among_many(dtype, window, grou
         assert torch.equal(alone.hv[0, 0], many.hv[0, l]) and torch.equal(alone.pref[0, 0], many.pref[0, l])
 
 
+def _form(names, pass_, group):
+    """Which form of a score pass ran: streaming, slices packed by the kernel's last argument, or a wave per head."""
+    mine = [n for n in names if f"_pass{pass_}" in n]
+    assert len(mine) == 1, names
+    if "stream_pass" in mine[0]:
+        return "stream"
+    m = re.search(r"Li(\d+)EEEv|, (\d+)>\(", mine[0])
+    slices = int(m[1] or m[2])
+    assert slices in (1, {5: 3, 6: 2}.get(group, 1)), mine
+    return "packed" if slices > 1 else "head"
+
+
 @pytest.mark.parametrize("mode", [0, 2])            # sums of the weights; about a pivot
-@pytest.mark.parametrize("window,group,d,n,layers", [
-    (32, 4, 128, 1000, 545),       # 8 x 545 x 968 keys: where groups of four begin to stream
-    (32, 5, 128, 32 + 97, 1010),   # a tile with one key in its second half, keys past the prefix in the same one
-    (32, 5, 128, 4093, 34),        # whole granules of 256 and a ragged one
-    (32, 6, 128, 16384 + 31, 6),   # granules of 1024
-    (32, 5, 64, 193, 700),
-    (32, 6, 64, 2048, 66),
-    (64, 3, 128, 2100, 70),        # pass 2 alone streams
-    (64, 4, 64, 193 + 64, 820),
+@pytest.mark.parametrize("window,group,d,h_kv,n,layers,forms", [
+    (32, 5, 128, 8, 1025, 60, ("stream", "stream")),     # a tile with one key in its second half, keys past the prefix in the same one
+    (32, 5, 128, 8, 4093, 30, ("stream", "stream")),     # whole granules of 256 and a ragged one
+    (32, 5, 128, 8, 2100, 19, ("head", "packed")),       # 152 slices: the last workgroup repeats one
+    (32, 6, 128, 8, 8231, 28, ("stream", "stream")),
+    (32, 6, 128, 9, 16384 + 31, 13, ("packed", "stream")),     # granules of 1024; 117 slices, one repeated
+    (32, 6, 128, 9, 225, 17, ("packed", "packed")),
+    (32, 5, 64, 8, 4093, 29, ("stream", "stream")),
+    (32, 5, 64, 8, 2100, 34, ("head", "packed")),
+    (32, 6, 64, 8, 4093, 16, ("packed", "stream")),
+    (32, 6, 64, 9, 225, 17, ("packed", "packed")),
+    (64, 3, 128, 8, 4093, 25, ("head", "stream")),
+    (64, 4, 64, 8, 2047, 29, ("head", "stream")),
 ])
-def test_waves_that_stream_give_the_bits_of_a_layer_alone(window, group, d, n, layers, mode):
-    """Launches beyond the line of the streaming kernels against one layer, which is below it."""
+def test_every_form_of_the_passes_gives_the_bits_of_a_layer_alone(window, group, d, h_kv, n, layers, forms, mode):
+    """Launches that stream, or pack slices, against a layer alone with a wave per head, and against the oracle; their queries and
+    keys in the order [B, N, H, d], the layer's alone contiguous."""
     cake = load_cake()
-    say(f"streaming scores S_w={window} G={group} d={d} N={n} layers={layers} mode={mode}")
-    h_kv, n_p = 8, n - window
-    line = 2048 * (512 if window == 64 else 2048 if group == 4 else 256)
-    assert h_kv * n < line <= h_kv * layers * n_p
+    say(f"forms of the score passes S_w={window} G={group} d={d} N={n} layers={layers} mode={mode}")
     q, k, v = _inputs(2, h_kv * group, h_kv, d, n, window, torch.bfloat16, n + group, 6.0)
+    tokens_first = lambda xs: [x.transpose(1, 2).contiguous().transpose(1, 2) for x in xs]
+    qt, kt, vt = tokens_first(q), tokens_first(k), tokens_first(v)
     params = cake.make_params(indicator_mode=mode)
-    many = cake.EvictionPass([q[i % 2] for i in range(layers)], [k[i % 2] for i in range(layers)], [v[i % 2] for i in range(layers)],
+    many = cake.EvictionPass([qt[i % 2] for i in range(layers)], [kt[i % 2] for i in range(layers)], [vt[i % 2] for i in range(layers)],
                              layers * window, params)
-    many.scores()
+    assert many.k[0].stride(2) == h_kv * d
+    names = kernels_of(many.scores)
+    assert (_form(names, 1, group), _form(names, 2, group)) == forms, names
     for l in range(2):
         alone = cake.EvictionPass(q[l:l + 1], k[l:l + 1], v[l:l + 1], window, params)
-        alone.scores()
+        names = kernels_of(alone.scores)
+        assert (_form(names, 1, group), _form(names, 2, group)) == ("head", "head"), names
         assert torch.equal(alone.indicator[0], many.indicator[l])
         assert torch.equal(alone.indicator[0], many.indicator[l + 2 * ((layers - 1 - l) // 2)])
         assert torch.equal(alone.hv[0, 0], many.hv[0, l]) and torch.equal(alone.pref[0, 0], many.pref[0, l])
+    want = oracle_layer(q[1][0], k[1][0], params)
+    assert_close(many.indicator[1, 0].cpu().numpy(), want["indicator"], "indicator")
+    assert_close(many.hv[0, 1].cpu().numpy(), [want["H"], want["V"]], "H, V")
 
 
 def test_streamed_segments_give_the_bits_of_the_resident_call():
@@ -122,14 +146,14 @@ def test_streamed_segments_give_the_bits_of_the_resident_call():
     say(f"streamed segments {layers} layers of {n} keys")
     q, k, v = _inputs(1, h_kv * group, h_kv, d, n, window, torch.bfloat16, 5, 3.0)
     ev = cake.EvictionPass(q * layers, k * layers, v * layers, layers * window)
-    assert layers * h_kv * 8192 >= 2048 * 256
     ev.scores()
     torch.cuda.synchronize()
     want, want_hv = ev.indicator.clone(), ev.hv.clone()
     ev.workspace.fill_(0xFF)
     ev.indicator.fill_(float("nan"))
-    ev.scores_segmented(8192)
-    torch.cuda.synchronize()
+    names = kernels_of(lambda: ev.scores_segmented(8192))
+    for pass_ in (1, 2):
+        assert sum(f"stream_pass{pass_}" in n for n in names) >= 3, names
     assert torch.equal(ev.indicator, want) and torch.equal(ev.hv, want_hv)
 
 
@@ -139,7 +163,7 @@ def test_streamed_end_of_the_longest_layer():
     from paper_2503_12491_amd import binding as C
     cake = load_cake()
     n, window, group, d = 2**31 - 2048 - 31, 32, 5, 64
-    lo, short = 2**31 - 4098 * 2048, 128 * 2048
+    lo, short = 2**31 - 4091 * 2048, 128 * 2048
     say(f"streamed segment [{lo}, {n})")
     q, k, _ = _inputs(1, group, 1, d, n - lo, window, torch.bfloat16, 3, 3.0)
     k = k[0]
