@@ -720,7 +720,11 @@ __global__ __launch_bounds__(kLongThreads) void select_topk_long_kernel(TopkArgs
 //    4000     7.4   8.5  13.8      5.9   6.8  13.3     5.8   6.6  23.4
 //    6000     9.7  10.0            7.4   7.9           7.7   8.1
 //    8100    11.4  11.8  19.9      8.5   9.1  19.2     8.0   8.5  29.8
-//   16300                         12.0  15.5          10.3  13.0        (in a pass of 256 rows 512 threads are the faster)
+//   16300                         12.0  15.5          10.3  13.0
+// In a pass, where workgroups beside the rows write the plan's copy, 1024 threads are not the faster at 256 rows: 5000, 6000, 8100, 9000
+// and 16300 entries 9.0, 9.4, 11.0, 13.0 and 15.4 us with 512 threads, 12.2, 12.7, 13.2, 15.0 and 17.5 with 1024; at 128 rows of
+// 9000 and 16000 entries 12.0 and 14.8, 10.6 and 12.4.  (1024 threads with two slots would save half a microsecond at 8 rows of
+// 8100: not built.)
 // Where `most` is only what the caller's shape suggests (!bounded: the lengths are device data), rows that do not fit it are
 // left out by that kernel and served by the one for any length, launched behind it.
 template <bool kPlanned>
@@ -733,7 +737,8 @@ int launch_topk(dim3 grid, int64_t most, bool bounded, const TopkArgs<kPlanned>&
     hipLaunchKernelGGL((select_topk_kernel<kPlanned, T, S>), grid, dim3(T), 0, stream, a, dims, plan);     \
     served_slots = T * S;                                                                                  \
   } while (0)
-  const int64_t rows = (int64_t)grid.x * grid.y;
+  int64_t rows = (int64_t)grid.x * grid.y;
+  if constexpr (kPlanned) rows = (int64_t)grid.x * plan.n_layers;      // not the workgroups that write the plan's copy
   if (need <= 256 * 1 * 4) CAKE_TOPK(256, 1);
   else if (need <= 256 * 2 * 4 && rows > 256) CAKE_TOPK(256, 2);
   else if (need <= 512 * 1 * 4) CAKE_TOPK(512, 1);

@@ -7,7 +7,7 @@ import torch
 
 from oracle import cake_oracle as co
 
-from gpu_util import load_cake, say
+from gpu_util import kernels_of, load_cake, say
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -117,3 +117,16 @@ def test_kernels_of_short_rows(cake, n, layers):
                     np.testing.assert_array_equal(idx[l, b, h].cpu().numpy(), want, err_msg=f"n={n} k={k} layer {l} row {b} {h}")
             for again in range(l + few, layers, few):
                 assert torch.equal(idx[again], idx[l]), (n, k, again)
+
+
+@pytest.mark.parametrize("layers,n,threads,slots", [(32, 2000, 512, 1), (33, 2000, 256, 2), (16, 9000, 1024, 4), (17, 9000, 512, 8)])
+def test_kernels_of_a_pass_by_its_rows(cake, layers, n, threads, slots):
+    """256 rows are 256 and 128 are 128, also where more workgroups write the host's copy of the plan beside them."""
+    say(f"top-k of a pass of {layers} x 8 rows of {n}")
+    gen = torch.Generator(device=DEV).manual_seed(n)
+    k = torch.randn(1, 8, n + 32, 64, device=DEV, generator=gen).bfloat16()
+    q = torch.randn(1, 8, 32, 64, device=DEV, generator=gen).bfloat16()
+    ev = cake.EvictionPass([q] * layers, [k] * layers, [k] * layers, layers * 128)
+    ev.run()
+    names = [x for x in kernels_of(ev.run) if "select_topk" in x]
+    assert len(names) == 1 and (f"<true, {threads}, {slots}>" in names[0] or f"Li{threads}ELi{slots}E" in names[0]), names
