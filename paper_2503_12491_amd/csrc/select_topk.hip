@@ -780,13 +780,14 @@ int cake::launch_topk_planned(const cake_shape* shape, const float* const* indic
 }
 
 // As many threads as leave a row the fewest slots each, while a row has a compute unit to itself: averages over the stages of
-// 32 layers of 8 heads (256 to 264 rows in the last), us with 256, 512 and 1024 threads: 1000 keys 6.8, 6.7, 7.4; 2000 7.6, 6.7, 7.5;
+// 32 layers of 8 heads (256 rows in the last), us with 256, 512 and 1024 threads: 1000 keys 6.8, 6.7, 7.4; 2000 7.6, 6.7, 7.5;
 // 4000 10.7, 8.3, 7.9; 6000 14.4, 11.3, 10.4; 8192 (512 threads with eight slots 13.2) 12.4, 11.3 for the last two; 15000 (16
-// layers) 17.6, 14.7.  64 layers of 8192 keys: 12.1, 13.4.
+// layers) 17.6, 14.7.  With more rows than compute units, in a 33rd stage, with 512 and 1024 threads: 3000 keys 9.9, 12.3; 6000
+// 12.6, 15.6; 15000 19.9, 21.9.  64 layers of 8192 keys on average: 12.1, 13.4.
 int cake::launch_topk_stage(const StageArgs& a, hipStream_t stream) {
   const dim3 grid(a.batch * a.h_kv, a.m + 1);
   const int need = a.prefix_len + 3;
-  const bool few = (int64_t)grid.x * grid.y <= 272;
+  const bool few = (int64_t)grid.x * grid.y <= 256;
   auto run = [&](auto kern, int threads) { hipLaunchKernelGGL(kern, grid, dim3(threads), 0, stream, a); };
   if (need <= 256 * 1 * 4) run(select_stage_kernel<256, 1>, 256);
   else if (need <= 512 * 1 * 4) run(select_stage_kernel<512, 1>, 512);

@@ -2,11 +2,13 @@
 per head, one gather for the result.  Its caches must equal those of CascadeSession, which copies every
 layer at every stage, also where rows change hands often, and a result taken between two stages must
 neither disturb the next ones nor change afterwards."""
+import re
+
 import numpy as np
 import pytest
 import torch
 
-from gpu_util import load_cake, say
+from gpu_util import kernels_of, load_cake, say
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -73,3 +75,20 @@ def test_kernels_of_a_stage(N, H_kv, L):
         dev.admit(q, k, v)
         host.admit(q, k, v)
     _same(dev.result(), host.result(), 32)
+
+
+def test_threads_of_a_stage_by_its_rows():
+    """A row has as many threads as it can use while there is a compute unit for each, 256 of them."""
+    cake = load_cake()
+    L, H_kv, N = 33, 8, 3032
+    say(f"cascade stage: kernels of {L} layers of {H_kv} heads of {N} keys")
+    gen = torch.Generator(device=DEV).manual_seed(N)
+    q, k = (torch.randn(1, H_kv, rows, 64, device=DEV, generator=gen).bfloat16() for rows in (32, N))
+    dev = cake.DeviceCascade(L, L * N // 6)
+
+    def admit():
+        for _ in range(L):
+            dev.admit(q, k, k)
+    names = [n for n in kernels_of(admit) if "select_stage" in n]
+    threads = [int(re.search(r"(?:<|Li)(\d+)", n[n.index("select_stage"):])[1]) for n in names]
+    assert threads == [1024] * 32 + [512], names
