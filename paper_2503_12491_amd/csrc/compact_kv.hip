@@ -48,6 +48,14 @@ static_assert(kThreads * kUnroll == kCopyBlockPieces, "a workgroup step is one b
 constexpr int kListLds = 4096;       // work-list entries searched from LDS (longer lists are searched in memory)
 constexpr int kListWave = 64;        // entries that a wave holds, one a lane
 
+// A table's address, the same in all lanes: in scalar registers, where it takes no vector ones.
+template <typename T>
+__device__ __forceinline__ T* uniform_global(T* p) {
+  const uint64_t x = reinterpret_cast<uintptr_t>(p);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)x), hi = __builtin_amdgcn_readfirstlane((uint32_t)(x >> 32));
+  return in_global(reinterpret_cast<T*>((uint64_t)hi << 32 | lo));
+}
+
 // A workgroup moves kThreads*kUnroll pieces of one (layer, sequence, head) slice per step.
 // Launches that know the row counts on the host give every slice the blocks it needs.  Planned
 // launches (counts known only on the device) run a fixed number of workgroups that stride over
@@ -59,14 +67,17 @@ constexpr int kListWave = 64;        // entries that a wave holds, one a lane
 // addresses, index, row.  A block's index loads go out together and its row loads behind them, without a branch about either (in
 // branches each of the four waited for the rows of the one before), the indicator's entries beside the rows instead of behind
 // their stores; the work list of a small plan is searched without LDS and its barrier, and a call that knows how long the list can
-// be brings no more workgroups.  Passes of 2 layers of 1024 keys 42.9 -> 42.0 us, of 2 layers of 4000 55.4 -> 50.9, of 8 layers of
-// 2000 70.0 -> 67.2; the eviction of 32 layers of 32768 keys 80.3 -> 78.2.
+// be brings no more workgroups.  Us of the kernel before that and now, with inputs in the caches and flushed out of them: planned, 2 layers of
+// 1024 keys 5.9, 4.8 (7.0, 4.9); 2 of 4000 8.0, 4.9 (11.1, 6.8); 8 of 2000 11.4, 7.6 (13.0, 9.7); 32 of 8192, 1024 rows kept, 57.6, 50.2
+// (85.1, 84.2).  Counts from the host: 4 layers of 4000 keys, 400 rows kept, 7.0, 5.3 (10.4, 8.4); 32 of 32768, 1048 rows, 48.4, 47.8 (87.8, 84.9).
+// Addresses lie in scalar registers and offsets are made where they are used: 61 and 44 vector registers (with both in vector registers 72 and 88, and the
+// index loads one by one behind a test for an empty list).
 template <bool kPlanned>
 __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned> a, DimsArg<kPlanned> dims, StridesArg<kPlanned> st,
                                                           typename std::conditional<kPlanned, CompactPlan, NoArgs>::type plan) {
   __shared__ int32_t list[kPlanned ? kListLds + 1 : 1];
   const int32_t* blocks = nullptr;
-  int32_t n_blocks = 1, begins = 0;
+  int32_t n_blocks = 0, begins = 0;
   if constexpr (kPlanned) {
     blocks = plan.copy_blocks;
     if (plan.n_entries <= kListWave) {
@@ -79,8 +90,7 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
     }
     n_blocks = blocks[plan.n_entries];
   }
-  const int32_t blk_end = kPlanned ? n_blocks : (int32_t)blockIdx.x + 1;      // host-sized launches: one step per workgroup
-  for (int32_t blk = blockIdx.x; blk < blk_end; blk += gridDim.x) {
+  auto step = [&](int32_t blk) {
   int ll, b, h;
   int64_t first;
   if constexpr (kPlanned) {
@@ -127,13 +137,13 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
   const int64_t in_row = s2 * a.elem_bytes;
   const int64_t out_row = (int64_t)a.pieces * 16;
   const int64_t out_off = ((int64_t)b * a.h_kv + h) * (cap_keep + a.window) * out_row;
-  const char* kin = in_global(static_cast<const char*>(a.k_in[ll])) + in_off;
-  const char* vin = in_global(static_cast<const char*>(a.v_in[ll])) + in_off;
-  char* kout = in_global(static_cast<char*>(a.k_out[ll])) + out_off;
-  char* vout = in_global(static_cast<char*>(a.v_out[ll])) + out_off;
-  const int32_t* idx = in_global(a.idx[ll]) + ((int64_t)b * a.h_kv + h) * cap_keep;
+  const char* kin = uniform_global(static_cast<const char*>(a.k_in[ll])) + in_off;
+  const char* vin = uniform_global(static_cast<const char*>(a.v_in[ll])) + in_off;
+  char* kout = uniform_global(static_cast<char*>(a.k_out[ll])) + out_off;
+  char* vout = uniform_global(static_cast<char*>(a.v_out[ll])) + out_off;
+  const int32_t* idx = uniform_global(a.idx[ll]) + ((int64_t)b * a.h_kv + h) * cap_keep;
 
-  if (first >= total) { if (kPlanned) continue; else return; }
+  if (first >= total) return;
   // Indicator entries of the retained prefix rows and, where the caller tracks them, their positions in
   // the prompt: composing the positions here takes the kernel no measurable time, a gather of its own
   // per layer and stage took a session of 16 layers of 6K keys two launches each.  A row split between two blocks is
@@ -145,68 +155,69 @@ __global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned>
   const int32_t* pin = nullptr;
   int32_t* pout = nullptr;
   if (entries) {
-    iin = in_global(a.ind_in[ll]) + head * cap_cur;
-    iout = in_global(a.ind_out[ll]) + head * cap_keep;
+    iin = uniform_global(a.ind_in[ll]) + head * cap_cur;
+    iout = uniform_global(a.ind_out[ll]) + head * cap_keep;
     if (positions) {
-      if (a.pos_in[ll] != nullptr) pin = in_global(a.pos_in[ll]) + head * cap_cur;
-      pout = in_global(a.pos_out[ll]) + head * cap_keep;
+      if (a.pos_in[ll] != nullptr) pin = uniform_global(a.pos_in[ll]) + head * cap_cur;
+      pout = uniform_global(a.pos_out[ll]) + head * cap_keep;
     }
   }
   const int64_t row0 = first / a.pieces;                               // of the block's first piece
   const uint32_t piece0 = (uint32_t)(first - row0 * a.pieces), pieces = (uint32_t)a.pieces;
-  const int64_t r_first = row0 + (piece0 > 0 ? 1 : 0);                  // rows that begin in the block
-  const int64_t r_end = min((first + kThreads * kUnroll + a.pieces - 1) / a.pieces, (int64_t)keep);
-  const int64_t own = r_first + threadIdx.x;
-  const bool has_entry = entries && own < r_end;
-  int own_src = 0;
-  if (has_entry) own_src = min(max(idx[own], 0), cur - 1);
-  const int64_t at = first + threadIdx.x;                              // the thread's first piece, here and in the output
-  // Pieces past the end repeat the last one: with no branch about them the loads of a block are in flight together, the
-  // indexes first and then the rows.
-  const uint32_t last = (uint32_t)min(total - 1 - first, (int64_t)(kThreads * kUnroll - 1)) + piece0;
+  uint32_t tid = threadIdx.x;
+  if (kPlanned) asm volatile("" : "+v"(tid));                            // what follows from it is made anew each turn, not kept in registers
+  const int r_first = (int)row0 + (piece0 > 0 ? 1 : 0);                 // rows that begin in the block
+  const int r_end = (int)min((first + kThreads * kUnroll + a.pieces - 1) / a.pieces, (int64_t)keep);
+  const uint32_t here = (uint32_t)min(total - first, (int64_t)(kThreads * kUnroll));      // pieces of the block
+  // The row that the list has at place r, or any where there is no list.  Pieces past the end repeat the last one, and every thread
+  // reads an entry: with no branch about them the loads of a block are in flight together, the indexes first and then the rows.
+  const int32_t* list_of_rows = keep > 0 ? idx : reinterpret_cast<const int32_t*>(kin);
+  auto chosen = [&](int r) { return min(max(list_of_rows[max(min(r, keep - 1), 0)], 0), max(cur - 1, 0)); };
+  const int own = r_first + (int)tid;
+  const int own_src = chosen(own);
   int64_t src[kUnroll];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
-    const uint32_t q = min(piece0 + u * kThreads + threadIdx.x, last), down = q / pieces, piece = q - down * pieces;
+    const uint32_t q = piece0 + min(u * kThreads + tid, here - 1), down = q / pieces, piece = q - down * pieces;
     const int r = (int)row0 + (int)down;
     // selected prefix rows first, then the window rows that follow the cur prefix rows
-    int from = cur + (r - keep);
-    if (keep > 0) {
-      const int chosen = min(max(idx[min(r, keep - 1)], 0), cur - 1);
-      from = r < keep ? chosen : from;
-    }
-    src[u] = (int64_t)from * in_row + piece * 16;
+    const int from = chosen(r);
+    src[u] = (int64_t)(r < keep ? from : cur + (r - keep)) * in_row + piece * 16;
   }
-  float own_ind = 0.f;
+  const float own_ind = (entries && keep > 0 ? iin : reinterpret_cast<const float*>(kin))[own_src];
   int own_pos = own_src;
-  if (has_entry) {
-    own_ind = iin[own_src];
-    if (pin != nullptr) own_pos = pin[own_src];
-  }
+  if (pin != nullptr && keep > 0) own_pos = pin[own_src];
   uint4 kv[kUnroll], vv[kUnroll];
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u) {
     kv[u] = *reinterpret_cast<const uint4*>(kin + src[u]);
     vv[u] = *reinterpret_cast<const uint4*>(vin + src[u]);
   }
-  if (has_entry) {
+  if (entries && own < r_end) {
     iout[own] = own_ind;
     if (pout != nullptr) pout[own] = own_pos;
   }
   // Streaming stores: the compacted rows are not read again by this pass, and plain stores were
   // measured to cost twice their bytes in memory writes (the rows pass through the cache first).
+  char* kto = kout + first * 16;
+  char* vto = vout + first * 16;
 #pragma unroll
   for (int u = 0; u < kUnroll; ++u)
-    if (at + u * kThreads < total) {
-      store_streaming(kout + (at + u * kThreads) * 16, kv[u]);
-      store_streaming(vout + (at + u * kThreads) * 16, vv[u]);
+    if (u * kThreads + tid < here) {
+      store_streaming(kto + (u * kThreads + tid) * 16, kv[u]);
+      store_streaming(vto + (u * kThreads + tid) * 16, vv[u]);
     }
   if (entries)                                                        // a block of more rows than threads: rows of fewer than five pieces
-    for (int64_t r = own + kThreads; r < r_end; r += kThreads) {
-      const int from = min(max(idx[r], 0), cur - 1);
+    for (int r = own + kThreads; r < r_end; r += kThreads) {
+      const int from = chosen(r);
       iout[r] = iin[from];
       if (pout != nullptr) pout[r] = pin != nullptr ? pin[from] : from;
     }
+  };
+  if constexpr (kPlanned) {
+    for (int32_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) step(blk);
+  } else {
+    step(blockIdx.x);                        // no loop: one of a single turn kept the offsets of its parts in 14 registers
   }
 }
 

@@ -115,3 +115,48 @@ def test_layer_without_shift_keeps_only_its_window(cake):
     assert list(res.budgets[:, 0]) == co.cascade_allocate(res.pref[0], total, S_w, N)
     assert res.budgets[0, 0] == S_w and res.keep[0, 0] == 0 and res.budgets[1, 0] == S_w + 100
     assert torch.equal(res.k_out[0][:, :, :S_w], k0[:, :, N - S_w:]) and torch.equal(res.v_out[0][:, :, :S_w], v0[:, :, N - S_w:])
+
+
+@pytest.mark.parametrize("d,dtype", [(8, torch.bfloat16), (24, torch.bfloat16), (12, torch.float32), (64, torch.bfloat16), (128, torch.float32)])
+@pytest.mark.parametrize("entries", [True, False])
+def test_compaction_with_counts_from_the_host(cake, d, dtype, entries):
+    """Rows of 1, 3, 8 and 32 pieces about blocks of 1024 pieces, layers that keep no row, hold no row (no list, no indicator) or keep all,
+    with token strides of their own and without indicators."""
+    from paper_2503_12491_amd import binding as C
+    say(f"compaction with counts from the host: rows of {d} {dtype}, entries {entries}")
+    S_w, H, B, n = 5, 2, 2, 1500
+    pieces = d * (2 if dtype == torch.bfloat16 else 4) // 16
+    block = 1024 // pieces                                            # rows of a block
+    rng = np.random.default_rng(d)
+    cur = [[n, n], [7, 0], [0, 0], [n, 900], [1200, 1], [300, 299]]
+    keep = [[block - S_w, 2 * block - S_w + 1], [0, 0], [0, 0], [n, 0], [min(block, 1200), 1], [1, 299]]
+    cur, keep = np.array(cur), np.minimum(np.array(keep), cur)
+    L = len(cur)
+    gen = torch.Generator(device=DEV).manual_seed(d)
+    wide = lambda c: torch.randn(B, c + S_w, H, d, device=DEV, generator=gen).to(dtype).transpose(1, 2)      # [B, H, rows, d]
+    caps, outs = cur.max(axis=1), keep.max(axis=1)
+    k, v = ([wide(int(c)) for c in caps] for _ in range(2))
+    ind = [torch.rand(B, H, int(c), device=DEV, generator=gen) for c in caps]
+    idx = [torch.zeros(B, H, int(c), dtype=torch.int32, device=DEV) for c in outs]
+    for l in range(L):
+        for b in range(B):
+            for h in range(H):
+                m = int(keep[l, b])
+                idx[l][b, h, :m] = torch.from_numpy(np.sort(rng.permutation(int(cur[l, b]))[:m])).int()
+    ko, vo = ([torch.full((B, H, int(c) + S_w, d), 3.0, dtype=dtype, device=DEV) for c in outs] for _ in range(2))
+    io = [torch.full((B, H, int(c)), -1.0, device=DEV) for c in outs]
+    shape = C.make_shape(B, L, H, H, d, n + S_w, S_w, dtype)
+    C.cake_compact_kv(shape, C.ptr_table(k), C.ptr_table(v), [[x.stride(i) for i in range(3)] for x in k], cur.reshape(-1), keep.reshape(-1),
+                      C.ptr_table(idx), C.ptr_table(ind) if entries else None, C.ptr_table(ko), C.ptr_table(vo),
+                      C.ptr_table(io) if entries else None)
+    torch.cuda.synchronize()
+    for l in range(L):
+        for b in range(B):
+            m, full = int(keep[l, b]), int(cur[l, b])
+            for h in range(H):
+                src = torch.cat([idx[l][b, h, :m].long(), torch.arange(full, full + S_w, device=DEV)])
+                assert torch.equal(ko[l][b, h, :m + S_w], k[l][b, h][src]) and torch.equal(vo[l][b, h, :m + S_w], v[l][b, h][src]), (l, b, h)
+                assert bool((ko[l][b, h, m + S_w:] == 3.0).all()) and bool((vo[l][b, h, m + S_w:] == 3.0).all()), (l, b, h)
+                if entries:
+                    assert torch.equal(io[l][b, h, :m], ind[l][b, h][idx[l][b, h, :m].long()]), (l, b, h)
+                assert bool((io[l][b, h, m if entries else 0:] == -1.0).all()), (l, b, h)
