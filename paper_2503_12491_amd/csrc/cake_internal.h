@@ -192,8 +192,8 @@ int launch_compact_planned(const cake_shape* shape, const void* const* k_in, con
 // The pointer, known to point to global memory (cast by way of an integer: a pair of pointer casts is folded away).  Where the
 // compiler cannot see that (an address from a table, or one of two), its accesses are flat ones, which count with those of
 // LDS as well: a wait for either waits for both, and independent loads come one after the other.  With global ones, a cascade of
-// 32 layers of 8192 keys takes 2055 us for 2155, a decode step of 12 layers of 4 sequences 59.2 for 61.7, the session of 16 layers of
-// 6007 keys 1230 for 1350 (the last two hang on the host as well: runs differ by 13 %), a pass of 1024 keys 44.2 for 44.7.
+// 32 layers of 8192 keys takes 2055 us for 2155 (runs of one side differ by 2 %), a decode step of 12 layers of 4 sequences 59.2 for
+// 61.7, a pass of 1024 keys 44.2 for 44.7.
 template <typename T>
 __device__ __forceinline__ T* in_global(T* p) {
   return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);

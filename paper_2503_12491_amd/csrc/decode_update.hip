@@ -387,8 +387,8 @@ __device__ __forceinline__ void store_new_row(const void* v_new, int64_t v_at, c
 // last-level cache from the token before; one layer of 1K rows per head 18 -> 6 us).  A compute unit gets some 35 bytes a nanosecond,
 // so four waves of one stay for 2 us where the rows would fit compute units of their own: small calls run one-wave workgroups
 // (4 layers of 2 heads, 12 queries and 335 rows at once in fp32: 14.7 -> 12.5 us, with the loads of the second kernel that no longer
-// wait for the state).  12 layers of 8 heads of 180 to 2900 rows called one by one gain nothing: the kernels
-// take 4.6 and 5.0 us a layer, and the host as long to launch them.
+// wait for the state).  Layers of 8 heads called one by one gain nothing from that: the two kernels take 4.6 and 5.0 us a layer, and
+// the host as long to launch them, which is what step_whole_kernel spares short lists.
 template <typename T, int D, int kStepWaves, typename Args>
 __global__ __launch_bounds__(64 * kStepWaves, 4) void step_logits_kernel(Args a) {
   using Dots = RowDots<T, D>;

@@ -2,12 +2,14 @@
 // streams keys of its own, 32 at a time.  The same products and sums in the same order as in window_scores.hip, where a wave
 // holds one head and the waves of a group share their keys: the same bits.
 //
-// What bounds the passes is the power that the chip has for products, vector instructions and transfers together (a register-only
-// loop of pass 2's step takes 32.5 ns per product, 27.6 where all operands are 0).  A wave per head adds to that what the
-// workgroup's barriers cost where its waves are not a multiple of the four SIMDs; here no wave waits for another one, the
-// group's mean is a sum in a register, and any number of heads loads the SIMDs evenly.  At 2 waves a SIMD and 256
-// registers, 128 of them hold queries; the rest of a larger group is read from LDS (5 heads of 128 all in registers spill
-// nine of them: 975 us for pass 1 against 850).  Times by group: stream_waves.
+// What bounds them, by counter at 5 heads of 128 and 8 to 64 layers of 4 x 8 x 32768 keys, where both run at a clock of 1.4 GHz that the
+// chip's power sets: pass 1 reads K at 5.2 to 5.6 TB/s, what a copy reaches, its waves wait for transfers and LDS 31 % of their time and a SIMD has a
+// product or a vector instruction in flight 65 % of its cycles; pass 2 is busy so 83 % of them (vector instructions 72 %, products 37 %, two
+// thirds of these at the same time) and reads 4.0 to 4.3 TB/s; its waves wait 18 % of their time, among other things once a sub-tile for all its key fragments.
+// A wave per head adds to that what the workgroup's barriers cost where its waves are not a multiple of the four SIMDs;
+// here no wave waits for another one, the group's mean is a sum in a register, and any number of heads loads the SIMDs
+// evenly.  At 2 waves a SIMD and 256 registers, 128 of them hold queries; the rest of a larger group is read from LDS (all of 5
+// heads of 128 in registers would spill nine).  Which launches take them: form_rates.
 //
 // A step is one row block's products (8 of 32x32x16 at d = 128) beside the sums or statistics of the block before, dealt out over
 // the products, so that two accumulator sets take turns.
@@ -17,7 +19,6 @@ namespace cake {
 namespace {
 
 constexpr int kSubKeys = 32;         // keys of a transfer, one MFMA sub-tile
-
 
 // A wave's ring of two transfers in LDS.  The transfers are written in assembly because the compiler takes any read of LDS for
 // one of a transfer in flight and waits for all of them; here a read waits for its own tile alone, and the one behind it stays under way.
