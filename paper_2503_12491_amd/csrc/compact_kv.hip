@@ -47,6 +47,7 @@ struct CompactPlan {
 static_assert(kThreads * kUnroll == kCopyBlockPieces, "a workgroup step is one block of the plan's work list");
 constexpr int kListLds = 4096;       // work-list entries searched from LDS (longer lists are searched in memory)
 constexpr int kListWave = 64;        // entries that a wave holds, one a lane
+constexpr int kHostWaves = 3;        // waves a SIMD, at most, where the counts come from the host
 
 // A table's address, the same in all lanes: in scalar registers, where it takes no vector ones.
 template <typename T>
@@ -71,9 +72,12 @@ __device__ __forceinline__ T* uniform_global(T* p) {
 // 1024 keys 5.9, 4.8 (7.0, 4.9); 2 of 4000 8.0, 4.9 (11.1, 6.8); 8 of 2000 11.4, 7.6 (13.0, 9.7); 32 of 8192, 1024 rows kept, 57.6, 50.2
 // (85.1, 84.2).  Counts from the host: 4 layers of 4000 keys, 400 rows kept, 7.0, 5.3 (10.4, 8.4); 32 of 32768, 1048 rows, 48.4, 47.8 (87.8, 84.9).
 // Addresses lie in scalar registers and offsets are made where they are used: 61 and 44 vector registers (with both in vector registers 72 and 88, and the
-// index loads one by one behind a test for an empty list).
+// index loads one by one behind a test for an empty list).  More waves do not copy faster: the gathers of three sessions (21 layers of 3782
+// keys of 4 fp32 heads, 19 of 3119 and 16 of 6007 keys of 8 bf16 heads) take 2.61 ms at 8 waves a SIMD, 2.51 at 5, 2.49 at 4, 2.45 at 3 (before,
+// with 88 registers and 5 waves, 2.58; before the grouped loads, with 8, 2.82), the eviction of 32 layers of 32768 keys 47.8, 47.0, 46.8 and
+// 47.3 us; of the planned form 5 to 7 waves make no difference.
 template <bool kPlanned>
-__global__ __launch_bounds__(kThreads) void compact_kernel(CompactArgs<kPlanned> a, DimsArg<kPlanned> dims, StridesArg<kPlanned> st,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1, kPlanned ? 8 : kHostWaves))) void compact_kernel(CompactArgs<kPlanned> a, DimsArg<kPlanned> dims, StridesArg<kPlanned> st,
                                                           typename std::conditional<kPlanned, CompactPlan, NoArgs>::type plan) {
   __shared__ int32_t list[kPlanned ? kListLds + 1 : 1];
   const int32_t* blocks = nullptr;
