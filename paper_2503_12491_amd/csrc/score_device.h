@@ -175,32 +175,35 @@ __device__ __forceinline__ float pass2_tile_stats(const ColSums& s0, const ColSu
 // Three forms of a pass over bf16 keys, to the same bits: a wave per head of a group, the group a workgroup; slices packed three
 // (groups of 5) or two (of 6) to a workgroup, which loads the four SIMDs of a compute unit evenly; waves that stream keys of their
 // own through all heads (scores_stream.hip), which do that too, without barriers, but take whole granules of keys each: 2048 waves
-// fill the chip.  Groups of other sizes load the SIMDs evenly with a wave per head and have no other form; streaming was
-// slower there, in pass 2 of two sizes of 64 rows apart (32 rows of 128, 4 heads, 12 to 33 million keys: pass 1 0.98-1.11 and pass 2 0.93-1.06 of a
-// wave per head; 64 of 128, 4 heads, pass 1 2450 us for 2187).
+// fill the chip.  Groups of other sizes load the SIMDs evenly with a wave per head and have no other form, but in pass 2 of
+// 4 heads of 128 and of two sizes of 64 rows streaming may be the faster; pass 1 was slower so (4 heads of 128, 12 to 33 million
+// keys, 0.98-1.11 of a wave per head; 64 rows of 128, 4 heads, 2450 us for 2187).  Pass 2 of 4 heads streams granules of 1024 keys
+// and more only: there, over 4 to 33 million keys, 0.94-1.005 of a wave per head (256 x 32768: 442 -> 426 us), 0.975-1.07 in
+// granules of 256 (976 x 4128: 221 -> 232).
 //
 // Waves of a streaming workgroup, 0 where there is no such kernel.
 constexpr int stream_waves(int pass, int head_dim, int mb, int group) {
-  if (head_dim == 128 && mb == 1) return group == 5 ? 4 : group == 6 ? 8 : 0;
+  if (head_dim == 128 && mb == 1) return group == 5 || (group == 4 && pass == 2) ? 4 : group == 6 ? 8 : 0;
   if (head_dim == 64 && mb == 1) return group == 5 || group == 6 ? 4 : 0;
   if (pass == 2 && head_dim == 128) return group == 3 ? 8 : 0;
   if (pass == 2 && head_dim == 64) return group == 4 ? 4 : 0;
   return 0;
 }
-// What a launch takes: nanoseconds per key of a workgroup (streaming: of a wave) in a round that has up to 1, 2 or 3 workgroups a
-// compute unit (packed: one; streaming: as many as make 4 or 8 waves); 0: no such kernel.  Fitted, to 6-13 %, to launches of each form
+// What a launch takes: nanoseconds per key of a workgroup (streaming: of a wave) in a round that has up to 1, 2, 3 or (4 heads) 4
+// workgroups a compute unit (packed: one; streaming: as many as make 4 or 8 waves); 0: no such kernel.  Fitted, to 6-13 %, to launches of each form
 // with all its spans over 140 thousand to 8.4 million keys (a call's slices together) in layers of 1100 to 131072.  The shape of it: a key
 // costs by the fullest SIMD, so that a second workgroup of 5 or 6 waves comes at half the price of the first, and streaming pays from
 // half the chip's waves on.  Us of pass 1 + pass 2 packed and streaming, slices x keys: 5 heads of 128, 367 x 32749 697 + 842, 591 + 728,
 // but 21 x 32749 45 + 52, 54 + 68; 6 heads, 367 x 32749 817 + 968, 691 + 850, but 43 x 16424 66 + 78, 91 + 114; pass 2 of 5 heads,
 // 127 x 2100: 30 packed, 37 with a wave per head.  Chosen so, a launch takes 1.004 to 1.03 times the fastest form's time on
-// average over those sizes.  Streaming counts 6 % more than it takes, for what the fit is off.  Pass 1 of 5 heads has no packed
+// average over those sizes.  Streaming counts 6 % more than it takes (4 heads: 12 %), for what the fit is off.  Pass 1 of 5 heads has no packed
 // kernel: of three slices at a few sizes the fastest by up to 7 %, but at more of them, under the same rule, the slower choice.
 struct FormRates {
-  int per_head[3], packed, stream[2];
+  int per_head[4], packed, stream[2], least_granule;     // least_granule: of shorter granules a wave per head is taken
 };
 constexpr FormRates form_rates(int pass, int head_dim, int mb, int group) {
   if (mb == 1 && head_dim == 128) {
+    if (group == 4 && pass == 2) return FormRates{{20, 27, 36, 40}, 0, {50, 80}, 1024};
     if (group == 5) return pass == 1 ? FormRates{{18, 26, 34}, 0, {41, 76}} : FormRates{{23, 34, 49}, 42, {53, 88}};
     if (group == 6) return pass == 1 ? FormRates{{18, 29, 39}, 26, {79, 0}} : FormRates{{24, 38, 55}, 34, {100, 0}};
   }

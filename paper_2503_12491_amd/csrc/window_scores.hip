@@ -902,7 +902,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
   auto choose = [&](int pass, int lo, int hi) -> Launch {
     const FormRates rates = sizeof(T) == 2 ? form_rates(pass, D, MB, a.group) : FormRates{};
     const int64_t granules = ((int64_t)hi - lo + a.granule - 1) / a.granule;
-    if (rates.per_head[0] == 0 || n_slices * granules <= 512) {
+    if (rates.per_head[0] == 0 || a.granule < rates.least_granule || n_slices * granules <= 512) {
       const unsigned gx = set_span(pass, lo, hi);
       return Launch{kPerHead, gx, a.key0, a.wg_keys};
     }
@@ -917,7 +917,7 @@ int launch_scores(const ScoreArgs& a_in, int64_t n_slices, const float* const* r
     };
     for (int per = a.chunk / a.granule; per >= 1; per >>= 1) {
       const int64_t gx = (granules + per - 1) / per;
-      consider(kPerHead, per, gx, n_slices, rates.per_head, 3, kFormPrologue);
+      consider(kPerHead, per, gx, n_slices, rates.per_head, rates.per_head[3] ? 4 : 3, kFormPrologue);
       if (rates.packed) consider(kPacked, per, gx, (n_slices + pack - 1) / pack, &rates.packed, 1, kFormPrologue);
     }
     const int waves = stream_waves(pass, D, MB, a.group);

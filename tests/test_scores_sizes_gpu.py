@@ -110,6 +110,8 @@ def _form(names, pass_, group):
     (32, 5, 64, 8, 2100, 34, ("head", "packed")),
     (32, 6, 64, 8, 4093, 16, ("packed", "stream")),
     (32, 6, 64, 9, 225, 17, ("packed", "packed")),
+    (32, 4, 128, 8, 16384 + 31, 32, ("head", "stream")),
+    (32, 4, 128, 8, 4128, 61, ("head", "head")),
     (64, 3, 128, 8, 4093, 25, ("head", "stream")),
     (64, 4, 64, 8, 2047, 29, ("head", "stream")),
 ])
